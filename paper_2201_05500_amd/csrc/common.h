@@ -33,7 +33,7 @@ struct DevHeader {
   u32 n_rows;       // rows in use
   u32 status;       // sticky deferred error bits; kernels are no-ops while it is set
   u32 pull_err;     // errors seen so far by the pull in flight
-  u32 rollback;     // 1: the pull in flight failed, its tentative inserts are being undone
+  u32 live;         // 1: the pull in flight runs (no earlier deferred error); set by its probe launch
   u32 n_rows_base;  // n_rows before the pull in flight
   u32 n_new;        // rows created by the last pull
   u32 n_unique;     // distinct keys of the last pushed batch
@@ -41,7 +41,8 @@ struct DevHeader {
   double bc1, bc2;  // 1 / (1 - beta1^t), 1 / (1 - beta2^t) of the push in flight (bias-corrected form only)
   u64 rows_merged;  // rows averaged by all k-step merges so far (those touched since the merge before)
   u64 merge_pending;  // (row, replica) pairs whose deferred model step those merges applied
-  u32 pad[48];
+  u32 pull_seen;    // errors the probe launch of the pull in flight found (pull_err is zero again by then)
+  u32 pad[47];
 };
 constexpr int HDR_WORD_N_PUSH = 7;  // index of n_push among the header's 32-bit words
 static_assert(sizeof(DevHeader) == 256, "header is one 256-byte block");
@@ -87,6 +88,13 @@ __device__ __forceinline__ u32 wave_inclusive_scan(u32 v) {
     u32 n = __shfl_up(v, off, WAVE);
     if (lane >= off) v += n;
   }
+  return v;
+}
+
+// Sum over the 64 lanes of a wave, in every lane.
+__device__ __forceinline__ u32 wave_sum(u32 v) {
+#pragma unroll
+  for (int off = WAVE / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, WAVE);
   return v;
 }
 

@@ -75,9 +75,9 @@ bool table_layout(const ctr_config* c, TableLayout* L) {
 }
 
 struct WorkLayout {
-  u32 n_bit_words, n_bit_tiles, probe_items, probe_tile, n_probe_tiles, span, n_spans, n_span_blocks;
+  u32 n_rank_tiles, n_rank_groups, probe_items, probe_tile, n_probe_tiles, span, n_spans, n_span_blocks;
   SortGeom geo;
-  size_t off_occ_row, off_seg_of, off_ka, off_va, off_kb, off_vb, off_hist, off_digit_total, off_tile_count, off_first_bits, off_pend_list, off_tile_pending,
+  size_t off_occ_row, off_seg_of, off_ka, off_va, off_kb, off_vb, off_hist, off_digit_total, off_tile_count, off_group_count, off_first_bits, off_pend_list, off_tile_pending,
       off_head, off_tail, off_block_head, off_span_flags, off_span_rows, total;
 };
 
@@ -97,8 +97,8 @@ SortGeom sort_geom(u64 n) {
 // force_span / force_items: 0 = chosen by batch size; otherwise the geometry a test asks for.
 void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force_items = 0) {
   const u64 n = n_keys;
-  L->n_bit_words = (u32)((n + 31) / 32);
-  L->n_bit_tiles = (L->n_bit_words + BITS_TILE_WORDS - 1) / BITS_TILE_WORDS;
+  L->n_rank_tiles = (u32)((n + RANK_TILE - 1) / RANK_TILE);
+  L->n_rank_groups = (L->n_rank_tiles + RANK_GROUP - 1) / RANK_GROUP;
   // shorter spans for smaller batches: the span walk is sequential, so parallelism = n / span groups
   L->span = n >= (8u << 20) ? 128u : n >= (4u << 20) ? 64u : n >= (2u << 20) ? 32u : 16u;
   if (force_span) L->span = force_span;
@@ -115,8 +115,9 @@ void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force
   L->off_vb = o; o += arr;
   L->off_hist = o; o += align256((size_t)RADIX * SORT_MAX_CHUNKS * sizeof(u32));
   L->off_digit_total = o; o += align256(RADIX * sizeof(u32));
-  L->off_tile_count = o; o += align256(((size_t)L->n_bit_tiles + 1) * sizeof(u32));
-  L->off_first_bits = o; o += align256(((size_t)L->n_bit_words + 1) * sizeof(u32));
+  L->off_tile_count = o; o += align256(((size_t)L->n_rank_tiles + 1) * sizeof(u32));
+  L->off_group_count = o; o += align256(((size_t)L->n_rank_groups + 1) * sizeof(u32));
+  L->off_first_bits = o; o += align256(((size_t)L->n_rank_tiles + 1) * RANK_WORDS * sizeof(u32));
   L->probe_items = n >= (4u << 20) ? PROBE_MAX_ITEMS : 1;
   if (force_items) L->probe_items = force_items;
   L->probe_tile = BLOCK * L->probe_items;
@@ -135,6 +136,18 @@ inline u32 lanes_per_row(u32 D) {
   u32 v = D / 4, p = 1;
   while (p < v) p <<= 1;
   return p;  // 1..64
+}
+
+// Which of the two pooling kernels a launch uses, and its grid (table_kernels.h).
+struct PoolGrid {
+  bool small;
+  u32 blocks;
+};
+inline PoolGrid pool_grid(u32 n_segments, u32 lpr) {
+  const u64 groups = BLOCK / lpr, per_block = groups * POOL_NS * POOL_ROUNDS;
+  const u64 blocks = (n_segments + per_block - 1) / per_block;
+  if (blocks >= POOL_MIN_BLOCKS) return {false, (u32)blocks};
+  return {true, (u32)((n_segments + groups - 1) / groups)};
 }
 
 inline u32 blocks_for(u64 threads) { return (u32)((threads + BLOCK - 1) / BLOCK); }
@@ -271,13 +284,14 @@ int status_code_from_bits(u32 bits) {
 }  // namespace
 
 // Key -> row for every occurrence, inserting unseen keys (rows numbered by first occurrence, state
-// initialised); on return of the enqueued work occ_row[p] holds the row of keys[p], or the pull has
+// initialised); after the enqueued work occ_row[p] leads to the row of keys[p] (resolve_row), or the pull has
 // failed and was rolled back (device status set).  d_offsets may be null (nothing to validate).
 // init_new_rows = false: the caller overwrites the state of every row of the batch anyway (a working-set load).
 static void enqueue_lookup_insert(ctr_table* t, const WorkLayout& wl, char* ws, const u64* d_keys, u32 n,
                                   const u32* d_offsets, u32 n_segments, bool init_new_rows, hipStream_t st) {
   u32* occ_row = (u32*)(ws + wl.off_occ_row);
   u32* tile_count = (u32*)(ws + wl.off_tile_count);
+  u32* group_count = (u32*)(ws + wl.off_group_count);
   u32* first_bits = (u32*)(ws + wl.off_first_bits);
   u32* pend_list = (u32*)(ws + wl.off_pend_list);
   u32* tile_pending = (u32*)(ws + wl.off_tile_pending);
@@ -287,29 +301,20 @@ static void enqueue_lookup_insert(ctr_table* t, const WorkLayout& wl, char* ws, 
     const u64 work = std::max<u64>(n, d_offsets ? (u64)n_segments + 1 : 1);
     const u32 grid = (u32)((work + wl.probe_tile - 1) / wl.probe_tile);  // >= n_probe_tiles
     hipLaunchKernelGGL(k_probe_insert, dim3(grid), dim3(BLOCK), 0, st, t->hdr, t->slots, slot_mask, d_keys, n,
-                       d_offsets, n_segments, occ_row, first_bits, pend_list, tile_pending, wl.probe_items);
+                       d_offsets, n_segments, occ_row, pend_list, tile_pending, wl.probe_items, group_count, wl.n_rank_groups);
   }
   {
     StageTimer tm(t, CTR_STAGE_INSERT, st);
-    if (n > 0) {
-      hipLaunchKernelGGL(k_flag_first, dim3(wl.n_probe_tiles), dim3(BLOCK), 0, st, t->hdr, t->slots, occ_row,
-                         pend_list, tile_pending, wl.probe_tile, first_bits);
-      hipLaunchKernelGGL(k_count_first, dim3(wl.n_bit_tiles), dim3(BLOCK), 0, st, t->hdr, first_bits,
-                         wl.n_bit_words, tile_count);
-    }
-    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(BLOCK), 0, st, t->hdr, tile_count, wl.n_bit_tiles, t->R);
-    if (n > 0) {
-      hipLaunchKernelGGL(k_assign_rows, dim3(wl.n_bit_tiles), dim3(BLOCK), 0, st, t->hdr, t->slots, occ_row,
-                         first_bits, wl.n_bit_words, tile_count, t->row_key);
-      if (init_new_rows) {
-        const u32 grid = std::min<u32>(blocks_for((u64)n * t->lpr), 4096);
-        LPR_DISPATCH(t->lpr, k_init_rows, grid, st, t->hdr, t->row_key, t->values, t->tl.replica_stride, t->W,
-                     t->vhat, t->D, t->rf, t->seed_mul, t->init_scale,
-                     (t->cfg.flags & CTR_F_BIAS_CORRECTION) ? 0.0f : t->cfg.eps);
-      }
-      hipLaunchKernelGGL(k_resolve, dim3(wl.n_probe_tiles), dim3(BLOCK), 0, st, t->hdr, t->slots, occ_row,
-                         pend_list, tile_pending, wl.probe_tile);
-    }
+    if (n > 0)
+      hipLaunchKernelGGL(k_rank_count, dim3(wl.n_rank_tiles), dim3(BLOCK), 0, st, t->hdr, t->slots, occ_row, pend_list,
+                         tile_pending, wl.probe_tile, wl.n_probe_tiles, first_bits, tile_count, group_count);
+    else  // no occurrences: the errors of the offsets are taken over, nothing is counted
+      hipLaunchKernelGGL(k_rank_count, dim3(1), dim3(BLOCK), 0, st, t->hdr, t->slots, occ_row, pend_list, tile_pending,
+                         wl.probe_tile, 0u, first_bits, tile_count, group_count);
+    LPR_DISPATCH(t->lpr, k_rank_assign, std::max<u32>(wl.n_rank_tiles, 1u), st, t->hdr, t->slots, occ_row, first_bits,
+                 tile_count, group_count, wl.n_rank_tiles, t->R, t->row_key, init_new_rows ? 1u : 0u, t->values,
+                 t->tl.replica_stride, t->W, t->vhat, t->D, t->rf, t->seed_mul, t->init_scale,
+                 (t->cfg.flags & CTR_F_BIAS_CORRECTION) ? 0.0f : t->cfg.eps);
   }
 }
 
@@ -434,10 +439,11 @@ static int pull_pool_impl(ctr_table* t, uint32_t replica, const uint64_t* d_keys
   if (n_segments > 0) {
     StageTimer tm(t, CTR_STAGE_POOL, st);
     const float* vals = t->values + (u64)replica * t->tl.replica_stride;
-    const u32 segs_per_block = (BLOCK / t->lpr) * POOL_NS * POOL_ROUNDS;
-    const u32 pgrid = (n_segments + segs_per_block - 1) / segs_per_block;
+    const PoolGrid pg = pool_grid(n_segments, t->lpr);
 #define CTR_POOL_LAUNCH(KERNEL) \
-  LPR_DISPATCH(t->lpr, KERNEL, pgrid, st, t->hdr, occ_row, seg_of, d_offsets, n_segments, vals, t->D, t->rf, d_pooled, d_pooled_bf16)
+  if (pg.small) { CTR_POOL_LAUNCH_1(KERNEL##_small); } else { CTR_POOL_LAUNCH_1(KERNEL); }
+#define CTR_POOL_LAUNCH_1(KERNEL) \
+  LPR_DISPATCH(t->lpr, KERNEL, pg.blocks, st, t->hdr, occ_row, t->slots, seg_of, d_offsets, n_segments, vals, t->D, t->rf, d_pooled, d_pooled_bf16)
     if (d_pooled && d_pooled_bf16) {
       CTR_POOL_LAUNCH(k_pool_both);
     } else if (d_pooled_bf16) {
@@ -446,6 +452,7 @@ static int pull_pool_impl(ctr_table* t, uint32_t replica, const uint64_t* d_keys
       CTR_POOL_LAUNCH(k_pool);
     }
 #undef CTR_POOL_LAUNCH
+#undef CTR_POOL_LAUNCH_1
   }
   if (n > 0) {
     StageTimer tm(t, CTR_STAGE_SORT, st);
@@ -517,10 +524,11 @@ static int lookup_pool_enqueue(ctr_table* t, uint32_t replica, const uint64_t* d
   if (n_segments > 0) {
     StageTimer tm(t, CTR_STAGE_POOL, st);
     const float* vals = t->values + (u64)replica * t->tl.replica_stride;
-    const u32 segs_per_block = (BLOCK / t->lpr) * POOL_NS * POOL_ROUNDS;
-    const u32 pgrid = (n_segments + segs_per_block - 1) / segs_per_block;
+    const PoolGrid pg = pool_grid(n_segments, t->lpr);
 #define CTR_POOL_LAUNCH(KERNEL) \
-  LPR_DISPATCH(t->lpr, KERNEL, pgrid, st, t->hdr, occ_row, seg_of, d_offsets, n_segments, vals, t->D, t->rf, d_pooled, pb)
+  if (pg.small) { CTR_POOL_LAUNCH_1(KERNEL##_small); } else { CTR_POOL_LAUNCH_1(KERNEL); }
+#define CTR_POOL_LAUNCH_1(KERNEL) \
+  LPR_DISPATCH(t->lpr, KERNEL, pg.blocks, st, t->hdr, occ_row, t->slots, seg_of, d_offsets, n_segments, vals, t->D, t->rf, d_pooled, pb)
     if (d_pooled && pb) {
       CTR_POOL_LAUNCH(k_pool_lookup_both);
     } else if (pb) {
@@ -529,6 +537,7 @@ static int lookup_pool_enqueue(ctr_table* t, uint32_t replica, const uint64_t* d
       CTR_POOL_LAUNCH(k_pool_lookup);
     }
 #undef CTR_POOL_LAUNCH
+#undef CTR_POOL_LAUNCH_1
   }
   t->profile = profile;
   return launch_status();
@@ -751,7 +760,7 @@ int ctr_table_load(ctr_table* t, const uint64_t* d_keys, uint64_t n_keys, const 
   enqueue_lookup_insert(t, wl, (char*)d_workspace, (const u64*)d_keys, n, nullptr, 0, false, st);
   if (n > 0) {
     const u32* occ_row = (const u32*)((char*)d_workspace + wl.off_occ_row);
-    LPR_DISPATCH(t->lpr, k_load_rows, blocks_for((u64)n * t->lpr), st, t->hdr, occ_row, n, t->values,
+    LPR_DISPATCH(t->lpr, k_load_rows, blocks_for((u64)n * t->lpr), st, t->hdr, occ_row, t->slots, n, t->values,
                  t->tl.replica_stride, t->W, t->vhat, t->D, t->rf, d_x, d_m, d_v);
   }
   return launch_status();
@@ -925,7 +934,7 @@ int ctr_last_status(ctr_table* t, void* hip_stream) {
   if (hipMemcpyAsync(&h, t->hdr, sizeof(h), hipMemcpyDeviceToHost, st) != hipSuccess) return CTR_E_DEVICE;
   if (hipStreamSynchronize(st) != hipSuccess) return CTR_E_DEVICE;
   if (h.status == 0) return CTR_OK;
-  // clear status, pull_err and rollback (three consecutive words after n_rows)
+  // clear status, pull_err and live (three consecutive words after n_rows)
   if (hipMemsetAsync((char*)t->hdr + offsetof(DevHeader, status), 0, 3 * sizeof(u32), st) != hipSuccess)
     return CTR_E_DEVICE;
   if (hipStreamSynchronize(st) != hipSuccess) return CTR_E_DEVICE;

@@ -35,16 +35,21 @@ __global__ void k_table_clear(DevHeader* hdr, Slot* slots, u64 n_slots, u32* row
 // later, so the occurrence records the slot index instead, lowers the slot's first_p to its
 // own position (the smallest position wins: new rows are numbered in order of first
 // occurrence) and is appended to its tile's list of pending occurrences (counted in LDS, so no
-// global atomic is shared between blocks).  The same launch checks the CSR offsets and clears
-// the bitmap of first occurrences.
+// global atomic is shared between blocks).  The same launch checks the CSR offsets.
 constexpr int PROBE_MAX_ITEMS = 8;  // occurrences per thread: 8 for large batches, 1 for small ones (host's choice)
 
 __global__ void __launch_bounds__(BLOCK)
 k_probe_insert(DevHeader* hdr, Slot* slots, u32 slot_mask, const u64* __restrict__ keys, u32 n_keys,
                const u32* __restrict__ offsets, u32 n_seg, u32* __restrict__ occ_row,
-               u32* __restrict__ first_bits, u32* __restrict__ pend_list, u32* __restrict__ tile_pending,
-               u32 items) {
-  if (hdr->status) return;
+               u32* __restrict__ pend_list, u32* __restrict__ tile_pending, u32 items,
+               u32* __restrict__ group_count, u32 n_groups) {
+  const bool refused = hdr->status != 0;  // an earlier call failed: this pull is a no-op
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    hdr->live = refused ? 0u : 1u;
+    hdr->n_rows_base = hdr->n_rows;
+  }
+  if (refused) return;
+  if (blockIdx.x * BLOCK + threadIdx.x < n_groups) group_count[blockIdx.x * BLOCK + threadIdx.x] = 0;
   __shared__ u32 n_pend;
   if (threadIdx.x == 0) n_pend = 0;
   __syncthreads();
@@ -66,7 +71,6 @@ k_probe_insert(DevHeader* hdr, Slot* slots, u32 slot_mask, const u64* __restrict
 
     bool pending = false;
     if (p < n_keys) {
-      if ((p & 31u) == 0) first_bits[p >> 5] = 0;
       const u64 key = keys[p];
       u32 out = OCC_INVALID;
       if (key == KEY_EMPTY) {
@@ -129,113 +133,123 @@ k_probe_insert(DevHeader* hdr, Slot* slots, u32 slot_mask, const u64* __restrict
 
 // ---------------------------------------------------------------- ranking of new keys
 
-constexpr int BITS_TILE_WORDS = BLOCK;  // one bitmap word per thread: 8192 occurrences per tile
+// New rows are numbered in order of first occurrence, so the launches below need a prefix sum over the whole
+// batch.  They are two: one that finds and counts the first occurrences, per rank tile and per group of
+// RANK_GROUP tiles, and one in which every tile that has any adds up the counts of the groups before its own and
+// of the tiles before it in its group by itself (a few hundred words that sit in L2).  A launch that only waits for the one before costs 4.5 us, and in mid-training almost no tile has new
+// keys: with flags, counts, scan, assignment, row creation and the patching of pending occurrences in launches
+// of their own they were a fifth of a step of 73 k keys.  (No spin-waits: they would need block tickets, and
+// 8 ns per ticket is more than the launch.)
+constexpr u32 RANK_TILE = PROBE_MAX_ITEMS * BLOCK;  // 2048 occurrences: a whole number of probe tiles of any size
+constexpr u32 RANK_WORDS = RANK_TILE / 32;
+constexpr u32 RANK_GROUP = 128;  // tiles: 39 M occurrences have 150 groups
 
-// Over the pending occurrences (one block per probe tile): marks those that are the first
-// occurrence of their (new) key.  A probe tile owns whole words of the bitmap (its size is a
-// multiple of 32 occurrences), so the bits are gathered in LDS and the words that hold any are
-// stored plainly; the probe launch has zeroed the bitmap.
-__global__ void k_flag_first(const DevHeader* hdr, const Slot* __restrict__ slots, const u32* __restrict__ occ_row,
-                             const u32* __restrict__ pend_list, const u32* __restrict__ tile_pending,
-                             u32 probe_tile, u32* __restrict__ first_bits) {
-  if (hdr->status) return;
-  const u32 cnt = tile_pending[blockIdx.x];
-  if (cnt == 0) return;
-  __shared__ u32 bits[PROBE_MAX_ITEMS * BLOCK / 32];
-  const u32 tile_words = probe_tile / 32u, tile0 = blockIdx.x * probe_tile;
-  for (u32 i = threadIdx.x; i < tile_words; i += BLOCK) bits[i] = 0;
-  __syncthreads();
-  for (u32 i = threadIdx.x; i < cnt; i += BLOCK) {
-    const u32 p = pend_list[tile0 + i];
-    const u32 h = occ_row[p] & ~OCC_PEND_FLAG;
-    if (slots[h].first_p == p) atomicOr(&bits[(p - tile0) >> 5], 1u << (p & 31u));
+// One block per rank tile, over the pending occurrences of its probe tiles: finds those that are the first
+// occurrence of their (new) key, leaves them as a bitmap (written only where there are any) and their number.
+__global__ void __launch_bounds__(BLOCK)
+k_rank_count(DevHeader* hdr, const Slot* __restrict__ slots, const u32* __restrict__ occ_row,
+             const u32* __restrict__ pend_list, const u32* __restrict__ tile_pending, u32 probe_tile,
+             u32 n_probe_tiles, u32* __restrict__ first_bits, u32* __restrict__ tile_count,
+             u32* __restrict__ group_count) {
+  if (!hdr->live) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    hdr->pull_seen = hdr->pull_err;
+    hdr->pull_err = 0;
   }
-  __syncthreads();
-  for (u32 i = threadIdx.x; i < tile_words; i += BLOCK)
-    if (bits[i]) first_bits[(tile0 >> 5) + i] = bits[i];
-}
-
-// Number of first occurrences per tile of the bitmap.
-__global__ void k_count_first(const DevHeader* hdr, const u32* __restrict__ first_bits, u32 n_words,
-                              u32* __restrict__ tile_count) {
-  if (hdr->status) return;
-  __shared__ u32 lds[4];
-  const u32 w = blockIdx.x * BITS_TILE_WORDS + threadIdx.x;
-  const u32 cnt = (w < n_words) ? (u32)__popc(first_bits[w]) : 0u;
-  u32 total;
-  block_exclusive_scan(cnt, lds, total);
-  if (threadIdx.x == 0) tile_count[blockIdx.x] = total;
-}
-
-// One block: exclusive scan of the tile counts, capacity check, commit or roll back.
-__global__ void k_scan_tiles(DevHeader* hdr, u32* __restrict__ tile_count, u32 n_tiles, u64 capacity_rows) {
-  if (hdr->status) {  // an earlier call failed: this pull is a no-op
-    if (threadIdx.x == 0) hdr->rollback = 0;
+  const u32 per = RANK_TILE / probe_tile;
+  const u32 t0 = blockIdx.x * per, t1 = min(t0 + per, n_probe_tiles);
+  u32 any = 0;
+  for (u32 t = t0; t < t1; ++t) any |= tile_pending[t];
+  if (any == 0) {  // uniform over the block
+    if (threadIdx.x == 0) tile_count[blockIdx.x] = 0;
     return;
   }
-  __shared__ u32 lds[4];
-  const u32 per = (n_tiles + BLOCK - 1) / BLOCK;  // consecutive tiles per thread, one block-wide scan in all
-  const u32 c0 = min(threadIdx.x * per, n_tiles), c1 = min(c0 + per, n_tiles);
-  u32 sum = 0;
-  for (u32 t = c0; t < c1; ++t) sum += tile_count[t];
-  u32 carry;
-  u32 ex = block_exclusive_scan(sum, lds, carry);
-  for (u32 t = c0; t < c1; ++t) {
-    const u32 v = tile_count[t];
-    tile_count[t] = ex;
-    ex += v;
+  __shared__ u32 bits[RANK_WORDS];
+  const u32 p0 = blockIdx.x * RANK_TILE;
+  if (threadIdx.x < RANK_WORDS) bits[threadIdx.x] = 0;
+  __syncthreads();
+  for (u32 t = t0; t < t1; ++t) {
+    const u32 cnt = tile_pending[t];
+    for (u32 i = threadIdx.x; i < cnt; i += BLOCK) {
+      const u32 p = pend_list[t * probe_tile + i];
+      if (slots[occ_row[p] & ~OCC_PEND_FLAG].first_p == p) atomicOr(&bits[(p - p0) >> 5], 1u << (p & 31u));
+    }
   }
-  if (threadIdx.x == 0) {
-    u32 err = hdr->pull_err;
-    const u32 base = hdr->n_rows;
-    if ((u64)base + carry > capacity_rows) err |= ST_FULL;
-    hdr->n_rows_base = base;
-    hdr->pull_err = 0;
-    hdr->n_unique = 0;
-    if (err) {
-      hdr->status = err;
-      hdr->rollback = 1;
-      hdr->n_new = 0;
-    } else {
-      hdr->rollback = 0;
-      hdr->n_new = carry;
-      hdr->n_rows = base + carry;
+  __syncthreads();
+  if (threadIdx.x < RANK_WORDS) {
+    const u32 w = bits[threadIdx.x];
+    first_bits[blockIdx.x * RANK_WORDS + threadIdx.x] = w;
+    const u32 total = wave_sum((u32)__popc(w));
+    if (threadIdx.x == 0) {
+      tile_count[blockIdx.x] = total;
+      if (total) atomicAdd(&group_count[blockIdx.x / RANK_GROUP], total);
     }
   }
 }
+static_assert(RANK_WORDS == WAVE && RANK_GROUP <= BLOCK, "one wave counts a rank tile, one block a group");
 
-// Gives the first occurrence of every new key its row id (tile base + rank in
-// occurrence order), or, when the pull failed, frees the slot again: clearing
-// exactly the slots claimed by this pull restores the index as it was.
-// A block takes one tile of the bitmap: the words and their exclusive popcount prefix go to LDS,
-// then every thread looks at 32 occurrences of its own (consecutive lanes, consecutive
-// occurrences), so the slot accesses of a block are independent of each other.
-__global__ void k_assign_rows(const DevHeader* hdr, Slot* slots, const u32* __restrict__ occ_row,
-                              const u32* __restrict__ first_bits, u32 n_words, const u32* __restrict__ tile_base,
-                              u64* __restrict__ row_key) {
-  const u32 rollback = hdr->rollback;
-  if (hdr->status && !rollback) return;
-  __shared__ u32 lds[4];
-  __shared__ u32 wbits[BITS_TILE_WORDS];
-  __shared__ u32 wrank[BITS_TILE_WORDS];
-  const u32 word0 = blockIdx.x * BITS_TILE_WORDS;
-  const u32 mine = (word0 + threadIdx.x < n_words) ? first_bits[word0 + threadIdx.x] : 0u;
-  u32 total;
-  const u32 ex = block_exclusive_scan((u32)__popc(mine), lds, total);
-  if (total == 0) return;
-  wbits[threadIdx.x] = mine;
-  wrank[threadIdx.x] = ex;
+// Commits the pull or undoes it, and gives the first occurrence of every new key its row: the row id (rows in
+// use + first occurrences before it), the key of the row and its initial state in every replica:
+// x = init(key, d); first moment 0 (rows that have one); second moment / AdaGrad accumulator = v0 (eps per
+// Algorithm 2's "Initialize", 0 for the bias-corrected form); shared denominator = v0.  When the pull failed
+// (an error of the probe, or more rows than the table has), clearing exactly the slots claimed by this pull
+// restores the index as it was.  rf = floats per row (3*D with a first moment, 2*D without); init_rows = 0: the
+// caller writes the state of every row of the batch itself (a working-set load).
+template <int LPR>
+__global__ void __launch_bounds__(BLOCK)
+k_rank_assign(DevHeader* hdr, Slot* slots, const u32* __restrict__ occ_row, const u32* __restrict__ first_bits,
+              const u32* __restrict__ tile_count, const u32* __restrict__ group_count, u32 n_tiles, u64 capacity_rows, u64* __restrict__ row_key,
+              u32 init_rows, float* values, u64 replica_stride, u32 n_replicas, float* vhat, u32 D, u32 rf,
+              u64 seed_mul, float scale, float v0) {
+  if (!hdr->live) return;
+  const u32 own = n_tiles ? tile_count[blockIdx.x] : 0u;
+  if (own == 0 && blockIdx.x != 0) return;
+  __shared__ u32 lds[8];
+  u32 before = 0, total = 0;  // first occurrences in the tiles before this one, in all tiles
+  const u32 n_groups = (n_tiles + RANK_GROUP - 1) / RANK_GROUP, group = blockIdx.x / RANK_GROUP;
+  for (u32 t = threadIdx.x; t < n_groups; t += BLOCK) {
+    const u32 c = group_count[t];
+    total += c;
+    if (t < group) before += c;
+  }
+  if (group * RANK_GROUP + threadIdx.x < blockIdx.x) before += tile_count[group * RANK_GROUP + threadIdx.x];
+  before = wave_sum(before);
+  total = wave_sum(total);
+  if (lane_id() == 0) {
+    lds[wave_id()] = before;
+    lds[4 + wave_id()] = total;
+  }
   __syncthreads();
-  const u32 row0 = hdr->n_rows_base + tile_base[blockIdx.x];
+  before = lds[0] + lds[1] + lds[2] + lds[3];
+  total = lds[4] + lds[5] + lds[6] + lds[7];
+  const u32 base = hdr->n_rows_base;
+  const u32 err = hdr->pull_seen | ((u64)base + total > capacity_rows ? ST_FULL : 0u);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {  // read by later launches only
+    hdr->n_unique = 0;
+    hdr->status = err;
+    hdr->n_new = err ? 0u : total;
+    if (!err) hdr->n_rows = base + total;
+  }
+  if (own == 0) return;
+
+  __shared__ u32 wbits[RANK_WORDS];
+  __shared__ u32 wrank[RANK_WORDS];
+  if (threadIdx.x < RANK_WORDS) {  // wave 0
+    const u32 w = first_bits[blockIdx.x * RANK_WORDS + threadIdx.x];
+    wbits[threadIdx.x] = w;
+    wrank[threadIdx.x] = wave_inclusive_scan((u32)__popc(w)) - (u32)__popc(w);
+  }
+  __syncthreads();
+  const u32 row0 = base + before;
   const u32 bit = threadIdx.x & 31u;
 #pragma unroll 4
-  for (u32 i = 0; i < 32; ++i) {
+  for (u32 i = 0; i < RANK_TILE / BLOCK; ++i) {  // consecutive lanes look at consecutive occurrences
     const u32 word = i * (BLOCK / 32) + (threadIdx.x >> 5);
     const u32 b = wbits[word];
     if ((b >> bit) & 1u) {
-      const u32 p = (word0 + word) * 32u + bit;
+      const u32 p = blockIdx.x * RANK_TILE + word * 32u + bit;
       Slot* s = &slots[occ_row[p] & ~OCC_PEND_FLAG];
-      if (rollback) {
+      if (err) {
         s->first_p = 0xFFFFFFFFu;
         s->key = KEY_EMPTY;
       } else {
@@ -245,23 +259,12 @@ __global__ void k_assign_rows(const DevHeader* hdr, Slot* slots, const u32* __re
       }
     }
   }
-}
-
-// Writes the initial state of the rows created by this pull, in every replica:
-// x = init(key, d); first moment 0 (rows that have one); second moment / AdaGrad accumulator
-// = v0 (eps per Algorithm 2's "Initialize", 0 for the bias-corrected form); shared denominator = v0.
-// rf = floats per row (3*D with a first moment, 2*D without).
-template <int LPR>
-__global__ void k_init_rows(const DevHeader* hdr, const u64* __restrict__ row_key, float* values,
-                            u64 replica_stride, u32 n_replicas, float* vhat, u32 D, u32 rf, u64 seed_mul,
-                            float scale, float v0) {
-  if (hdr->status) return;
-  const u32 n_new = hdr->n_new, row_base = hdr->n_rows_base;
+  if (err || !init_rows) return;
+  __syncthreads();  // the keys of the tile's rows are written
   const u32 c = threadIdx.x % LPR;
-  const u32 groups = gridDim.x * (BLOCK / LPR);
   if (c * 4 >= D) return;
-  for (u32 i = (blockIdx.x * BLOCK + threadIdx.x) / LPR; i < n_new; i += groups) {
-    const u32 row = row_base + i;
+  for (u32 i = threadIdx.x / LPR; i < own; i += BLOCK / LPR) {
+    const u32 row = row0 + i;
     const u64 key = row_key[row];
     f4 x, z, e;
     x.x = init_value(seed_mul, key, 4 * c + 0, scale);
@@ -284,27 +287,20 @@ __global__ void k_init_rows(const DevHeader* hdr, const u64* __restrict__ row_ke
   }
 }
 
-// Replaces "slot index, row pending" entries by the row id now that rows are assigned
-// (one block per probe tile, over its list of pending occurrences).
-__global__ void k_resolve(const DevHeader* hdr, const Slot* __restrict__ slots, u32* __restrict__ occ_row,
-                          const u32* __restrict__ pend_list, const u32* __restrict__ tile_pending,
-                          u32 probe_tile) {
-  if (hdr->status) return;
-  const u32 cnt = tile_pending[blockIdx.x];
-  for (u32 i = threadIdx.x; i < cnt; i += BLOCK) {
-    const u32 p = pend_list[blockIdx.x * probe_tile + i];
-    occ_row[p] = slots[occ_row[p] & ~OCC_PEND_FLAG].row;
-  }
+// Row of an occurrence as the probe left it: a row id, or a slot whose row has been assigned since.
+__device__ __forceinline__ u32 resolve_row(u32 entry, const Slot* __restrict__ slots) {
+  return (entry & OCC_PEND_FLAG) ? slots[entry & ~OCC_PEND_FLAG].row : entry;
 }
 
 // ---------------------------------------------------------------- working-set load / collection
 
-// After the keys of a working set have been looked up or inserted (occ_row[p] = row of keys[p]):
+// After the keys of a working set have been looked up or inserted (occ_row[p] leads to the row of keys[p]):
 // overwrites the state of those rows, in every replica, with the values supplied by the caller
 // (the shared denominator, where there is one, is set to v).  m_src may be null for rows without
 // a first moment.
 template <int LPR>
-__global__ void k_load_rows(const DevHeader* hdr, const u32* __restrict__ occ_row, u32 n, float* values,
+__global__ void k_load_rows(const DevHeader* hdr, const u32* __restrict__ occ_row, const Slot* __restrict__ slots,
+                            u32 n, float* values,
                             u64 replica_stride, u32 n_replicas, float* vhat, u32 D, u32 rf,
                             const float* __restrict__ x_src, const float* __restrict__ m_src,
                             const float* __restrict__ v_src) {
@@ -313,7 +309,7 @@ __global__ void k_load_rows(const DevHeader* hdr, const u32* __restrict__ occ_ro
   const u32 c = threadIdx.x % LPR;
   if (p64 >= n || c * 4 >= D) return;
   const u32 p = (u32)p64;
-  const u32 row = occ_row[p];
+  const u32 row = resolve_row(occ_row[p], slots);
   const f4 x = ldg4(x_src + (u64)p * D + 4 * c);
   const f4 v = ldg4(v_src + (u64)p * D + 4 * c);
   f4 m = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -427,126 +423,192 @@ __global__ void k_collect_rows(const DevHeader* hdr, const Slot* __restrict__ sl
 
 // ---------------------------------------------------------------- gather + per-segment sum
 
-// A block takes POOL_TILE consecutive segments and stages their CSR boundaries in LDS.
-// First all threads record, for every occurrence of the tile, the segment it belongs to
-// (binary search in the staged boundaries; coalesced writes) - the push needs it.
-// Then each group of LPR lanes (a lane owns 4 consecutive columns) sums its segments, two
-// at a time so that up to 8 independent row loads are in flight per group:
-// pooled[g, :] = sum over the segment's occurrences of x[row, :], in CSR order, binary32
-// inside a batch of 4 consecutive occurrences and binary64 across batches, rounded once
-// (error <= 3 * 2^-24 * sum |x|).  A row is rf floats and starts with x.
+// pooled[g, :] = sum over the segment's occurrences of x[row, :], in CSR order, binary32 inside a batch of 4
+// consecutive occurrences and binary64 across batches, rounded once (error <= 3 * 2^-24 * sum |x|).  A row is
+// rf floats and starts with x; a group of LPR lanes (a lane owns 4 consecutive columns) sums a segment.
+// On the way a training pull records the segment of every occurrence (the push needs it) and replaces
+// "slot, row assigned later" entries by the row (the sort reads them).  Two kernels:
+//  * k_pool, for large batches, is bound by the rate of L2 requests (two 128-byte lines per gathered row), so
+//    everything else is kept off that path: a block stages the boundaries and the row ids of its POOL_NS *
+//    POOL_ROUNDS segments per group in LDS with coalesced loads, and the segment ids leave coalesced (found by
+//    binary search in the staged boundaries).  A group sums two segments at a time: up to 8 row loads in flight.
+//  * k_pool_small, for grids that leave the chip mostly idle, is bound by its chain of dependent loads: one
+//    segment per group, no barrier, nothing staged.  (16384 segments of 8 columns: 15.1 -> 9.2 us; at 10 M
+//    segments of 64 columns the unstaged form costs 1.38 against 1.31 ms.)
 #ifndef CTR_POOL_NT_OUT
 #define CTR_POOL_NT_OUT 1  // the pooled output (written once, read by the next stage) leaves with the non-temporal hint
 #endif
-constexpr int POOL_NS = 2;      // segments a group works on at once
-constexpr int POOL_ROUNDS = 2;  // such pairs per group
+constexpr u32 POOL_NS = 2;      // k_pool: segments a group works on at once
+constexpr u32 POOL_ROUNDS = 2;  // such pairs per group
+constexpr u32 POOL_MIN_BLOCKS = 1024;  // grids of k_pool below this go to k_pool_small
+template <int LPR>
+constexpr u32 pool_staged_rows() {  // row ids a block of k_pool stages: 6 per segment, at most 16 KB
+  constexpr u32 want = BLOCK / LPR * POOL_NS * POOL_ROUNDS * 6;
+  return want < 4096 ? want : 4096;
+}
 
 // OUT: 1 = fp32 output, 2 = bf16 output, 3 = both; + 4 = lookup-only input, where an occurrence may have
 // no row (compile-time, so the common fp32-only training kernel carries none of the other cases).
+template <int OUT>
+__device__ __forceinline__ void pool_store(u64 g, u32 D, u32 c, d4 acc, float* __restrict__ pooled,
+                                           bf16_t* __restrict__ pooled_bf16) {
+  const f4 o = {(float)acc.x, (float)acc.y, (float)acc.z, (float)acc.w};
+#if CTR_POOL_NT_OUT
+  if constexpr (OUT & 1) stg4_stream(pooled + g * D + 4 * c, o);
+#else
+  if constexpr (OUT & 1) stg4(pooled + g * D + 4 * c, o);
+#endif
+  if constexpr (OUT & 2) stg4_bf16(pooled_bf16 + g * D + 4 * c, o);  // the fp32 value, rounded again
+}
+
+// Adds a batch of 4 gathered rows to a segment's sum (padded entries add +0.0).
+__device__ __forceinline__ void pool_add4(const f4 (&xv)[4], d4& acc) {
+  f4 f = xv[0];
+#pragma unroll
+  for (int i = 1; i < 4; ++i) {
+    f.x += xv[i].x; f.y += xv[i].y; f.z += xv[i].z; f.w += xv[i].w;
+  }
+  acc.x += (double)f.x; acc.y += (double)f.y; acc.z += (double)f.z; acc.w += (double)f.w;
+}
+
 template <int LPR, int OUT>
-__device__ __forceinline__ void pool_body(const DevHeader* hdr, const u32* __restrict__ occ_row,
-                                          u32* __restrict__ seg_of, const u32* __restrict__ offsets, u32 n_seg,
+__device__ __forceinline__ void pool_body(const DevHeader* hdr, u32* occ_row,
+                                          const Slot* __restrict__ slots, u32* __restrict__ seg_of,
+                                          const u32* __restrict__ offsets, u32 n_seg,
                                           const float* __restrict__ values, u32 D, u32 rf,
                                           float* __restrict__ pooled, bf16_t* __restrict__ pooled_bf16) {
   if (hdr->status) return;
-  constexpr int GROUPS = BLOCK / LPR;
-  constexpr int TILE = GROUPS * POOL_NS * POOL_ROUNDS;
+  constexpr bool LOOKUP = (OUT & 4) != 0;
+  constexpr u32 GROUPS = BLOCK / LPR;
+  constexpr u32 TILE = GROUPS * POOL_NS * POOL_ROUNDS;
+  constexpr u32 STAGED = pool_staged_rows<LPR>();
   __shared__ u32 off_lds[TILE + 1];
+  __shared__ u32 row_lds[STAGED];
   const u32 tile_g0 = blockIdx.x * TILE;
-  const u32 tile_n = min((u32)TILE, n_seg - tile_g0);
+  const u32 tile_n = min(TILE, n_seg - tile_g0);
   for (u32 i = threadIdx.x; i <= tile_n; i += BLOCK) off_lds[i] = offsets[tile_g0 + i];
   __syncthreads();
 
   const u32 P0 = off_lds[0], P1 = off_lds[tile_n];
   for (u32 p = P0 + threadIdx.x; p < P1; p += BLOCK) {
-    u32 lo = 0, hi = tile_n;  // last l with off[l] <= p (skips empty segments)
-    while (hi - lo > 1) {
-      const u32 mid = (lo + hi) >> 1;
-      if (off_lds[mid] <= p) lo = mid; else hi = mid;
+    u32 entry = occ_row[p];
+    if constexpr (!LOOKUP) {
+      if (entry & OCC_PEND_FLAG) occ_row[p] = entry = resolve_row(entry, slots);
     }
-    seg_of[p] = tile_g0 + lo;
+    if (p - P0 < STAGED) row_lds[p - P0] = entry;
+    if constexpr (!LOOKUP) {
+      u32 lo = 0, hi = tile_n;  // last l with off[l] <= p (skips empty segments)
+      while (hi - lo > 1) {
+        const u32 mid = (lo + hi) >> 1;
+        if (off_lds[mid] <= p) lo = mid; else hi = mid;
+      }
+      seg_of[p] = tile_g0 + lo;
+    }
   }
+  __syncthreads();
 
   const u32 grp = threadIdx.x / LPR, c = threadIdx.x % LPR;
   const bool col_ok = c * 4 < D;
+  // row_at(p): row id of occurrence p; all ids of a batch are read before the first row is requested
+  const auto sum_segments = [&](const auto& row_at) {
 #pragma unroll
-  for (int rnd = 0; rnd < POOL_ROUNDS; ++rnd) {
-    u32 beg[POOL_NS], end[POOL_NS];
-    d4 acc[POOL_NS];
-    u32 maxlen = 0;
+    for (u32 rnd = 0; rnd < POOL_ROUNDS; ++rnd) {
+      u32 beg[POOL_NS], end[POOL_NS];
+      d4 acc[POOL_NS];
+      u32 maxlen = 0;
 #pragma unroll
-    for (int s = 0; s < POOL_NS; ++s) {
-      const u32 l = (rnd * POOL_NS + s) * GROUPS + grp;
-      beg[s] = l < tile_n ? off_lds[l] : 0u;
-      end[s] = l < tile_n ? off_lds[l + 1] : 0u;
-      acc[s] = d4{0.0, 0.0, 0.0, 0.0};
-      maxlen = max(maxlen, end[s] - beg[s]);
-    }
-    u32 win[POOL_NS];  // lane c of the group holds the row id of occurrence (window start + c)
-    for (u32 k = 0; k < maxlen; k += 4) {
-      u32 r[POOL_NS][4];
-      f4 xv[POOL_NS][4];
-      if constexpr (LPR >= 4) {
-        // one coalesced load per group brings the row ids of the next LPR occurrences (a whole
-        // segment, usually); they are handed out by shuffles: a quarter of the memory requests
-        // of one broadcast load per occurrence
-        if (k % LPR == 0) {
+      for (u32 s = 0; s < POOL_NS; ++s) {
+        const u32 l = (rnd * POOL_NS + s) * GROUPS + grp;
+        beg[s] = l < tile_n ? off_lds[l] : P0;
+        end[s] = l < tile_n ? off_lds[l + 1] : P0;
+        acc[s] = d4{0.0, 0.0, 0.0, 0.0};
+        maxlen = max(maxlen, end[s] - beg[s]);
+      }
+      for (u32 k = 0; k < maxlen; k += 4) {
+        u32 r[POOL_NS][4];
+        f4 xv[POOL_NS][4];
 #pragma unroll
-          for (int s = 0; s < POOL_NS; ++s) win[s] = (beg[s] + k + c < end[s]) ? occ_row[beg[s] + k + c] : 0u;
-        }
+        for (u32 s = 0; s < POOL_NS; ++s)
 #pragma unroll
-        for (int s = 0; s < POOL_NS; ++s)
+          for (u32 i = 0; i < 4; ++i) r[s][i] = row_at(min(beg[s] + k + i, P1 - 1u));
 #pragma unroll
-          for (int i = 0; i < 4; ++i) r[s][i] = __shfl(win[s], (int)((k + i) % LPR), LPR);
-      } else {
+        for (u32 s = 0; s < POOL_NS; ++s)
 #pragma unroll
-        for (int s = 0; s < POOL_NS; ++s)
+          for (u32 i = 0; i < 4; ++i) {
+            xv[s][i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+            bool take = beg[s] + k + i < end[s] && col_ok;
+            if constexpr (LOOKUP) take = take && r[s][i] != OCC_INVALID;  // absent keys add nothing
+            if (take) xv[s][i] = ldg4(values + (u64)r[s][i] * rf + 4 * c);
+          }
 #pragma unroll
-          for (int i = 0; i < 4; ++i) r[s][i] = (beg[s] + k + i < end[s]) ? occ_row[beg[s] + k + i] : 0u;
+        for (u32 s = 0; s < POOL_NS; ++s) pool_add4(xv[s], acc[s]);
       }
 #pragma unroll
-      for (int s = 0; s < POOL_NS; ++s)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          xv[s][i].x = xv[s][i].y = xv[s][i].z = xv[s][i].w = 0.0f;
-          bool take = beg[s] + k + i < end[s] && col_ok;
-          if constexpr (OUT & 4) take = take && r[s][i] != OCC_INVALID;  // lookup-only: absent keys add nothing
-          if (take) xv[s][i] = ldg4(values + (u64)r[s][i] * rf + 4 * c);
-        }
-#pragma unroll
-      for (int s = 0; s < POOL_NS; ++s) {  // padded entries add +0.0
-        f4 f = xv[s][0];
-#pragma unroll
-        for (int i = 1; i < 4; ++i) {
-          f.x += xv[s][i].x; f.y += xv[s][i].y; f.z += xv[s][i].z; f.w += xv[s][i].w;
-        }
-        acc[s].x += (double)f.x; acc[s].y += (double)f.y; acc[s].z += (double)f.z; acc[s].w += (double)f.w;
+      for (u32 s = 0; s < POOL_NS; ++s) {
+        const u32 l = (rnd * POOL_NS + s) * GROUPS + grp;
+        if (l < tile_n && col_ok) pool_store<OUT>((u64)tile_g0 + l, D, c, acc[s], pooled, pooled_bf16);
       }
     }
-#pragma unroll
-    for (int s = 0; s < POOL_NS; ++s) {
-      const u32 l = (rnd * POOL_NS + s) * GROUPS + grp;
-      if (l < tile_n && col_ok) {
-        f4 o = {(float)acc[s].x, (float)acc[s].y, (float)acc[s].z, (float)acc[s].w};
-#if CTR_POOL_NT_OUT
-        if constexpr (OUT & 1) stg4_stream(pooled + (u64)(tile_g0 + l) * D + 4 * c, o);
-#else
-        if constexpr (OUT & 1) stg4(pooled + (u64)(tile_g0 + l) * D + 4 * c, o);
-#endif
-        if constexpr (OUT & 2) stg4_bf16(pooled_bf16 + (u64)(tile_g0 + l) * D + 4 * c, o);  // the fp32 value, rounded again
-      }
-    }
+  };
+  if (P1 - P0 <= STAGED) {  // uniform over the block
+    sum_segments([&](u32 p) { return row_lds[p - P0]; });
+  } else {  // segments much longer than usual (their ids were resolved by this block above)
+    sum_segments([&](u32 p) { return occ_row[p]; });
   }
 }
 
+template <int LPR, int OUT>
+__device__ __forceinline__ void pool_small_body(const DevHeader* hdr, u32* __restrict__ occ_row,
+                                                const Slot* __restrict__ slots, u32* __restrict__ seg_of,
+                                                const u32* __restrict__ offsets, u32 n_seg,
+                                                const float* __restrict__ values, u32 D, u32 rf,
+                                                float* __restrict__ pooled, bf16_t* __restrict__ pooled_bf16) {
+  if (hdr->status) return;
+  constexpr bool LOOKUP = (OUT & 4) != 0;
+  const u32 g = (blockIdx.x * BLOCK + threadIdx.x) / LPR, c = threadIdx.x % LPR;
+  if (g >= n_seg) return;
+  const u32 beg = offsets[g], end = offsets[g + 1];
+  const bool col_ok = c * 4 < D;
+  d4 acc = {0.0, 0.0, 0.0, 0.0};
+  for (u32 k = beg; k < end; k += 4) {
+    u32 r[4];
+    f4 xv[4];
+#pragma unroll
+    for (u32 i = 0; i < 4; ++i) r[i] = k + i < end ? occ_row[k + i] : 0u;
+    if constexpr (!LOOKUP) {
+#pragma unroll
+      for (u32 i = 0; i < 4; ++i)
+        if (k + i < end && (r[i] & OCC_PEND_FLAG)) occ_row[k + i] = r[i] = resolve_row(r[i], slots);
+    }
+#pragma unroll
+    for (u32 i = 0; i < 4; ++i) {
+      xv[i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+      bool take = k + i < end && col_ok;
+      if constexpr (LOOKUP) take = take && r[i] != OCC_INVALID;
+      if (take) xv[i] = ldg4(values + (u64)r[i] * rf + 4 * c);
+    }
+    if constexpr (!LOOKUP) {  // lane i % LPR writes entry i
+#pragma unroll
+      for (u32 i = 0; i < 4; ++i)
+        if (k + i < end && i % LPR == c) seg_of[k + i] = g;
+    }
+    pool_add4(xv, acc);
+  }
+  if (col_ok) pool_store<OUT>(g, D, c, acc, pooled, pooled_bf16);
+}
+
 #define CTR_POOL_ARGS                                                                                       \
-  const DevHeader *hdr, const u32 *__restrict__ occ_row, u32 *__restrict__ seg_of,                          \
+  const DevHeader *hdr, u32 *__restrict__ occ_row, const Slot *__restrict__ slots, u32 *__restrict__ seg_of, \
       const u32 *__restrict__ offsets, u32 n_seg, const float *__restrict__ values, u32 D, u32 rf,          \
       float *__restrict__ pooled, bf16_t *__restrict__ pooled_bf16
-#define CTR_DEFINE_POOL(NAME, OUT)                                                            \
-  template <int LPR>                                                                          \
-  __global__ void __launch_bounds__(BLOCK) NAME(CTR_POOL_ARGS) {                              \
-    pool_body<LPR, OUT>(hdr, occ_row, seg_of, offsets, n_seg, values, D, rf, pooled, pooled_bf16); \
+#define CTR_DEFINE_POOL(NAME, OUT)                                                                           \
+  template <int LPR>                                                                                         \
+  __global__ void __launch_bounds__(BLOCK) NAME(CTR_POOL_ARGS) {                                             \
+    pool_body<LPR, OUT>(hdr, occ_row, slots, seg_of, offsets, n_seg, values, D, rf, pooled, pooled_bf16);    \
+  }                                                                                                          \
+  template <int LPR>                                                                                         \
+  __global__ void __launch_bounds__(BLOCK) NAME##_small(CTR_POOL_ARGS) {                                     \
+    pool_small_body<LPR, OUT>(hdr, occ_row, slots, seg_of, offsets, n_seg, values, D, rf, pooled, pooled_bf16); \
   }
 CTR_DEFINE_POOL(k_pool, 1)
 CTR_DEFINE_POOL(k_pool_bf16, 2)
