@@ -26,6 +26,8 @@
 // All dimensions are multiples of 8 (16-byte vectors never straddle an edge); tiles that stick out
 // of the matrices are zero-filled on load and clipped on store.
 #pragma once
+#include <algorithm>
+
 #include "common.h"
 
 namespace ctr {
@@ -54,6 +56,7 @@ struct GemmArgs {
   u32 lda, ldb;  // elements between consecutive rows of the operand as stored
   u32 M, N, K;
   u32 n_split, k_per_split;  // K is cut into n_split ranges of k_per_split (a multiple of GEMM_BK)
+  u32 k_per_sum;             // small tiles: the length of the ranges whose sums are taken on their own
   u32 tiles_m, tiles_n;
   float* C32;
   bf16_t* C16;
@@ -396,37 +399,267 @@ k_gemm_bf16(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Bp, GemmAr
   gemm_write_tile(g, g.n_split > 1 ? (int)EPI_PARTIAL : g.epilogue, acc, gemm_lds, m0 + wm * 128, n0 + wn * 128, split);
 }
 
+// ---------------------------------------------------------------- smaller tiles
+//
+// The 256 x 256 tile leaves the chip idle when the product has few of them: 1000 x 400 outputs are 8 tiles, and
+// each walks its contraction alone, one memory latency per step.  This kernel takes T x T tiles, T = 128 (steps of
+// 64) or 64 (steps of 128), 4 waves of T/2 x T/2, two workgroups per CU.  Bound by latency and by LDS bandwidth,
+// not by the matrix cores, so requests run up to three steps ahead: half of the workgroup's threads carry the tile of A and
+// half the tile of B (8 vectors of 16 bytes per thread and step, the same for both tile sizes and both layouts), in
+// two register sets that are refilled as soon as they have been staged into the other of two LDS buffers.
+// LDS rows hold the step's k values as chunks of 16 bytes, chunk c of row r at c ^ ((r ^ r / 8) & 7): the 8 lanes
+// served together fall on 8 chunk columns for the fragment reads (8 consecutive rows), for the writes of a
+// k-contiguous operand (8 chunks of a row) and for those of a transposed one (lanes along the rows, 8 apart, so that
+// the loads of a wave cover 128 contiguous bytes of memory).
+// A result has the same bits whatever the tile: every element is the sum of its ranges' sums (gemm_sum_ranges), each
+// accumulated along k by the same matrix instruction.  A work item that takes all ranges folds each finished one into
+// `sum`, one that takes a single range leaves it for k_gemm_reduce.
+// Measured, best split of each (us, 256-wide tiles -> these): 1000 x 400 x 624 22 -> 8.3; 8 x 1024 x 19200 33 -> 17;
+// 4096 x 512 x 1024 33 -> 16; 4096 x 1024 x 512 26 -> 14; 16384 x 512 x 1024 51 -> 34; 640 x 96 x 16384 37 -> 21.
+// 4096 x 3200 x 1024 41 -> 53 and larger stay with the large tile.
+constexpr u32 SMALL_TILE_ELEMS = 8192;                  // T * steps: one operand tile, 16 KB
+constexpr u32 SMALL_LDS_BYTES = 4 * 2 * SMALL_TILE_ELEMS;
+
+template <int T>
+__device__ __forceinline__ char* small_lds_at(char* tile, u32 row, u32 chunk) {
+  const u32 swizzle = (T == 128 ? row : row ^ (row >> 3)) & 7u;
+  return tile + row * (2 * SMALL_TILE_ELEMS / T) + ((chunk ^ swizzle) << 4);
+}
+
+// This thread's share of an operand tile: rows and k chunk, as in gemm_offsets.
+template <int T, bool KC>
+struct SmallShare {
+  static constexpr u32 CHUNKS = SMALL_TILE_ELEMS / T / 8;  // of 8 k values, per step
+  u32 kb, rb;                                              // k-contiguous: rows rb + (128 / CHUNKS) j; else 8 rb + j
+  __device__ __forceinline__ explicit SmallShare(u32 t)
+      : kb(KC || T == 128 ? t % CHUNKS : t / (T / 8)), rb(KC || T == 128 ? t / CHUNKS : t % (T / 8)) {}
+  __device__ __forceinline__ void offsets(u32 ld, u32 rows_total, u32 row0, u32 (&off)[8]) const {
+#pragma unroll
+    for (u32 j = 0; j < 8; ++j) {
+      if constexpr (KC) {
+        const u32 row = row0 + rb + (128 / CHUNKS) * j;
+        off[j] = ((row < rows_total ? row : 0u) * ld + kb * 8) * 2u;
+      } else {
+        const u32 row = row0 + rb * 8;
+        off[j] = ((kb * 8 + j) * ld + (row < rows_total ? row : 0u)) * 2u;
+      }
+    }
+  }
+  __device__ __forceinline__ void stage(char* tile, const u32x4 (&R)[8]) const {
+    if constexpr (KC) {
+#pragma unroll
+      for (u32 j = 0; j < 8; ++j)
+        *reinterpret_cast<u32x4*>(small_lds_at<T>(tile, rb + (128 / CHUNKS) * j, kb)) = R[j];
+    } else {
+      u32x4 X[8];
+      gemm_transpose8x8(R, X);
+#pragma unroll
+      for (u32 i = 0; i < 8; ++i) *reinterpret_cast<u32x4*>(small_lds_at<T>(tile, rb * 8 + i, kb)) = X[i];
+    }
+  }
+};
+
+template <int T, bool A_KC, bool B_KC>
+__global__ void __launch_bounds__(256, 2)
+k_gemm_small(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Bp, GemmArgs g) {
+  constexpr u32 BK = SMALL_TILE_ELEMS / T, F = T / 64;  // F x F accumulators of 32 x 32 per wave
+  constexpr u32 TILE_BYTES = 2 * SMALL_TILE_ELEMS;
+  __shared__ __align__(16) char lds[SMALL_LDS_BYTES];   // A0 A1 B0 B1
+  const u32 tiles = g.tiles_m * g.tiles_n, total = tiles * g.n_split;
+  u32 id = blockIdx.x;  // one XCD gets a contiguous range of work items, as above
+  if (total % 8u == 0u) id = (blockIdx.x % 8u) * (total / 8u) + blockIdx.x / 8u;
+  const u32 split = id / tiles, tid = id % tiles;
+  const u32 group_size = GEMM_GROUP_M * g.tiles_n;
+  const u32 first_m = (tid / group_size) * GEMM_GROUP_M;
+  const u32 gm = min(GEMM_GROUP_M, g.tiles_m - first_m);
+  const u32 m0 = (first_m + (tid % group_size) % gm) * T, n0 = ((tid % group_size) / gm) * T;
+  const u32 k_begin = split * g.k_per_split, k_end = min(g.K, k_begin + g.k_per_split);
+  const u32 n_steps = (k_end - k_begin + BK - 1) / BK;  // the last one may reach beyond k_end
+
+  const u32 w = (u32)__builtin_amdgcn_readfirstlane(wave_id()), lane = (u32)lane_id();
+  const bool of_a = w < 2;  // waves 0, 1 carry A, waves 2, 3 carry B
+  const SmallShare<T, A_KC> share_a(threadIdx.x & 127u);
+  const SmallShare<T, B_KC> share_b(threadIdx.x & 127u);
+  const u32 kb = of_a ? share_a.kb : share_b.kb;
+  u32 off[8];
+  if (of_a)
+    share_a.offsets(g.lda, g.M, m0, off);
+  else
+    share_b.offsets(g.ldb, g.N, n0, off);
+  const char* first = reinterpret_cast<const char*>(of_a ? Ap : Bp);
+  const u64 k_bytes = 2ull * ((of_a ? A_KC : B_KC) ? 1u : (of_a ? g.lda : g.ldb));  // bytes from one k to the next
+  char* const my_tile = lds + (of_a ? 0u : 2u * TILE_BYTES);
+
+  // vectors beyond k_end are requested from the operand's first bytes (always readable) and replaced by zeros when staged
+  const auto fetch = [&](u32 s, u32x4 (&R)[8]) {
+    if (s >= n_steps) return;
+    const u32 k0 = k_begin + s * BK;
+    const char* base = first + (u64)k0 * k_bytes;
+    if (k0 + BK <= k_end) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) R[j] = *reinterpret_cast<const u32x4*>(base + off[j]);
+    } else {
+      const bool in = k0 + kb * 8 < k_end;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) R[j] = *reinterpret_cast<const u32x4*>(in ? base + off[j] : first);
+    }
+  };
+  const auto stage = [&](u32 s, u32x4 (&R)[8]) {
+    if (s >= n_steps) return;
+    const u32 k0 = k_begin + s * BK;
+    if (k0 + BK > k_end && k0 + kb * 8 >= k_end) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) R[j] = u32x4{0u, 0u, 0u, 0u};
+    }
+    char* tile = my_tile + (s & 1u) * TILE_BYTES;
+    if (A_KC == B_KC || of_a)
+      share_a.stage(tile, R);
+    else
+      share_b.stage(tile, R);
+  };
+
+  f32x16 acc[F][F], sum[F][F];
+#pragma unroll
+  for (u32 mi = 0; mi < F; ++mi)
+#pragma unroll
+    for (u32 ni = 0; ni < F; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = sum[mi][ni][r] = 0.0f;
+  const auto fold = [&]() {
+#pragma unroll
+    for (u32 mi = 0; mi < F; ++mi)
+#pragma unroll
+      for (u32 ni = 0; ni < F; ++ni)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          sum[mi][ni][r] += acc[mi][ni][r];
+          acc[mi][ni][r] = 0.0f;
+        }
+  };
+  u32 left = g.k_per_sum / GEMM_BK;  // 64-blocks of k until the range ends
+  const u32 wm = w >> 1, wn = w & 1u, frag_row = lane & 31u, frag_half = lane >> 5;
+  // fragments of sub-step kk + 1 are read while the products of sub-step kk run; the scheduling barriers keep the
+  // compiler from reading more ahead than that (it would spill)
+  const auto multiply = [&](u32 s) {
+    char* ta = lds + (s & 1u) * TILE_BYTES;
+    char* tb = ta + 2 * TILE_BYTES;
+    bf16x8 a[2][F], b[2][F];
+    const auto read = [&](u32 kk) {
+#pragma unroll
+      for (u32 i = 0; i < F; ++i) {
+        const u32 row = i * 32 + frag_row, chunk = 2 * kk + frag_half;
+        a[kk & 1u][i] = *reinterpret_cast<const bf16x8*>(small_lds_at<T>(ta, wm * (T / 2) + row, chunk));
+        b[kk & 1u][i] = *reinterpret_cast<const bf16x8*>(small_lds_at<T>(tb, wn * (T / 2) + row, chunk));
+      }
+    };
+    read(0);
+#pragma unroll
+    for (u32 kk = 0; kk < BK / 16; ++kk) {
+      if (kk + 1 < BK / 16) read(kk + 1);
+      if (kk % (GEMM_BK / 16) == 0) {
+        if (left == 0) {
+          fold();
+          left = g.k_per_sum / GEMM_BK;
+        }
+        --left;
+      }
+#pragma unroll
+      for (u32 mi = 0; mi < F; ++mi)
+#pragma unroll
+        for (u32 ni = 0; ni < F; ++ni)
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk & 1u][mi], b[kk & 1u][ni], acc[mi][ni], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  // One barrier per step: the buffer staged in step s was last read in step s - 1, before its barrier.
+  u32x4 r0[8];
+  fetch(0, r0);
+  if constexpr (T == 64) {
+    u32x4 r1[8];
+    fetch(1, r1);
+    stage(0, r0);
+    fetch(2, r0);
+    __syncthreads();
+    for (u32 s = 0; s < n_steps; s += 2) {
+      multiply(s);
+      stage(s + 1, r1);
+      fetch(s + 3, r1);
+      __syncthreads();
+      if (s + 1 >= n_steps) break;
+      multiply(s + 1);
+      stage(s + 2, r0);
+      fetch(s + 4, r0);
+      __syncthreads();
+    }
+  } else {
+    stage(0, r0);
+    fetch(1, r0);
+    __syncthreads();
+    for (u32 s = 0; s < n_steps; ++s) {
+      multiply(s);
+      stage(s + 1, r0);
+      fetch(s + 2, r0);
+      __syncthreads();
+    }
+  }
+
+  // sums to rows through LDS (free after the loop's last barrier), each wave in its own region
+  fold();
+  constexpr u32 TW = T / 2, LPRow = TW / 4;  // lanes that read back one row
+  float* region = reinterpret_cast<float*>(lds) + w * (TW * TW);
+#pragma unroll
+  for (u32 mi = 0; mi < F; ++mi)
+#pragma unroll
+    for (u32 ni = 0; ni < F; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        region[(mi * 32 + 8 * (r / 4) + 4 * frag_half + (r % 4)) * TW + ni * 32 + frag_row] = sum[mi][ni][r];
+  __syncthreads();
+  const int epilogue = g.n_split > 1 ? (int)EPI_PARTIAL : g.epilogue;
+  const u32 n = n0 + wn * TW + (lane % LPRow) * 4;
+  for (u32 row = lane / LPRow; row < TW; row += WAVE / LPRow) {
+    const u32 m = m0 + wm * TW + row;
+    const f4 v = *reinterpret_cast<const f4*>(region + row * TW + (lane % LPRow) * 4);
+    if (m < g.M && n < g.N) gemm_emit4(g, epilogue, m, n, v, split);
+  }
+}
+static_assert(SMALL_LDS_BYTES == 4 * 64 * 64 * sizeof(float), "a wave's accumulators fit its quarter of the buffers");
+
 // Second launch of a split product: adds the partial tiles in the order of the splits and applies the epilogue.
 __global__ void __launch_bounds__(BLOCK) k_gemm_reduce(GemmArgs g) {
   const u64 i4 = ((u64)blockIdx.x * BLOCK + threadIdx.x) * 4;  // 4 consecutive columns of one row
   const u64 mn = (u64)g.M * g.N;
   if (i4 >= mn) return;
   f4 s = ldg4(g.partial + i4);
-  for (u32 sp = 1; sp < g.n_split; ++sp) {
-    const f4 p = ldg4(g.partial + sp * mn + i4);
-    s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+  for (u32 sp = 1; sp < g.n_split; sp += 8) {  // eight partials are requested together and added in order
+    f4 p[8];
+#pragma unroll
+    for (u32 j = 0; j < 8; ++j) p[j] = ldg4(g.partial + min(sp + j, g.n_split - 1u) * mn + i4);
+#pragma unroll
+    for (u32 j = 0; j < 8; ++j)
+      if (sp + j < g.n_split) {
+        s.x += p[j].x; s.y += p[j].y; s.z += p[j].z; s.w += p[j].w;
+      }
   }
   gemm_emit4(g, g.epilogue, (u32)(i4 / g.N), (u32)(i4 % g.N), s, 0);
 }
 
 // ---------------------------------------------------------------- host side
 
-// How a product of this size is cut into work items: 256 x 256 tiles, and the number of ranges the
-// contraction is split into.  The split is the one that minimises (rounds of 256 workgroups) x
-// (contraction steps per work item + a fixed cost per item) + the cost of adding the partials.
-struct GemmPlan {
-  u32 tiles_m, tiles_n, n_split, k_per_split;
-  size_t partial_bytes;  // fp32 scratch the split needs (0 when n_split == 1)
+// The ranges of K whose sums are taken on their own and then added in order: a property of the product's size, so
+// that its result does not depend on how it is executed.  The cut is the one that minimises (rounds of 256
+// workgroups with 256 x 256 tiles) x (contraction steps per work item + a fixed cost per item) + the cost of adding
+// the partials, within the scratch there is for them.
+struct GemmRanges {
+  u32 n, length;  // length: a multiple of GEMM_BK
 };
 
-inline GemmPlan gemm_plan(u32 M, u32 N, u32 K, size_t partial_capacity) {
-  GemmPlan p;
-  p.tiles_m = (M + GEMM_BM - 1) / GEMM_BM;
-  p.tiles_n = (N + GEMM_BN - 1) / GEMM_BN;
-  const double tiles = (double)p.tiles_m * p.tiles_n, cus = 256.0;
+inline GemmRanges gemm_sum_ranges(u32 M, u32 N, u32 K, size_t partial_capacity) {
+  const double tiles = (double)((M + GEMM_BM - 1) / GEMM_BM) * ((N + GEMM_BN - 1) / GEMM_BN), cus = 256.0;
   const u32 k_steps = (K + GEMM_BK - 1) / GEMM_BK;
   double best = 0.0;
-  p.n_split = 1;
+  u32 n = 1;
   for (u32 s = 1; s <= 32 && s <= k_steps; ++s) {
     const u32 steps_per = (k_steps + s - 1) / s;
     if (s > 1 && steps_per < 4) break;
@@ -438,30 +671,75 @@ inline GemmPlan gemm_plan(u32 M, u32 N, u32 K, size_t partial_capacity) {
     const double cost = rounds * (steps_per + 2.0) + (s > 1 ? (s + 1.0) * M * N * 4.0 / 4e12 / 3e-6 : 0.0);
     if (s == 1 || cost < best) {
       best = cost;
-      p.n_split = s;
+      n = s;
     }
   }
-  const u32 steps_per = (k_steps + p.n_split - 1) / p.n_split;
-  p.k_per_split = steps_per * GEMM_BK;
-  p.n_split = (k_steps + steps_per - 1) / steps_per;  // no empty range at the end
-  p.partial_bytes = p.n_split > 1 ? (size_t)p.n_split * M * N * sizeof(float) : 0;
+  const u32 steps_per = (k_steps + n - 1) / n;
+  return {(k_steps + steps_per - 1) / steps_per, steps_per * GEMM_BK};  // no empty range at the end
+}
+
+// How a product is cut into work items: the tile, and whether an item takes one range of the contraction or all.
+struct GemmPlan {
+  u32 tile, tiles_m, tiles_n, n_split, k_per_split, k_per_sum;
+  double cost;  // estimated time, us
+};
+
+// Times the plan is made from, in us, fitted to sweeps over tile and split of 45 products from 8 x 256 x 512 to
+// 19200 x 1024 x 16384 (which it predicts to about a fifth).
+struct GemmTileCost {
+  u32 tile, bk;
+  double fixed;         // launch, first requests and epilogue of a work item
+  double step1, step2;  // a contraction step with one work item per CU, with two
+  double next;          // an item that follows another one
+};
+constexpr GemmTileCost GEMM_TILE_COSTS[3] = {
+    {256, GEMM_BK, 10.0, 2.3, 2.3, 10.0},  // one work item per CU
+    {128, SMALL_TILE_ELEMS / 128, 5.5, 1.1, 1.75, 1.0},
+    {64, SMALL_TILE_ELEMS / 64, 3.3, 0.9, 1.45, 0.8},
+};
+// A small tile requests two or four times the operand bytes of a large one.  They come from the L2s and the 256 MB
+// last-level cache at about 9 TB/s; operands that do not stay there come at half that rate (16384 x 1024 x 19200,
+// 630 MB of A: 0.84 ms with the large tile, 1.18 ms with T = 128, where the steps alone would be 0.5 ms).
+constexpr double GEMM_SMALL_TILE_OPERAND_BYTES = 128.0 * (1 << 20), GEMM_STREAMING_FACTOR = 2.2;
+
+inline GemmPlan gemm_plan_one(const GemmTileCost& c, bool split, const GemmRanges& ranges, u32 M, u32 N, u32 K) {
+  GemmPlan p;
+  p.tile = c.tile;
+  p.tiles_m = (M + c.tile - 1) / c.tile;
+  p.tiles_n = (N + c.tile - 1) / c.tile;
+  p.n_split = split ? ranges.n : 1;
+  p.k_per_sum = ranges.length;
+  p.k_per_split = split ? ranges.length : ranges.length * ranges.n;
+  const bool streaming = c.tile != 256 && 2.0 * K * ((double)M + N) > GEMM_SMALL_TILE_OPERAND_BYTES;
+  const u64 items = (u64)p.tiles_m * p.tiles_n * p.n_split, per_round = c.tile == 256 ? 256 : 512;
+  const u64 full = items / per_round, rest = items % per_round;
+  const u32 steps = (std::min(K, p.k_per_split) + c.bk - 1) / c.bk;
+  const double rest_step = rest == 0 ? 0.0 : (rest <= 256 ? c.step1 : c.step2);
+  p.cost = c.fixed + steps * (streaming ? GEMM_STREAMING_FACTOR : 1.0) * (full * c.step2 + rest_step) +
+           (full + (rest ? 1 : 0) - 1.0) * c.next;
+  // the second launch; the partials move at about 5 TB/s
+  if (p.n_split > 1) p.cost += 4.0 + (p.n_split + 1.0) * M * N * 4.0 / 5e6;
   return p;
 }
 
-// Enqueues C = A B with the epilogue in `g` (operands, sizes, outputs and epilogue fields filled in by
-// the caller).  partial: fp32 scratch of partial_capacity bytes for split products.
-inline hipError_t gemm_enqueue(bool a_kc, bool b_kc, GemmArgs g, float* partial, size_t partial_capacity,
-                               hipStream_t st) {
-  if (g.M == 0 || g.N == 0 || g.K == 0) return hipErrorInvalidValue;
-  if ((g.M | g.N | g.K | g.lda | g.ldb) % 8u != 0u) return hipErrorInvalidValue;
-  // lanes address an operand with 32-bit byte offsets
-  const u64 a_bytes = 2ull * g.lda * (a_kc ? g.M : g.K), b_bytes = 2ull * g.ldb * (b_kc ? g.N : g.K);
-  if (a_bytes >= (1ull << 32) || b_bytes >= (1ull << 32)) return hipErrorInvalidValue;
-  const GemmPlan p = gemm_plan(g.M, g.N, g.K, partial ? partial_capacity : 0);
+inline GemmPlan gemm_plan(u32 M, u32 N, u32 K, size_t partial_capacity) {
+  const GemmRanges ranges = gemm_sum_ranges(M, N, K, partial_capacity);
+  GemmPlan best = gemm_plan_one(GEMM_TILE_COSTS[0], true, ranges, M, N, K);
+  for (int i = 1; i < 3; ++i)
+    for (bool split : {false, true}) {
+      const GemmPlan p = gemm_plan_one(GEMM_TILE_COSTS[i], split, ranges, M, N, K);
+      if (p.cost < best.cost) best = p;
+    }
+  return best;
+}
+
+// Enqueues C = A B as planned (operands, sizes, outputs and epilogue fields of `g` filled in by the caller).
+inline hipError_t gemm_launch(bool a_kc, bool b_kc, GemmArgs g, const GemmPlan& p, float* partial, hipStream_t st) {
   g.tiles_m = p.tiles_m;
   g.tiles_n = p.tiles_n;
   g.n_split = p.n_split;
   g.k_per_split = p.k_per_split;
+  g.k_per_sum = p.k_per_sum;
   g.partial = partial;
   const u32 grid = p.tiles_m * p.tiles_n * p.n_split;
   hipError_t rc = hipSuccess;
@@ -476,24 +754,54 @@ inline hipError_t gemm_enqueue(bool a_kc, bool b_kc, GemmArgs g, float* partial,
     }                                                                                                             \
     hipLaunchKernelGGL((k_gemm_bf16<AK, BK_, EA>), dim3(grid), dim3(BLOCK), GEMM_LDS_BYTES, st, g.A, g.B, g);     \
   } while (0)
-  const bool early = p.k_per_split / GEMM_BK >= 32;  // steps per work item
-  const int which = (a_kc ? 4 : 0) | (b_kc ? 2 : 0) | (early ? 1 : 0);
-  switch (which) {
-    case 7: CTR_GEMM_LAUNCH(true, true, true); break;
-    case 6: CTR_GEMM_LAUNCH(true, true, false); break;
-    case 5: CTR_GEMM_LAUNCH(true, false, true); break;
-    case 4: CTR_GEMM_LAUNCH(true, false, false); break;
-    case 3: CTR_GEMM_LAUNCH(false, true, true); break;
-    case 2: CTR_GEMM_LAUNCH(false, true, false); break;
-    case 1: CTR_GEMM_LAUNCH(false, false, true); break;
-    default: CTR_GEMM_LAUNCH(false, false, false); break;
+#define CTR_GEMM_LAUNCH_SMALL(T, AK, BK_) \
+  hipLaunchKernelGGL((k_gemm_small<T, AK, BK_>), dim3(grid), dim3(BLOCK), 0, st, g.A, g.B, g)
+  const int layout = (a_kc ? 2 : 0) | (b_kc ? 1 : 0);
+  if (p.tile == 256) {
+    const bool early = p.k_per_split / GEMM_BK >= 32;  // steps per work item
+    switch (layout * 2 + (early ? 1 : 0)) {
+      case 7: CTR_GEMM_LAUNCH(true, true, true); break;
+      case 6: CTR_GEMM_LAUNCH(true, true, false); break;
+      case 5: CTR_GEMM_LAUNCH(true, false, true); break;
+      case 4: CTR_GEMM_LAUNCH(true, false, false); break;
+      case 3: CTR_GEMM_LAUNCH(false, true, true); break;
+      case 2: CTR_GEMM_LAUNCH(false, true, false); break;
+      case 1: CTR_GEMM_LAUNCH(false, false, true); break;
+      default: CTR_GEMM_LAUNCH(false, false, false); break;
+    }
+  } else if (p.tile == 128) {
+    switch (layout) {
+      case 3: CTR_GEMM_LAUNCH_SMALL(128, true, true); break;
+      case 2: CTR_GEMM_LAUNCH_SMALL(128, true, false); break;
+      case 1: CTR_GEMM_LAUNCH_SMALL(128, false, true); break;
+      default: CTR_GEMM_LAUNCH_SMALL(128, false, false); break;
+    }
+  } else {
+    switch (layout) {
+      case 3: CTR_GEMM_LAUNCH_SMALL(64, true, true); break;
+      case 2: CTR_GEMM_LAUNCH_SMALL(64, true, false); break;
+      case 1: CTR_GEMM_LAUNCH_SMALL(64, false, true); break;
+      default: CTR_GEMM_LAUNCH_SMALL(64, false, false); break;
+    }
   }
 #undef CTR_GEMM_LAUNCH
+#undef CTR_GEMM_LAUNCH_SMALL
   if (g.n_split > 1) {
     const u64 mn = (u64)g.M * g.N;
     hipLaunchKernelGGL(k_gemm_reduce, dim3((u32)((mn / 4 + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, st, g);
   }
   return hipGetLastError();
+}
+
+// partial: fp32 scratch of partial_capacity bytes for split products.
+inline hipError_t gemm_enqueue(bool a_kc, bool b_kc, const GemmArgs& g, float* partial, size_t partial_capacity,
+                               hipStream_t st) {
+  if (g.M == 0 || g.N == 0 || g.K == 0) return hipErrorInvalidValue;
+  if ((g.M | g.N | g.K | g.lda | g.ldb) % 8u != 0u) return hipErrorInvalidValue;
+  // lanes address an operand with 32-bit byte offsets
+  const u64 a_bytes = 2ull * g.lda * (a_kc ? g.M : g.K), b_bytes = 2ull * g.ldb * (b_kc ? g.N : g.K);
+  if (a_bytes >= (1ull << 32) || b_bytes >= (1ull << 32)) return hipErrorInvalidValue;
+  return gemm_launch(a_kc, b_kc, g, gemm_plan(g.M, g.N, g.K, partial ? partial_capacity : 0), partial, st);
 }
 
 }  // namespace ctr
