@@ -81,17 +81,22 @@ struct WorkLayout {
       off_head, off_tail, off_block_head, off_span_flags, off_span_rows, total;
 };
 
-// How a list of n elements is cut into the chunks the sort's launches work on.
-SortGeom sort_geom(u64 n) {
-  const u64 tiles = (n + SORT_TILE - 1) / SORT_TILE;
-  const u64 chunks = std::min<u64>(std::max<u64>(tiles, 1), SORT_MAX_CHUNKS);
-  const u64 per = (n + chunks - 1) / chunks;
-  const u64 chunk_elems = std::max<u64>(((per + SORT_TILE - 1) / SORT_TILE) * SORT_TILE, SORT_TILE);
-  SortGeom g;
-  g.n = (u32)n;
-  g.chunk_elems = (u32)chunk_elems;
-  g.n_chunks = (u32)std::max<u64>((n + chunk_elems - 1) / chunk_elems, 1);
-  return g;
+inline u32 lanes_per_row(u32 D) {
+  u32 v = D / 4, p = 1;
+  while (p < v) p <<= 1;
+  return p;  // 1..64
+}
+
+// Occurrences per span of the push.  The span walk is sequential, so its parallelism is n / span lane groups:
+// shorter spans for smaller batches, down to what keeps a wave on every SIMD (64 Ki lanes) - the walk of a batch that
+// leaves the chip idle is a chain of dependent loads - but every span border costs partial sums and fix-up work.
+// (73 k occurrences of 8 columns, span walk + fix-up: 28 us with 16, 16 us with 4; 160 k of 16 columns: 31 us with 16, 24 us with 8.)
+inline u32 push_span(u32 D, u64 n) {
+  if (n >= (8u << 20)) return 128;
+  if (n >= (4u << 20)) return 64;
+  if (n >= (2u << 20)) return 32;
+  const u64 lanes = n * lanes_per_row(D);
+  return lanes >= (1u << 20) ? 16 : lanes >= (1u << 19) ? 8 : 4;
 }
 
 // force_span / force_items: 0 = chosen by batch size; otherwise the geometry a test asks for.
@@ -99,8 +104,7 @@ void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force
   const u64 n = n_keys;
   L->n_rank_tiles = (u32)((n + RANK_TILE - 1) / RANK_TILE);
   L->n_rank_groups = (L->n_rank_tiles + RANK_GROUP - 1) / RANK_GROUP;
-  // shorter spans for smaller batches: the span walk is sequential, so parallelism = n / span groups
-  L->span = n >= (8u << 20) ? 128u : n >= (4u << 20) ? 64u : n >= (2u << 20) ? 32u : 16u;
+  L->span = push_span(D, n);
   if (force_span) L->span = force_span;
   L->n_spans = (u32)((n + L->span - 1) / L->span);
   L->n_span_blocks = (L->n_spans + SPANS_PER_BLOCK - 1) / SPANS_PER_BLOCK;
@@ -130,12 +134,6 @@ void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force
   L->off_span_flags = o; o += align256((size_t)L->n_spans * sizeof(u32));
   L->off_span_rows = o; o += align256((size_t)L->n_spans * sizeof(u32));
   L->total = std::max<size_t>(o, 256);
-}
-
-inline u32 lanes_per_row(u32 D) {
-  u32 v = D / 4, p = 1;
-  while (p < v) p <<= 1;
-  return p;  // 1..64
 }
 
 // Which of the two pooling kernels a launch uses, and its grid (table_kernels.h).
@@ -335,7 +333,8 @@ size_t ctr_workspace_bytes(const ctr_config* cfg, uint64_t max_keys, uint32_t ma
   WorkLayout L;
   work_layout(cfg->dim, max_keys, &L);
   size_t need = L.total;
-  for (u64 threshold : {(u64)2 << 20, (u64)4 << 20, (u64)8 << 20}) {
+  const u64 lpr = lanes_per_row(cfg->dim);  // the first size of every span length of push_span
+  for (u64 threshold : {((u64)1 << 19) / lpr, ((u64)1 << 20) / lpr, (u64)2 << 20, (u64)4 << 20, (u64)8 << 20}) {
     if (threshold - 1 < max_keys) {
       work_layout(cfg->dim, threshold - 1, &L);
       need = std::max(need, L.total);
@@ -472,11 +471,7 @@ static int pull_pool_impl(ctr_table* t, uint32_t replica, const uint64_t* d_keys
       const u32 mask = (1u << bits) - 1u;
       u32* kout = (p & 1) ? kb : ka;
       u32* vout = (p & 1) ? vb : va;
-      hipLaunchKernelGGL(k_sort_hist, dim3(wl.geo.n_chunks), dim3(BLOCK), 0, st, t->hdr, kin, wl.geo, shift, mask,
-                         hist);
-      hipLaunchKernelGGL(k_sort_scan, dim3(RADIX), dim3(BLOCK), 0, st, t->hdr, hist, wl.geo.n_chunks, digit_total);
-      hipLaunchKernelGGL(k_sort_scatter, dim3(wl.geo.n_chunks), dim3(BLOCK), 0, st, t->hdr, kin, vin, kout, vout,
-                         wl.geo, shift, mask, hist, digit_total);
+      sort_pass_enqueue(t->hdr, kin, vin, kout, vout, wl.geo, shift, mask, hist, digit_total, st);
       kin = kout;
       vin = vout;
       shift += bits;
@@ -634,7 +629,7 @@ static int push_adam_impl(ctr_table* t, uint32_t replica, ctr_batch* handle, con
                vals, t->vhat, t->row_state, t->D, t->rf, P, head, tail, span_flags, span_rows, order, cold_count)
 #define CTR_FIXUP_LAUNCH(KERNEL)                                                                                 \
   LPR_DISPATCH(t->lpr, KERNEL, fgrid, st, t->hdr, batch->sorted_rows, n, wl.n_spans, wl.span, vals, t->vhat,       \
-               t->row_state, t->D, t->rf, P, head, tail, block_head, span_flags)
+               t->row_state, t->D, t->rf, P, head, tail, block_head, span_flags, span_rows)
     const u32 grid = blocks_for((u64)wl.n_spans * t->lpr);
     const u32 *order = nullptr, *cold_count = nullptr;
     bool hot_launch = false;
@@ -657,10 +652,7 @@ static int push_adam_impl(ctr_table* t, uint32_t replica, ctr_batch* handle, con
         hipLaunchKernelGGL(k_span_keys, dim3(blocks_for(wl.n_spans)), dim3(BLOCK), 0, st, t->hdr, batch->sorted_rows,
                            batch->sorted_segs, n, wl.span, wl.n_spans, seg_shift, t->push_windows,
                            t->push_split == 2u ? 1u : 0u, key_in, val_in);
-        hipLaunchKernelGGL(k_sort_hist, dim3(g2.n_chunks), dim3(BLOCK), 0, st, t->hdr, key_in, g2, 0u, 255u, hist);
-        hipLaunchKernelGGL(k_sort_scan, dim3(RADIX), dim3(BLOCK), 0, st, t->hdr, hist, g2.n_chunks, digit_total);
-        hipLaunchKernelGGL(k_sort_scatter, dim3(g2.n_chunks), dim3(BLOCK), 0, st, t->hdr, key_in, val_in, key_out,
-                           val_out, g2, 0u, 255u, hist, digit_total);
+        sort_pass_enqueue(t->hdr, key_in, val_in, key_out, val_out, g2, 0u, 255u, hist, digit_total, st);
         order = val_out;
         if (t->push_split == 1u) {
           cold_count = digit_total + t->push_windows;  // spans with the key one past the last window
@@ -698,16 +690,14 @@ static int push_adam_impl(ctr_table* t, uint32_t replica, ctr_batch* handle, con
     {
       StageTimer tm(t, CTR_STAGE_FIXUP, st);
       LPR_DISPATCH(t->lpr, k_push_block_heads, blocks_for((u64)wl.n_span_blocks * WAVE), st, t->hdr,
-                   batch->sorted_rows, wl.n_spans, wl.span, t->D, head, block_head, span_flags);
-      const u32 fgrid = blocks_for((u64)wl.n_spans * WAVE);
+                   batch->sorted_rows, wl.n_spans, wl.span, t->D, head, block_head, span_flags, span_rows);
+      const u32 fgrid = blocks_for((u64)wl.n_spans * fixup_lanes(t->lpr));
       switch (kind) {
         case STEP_ADAM_SHARED: CTR_FIXUP_LAUNCH(k_push_fixup_shared); break;
         case STEP_ADAGRAD: CTR_FIXUP_LAUNCH(k_push_fixup_adagrad); break;
         case STEP_ADAM_KINGMA: CTR_FIXUP_LAUNCH(k_push_fixup_kingma); break;
         default: CTR_FIXUP_LAUNCH(k_push_fixup); break;
       }
-      const u32 grid = std::min<u32>(blocks_for(wl.n_spans), 128);
-      hipLaunchKernelGGL(k_count_unique, dim3(grid), dim3(BLOCK), 0, st, t->hdr, span_rows, wl.n_spans);
     }
 #undef CTR_SPAN_LAUNCH
 #undef CTR_FIXUP_LAUNCH

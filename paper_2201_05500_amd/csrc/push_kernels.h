@@ -495,91 +495,151 @@ __device__ __forceinline__ void combine_groups(d4& a) {
   }
 }
 
-// One wave per block of SPANS_PER_BLOCK spans (block j >= 1): sums the heads of the
-// block's leading spans that continue the row open at the block's start.
+// Adds the partial sums first, first + GPW, ... below end in this order.  Wide rows leave a wave few groups and long
+// lists: four partials are requested together.  (Narrower rows lose by the registers: fix-up of 16 columns 10.1 -> 13.7 us, of 64 columns 63 -> 78.)
+template <int LPR>
+__device__ __forceinline__ void add_partials(const double* __restrict__ part, u32 first, u32 end, u32 D, u32 c, d4& a) {
+  constexpr u32 GPW = WAVE / LPR, BATCH = LPR >= 32 ? 4 : 1;
+  for (u32 k = first; k < end; k += BATCH * GPW) {
+    d4 p[BATCH];
+#pragma unroll
+    for (u32 i = 0; i < BATCH; ++i) {
+      p[i] = d4{0.0, 0.0, 0.0, 0.0};
+      if (k + i * GPW < end) add_partial(part, k + i * GPW, D, c, p[i]);
+    }
+#pragma unroll
+    for (u32 i = 0; i < BATCH; ++i) {
+      a.x += p[i].x; a.y += p[i].y; a.z += p[i].z; a.w += p[i].w;
+    }
+  }
+}
+
+// One wave per block of SPANS_PER_BLOCK spans: sums the heads of the block's leading spans that continue the row
+// open at the block's start (block j >= 1), and the block's counts of rows that start in a span, left in the place of
+// the first of them.
 template <int LPR>
 __global__ void __launch_bounds__(BLOCK)
 k_push_block_heads(const DevHeader* hdr, const u32* __restrict__ sr, u32 n_spans, u32 span, u32 D,
                    const double* __restrict__ head_part, double* __restrict__ block_head,
-                   const u32* __restrict__ span_flags) {
+                   const u32* __restrict__ span_flags, u32* __restrict__ span_rows) {
   if (hdr->status) return;
-  constexpr int GPW = WAVE / LPR;
   const u32 j = (blockIdx.x * BLOCK + threadIdx.x) / WAVE;  // wave-uniform
   const u32 first = j * SPANS_PER_BLOCK;
-  if (j == 0 || first >= n_spans) return;
+  if (first >= n_spans) return;
   const int lane = lane_id();
+  const u32 t = first + lane;
+  const u32 started = wave_sum(t < n_spans ? span_rows[t] : 0u);
+  if (lane == 0) span_rows[first] = started;
+  if (j == 0) return;
   const u32 c = lane % LPR, grp = lane / LPR;
   const bool col_ok = c * 4 < D;
   const u32 row = sr[first * span - 1];
-  const u32 t = first + lane;
   const u32 n_lead = leading_true(t < n_spans && (span_flags[t] >> 2) == row);  // coalesced, unlike sr[t * span]
   if (n_lead == 0) return;
   d4 acc = {0.0, 0.0, 0.0, 0.0};
-  if (col_ok)
-    for (u32 k = grp; k < n_lead; k += GPW) add_partial(head_part, first + k, D, c, acc);
+  if (col_ok) add_partials<LPR>(head_part, first + grp, first + n_lead, D, c, acc);
   combine_groups<LPR>(acc);
   if (grp == 0 && col_ok) store_partial(block_head, j, D, c, acc);
 }
 
-// One wave per span that holds a tail: tail + heads of the following spans of
-// the same block + block sums of the following blocks, while they continue
-// the same row; then the row update.
+// Rows that cross span borders: one group of LPR lanes per span that holds a tail adds the heads of the following
+// spans while they continue the row, then updates the row.  Nearly all end within FIXUP_NEAR spans.  Longer ones are
+// then taken by the whole wave, one after the other: the heads of the rest of the span's block and the block sums of
+// the following blocks, spread over the wave's groups.  Bound by its chain of dependent loads (flags, partials, row),
+// so the groups have to be many: with a wave for every span only 4 of 64 lanes worked on rows of 16 columns (80 k
+// spans 17.3 -> FIXUP_US_A us, 300 k spans of 64 columns 88 -> FIXUP_US_B us).  Not less than 16 lanes per span, though: the
+// long rows of a wave's spans wait for each other (2 lanes: 8.8 us for 4.6 k spans that take 4.6).
+// The first workgroup also adds up the blocks' counts of rows: the distinct keys of the batch.  (In a launch of its
+// own that cost 2.5 to 6.5 us; with an atomic per workgroup of the launch before, 6 us at 300 k spans.)
+constexpr u32 FIXUP_NEAR = 4, FIXUP_MIN_LANES = 16;
+constexpr u32 fixup_lanes(u32 lpr) { return lpr < FIXUP_MIN_LANES ? FIXUP_MIN_LANES : lpr; }
+
 template <int LPR, int KIND>
-__device__ __forceinline__ void push_fixup_body(const DevHeader* hdr, const u32* __restrict__ sr, u32 n, u32 n_spans,
+__device__ __forceinline__ void push_fixup_body(DevHeader* hdr, const u32* __restrict__ sr, u32 n, u32 n_spans,
                                                 u32 span, float* __restrict__ values,
                                                 const float* __restrict__ vhat, u32* __restrict__ row_state, u32 D,
                                                 u32 rf, const AdamParams& P_in, const double* __restrict__ head_part,
                                                 const double* __restrict__ tail_part,
                                                 const double* __restrict__ block_head,
-                                                const u32* __restrict__ span_flags) {
+                                                const u32* __restrict__ span_flags,
+                                                const u32* __restrict__ span_rows) {
   if (hdr->status) return;
   AdamParams P = P_in;
   if constexpr (KIND == STEP_ADAM_KINGMA) {
     P.bc1 = hdr->bc1;
     P.bc2 = hdr->bc2;
   }
-  constexpr int GPW = WAVE / LPR;
-  const u32 s = (blockIdx.x * BLOCK + threadIdx.x) / WAVE;  // wave-uniform
-  if (s >= n_spans) return;
-  if (!(span_flags[s] & SF_TAIL)) return;
   const int lane = lane_id();
-  const u32 c = lane % LPR, grp = lane / LPR;
-  const bool col_ok = c * 4 < D;
-  const u32 row = sr[(s + 1) * span - 1];  // a tail means the span is full and the list goes on
-  const u32 n_blocks = (n_spans + SPANS_PER_BLOCK - 1) / SPANS_PER_BLOCK;
-  const u32 blk_end = min((s / SPANS_PER_BLOCK + 1) * SPANS_PER_BLOCK, n_spans);
-
-  d4 acc = {0.0, 0.0, 0.0, 0.0};
-  RowState4 st;
-  if (grp == 0 && col_ok) {
-    add_partial(tail_part, s, D, c, acc);
-    st = load_row4<KIND>(values, vhat, row, D, rf, c);
+  if (blockIdx.x == 0) {
+    __shared__ u32 rows[BLOCK / WAVE];
+    u32 sum = 0;
+#pragma unroll 4
+    for (u32 t = threadIdx.x * SPANS_PER_BLOCK; t < n_spans; t += BLOCK * SPANS_PER_BLOCK) sum += span_rows[t];
+    sum = wave_sum(sum);
+    if (lane == 0) rows[wave_id()] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) hdr->n_unique = rows[0] + rows[1] + rows[2] + rows[3];
   }
-  // spans after s inside its block (at most SPANS_PER_BLOCK - 1 = one per lane)
-  const u32 t = s + 1 + lane;
-  const u32 n_in = leading_true(t < blk_end && (span_flags[t] >> 2) == row);
-  if (col_ok)
-    for (u32 k = grp; k < n_in; k += GPW) add_partial(head_part, s + 1 + k, D, c, acc);
-  if (s + 1 + n_in == blk_end) {  // the row reaches the end of the block: go on block by block
-    for (u32 jb = s / SPANS_PER_BLOCK + 1; jb < n_blocks; jb += WAVE) {
-      const u32 jj = jb + lane;
-      const u32 nb = leading_true(jj < n_blocks && (span_flags[jj * SPANS_PER_BLOCK] >> 2) == row);
-      if (col_ok)
-        for (u32 k = grp; k < nb; k += GPW) add_partial(block_head, jb + k, D, c, acc);
-      if (nb < WAVE) break;
+  constexpr u32 LANES = fixup_lanes(LPR);
+  const u32 own = (blockIdx.x * BLOCK + threadIdx.x) / LANES, own_c = lane % LANES;
+  const bool tail = own < n_spans && (span_flags[own] & SF_TAIL);
+  bool far = false;
+  if (tail) {
+    const u32 row = sr[(own + 1) * span - 1];  // a tail means the span is full and the list goes on
+    u32 next[FIXUP_NEAR];
+#pragma unroll
+    for (u32 k = 0; k < FIXUP_NEAR; ++k) next[k] = own + 1 + k < n_spans ? span_flags[own + 1 + k] >> 2 : NO_ROW;
+    u32 n_near = 0;
+#pragma unroll
+    for (u32 k = 0; k < FIXUP_NEAR; ++k) n_near += (n_near == k && next[k] == row) ? 1u : 0u;
+    far = n_near == FIXUP_NEAR;
+    if (!far && own_c * 4 < D) {
+      d4 acc = {0.0, 0.0, 0.0, 0.0};
+      const RowState4 st = load_row4<KIND>(values, vhat, row, D, rf, own_c);
+      add_partial(tail_part, own, D, own_c, acc);
+#pragma unroll
+      for (u32 k = 0; k + 1 < FIXUP_NEAR; ++k)
+        if (k < n_near) add_partial(head_part, own + 1 + k, D, own_c, acc);
+      finish_row_loaded<KIND>(row, st, acc, own_c, true, values, row_state, D, rf, P);
     }
   }
-  combine_groups<LPR>(acc);
-  if (grp == 0) finish_row_loaded<KIND>(row, st, acc, c, col_ok, values, row_state, D, rf, P);
+  const u32 c = lane % LPR, grp = lane / LPR;
+  const bool col_ok = c * 4 < D;
+  for (u64 todo = __ballot(far && own_c == 0); todo; todo &= todo - 1) {
+    const u32 s = __shfl(own, __ffsll((long long)todo) - 1, WAVE);
+    const u32 row = sr[(s + 1) * span - 1];
+    const u32 n_blocks = (n_spans + SPANS_PER_BLOCK - 1) / SPANS_PER_BLOCK;
+    const u32 blk_end = min((s / SPANS_PER_BLOCK + 1) * SPANS_PER_BLOCK, n_spans);
+    d4 acc = {0.0, 0.0, 0.0, 0.0};
+    RowState4 st;
+    if (grp == 0 && col_ok) {
+      add_partial(tail_part, s, D, c, acc);
+      st = load_row4<KIND>(values, vhat, row, D, rf, c);
+    }
+    // spans after s inside its block (at most SPANS_PER_BLOCK - 1 = one per lane)
+    const u32 t = s + 1 + lane;
+    const u32 n_in = leading_true(t < blk_end && (span_flags[t] >> 2) == row);
+    if (col_ok) add_partials<LPR>(head_part, s + 1 + grp, s + 1 + n_in, D, c, acc);
+    if (s + 1 + n_in == blk_end) {  // the row reaches the end of the block: go on block by block
+      for (u32 jb = s / SPANS_PER_BLOCK + 1; jb < n_blocks; jb += WAVE) {
+        const u32 jj = jb + lane;
+        const u32 nb = leading_true(jj < n_blocks && (span_flags[jj * SPANS_PER_BLOCK] >> 2) == row);
+        if (col_ok) add_partials<LPR>(block_head, jb + grp, jb + nb, D, c, acc);
+        if (nb < WAVE) break;
+      }
+    }
+    combine_groups<LPR>(acc);
+    if (grp == 0) finish_row_loaded<KIND>(row, st, acc, c, col_ok, values, row_state, D, rf, P);
+  }
 }
 
 #define CTR_PUSH_FIXUP_ARGS                                                                                     \
-  const DevHeader *hdr, const u32 *__restrict__ sr, u32 n, u32 n_spans, u32 span, float *__restrict__ values,  \
+  DevHeader *hdr, const u32 *__restrict__ sr, u32 n, u32 n_spans, u32 span, float *__restrict__ values,  \
       const float *__restrict__ vhat, u32 *__restrict__ row_state, u32 D, u32 rf, AdamParams P,                \
       const double *__restrict__ head_part, const double *__restrict__ tail_part,                              \
-      const double *__restrict__ block_head, const u32 *__restrict__ span_flags
+      const double *__restrict__ block_head, const u32 *__restrict__ span_flags, const u32 *__restrict__ span_rows
 #define CTR_PUSH_FIXUP_PASS \
-  hdr, sr, n, n_spans, span, values, vhat, row_state, D, rf, P, head_part, tail_part, block_head, span_flags
+  hdr, sr, n, n_spans, span, values, vhat, row_state, D, rf, P, head_part, tail_part, block_head, span_flags, span_rows
 
 #define CTR_DEFINE_PUSH_FIXUP(NAME, KIND)                                    \
   template <int LPR>                                                         \
@@ -590,18 +650,6 @@ CTR_DEFINE_PUSH_FIXUP(k_push_fixup, STEP_ADAM_OWN)
 CTR_DEFINE_PUSH_FIXUP(k_push_fixup_shared, STEP_ADAM_SHARED)
 CTR_DEFINE_PUSH_FIXUP(k_push_fixup_adagrad, STEP_ADAGRAD)
 CTR_DEFINE_PUSH_FIXUP(k_push_fixup_kingma, STEP_ADAM_KINGMA)
-
-// Sum of the per-span counts of rows that start in the span = distinct keys of the batch.
-// The counter is zeroed by the pull (k_scan_tiles).
-__global__ void k_count_unique(DevHeader* hdr, const u32* __restrict__ span_rows, u32 n_spans) {
-  if (hdr->status) return;
-  __shared__ u32 lds[4];
-  u32 s = 0;
-  for (u32 i = blockIdx.x * BLOCK + threadIdx.x; i < n_spans; i += gridDim.x * BLOCK) s += span_rows[i];
-  u32 total;
-  block_exclusive_scan(s, lds, total);
-  if (threadIdx.x == 0 && total) atomicAdd(&hdr->n_unique, total);
-}
 
 // k-step merge.  One group of LPR lanes per row in use; rows nobody touched since the last merge
 // are skipped.  Sums in binary64, rounded once.

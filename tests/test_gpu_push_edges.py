@@ -1,0 +1,51 @@
+"""The push at the edges of its work geometry: the span length by batch size and width, rows that cross one, a few and
+many spans, and the sort's tile sizes.  Oracle and bounds are those of parity_util."""
+import numpy as np
+import pytest
+
+from oracle import ctr_oracle as O
+from tests.parity_util import compare_tables, run_step, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(keys, D, seed):
+    rng = np.random.default_rng(seed)
+    n = len(keys)
+    cuts = np.sort(rng.integers(0, n + 1, max(n // 4, 1) - 1)) if n > 4 else np.zeros(0, np.int64)
+    offsets = np.concatenate([[0], cuts, [n]]).astype(np.uint32)
+    return {"keys": np.asarray(keys, np.uint64), "offsets": offsets,
+            "grad": rng.standard_normal((offsets.size - 1, D)).astype(np.float32)}
+
+
+def _step(keys, D, R, seed=1):
+    from paper_2201_05500_amd.binding import CtrTable
+    gt, ot = CtrTable(R, D, init_seed=3), O.OracleTable(R, D, init_seed=3)
+    for step in range(2):
+        b = _batch(keys, D, seed + step)
+        run_step(gt, ot, to_device(b), b)
+    compare_tables(gt, ot)
+
+
+# rows of 1, 4 spans +- 1 occurrence (a span has 4, 8 or 16 here), and one that crosses many blocks of 64 spans
+@pytest.mark.parametrize("D", [4, 12, 64, 132, 256])
+@pytest.mark.parametrize("run", [3, 15, 16, 17, 63, 64, 65, 81, 1100, 5000])
+def test_rows_across_spans(D, run):
+    lengths = [run, 1, run + 1, 2, run, 7]
+    keys = np.repeat(np.arange(1, len(lengths) + 1), lengths)
+    _step(np.random.default_rng(run).permutation(keys), D, 64)
+
+
+# one below and at the sizes where the span length changes for a width (lanes per row * n = 2^19, 2^20)
+@pytest.mark.parametrize("D,n", [(D, n) for D, lpr in ((8, 2), (100, 32), (256, 64)) for edge in (1 << 19, 1 << 20)
+                                 for n in (edge // lpr - 1, edge // lpr)])
+def test_span_length_changes(D, n):
+    rng = np.random.default_rng(n)
+    _step((5000 ** rng.random(n)).astype(np.uint64) + 1, D, 6000)
+
+
+# the sort's tiles: 1024 elements up to 300000, 2048 up to 1750000
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 299999, 300000, 300001, 1749999, 1750001])
+def test_sort_tiles(n):
+    rng = np.random.default_rng(n)
+    _step((60000 ** rng.random(n)).astype(np.uint64) + 1, 4, 70000)
