@@ -20,6 +20,7 @@ using namespace ctr;
 
 namespace {
 
+static_assert(CTR_MLP_MAX_HIDDEN + 1 <= COLSUM_MAX_JOBS, "a batch sum per hidden layer and one");
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Scratch for products whose contraction is split over several workgroups (gemm_kernels.h): room for
 // four fp32 partial copies of the largest weight gradient, at least 32 MiB, at most 512 MiB.  A product
@@ -78,28 +79,24 @@ void mem_layout(const ctr_mlp_config* c, const MlpLayout& L, MemLayout* M) {
 }
 
 struct WsLayout {
-  u32 max_h;
-  size_t off_h0, off_act[CTR_MLP_MAX_HIDDEN], off_dz[2], off_logits, off_dlogit, off_lterm, off_grads, off_partial,
-      off_gemm, gemm_bytes, total;
+  size_t off_h0, off_act[CTR_MLP_MAX_HIDDEN], off_dz, off_dlogit, off_lterm, off_grads, off_partial, off_gemm,
+      gemm_bytes, total;
 };
 
 void ws_layout(const ctr_mlp_config* c, const MlpLayout& L, u32 B, WsLayout* S) {
-  u32 mh = 8;
-  for (u32 i = 0; i < c->n_hidden; ++i) mh = std::max(mh, c->hidden[i]);
-  S->max_h = mh;
-  size_t o = 0;
+  const u32 last = c->hidden[c->n_hidden - 1];
+  size_t o = 0, n_cols = last;  // columns summed over the batch: every bias, the output layer's weights
+  for (u32 i = 0; i < c->n_hidden; ++i) n_cols += c->hidden[i];
   S->off_h0 = o; o += align256((size_t)B * c->in_dim * sizeof(bf16_t));
   for (u32 i = 0; i < c->n_hidden; ++i) {
     S->off_act[i] = o;
     o += align256((size_t)B * c->hidden[i] * sizeof(bf16_t));
   }
-  S->off_dz[0] = o; o += align256((size_t)B * mh * sizeof(bf16_t));
-  S->off_dz[1] = o; o += align256((size_t)B * mh * sizeof(bf16_t));
-  S->off_logits = o; o += align256((size_t)B * sizeof(float));
+  S->off_dz = o; o += align256((size_t)B * last * sizeof(bf16_t));  // the other layers' dz take the place of act
   S->off_dlogit = o; o += align256((size_t)B * sizeof(float));
   S->off_lterm = o; o += align256((size_t)B * sizeof(double));
   S->off_grads = o; o += align256((size_t)L.n_params * sizeof(float));
-  S->off_partial = o; o += align256((size_t)COLSUM_SLICES * mh * sizeof(float));
+  S->off_partial = o; o += align256(COLSUM_SLICES * n_cols * sizeof(float));
   S->off_gemm = o; S->gemm_bytes = gemm_scratch_bytes(c); o += S->gemm_bytes;
   S->total = o;
 }
@@ -164,10 +161,10 @@ bool product_input_grad(const MlpLayout& L, u32 l, u32 B, const bf16_t* dz, cons
   return gemm_enqueue(true, true, g, (float*)(ws + S.off_gemm), S.gemm_bytes, st) == hipSuccess;
 }
 
-// Forward through the hidden layers and the output layer; activations stay in the workspace.
+// Forward through the hidden layers; activations stay in the workspace.
 // The input is either fp32 (rounded to bf16 into the workspace) or already bf16 (used in place).
-bool forward(ctr_mlp* t, u32 replica, const float* d_pooled, const bf16_t* d_pooled_bf16, u32 B, char* ws,
-             const WsLayout& S, float* logits, hipStream_t st) {
+bool forward_hidden(ctr_mlp* t, u32 replica, const float* d_pooled, const bf16_t* d_pooled_bf16, u32 B, char* ws,
+                    const WsLayout& S, hipStream_t st) {
   const MlpLayout& L = t->L;
   const float* P = t->params + (u64)replica * t->M.stride;
   const bf16_t* PB = t->pb + (u64)replica * t->M.stride;
@@ -182,9 +179,6 @@ bool forward(ctr_mlp* t, u32 replica, const float* d_pooled, const bf16_t* d_poo
     if (!product_forward(L, l, B, h, PB + L.w_off[l], P + L.w_off[l] + (u64)L.in[l] * L.out[l], a, ws, S, st)) return false;
     h = a;
   }
-  const u32 lo = L.n_layers - 1;
-  hipLaunchKernelGGL(k_out_forward, dim3(blocks_for((u64)B * WAVE)), dim3(BLOCK), 0, st, h, PB + L.w_off[lo],
-                     P + L.w_off[lo] + L.in[lo], B, L.in[lo], logits);
   return true;
 }
 
@@ -265,7 +259,14 @@ static int mlp_forward_impl(ctr_mlp* t, uint32_t replica, const float* d_pooled,
   ws_layout(&t->cfg, t->L, batch, &S);
   if (workspace_bytes < S.total) return CTR_E_NOMEM;
   hipStream_t st = (hipStream_t)hip_stream;
-  if (!forward(t, replica, d_pooled, d_pooled_bf16, batch, (char*)d_workspace, S, d_logits, st)) return CTR_E_DEVICE;
+  char* ws = (char*)d_workspace;
+  if (!forward_hidden(t, replica, d_pooled, d_pooled_bf16, batch, ws, S, st)) return CTR_E_DEVICE;
+  const MlpLayout& L = t->L;
+  const u32 lo = L.n_layers - 1;
+  const u64 base = (u64)replica * t->M.stride + L.w_off[lo];
+  hipLaunchKernelGGL(k_out_forward, dim3(blocks_for((u64)batch * WAVE)), dim3(BLOCK), 0, st,
+                     (const bf16_t*)(ws + S.off_act[lo - 1]), t->pb + base, t->params + base + L.in[lo], batch, L.in[lo],
+                     d_logits);
   return launch_status();
 }
 
@@ -288,52 +289,60 @@ static int mlp_step_impl(ctr_mlp* t, uint32_t replica, const float* d_pooled, co
   const MlpLayout& L = t->L;
   char* ws = (char*)d_workspace;
   const u32 B = batch;
-  float* logits = (float*)(ws + S.off_logits);
   float* dlogit = (float*)(ws + S.off_dlogit);
   float* grads = (float*)(ws + S.off_grads);
-  float* partial = (float*)(ws + S.off_partial);
+  const float* P = t->params + (u64)replica * t->M.stride;
   const bf16_t* PB = t->pb + (u64)replica * t->M.stride;
 
   double* lterm = (double*)(ws + S.off_lterm);
   const bf16_t* h0 = d_pooled_bf16 ? d_pooled_bf16 : (const bf16_t*)(ws + S.off_h0);
-  if (!forward(t, replica, d_pooled, d_pooled_bf16, B, ws, S, logits, st)) return CTR_E_DEVICE;
-  hipLaunchKernelGGL(k_bce, dim3(blocks_for(B)), dim3(BLOCK), 0, st, logits, d_labels, B, dlogit, lterm);
-  hipLaunchKernelGGL(k_loss_mean, dim3(1), dim3(BLOCK), 0, st, lterm, B, d_loss);
+  if (!forward_hidden(t, replica, d_pooled, d_pooled_bf16, B, ws, S, st)) return CTR_E_DEVICE;
 
-  // output layer: weight and bias gradients, then back through the last ReLU
+  // output layer: logits, loss terms, and back through the last ReLU
   const u32 lo = L.n_layers - 1;
   const u32 Hl = L.in[lo];
   const bf16_t* a_last = (const bf16_t*)(ws + S.off_act[lo - 1]);
-  hipLaunchKernelGGL(k_colsum_partial, dim3((Hl + 31) / 32, COLSUM_SLICES), dim3(BLOCK), 0, st, a_last, dlogit, B, Hl,
-                     partial);
-  hipLaunchKernelGGL(k_colsum_final, dim3(blocks_for(Hl)), dim3(BLOCK), 0, st, partial, Hl, grads + L.w_off[lo]);
-  hipLaunchKernelGGL(k_sum_f32, dim3(1), dim3(BLOCK), 0, st, dlogit, B, grads + L.w_off[lo] + Hl);
-  bf16_t* dz = (bf16_t*)(ws + S.off_dz[0]);
-  bf16_t* dz_next = (bf16_t*)(ws + S.off_dz[1]);
-  {
-    const u64 n = (u64)B * Hl;
-    hipLaunchKernelGGL(k_out_backward_dz, dim3(blocks_for(n)), dim3(BLOCK), 0, st, a_last, dlogit, PB + L.w_off[lo],
-                       Hl, n, dz);
-  }
+  bf16_t* dz = (bf16_t*)(ws + S.off_dz);
+  hipLaunchKernelGGL(k_out_step, dim3(blocks_for((u64)B * WAVE)), dim3(BLOCK), 0, st, a_last, PB + L.w_off[lo],
+                     P + L.w_off[lo] + Hl, d_labels, B, Hl, dlogit, lterm, dz);
+
+  BatchSums q{};
+  q.rows = B;
+  q.partial = (float*)(ws + S.off_partial);
+  q.lterm = lterm;
+  q.dlogit = dlogit;
+  q.loss = d_loss;
+  q.out_bias_grad = grads + L.w_off[lo] + Hl;
+  const auto add_sum = [&q](const bf16_t* x, const float* weight, u32 H, float* out) {
+    const u32 j = q.n_jobs++;
+    q.x[j] = x;
+    q.weight[j] = weight;
+    q.out[j] = out;
+    q.H[j] = H;
+    q.col0[j] = q.n_cols;
+    q.n_cols += H;
+    q.n_tiles += (H + COLSUM_TILE - 1) / COLSUM_TILE;
+  };
+  add_sum(a_last, dlogit, Hl, grads + L.w_off[lo]);
   // hidden layers, last to first
   for (int l = (int)lo - 1; l >= 0; --l) {
-    const int i = (int)L.in[l], o = (int)L.out[l];
     const bf16_t* h_prev = l == 0 ? h0 : (const bf16_t*)(ws + S.off_act[l - 1]);
     if (!product_weight_grad(L, (u32)l, B, h_prev, dz, grads + L.w_off[l], ws, S, st)) return CTR_E_DEVICE;
-    hipLaunchKernelGGL(k_colsum_partial, dim3((o + 31) / 32, COLSUM_SLICES), dim3(BLOCK), 0, st, dz, (const float*)nullptr,
-                       B, (u32)o, partial);
-    hipLaunchKernelGGL(k_colsum_final, dim3(blocks_for(o)), dim3(BLOCK), 0, st, partial, (u32)o,
-                       grads + L.w_off[l] + (u64)i * o);
+    add_sum(dz, nullptr, L.out[l], grads + L.w_off[l] + (u64)L.in[l] * L.out[l]);
     // dH_prev[B x i] = dZ[B x o] W^T[o x i]: for the first layer the gradient of the pooled input; for a hidden
-    // layer gated by the ReLU below and rounded to bf16 on the way out (the next dZ)
+    // layer gated by the ReLU below and rounded to bf16 on the way out (the next dZ).  It takes the place of the
+    // activation that gates it, which nothing reads any more: an element is read and written by the same thread.
     if (l == 0) {
       if (!product_input_grad(L, 0, B, dz, PB + L.w_off[0], d_grad_pooled, d_grad_pooled_bf16, nullptr, ws, S, st))
         return CTR_E_DEVICE;
     } else {
-      if (!product_input_grad(L, (u32)l, B, dz, PB + L.w_off[l], nullptr, dz_next, h_prev, ws, S, st)) return CTR_E_DEVICE;
-      std::swap(dz, dz_next);
+      bf16_t* below = (bf16_t*)(ws + S.off_act[l - 1]);
+      if (!product_input_grad(L, (u32)l, B, dz, PB + L.w_off[l], nullptr, below, below, ws, S, st)) return CTR_E_DEVICE;
+      dz = below;
     }
   }
+  hipLaunchKernelGGL(k_batch_sums, dim3(2 + q.n_tiles * COLSUM_SLICES), dim3(BLOCK), 0, st, q);
+  hipLaunchKernelGGL(k_batch_sums_final, dim3(blocks_for(q.n_cols)), dim3(BLOCK), 0, st, q);
   // dense optimizer
   const u32 amode = mode == CTR_STEP_MERGE_PENDING ? 2u : (t->cfg.kstep ? 1u : 0u);
   hipLaunchKernelGGL(k_dense_adam, dim3(blocks_for(L.n_params)), dim3(BLOCK), 0, st,

@@ -39,87 +39,127 @@ __global__ void k_out_forward(const bf16_t* __restrict__ a, const bf16_t* __rest
   if (lane == 0) logits[r] = s + bias[0];
 }
 
-// Sigmoid cross-entropy with logits, evaluated in binary64 per sample:
-// lterm[b] = max(z, 0) - z y + log1p(exp(-|z|)) and dlogit[b] = (sigmoid(z) - y) / rows.
-__global__ void k_bce(const float* __restrict__ logits, const float* __restrict__ labels, u32 rows,
-                      float* __restrict__ dlogit, double* __restrict__ lterm) {
-  const u32 r = blockIdx.x * BLOCK + threadIdx.x;
+// Output layer of a training step, forward and back through the last ReLU, one wave per sample: the logit as in
+// k_out_forward; sigmoid cross-entropy with logits in binary64, lterm[b] = max(z, 0) - z y + log1p(exp(-|z|)) and
+// dlogit[b] = (sigmoid(z) - y) / rows; dz[b, j] = bf16(dlogit[b] * w[j] * [a[b, j] > 0]).
+// (In launches of their own the three parts cost a launch each, 4.5 us on a small batch, and a second pass over a.)
+__global__ void __launch_bounds__(BLOCK)
+k_out_step(const bf16_t* __restrict__ a, const bf16_t* __restrict__ w, const float* __restrict__ bias,
+           const float* __restrict__ labels, u32 rows, u32 H, float* __restrict__ dlogit, double* __restrict__ lterm,
+           bf16_t* __restrict__ dz) {
+  const u32 r = (blockIdx.x * BLOCK + threadIdx.x) / WAVE;
   if (r >= rows) return;
-  const double z = (double)logits[r], y = (double)labels[r];
-  lterm[r] = fmax(z, 0.0) - z * y + log1p(exp(-fabs(z)));
-  dlogit[r] = (float)((1.0 / (1.0 + exp(-z)) - y) / (double)rows);
+  const int lane = lane_id();
+  float s = 0.0f;
+  for (u32 j = lane; j < H; j += WAVE) s += from_bf16(a[(u64)r * H + j]) * from_bf16(w[j]);
+#pragma unroll
+  for (int off = WAVE / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, WAVE);
+  const double z = (double)(s + bias[0]), y = (double)labels[r];
+  const float d = (float)((1.0 / (1.0 + exp(-z)) - y) / (double)rows);
+  if (lane == 0) {
+    lterm[r] = fmax(z, 0.0) - z * y + log1p(exp(-fabs(z)));
+    dlogit[r] = d;
+  }
+  for (u32 j = lane; j < H; j += WAVE) {
+    const u64 i = (u64)r * H + j;
+    dz[i] = to_bf16(from_bf16(a[i]) > 0.0f ? d * from_bf16(w[j]) : 0.0f);
+  }
 }
 
-// Mean of the per-sample loss terms, summed by ONE block in a fixed order.
-__global__ void k_loss_mean(const double* __restrict__ lterm, u32 rows, float* __restrict__ loss) {
-  __shared__ double part[BLOCK];
-  double s = 0.0;
-  for (u32 r = threadIdx.x; r < rows; r += BLOCK) s += lterm[r];
+// Sum over the threads of a block, left in part[0], in a fixed order (a binary tree).
+template <class T>
+__device__ __forceinline__ T block_tree_sum(T s, T* part) {
   part[threadIdx.x] = s;
   __syncthreads();
   for (int off = BLOCK / 2; off > 0; off >>= 1) {
     if ((int)threadIdx.x < off) part[threadIdx.x] += part[threadIdx.x + off];
     __syncthreads();
   }
-  if (threadIdx.x == 0) *loss = (float)(part[0] / (double)rows);
+  return part[0];
 }
 
-// Back through the output layer and the last ReLU: dz[b, j] = bf16(dlogit[b] * w[j] * [a[b, j] > 0]).
-__global__ void k_out_backward_dz(const bf16_t* __restrict__ a, const float* __restrict__ dlogit,
-                                  const bf16_t* __restrict__ w, u32 H, u64 n, bf16_t* __restrict__ dz) {
-  const u64 i = (u64)blockIdx.x * BLOCK + threadIdx.x;
-  if (i >= n) return;
-  const u32 j = (u32)(i % H);
-  const float av = from_bf16(a[i]);
-  dz[i] = to_bf16(av > 0.0f ? dlogit[i / H] * from_bf16(w[j]) : 0.0f);
-}
+// The sums over the batch of a training step, all in one launch behind its products: column sums in a fixed order,
+// out[j] = sum_b x[b, j] * (weight ? weight[b] : 1) (bias gradients, the output layer's weight gradient), the mean
+// loss and the output bias gradient.
+// Stage 1: a block takes a tile of columns (a thread 4 neighbouring ones) and a slice of the rows - its 8 row groups
+// each sum the slice's rows congruent to them, the 8 partial sums are added in order -> partial[slice][column].
+// Stage 2: the slices are added in order.
+// (Per layer, with one column per thread and the two scalar sums in launches of their own, a tower of three hidden
+// layers took ten launches here.)
+constexpr u32 COLSUM_SLICES = 64, COLSUM_TILE = 128;
+constexpr u32 COLSUM_MAX_JOBS = 8;  // a sum per hidden layer and one
 
-// Column sums over the batch in a fixed order: out[j] = sum_b x[b, j] * (wgt ? wgt[b] : 1).
-// Stage 1: block (column tile of 32, row slice) - its 8 row groups each sum the slice's rows
-// congruent to them, the 8 partial sums are added in order -> partial[slice][column].
-// Stage 2: the slices are added in order.  Used for bias gradients and the output layer's weights.
-constexpr u32 COLSUM_SLICES = 64;
+struct BatchSums {
+  const bf16_t* x[COLSUM_MAX_JOBS];
+  const float* weight[COLSUM_MAX_JOBS];  // null: 1
+  float* out[COLSUM_MAX_JOBS];
+  u32 H[COLSUM_MAX_JOBS];                // a multiple of 8
+  u32 col0[COLSUM_MAX_JOBS];             // first column of the job in a row of `partial`
+  u32 n_jobs, n_cols, n_tiles, rows;     // n_cols: columns of all jobs, n_tiles: their tiles
+  float* partial;                        // [COLSUM_SLICES][n_cols]
+  const double* lterm;
+  const float* dlogit;
+  float *loss, *out_bias_grad;
+};
 
-__global__ void k_colsum_partial(const bf16_t* __restrict__ x, const float* __restrict__ wgt, u32 rows, u32 H,
-                                 float* __restrict__ partial) {
-  __shared__ float part[8][32];
-  const u32 col = blockIdx.x * 32 + (threadIdx.x & 31);
-  const u32 rg = threadIdx.x >> 5;
-  const u32 per = (rows + COLSUM_SLICES - 1) / COLSUM_SLICES;
-  const u32 r0 = blockIdx.y * per, r1 = min(r0 + per, rows);
-  float s = 0.0f;
-  if (col < H)
-    for (u32 r = r0 + rg; r < r1; r += 8) s += from_bf16(x[(u64)r * H + col]) * (wgt ? wgt[r] : 1.0f);
-  part[rg][threadIdx.x & 31] = s;
+// grid: 2 + n_tiles * COLSUM_SLICES blocks
+__global__ void __launch_bounds__(BLOCK) k_batch_sums(BatchSums q) {
+  __shared__ __align__(16) float part[8][COLSUM_TILE];
+  if (blockIdx.x == 0) {  // mean of the per-sample loss terms
+    double s = 0.0;
+#pragma unroll 8
+    for (u32 r = threadIdx.x; r < q.rows; r += BLOCK) s += q.lterm[r];
+    s = block_tree_sum(s, reinterpret_cast<double*>(part));
+    if (threadIdx.x == 0) *q.loss = (float)(s / (double)q.rows);
+    return;
+  }
+  if (blockIdx.x == 1) {
+    float s = 0.0f;
+#pragma unroll 8
+    for (u32 r = threadIdx.x; r < q.rows; r += BLOCK) s += q.dlogit[r];
+    s = block_tree_sum(s, &part[0][0]);
+    if (threadIdx.x == 0) *q.out_bias_grad = s;
+    return;
+  }
+  u32 tile = (blockIdx.x - 2) % q.n_tiles;
+  const u32 slice = (blockIdx.x - 2) / q.n_tiles;
+  u32 job = 0;
+  while (tile >= (q.H[job] + COLSUM_TILE - 1) / COLSUM_TILE) tile -= (q.H[job++] + COLSUM_TILE - 1) / COLSUM_TILE;
+  const u32 H = q.H[job], rg = threadIdx.x >> 5, in_tile = (threadIdx.x & 31) * 4, col = tile * COLSUM_TILE + in_tile;
+  const u32 per = (q.rows + COLSUM_SLICES - 1) / COLSUM_SLICES;
+  const u32 r0 = slice * per, r1 = min(r0 + per, q.rows);
+  const bf16_t* x = q.x[job] + col;
+  const float* weight = q.weight[job];
+  f4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (col < H) {
+#pragma unroll 4
+    for (u32 r = r0 + rg; r < r1; r += 8) {
+      const ushort4 v = *reinterpret_cast<const ushort4*>(x + (u64)r * H);
+      const float f = weight ? weight[r] : 1.0f;
+      s.x += from_bf16(v.x) * f; s.y += from_bf16(v.y) * f; s.z += from_bf16(v.z) * f; s.w += from_bf16(v.w) * f;
+    }
+  }
+  stg4(&part[rg][in_tile], s);
   __syncthreads();
   if (rg == 0 && col < H) {
-    float t = part[0][threadIdx.x];
 #pragma unroll
-    for (int g = 1; g < 8; ++g) t += part[g][threadIdx.x];
-    partial[(u64)blockIdx.y * H + col] = t;
+    for (int g = 1; g < 8; ++g) {
+      const f4 t = ldg4(&part[g][in_tile]);
+      s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+    }
+    stg4(q.partial + (u64)slice * q.n_cols + q.col0[job] + col, s);
   }
 }
 
-__global__ void k_colsum_final(const float* __restrict__ partial, u32 H, float* __restrict__ out) {
-  const u32 col = blockIdx.x * BLOCK + threadIdx.x;
-  if (col >= H) return;
+__global__ void __launch_bounds__(BLOCK) k_batch_sums_final(BatchSums q) {
+  const u32 c = blockIdx.x * BLOCK + threadIdx.x;
+  if (c >= q.n_cols) return;
   float t = 0.0f;
-  for (u32 sl = 0; sl < COLSUM_SLICES; ++sl) t += partial[(u64)sl * H + col];
-  out[col] = t;
-}
-
-// Sum of a vector (the output bias gradient = sum of dlogit), one block, fixed order.
-__global__ void k_sum_f32(const float* __restrict__ x, u32 n, float* __restrict__ out) {
-  __shared__ float part[BLOCK];
-  float s = 0.0f;
-  for (u32 i = threadIdx.x; i < n; i += BLOCK) s += x[i];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (int off = BLOCK / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) part[threadIdx.x] += part[threadIdx.x + off];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *out = part[0];
+#pragma unroll 16
+  for (u32 sl = 0; sl < COLSUM_SLICES; ++sl) t += q.partial[(u64)sl * q.n_cols + c];
+  u32 job = 0;
+  while (job + 1 < q.n_jobs && c >= q.col0[job + 1]) ++job;
+  q.out[job][c - q.col0[job]] = t;
 }
 
 // Initial parameters of every replica: weights from the integer recipe of the row initialiser with
