@@ -345,10 +345,12 @@ static int mlp_step_impl(ctr_mlp* t, uint32_t replica, const float* d_pooled, co
   hipLaunchKernelGGL(k_batch_sums_final, dim3(blocks_for(q.n_cols)), dim3(BLOCK), 0, st, q);
   // dense optimizer
   const u32 amode = mode == CTR_STEP_MERGE_PENDING ? 2u : (t->cfg.kstep ? 1u : 0u);
-  hipLaunchKernelGGL(k_dense_adam, dim3(blocks_for(L.n_params)), dim3(BLOCK), 0, st,
+  const u64 n4 = L.n_params >= DENSE_ADAM_WIDE_MIN ? L.n_params / 4 : 0;
+  const DenseAdam adam = {(double)t->cfg.beta1, (double)t->cfg.beta2, (double)t->cfg.lr, amode};
+  hipLaunchKernelGGL(k_dense_adam, dim3(blocks_for(L.n_params - 3 * n4)), dim3(BLOCK), 0, st,
                      t->params + (u64)replica * t->M.stride, t->m + (u64)replica * t->M.stride,
                      t->v + (u64)replica * t->M.stride, t->vhat, grads, t->pb + (u64)replica * t->M.stride,
-                     L.n_params, (double)t->cfg.beta1, (double)t->cfg.beta2, (double)t->cfg.lr, amode);
+                     L.n_params, n4, adam);
   if (mode == CTR_STEP_MERGE_PENDING) t->pend_mask |= 1u << replica;
   return launch_status();
 }
