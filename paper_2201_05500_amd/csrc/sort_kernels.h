@@ -9,7 +9,7 @@
 // 64-bit keys.
 //
 // One pass = three launches:
-//   k_sort_hist    per-chunk digit histogram           -> hist[digit][chunk]
+//   k_sort_hist    per-chunk digit histogram           -> hist[digit][chunk] (wide digits: hist[chunk][digit])
 //   k_sort_scan    per digit: exclusive scan over chunks, digit totals
 //   k_sort_scatter per chunk: for each sub-tile, rank elements
 //                  per digit inside each wave with ballots (stable), counting-
@@ -20,6 +20,11 @@
 // an idle chip and take fewer: 300 k elements 17.2 us with 16, 13.8 with 4; 1.25 M 22.1 with 16, 20.0 with 8.
 // (Two launches instead of three, every scatter block adding up the histograms before its own: 8.6 instead of 10.2 us
 // at 20 k elements, but 14.8 instead of 11.3 at 160 k.)
+// Digits have 8 bits, or 10 or 11 where that saves a pass and the list is short.  A pass of a short list costs its
+// three launches and their chains rather than bytes, so fewer passes win: 20-bit keys, 73 k elements 36 -> 29 us,
+// 400 k 46 -> 39, 800 k 54 -> 46; 22-bit keys, 175 k 38 -> 36, 400 k 46 -> 42.  Long lists lose by it: a sub-tile then
+// leaves runs of one or two elements per digit (2.5 M elements, 20 bits 79 -> 83 us, 22 bits 80 -> 92).  Wide digits
+// keep their histograms as [chunk][digit], which a block writes and reads coalesced.
 #pragma once
 #include <algorithm>
 
@@ -28,6 +33,7 @@
 namespace ctr {
 
 constexpr u32 SORT_ITEMS_4_MAX = 300000, SORT_ITEMS_8_MAX = 1750000;  // elements
+constexpr u32 SORT_10_BITS_MAX = 1000000, SORT_11_BITS_MAX = 500000;
 #ifndef CTR_SORT_MAX_CHUNKS
 #define CTR_SORT_MAX_CHUNKS 4096
 #endif
@@ -45,18 +51,23 @@ struct SortGeom {
   u32 items;        // elements per thread of a sub-tile: 4, 8 or 16
 };
 
-__global__ void k_sort_hist(const DevHeader* hdr, const u32* __restrict__ keys, SortGeom geo, u32 shift,
-                            u32 digit_mask, u32* __restrict__ hist) {
+template <int R>
+__global__ void __launch_bounds__(BLOCK)
+k_sort_hist(const DevHeader* hdr, const u32* __restrict__ keys, SortGeom geo, u32 shift, u32 digit_mask,
+            u32* __restrict__ hist) {
   if (hdr->status) return;
-  // HIST_COPIES histograms per wave, chosen by lane: a popular digit (row ids of popular keys share
+  // COPIES histograms per wave, chosen by lane: a popular digit (row ids of popular keys share
   // their high bits) would otherwise serialise all 64 lanes on one LDS address
-  __shared__ u32 h[4 * HIST_COPIES][RADIX];
+  constexpr int COPIES = R == RADIX ? HIST_COPIES : 1;
+  __shared__ u32 h[4 * COPIES][R];
 #pragma unroll
-  for (int i = 0; i < 4 * HIST_COPIES; ++i) h[i][threadIdx.x] = 0;
+  for (int i = 0; i < 4 * COPIES; ++i)
+#pragma unroll
+    for (int q = 0; q < R / BLOCK; ++q) h[i][q * BLOCK + threadIdx.x] = 0;
   __syncthreads();
   const u32 beg = blockIdx.x * geo.chunk_elems;  // multiple of 1024, so 16-byte aligned
   const u32 end = min(beg + geo.chunk_elems, geo.n);
-  u32* mine = h[wave_id() * HIST_COPIES + (lane_id() & (HIST_COPIES - 1))];
+  u32* mine = h[wave_id() * COPIES + (lane_id() & (COPIES - 1))];
   for (u32 e = beg + threadIdx.x * 4; e < end; e += BLOCK * 4) {
     if (e + 4 <= end) {
       const uint4 k4 = *reinterpret_cast<const uint4*>(keys + e);
@@ -77,10 +88,14 @@ __global__ void k_sort_hist(const DevHeader* hdr, const u32* __restrict__ keys, 
     }
   }
   __syncthreads();
-  u32 total = 0;
 #pragma unroll
-  for (int i = 0; i < 4 * HIST_COPIES; ++i) total += h[i][threadIdx.x];
-  hist[threadIdx.x * geo.n_chunks + blockIdx.x] = total;
+  for (int q = 0; q < R / BLOCK; ++q) {
+    const u32 d = q * BLOCK + threadIdx.x;
+    u32 total = 0;
+#pragma unroll
+    for (int i = 0; i < 4 * COPIES; ++i) total += h[i][d];
+    hist[R == RADIX ? d * geo.n_chunks + blockIdx.x : blockIdx.x * R + d] = total;
+  }
 }
 
 // grid = RADIX blocks; block d turns hist[d][0..n_chunks) into exclusive prefix sums.
@@ -104,26 +119,63 @@ __global__ void k_sort_scan(const DevHeader* hdr, u32* __restrict__ hist, u32 n_
   if (threadIdx.x == 0) digit_total[blockIdx.x] = total;
 }
 
-template <int ITEMS>
+// The same for hist[chunk][digit]: a block takes 16 neighbouring digits, 16 groups of threads a share of the chunks.
+__global__ void __launch_bounds__(BLOCK)
+k_sort_scan_wide(const DevHeader* hdr, u32* __restrict__ hist, u32 n_chunks, u32 radix, u32* __restrict__ digit_total) {
+  if (hdr->status) return;
+  __shared__ u32 sums[16][16];
+  const u32 in = threadIdx.x & 15u, group = threadIdx.x >> 4, d = blockIdx.x * 16 + in;
+  const u32 per = (n_chunks + 15) / 16, c0 = min(group * per, n_chunks), c1 = min(c0 + per, n_chunks);
+  u32 s = 0;
+#pragma unroll 8
+  for (u32 i = c0; i < c1; ++i) s += hist[i * radix + d];
+  sums[group][in] = s;
+  __syncthreads();
+  u32 ex = 0, total = 0;
+#pragma unroll
+  for (u32 g = 0; g < 16; ++g) {
+    const u32 v = sums[g][in];
+    if (g < group) ex += v;
+    total += v;
+  }
+#pragma unroll 8
+  for (u32 i = c0; i < c1; ++i) {
+    const u32 v = hist[i * radix + d];
+    hist[i * radix + d] = ex;
+    ex += v;
+  }
+  if (group == 0) digit_total[d] = total;
+}
+
+template <int ITEMS, int R>
 __global__ void __launch_bounds__(BLOCK)
 k_sort_scatter(const DevHeader* hdr, const u32* __restrict__ keys_in, const u32* __restrict__ vals_in,
                u32* __restrict__ keys_out, u32* __restrict__ vals_out, SortGeom geo, u32 shift,
                u32 digit_mask, const u32* __restrict__ hist, const u32* __restrict__ digit_total) {
   if (hdr->status) return;
-  constexpr int TILE = BLOCK * ITEMS;
+  constexpr int TILE = BLOCK * ITEMS, DIGITS = R / BLOCK;  // digits a thread owns: DIGITS neighbouring ones
+  constexpr int BITS = __builtin_ctz(R);
   __shared__ u32 scan_lds[4];
-  __shared__ u32 gbase[RADIX];        // next global position of each digit for this chunk
-  __shared__ u32 whist[4][RADIX];     // per-wave digit counts, then per-wave local bases
-  __shared__ u32 dstart[RADIX];       // sub-tile-local start of each digit
-  __shared__ u32 dcount[RADIX];
+  __shared__ u32 whist[4][R];  // per-wave digit counts, then per-wave local bases
+  __shared__ u32 delta[R];     // global position of a digit's first element of the sub-tile - its sub-tile position
   __shared__ u32 lkeys[TILE];
   __shared__ u32 lvals[TILE];
 
   const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
+  u32 gbase[DIGITS];  // next global position of the thread's digits for this chunk
   {
-    u32 total;
-    const u32 ex = block_exclusive_scan(digit_total[tid], scan_lds, total);
-    gbase[tid] = ex + hist[tid * geo.n_chunks + blockIdx.x];
+    u32 sum = 0, total;
+#pragma unroll
+    for (int q = 0; q < DIGITS; ++q) {
+      gbase[q] = sum;
+      sum += digit_total[tid * DIGITS + q];
+    }
+    const u32 ex = block_exclusive_scan(sum, scan_lds, total);
+#pragma unroll
+    for (int q = 0; q < DIGITS; ++q) {
+      const u32 d = tid * DIGITS + q;
+      gbase[q] += ex + hist[R == RADIX ? d * geo.n_chunks + blockIdx.x : blockIdx.x * R + d];
+    }
   }
   const u32 chunk_beg = blockIdx.x * geo.chunk_elems;
   const u32 chunk_end = min(chunk_beg + geo.chunk_elems, geo.n);
@@ -132,7 +184,9 @@ k_sort_scatter(const DevHeader* hdr, const u32* __restrict__ keys_in, const u32*
   for (u32 sub = chunk_beg; sub < chunk_end; sub += TILE) {
     const u32 n_valid = min((u32)TILE, chunk_end - sub);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) whist[i][tid] = 0;
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int q = 0; q < DIGITS; ++q) whist[i][q * BLOCK + tid] = 0;
     __syncthreads();
 
     u32 k[ITEMS], v[ITEMS], rank[ITEMS];
@@ -153,7 +207,7 @@ k_sort_scatter(const DevHeader* hdr, const u32* __restrict__ keys_in, const u32*
       // 0 or ~0); the disagreements are OR-ed per 32-bit half, lanes past the end masked at the end
       u32 diff_lo = 0, diff_hi = 0;
 #pragma unroll
-      for (int b = 0; b < 8; ++b) {
+      for (int b = 0; b < BITS; ++b) {
         const u32 m = (u32)__builtin_amdgcn_sbfe((int)d, b, 1);
         const u64 bal = __builtin_amdgcn_ballot_w64(m != 0u);
         diff_lo |= (u32)bal ^ m;
@@ -173,15 +227,25 @@ k_sort_scatter(const DevHeader* hdr, const u32* __restrict__ keys_in, const u32*
     __syncthreads();
 
     {  // digit-major, wave-minor exclusive scan of the counts
-      const u32 c0 = whist[0][tid], c1 = whist[1][tid], c2 = whist[2][tid], c3 = whist[3][tid];
-      u32 total;
-      const u32 ex = block_exclusive_scan(c0 + c1 + c2 + c3, scan_lds, total);
-      dstart[tid] = ex;
-      dcount[tid] = c0 + c1 + c2 + c3;
-      whist[0][tid] = ex;
-      whist[1][tid] = ex + c0;
-      whist[2][tid] = ex + c0 + c1;
-      whist[3][tid] = ex + c0 + c1 + c2;
+      u32 sum = 0, total;
+#pragma unroll
+      for (int q = 0; q < DIGITS; ++q) {
+        const int d = tid * DIGITS + q;
+        sum += whist[0][d] + whist[1][d] + whist[2][d] + whist[3][d];
+      }
+      u32 at = block_exclusive_scan(sum, scan_lds, total);
+#pragma unroll
+      for (int q = 0; q < DIGITS; ++q) {
+        const int d = tid * DIGITS + q;
+        const u32 c0 = whist[0][d], c1 = whist[1][d], c2 = whist[2][d], c3 = whist[3][d];
+        delta[d] = gbase[q] - at;
+        gbase[q] += c0 + c1 + c2 + c3;
+        whist[0][d] = at;
+        whist[1][d] = at += c0;
+        whist[2][d] = at += c1;
+        whist[3][d] = at += c2;
+        at += c3;
+      }
     }
     __syncthreads();
 
@@ -199,25 +263,22 @@ k_sort_scatter(const DevHeader* hdr, const u32* __restrict__ keys_in, const u32*
 
     for (u32 j = tid; j < n_valid; j += BLOCK) {
       const u32 kk = lkeys[j];
-      const u32 d = (kk >> shift) & digit_mask;
-      const u32 pos = gbase[d] + (j - dstart[d]);
+      const u32 pos = delta[(kk >> shift) & digit_mask] + j;
       keys_out[pos] = kk;
       vals_out[pos] = lvals[j];
     }
-    __syncthreads();
-    gbase[tid] += dcount[tid];
-    // the barrier at the top of the next iteration orders this against its readers
+    // the barriers of the next iteration order these reads of the LDS lists before their next writes
   }
 }
 
 // ---------------------------------------------------------------- host side
 
 // How a list of n elements is cut into the chunks the sort's launches work on.
-inline SortGeom sort_geom(u64 n) {
+inline SortGeom sort_geom(u64 n, u32 items, u64 max_chunks) {
   SortGeom g;
-  g.items = n <= SORT_ITEMS_4_MAX ? 4u : n <= SORT_ITEMS_8_MAX ? 8u : 16u;
+  g.items = items;
   const u64 tile = (u64)BLOCK * g.items, tiles = (n + tile - 1) / tile;
-  const u64 chunks = std::min<u64>(std::max<u64>(tiles, 1), SORT_MAX_CHUNKS);
+  const u64 chunks = std::min<u64>(std::max<u64>(tiles, 1), max_chunks);
   const u64 per = (n + chunks - 1) / chunks;
   const u64 chunk_elems = std::max<u64>(((per + tile - 1) / tile) * tile, tile);
   g.n = (u32)n;
@@ -225,20 +286,62 @@ inline SortGeom sort_geom(u64 n) {
   g.n_chunks = (u32)std::max<u64>((n + chunk_elems - 1) / chunk_elems, 1);
   return g;
 }
+inline SortGeom sort_geom(u64 n) {
+  return sort_geom(n, n <= SORT_ITEMS_4_MAX ? 4u : n <= SORT_ITEMS_8_MAX ? 8u : 16u, SORT_MAX_CHUNKS);
+}
+
+// Words of `hist`: the histograms of SORT_MAX_CHUNKS chunks of RADIX digits.
+constexpr size_t SORT_HIST_WORDS = (size_t)RADIX * SORT_MAX_CHUNKS;
 
 // One pass over the digit (key >> shift) & digit_mask.
 inline void sort_pass_enqueue(const DevHeader* hdr, const u32* keys_in, const u32* vals_in, u32* keys_out, u32* vals_out,
                               const SortGeom& geo, u32 shift, u32 digit_mask, u32* hist, u32* digit_total,
                               hipStream_t st) {
-  hipLaunchKernelGGL(k_sort_hist, dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
+  hipLaunchKernelGGL(k_sort_hist<RADIX>, dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
   hipLaunchKernelGGL(k_sort_scan, dim3(RADIX), dim3(BLOCK), 0, st, hdr, hist, geo.n_chunks, digit_total);
-#define CTR_SORT_SCATTER(ITEMS)                                                                                   \
-  hipLaunchKernelGGL(k_sort_scatter<ITEMS>, dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, vals_in, keys_out, \
-                     vals_out, geo, shift, digit_mask, hist, digit_total)
-  if (geo.items == 4) CTR_SORT_SCATTER(4);
-  else if (geo.items == 8) CTR_SORT_SCATTER(8);
-  else CTR_SORT_SCATTER(16);
+#define CTR_SORT_SCATTER(ITEMS, R)                                                                                \
+  hipLaunchKernelGGL((k_sort_scatter<ITEMS, R>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, vals_in,      \
+                     keys_out, vals_out, geo, shift, digit_mask, hist, digit_total)
+  if (geo.items == 4) CTR_SORT_SCATTER(4, RADIX);
+  else if (geo.items == 8) CTR_SORT_SCATTER(8, RADIX);
+  else CTR_SORT_SCATTER(16, RADIX);
+}
+
+// A pass of wide digits (R = 1024 or 2048; the digit totals stand behind the histograms).
+template <int R>
+inline void sort_pass_wide_enqueue(const DevHeader* hdr, const u32* keys_in, const u32* vals_in, u32* keys_out,
+                                   u32* vals_out, const SortGeom& geo, u32 shift, u32 digit_mask, u32* hist,
+                                   hipStream_t st) {
+  u32* digit_total = hist + (size_t)R * geo.n_chunks;
+  hipLaunchKernelGGL(k_sort_hist<R>, dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
+  hipLaunchKernelGGL(k_sort_scan_wide, dim3(R / 16), dim3(BLOCK), 0, st, hdr, hist, geo.n_chunks, (u32)R, digit_total);
+  if (geo.items == 4) CTR_SORT_SCATTER(4, R);
+  else CTR_SORT_SCATTER(8, R);
 #undef CTR_SORT_SCATTER
+}
+
+// Sorts n (key, value) pairs by the low key_bits bits of the key, between the two pairs of arrays; returns which of
+// them (0 = a, 1 = b) holds the result.
+inline u32 sort_enqueue(const DevHeader* hdr, const u32* keys_in, const u32* vals_in, u32* const (&keys)[2],
+                        u32* const (&vals)[2], u64 n, u32 key_bits, u32* hist, u32* digit_total, hipStream_t st) {
+  const u32 wide_bits = key_bits > 20 ? 11u : 10u;
+  u32 passes = (key_bits + 7) / 8;
+  const u32 wide_passes = (key_bits + wide_bits - 1) / wide_bits;
+  const bool wide = wide_passes < passes && n <= (wide_bits == 10 ? SORT_10_BITS_MAX : SORT_11_BITS_MAX);
+  if (wide) passes = wide_passes;
+  const SortGeom geo = wide ? sort_geom(n, n <= SORT_ITEMS_4_MAX ? 4u : 8u, (SORT_HIST_WORDS >> wide_bits) - 1) : sort_geom(n);
+  u32 shift = 0;
+  for (u32 p = 0; p < passes; ++p) {
+    const u32 bits = (key_bits - shift + (passes - p) - 1) / (passes - p);  // spread evenly over the passes
+    const u32 mask = (1u << bits) - 1u;
+    if (!wide) sort_pass_enqueue(hdr, keys_in, vals_in, keys[p & 1], vals[p & 1], geo, shift, mask, hist, digit_total, st);
+    else if (wide_bits == 10) sort_pass_wide_enqueue<1024>(hdr, keys_in, vals_in, keys[p & 1], vals[p & 1], geo, shift, mask, hist, st);
+    else sort_pass_wide_enqueue<2048>(hdr, keys_in, vals_in, keys[p & 1], vals[p & 1], geo, shift, mask, hist, st);
+    keys_in = keys[p & 1];
+    vals_in = vals[p & 1];
+    shift += bits;
+  }
+  return (passes - 1) & 1;
 }
 
 }  // namespace ctr

@@ -49,3 +49,12 @@ def test_span_length_changes(D, n):
 def test_sort_tiles(n):
     rng = np.random.default_rng(n)
     _step((60000 ** rng.random(n)).astype(np.uint64) + 1, 4, 70000)
+
+
+# the sort's digits, chosen by the bits of a row id: one wide digit (9 to 11 bits), two of 8, two of 10, two of 11,
+# three of 8; lists of one element, of a tile and one, of several chunks, and around the lengths that end wide digits
+@pytest.mark.parametrize("R", [1 << 9, 1 << 10, 1 << 11, (1 << 11) + 1, (1 << 16) + 1, 1 << 20, (1 << 20) + 1, 1 << 22,
+                               (1 << 22) + 1])
+@pytest.mark.parametrize("n", [1, 4097, 500000, 500001, 1000001])
+def test_sort_digits(R, n):
+    _step(np.random.default_rng(R + n).integers(1, R, n), 4, R)
