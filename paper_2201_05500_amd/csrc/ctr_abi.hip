@@ -496,7 +496,8 @@ static int lookup_pool_enqueue(ctr_table* t, uint32_t replica, const uint64_t* d
     const u64 work = std::max<u64>(n, (u64)n_segments + 1);
     hipLaunchKernelGGL(k_lookup, dim3(blocks_for(work)), dim3(BLOCK), 0, st, t->hdr, t->slots,
                        (u32)(t->tl.n_slots - 1), (const u64*)d_keys, n, d_offsets, n_segments, occ_row);
-    hipLaunchKernelGGL(k_lookup_commit, dim3(1), dim3(WAVE), 0, st, t->hdr);
+    if (n_segments == 0)  // the pooling launch does it otherwise
+      hipLaunchKernelGGL(k_lookup_commit, dim3(1), dim3(WAVE), 0, st, t->hdr);
   }
   if (n_segments > 0) {
     StageTimer tm(t, CTR_STAGE_POOL, st);

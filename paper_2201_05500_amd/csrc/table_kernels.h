@@ -329,7 +329,8 @@ __global__ void k_load_rows(const DevHeader* hdr, const u32* __restrict__ occ_ro
 
 // Lookup without insert for every occurrence of a batch (prediction): occ_row[p] = row of keys[p],
 // or OCC_INVALID if the key is not in the table.  Checks keys and offsets like the training probe;
-// what it finds goes to pull_err and is folded into the status by k_lookup_commit.
+// what it finds goes to pull_err, which the pooling kernel folds into the status (k_lookup_commit, where there are
+// no segments to pool).
 __global__ void __launch_bounds__(BLOCK)
 k_lookup(DevHeader* hdr, const Slot* __restrict__ slots, u32 slot_mask, const u64* __restrict__ keys, u32 n_keys,
          const u32* __restrict__ offsets, u32 n_seg, u32* __restrict__ occ_row) {
@@ -365,12 +366,17 @@ k_lookup(DevHeader* hdr, const Slot* __restrict__ slots, u32 slot_mask, const u6
   occ_row[p] = out;
 }
 
-__global__ void k_lookup_commit(DevHeader* hdr) {
-  if (threadIdx.x == 0 && blockIdx.x == 0 && !hdr->status) {
-    hdr->status = hdr->pull_err;
-    hdr->pull_err = 0;
-  }
+// True if the table refuses calls or the lookup before this launch failed; the failure becomes the table's status.
+// pull_err stays as it is beside a status: other blocks read it, and whatever clears the status clears both.
+// (In a launch of its own this cost 4.5 us, a tenth of a prediction for 8 requests.)
+__device__ __forceinline__ bool lookup_failed(DevHeader* hdr) {
+  if (hdr->status) return true;
+  const u32 err = hdr->pull_err;
+  if (err && blockIdx.x == 0 && threadIdx.x == 0) hdr->status = err;
+  return err != 0;
 }
+
+__global__ void k_lookup_commit(DevHeader* hdr) { (void)lookup_failed(hdr); }
 
 // Pure lookup (no insert) of n keys and copy of their rows of one replica to dense arrays; a key
 // that is not in the table gets found = 0 and zeros.
@@ -472,13 +478,13 @@ __device__ __forceinline__ void pool_add4(const f4 (&xv)[4], d4& acc) {
 }
 
 template <int LPR, int OUT>
-__device__ __forceinline__ void pool_body(const DevHeader* hdr, u32* occ_row,
+__device__ __forceinline__ void pool_body(DevHeader* hdr, u32* occ_row,
                                           const Slot* __restrict__ slots, u32* __restrict__ seg_of,
                                           const u32* __restrict__ offsets, u32 n_seg,
                                           const float* __restrict__ values, u32 D, u32 rf,
                                           float* __restrict__ pooled, bf16_t* __restrict__ pooled_bf16) {
-  if (hdr->status) return;
   constexpr bool LOOKUP = (OUT & 4) != 0;
+  if (LOOKUP ? lookup_failed(hdr) : hdr->status != 0) return;
   constexpr u32 GROUPS = BLOCK / LPR;
   constexpr u32 TILE = GROUPS * POOL_NS * POOL_ROUNDS;
   constexpr u32 STAGED = pool_staged_rows<LPR>();
@@ -558,13 +564,13 @@ __device__ __forceinline__ void pool_body(const DevHeader* hdr, u32* occ_row,
 }
 
 template <int LPR, int OUT>
-__device__ __forceinline__ void pool_small_body(const DevHeader* hdr, u32* __restrict__ occ_row,
+__device__ __forceinline__ void pool_small_body(DevHeader* hdr, u32* __restrict__ occ_row,
                                                 const Slot* __restrict__ slots, u32* __restrict__ seg_of,
                                                 const u32* __restrict__ offsets, u32 n_seg,
                                                 const float* __restrict__ values, u32 D, u32 rf,
                                                 float* __restrict__ pooled, bf16_t* __restrict__ pooled_bf16) {
-  if (hdr->status) return;
   constexpr bool LOOKUP = (OUT & 4) != 0;
+  if (LOOKUP ? lookup_failed(hdr) : hdr->status != 0) return;
   const u32 g = (blockIdx.x * BLOCK + threadIdx.x) / LPR, c = threadIdx.x % LPR;
   if (g >= n_seg) return;
   const u32 beg = offsets[g], end = offsets[g + 1];
@@ -598,7 +604,7 @@ __device__ __forceinline__ void pool_small_body(const DevHeader* hdr, u32* __res
 }
 
 #define CTR_POOL_ARGS                                                                                       \
-  const DevHeader *hdr, u32 *__restrict__ occ_row, const Slot *__restrict__ slots, u32 *__restrict__ seg_of, \
+  DevHeader *hdr, u32 *__restrict__ occ_row, const Slot *__restrict__ slots, u32 *__restrict__ seg_of, \
       const u32 *__restrict__ offsets, u32 n_seg, const float *__restrict__ values, u32 D, u32 rf,          \
       float *__restrict__ pooled, bf16_t *__restrict__ pooled_bf16
 #define CTR_DEFINE_POOL(NAME, OUT)                                                                           \

@@ -97,3 +97,33 @@ def test_prediction_chain_lookup_then_forward():
     # the tower's oracle is fed what the GPU lookup produced (checked above against the table oracle)
     ologits = om.forward(0, p16.float().cpu().numpy().reshape(w.batch, in_dim))
     close_rows(logits.cpu().numpy(), ologits, "prediction logits", 1)
+
+
+@pytest.mark.parametrize("dim,n_seg", [(8, 0), (8, 300), (8, 300000), (256, 5000)])  # no pooling; one kernel; the other
+def test_failed_lookup_is_reported_and_writes_nothing(dim, n_seg):
+    import torch
+    from paper_2201_05500_amd import binding as B
+    w = WL.scaled(WL.WORKLOADS["tiny"], capacity_rows=4096, zipf_universe=3000, batch=16, dim=dim)
+    gt, _ = _trained_pair(w, steps=1)
+    keys = torch.arange(1, max(n_seg, 1) + 1, dtype=torch.int64, device="cuda") % 3000 + 1
+    offs = torch.arange(0, n_seg + 1, dtype=torch.int32, device="cuda") if n_seg else \
+        torch.tensor([1], dtype=torch.int32, device="cuda")          # no segment may not hold a key, nor begin at 1
+    good = [gt.lookup_pool(0, keys[:n_seg], torch.arange(0, n_seg + 1, dtype=torch.int32, device="cuda"))[1].clone()
+            for _ in range(2)]
+    assert gt.last_status() == B.CTR_OK and torch.equal(good[0], good[1])
+    keys[-1] = -1                                                    # the reserved key
+    out = torch.full((n_seg, dim), 7.0, device="cuda")
+    for _ in range(2):                                               # the second call is a no-op
+        st, _ = gt.lookup_pool(0, keys, offs, out=out)
+        assert st == B.CTR_OK
+    assert bool((out == 7.0).all())
+    assert gt.last_status() == (B.CTR_E_BADKEY if n_seg else B.CTR_E_INVAL)
+    assert gt.last_status() == B.CTR_OK
+    if n_seg:
+        offs[n_seg // 2] += 2                                        # both errors: the offsets' comes first
+        st, _ = gt.lookup_pool(0, keys, offs, out=out)
+        assert st == B.CTR_OK and gt.last_status() == B.CTR_E_INVAL and bool((out == 7.0).all())
+        keys[-1] = (n_seg % 3000) + 1
+        offs[n_seg // 2] -= 2
+        st, _ = gt.lookup_pool(0, keys, offs, out=out)
+        assert st == B.CTR_OK and gt.last_status() == B.CTR_OK and torch.equal(out, good[0])
