@@ -98,13 +98,15 @@ inline u32 push_span(u32 D, u64 n) {
   return lanes >= (1u << 20) ? 16 : lanes >= (1u << 19) ? 8 : 4;
 }
 
-// force_span / force_items: 0 = chosen by batch size; otherwise the geometry a test asks for.
-void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force_items = 0) {
+// force_span / force_items: 0 = chosen by batch size; otherwise the geometry a test asks for.  compact: spans of at
+// least 16 and no more room for the sort's histograms than the list needs, for a workspace that holds no more.
+void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force_items = 0, bool compact = false) {
   const u64 n = n_keys;
   L->n_rank_tiles = (u32)((n + RANK_TILE - 1) / RANK_TILE);
   L->n_rank_groups = (L->n_rank_tiles + RANK_GROUP - 1) / RANK_GROUP;
   L->span = push_span(D, n);
   if (force_span) L->span = force_span;
+  if (compact) L->span = std::max(L->span, 16u);
   L->n_spans = (u32)((n + L->span - 1) / L->span);
   L->n_span_blocks = (L->n_spans + SPANS_PER_BLOCK - 1) / SPANS_PER_BLOCK;
   size_t o = 0;
@@ -115,7 +117,7 @@ void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force
   L->off_va = o; o += arr;
   L->off_kb = o; o += arr;
   L->off_vb = o; o += arr;
-  L->off_hist = o; o += align256(SORT_HIST_WORDS * sizeof(u32));
+  L->off_hist = o; o += align256((compact ? sort_hist_words(n, L->n_spans) : SORT_HIST_WORDS) * sizeof(u32));
   L->off_digit_total = o; o += align256(RADIX * sizeof(u32));
   L->off_tile_count = o; o += align256(((size_t)L->n_rank_tiles + 1) * sizeof(u32));
   L->off_group_count = o; o += align256(((size_t)L->n_rank_groups + 1) * sizeof(u32));
@@ -132,6 +134,16 @@ void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force
   L->off_span_flags = o; o += align256((size_t)L->n_spans * sizeof(u32));
   L->off_span_rows = o; o += align256((size_t)L->n_spans * sizeof(u32));
   L->total = std::max<size_t>(o, 256);
+}
+
+// The layout of a batch of n keys in a workspace of that many bytes; false if it does not fit.  Below the size
+// ctr_workspace_bytes asks for, down to what spans of 16 occurrences need, the batch runs with longer spans.
+bool fit_layout(u32 D, u64 n, size_t bytes, WorkLayout* L, u32 force_span, u32 force_items) {
+  work_layout(D, n, L, force_span, force_items);
+  if (L->total <= bytes) return true;
+  if (force_span) return false;
+  work_layout(D, n, L, 0, force_items, true);
+  return L->total <= bytes;
 }
 
 // Which of the two pooling kernels a launch uses, and its grid (table_kernels.h).
@@ -413,8 +425,7 @@ static int pull_pool_impl(ctr_table* t, uint32_t replica, const uint64_t* d_keys
   if (n_segments > 0 && !d_pooled && !d_pooled_bf16) return CTR_E_INVAL;
   if (((uintptr_t)d_workspace & 255) != 0) return CTR_E_INVAL;
   WorkLayout wl;
-  work_layout(t->D, n_keys, &wl, t->force_span, t->force_items);
-  if (workspace_bytes < wl.total) return CTR_E_NOMEM;
+  if (!fit_layout(t->D, n_keys, workspace_bytes, &wl, t->force_span, t->force_items)) return CTR_E_NOMEM;
 
   t->has_live = false;  // an unpushed batch goes stale
   ctr_batch* b = &t->cur;
@@ -540,8 +551,7 @@ int ctr_lookup_pool(ctr_table* t, uint32_t replica, const uint64_t* d_keys, uint
   if (rc != CTR_OK) return rc;
   if (!d_workspace || ((uintptr_t)d_workspace & 255) != 0) return CTR_E_INVAL;
   WorkLayout wl;
-  work_layout(t->D, n_keys, &wl, t->force_span, t->force_items);
-  if (workspace_bytes < wl.total) return CTR_E_NOMEM;
+  if (!fit_layout(t->D, n_keys, workspace_bytes, &wl, t->force_span, t->force_items)) return CTR_E_NOMEM;
   if (t->has_live && t->cur.ws == (char*)d_workspace) t->has_live = false;  // the live batch's lists are overwritten
   char* ws = (char*)d_workspace;
   return lookup_pool_enqueue(t, replica, d_keys, (u32)n_keys, d_offsets, n_segments, d_pooled,
@@ -724,8 +734,7 @@ int ctr_table_load(ctr_table* t, const uint64_t* d_keys, uint64_t n_keys, const 
   if (n_keys > 0 && (!d_keys || !d_x || !d_v || (has_m && !d_m))) return CTR_E_INVAL;
   if (((uintptr_t)d_workspace & 255) != 0) return CTR_E_INVAL;
   WorkLayout wl;
-  work_layout(t->D, n_keys, &wl, t->force_span, t->force_items);
-  if (workspace_bytes < wl.total) return CTR_E_NOMEM;
+  if (!fit_layout(t->D, n_keys, workspace_bytes, &wl, t->force_span, t->force_items)) return CTR_E_NOMEM;
   t->has_live = false;  // the workspace of an unpushed batch may be this one: it goes stale
   ++t->generation;
   hipStream_t st = (hipStream_t)hip_stream;

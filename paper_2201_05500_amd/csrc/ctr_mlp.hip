@@ -96,8 +96,9 @@ void ws_layout(const ctr_mlp_config* c, const MlpLayout& L, u32 B, WsLayout* S) 
   S->off_dlogit = o; o += align256((size_t)B * sizeof(float));
   S->off_lterm = o; o += align256((size_t)B * sizeof(double));
   S->off_grads = o; o += align256((size_t)L.n_params * sizeof(float));
-  S->off_partial = o; o += align256(COLSUM_SLICES * n_cols * sizeof(float));
-  S->off_gemm = o; S->gemm_bytes = gemm_scratch_bytes(c); o += S->gemm_bytes;
+  S->off_gemm = o; S->gemm_bytes = gemm_scratch_bytes(c);
+  S->off_partial = o;  // the sums over the batch follow the last product, whose scratch is free again
+  o += std::max(S->gemm_bytes, align256(COLSUM_SLICES * n_cols * sizeof(float)));
   S->total = o;
 }
 

@@ -293,6 +293,20 @@ inline SortGeom sort_geom(u64 n) {
 // Words of `hist`: the histograms of SORT_MAX_CHUNKS chunks of RADIX digits.
 constexpr size_t SORT_HIST_WORDS = (size_t)RADIX * SORT_MAX_CHUNKS;
 
+// Geometry of a list of n elements that takes digits of `bits` (10 or 11) bits.
+inline bool sort_takes_wide(u64 n, u32 bits) { return n <= (bits == 10 ? SORT_10_BITS_MAX : SORT_11_BITS_MAX); }
+inline SortGeom sort_geom_wide(u64 n, u32 bits) {
+  return sort_geom(n, n <= SORT_ITEMS_4_MAX ? 4u : 8u, (SORT_HIST_WORDS >> bits) - 1);
+}
+
+// Words of `hist` that a list of n elements uses, whatever its keys, and the order of a push's n_spans spans.
+inline size_t sort_hist_words(u64 n, u64 n_spans) {
+  size_t words = (size_t)RADIX * std::max(sort_geom(n).n_chunks, sort_geom(n_spans).n_chunks);
+  for (u32 bits : {10u, 11u})
+    if (sort_takes_wide(n, bits)) words = std::max(words, ((size_t)sort_geom_wide(n, bits).n_chunks + 1) << bits);
+  return words;
+}
+
 // One pass over the digit (key >> shift) & digit_mask.
 inline void sort_pass_enqueue(const DevHeader* hdr, const u32* keys_in, const u32* vals_in, u32* keys_out, u32* vals_out,
                               const SortGeom& geo, u32 shift, u32 digit_mask, u32* hist, u32* digit_total,
@@ -327,9 +341,9 @@ inline u32 sort_enqueue(const DevHeader* hdr, const u32* keys_in, const u32* val
   const u32 wide_bits = key_bits > 20 ? 11u : 10u;
   u32 passes = (key_bits + 7) / 8;
   const u32 wide_passes = (key_bits + wide_bits - 1) / wide_bits;
-  const bool wide = wide_passes < passes && n <= (wide_bits == 10 ? SORT_10_BITS_MAX : SORT_11_BITS_MAX);
+  const bool wide = wide_passes < passes && sort_takes_wide(n, wide_bits);
   if (wide) passes = wide_passes;
-  const SortGeom geo = wide ? sort_geom(n, n <= SORT_ITEMS_4_MAX ? 4u : 8u, (SORT_HIST_WORDS >> wide_bits) - 1) : sort_geom(n);
+  const SortGeom geo = wide ? sort_geom_wide(n, wide_bits) : sort_geom(n);
   u32 shift = 0;
   for (u32 p = 0; p < passes; ++p) {
     const u32 bits = (key_bits - shift + (passes - p) - 1) / (passes - p);  // spread evenly over the passes

@@ -58,3 +58,25 @@ def test_sort_tiles(n):
 @pytest.mark.parametrize("n", [1, 4097, 500000, 500001, 1000001])
 def test_sort_digits(R, n):
     _step(np.random.default_rng(R + n).integers(1, R, n), 4, R)
+
+
+# a workspace with room for spans of 16 occurrences only (shorter ones are asked for), and one below that
+@pytest.mark.parametrize("D,n,ws_bytes", [(256, 9000, 6780672), (64, 1000, 4291328), (16, 200000, 13151232)])
+def test_workspace_for_longer_spans(D, n, ws_bytes):
+    import torch
+    from paper_2201_05500_amd.binding import CTR_E_NOMEM, CtrTable, ctr_workspace_bytes
+    R = 1 << 18
+    gt, ot = CtrTable(R, D, init_seed=3), O.OracleTable(R, D, init_seed=3)
+    assert ws_bytes < ctr_workspace_bytes(gt.cfg, n, 10)
+    guard = 1 << 16
+    gt.reserve = lambda *a: None
+    gt._ws = torch.full((ws_bytes + guard,), 0x5A, dtype=torch.uint8, device="cuda:0")
+    gt.ws_bytes = ws_bytes
+    for step in range(2):
+        b = _batch((n ** np.random.default_rng(n + step).random(n)).astype(np.uint64) + 1, D, step)
+        run_step(gt, ot, to_device(b), b)
+    compare_tables(gt, ot)
+    assert bool((gt._ws[ws_bytes:] == 0x5A).all())
+    gt.ws_bytes = 8 * D * n // 16
+    b = to_device(b)
+    assert gt.pull_pool(0, b["keys"], b["offsets"])[0] == CTR_E_NOMEM
