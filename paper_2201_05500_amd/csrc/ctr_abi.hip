@@ -120,7 +120,7 @@ void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force
   L->off_hist = o; o += align256((compact ? sort_hist_words(n, L->n_spans) : SORT_HIST_WORDS) * sizeof(u32));
   L->off_digit_total = o; o += align256(RADIX * sizeof(u32));
   L->off_tile_count = o; o += align256(((size_t)L->n_rank_tiles + 1) * sizeof(u32));
-  L->off_group_count = o; o += align256(((size_t)L->n_rank_groups + 1) * sizeof(u32));
+  L->off_group_count = o; o += align256(((size_t)L->n_rank_groups + 1) * RANK_GROUP_STRIDE * sizeof(u32));
   L->off_first_bits = o; o += align256(((size_t)L->n_rank_tiles + 1) * RANK_WORDS * sizeof(u32));
   L->probe_items = n >= (4u << 20) ? PROBE_MAX_ITEMS : 1;
   if (force_items) L->probe_items = force_items;
@@ -313,16 +313,25 @@ static void enqueue_lookup_insert(ctr_table* t, const WorkLayout& wl, char* ws, 
   }
   {
     StageTimer tm(t, CTR_STAGE_INSERT, st);
-    if (n > 0)
-      hipLaunchKernelGGL(k_rank_count, dim3(wl.n_rank_tiles), dim3(BLOCK), 0, st, t->hdr, t->slots, occ_row, pend_list,
-                         tile_pending, wl.probe_tile, wl.n_probe_tiles, first_bits, tile_count, group_count);
-    else  // no occurrences: the errors of the offsets are taken over, nothing is counted
-      hipLaunchKernelGGL(k_rank_count, dim3(1), dim3(BLOCK), 0, st, t->hdr, t->slots, occ_row, pend_list, tile_pending,
-                         wl.probe_tile, 0u, first_bits, tile_count, group_count);
-    LPR_DISPATCH(t->lpr, k_rank_assign, std::max<u32>(wl.n_rank_tiles, 1u), st, t->hdr, t->slots, occ_row, first_bits,
-                 tile_count, group_count, wl.n_rank_tiles, t->R, t->row_key, init_new_rows ? 1u : 0u, t->values,
-                 t->tl.replica_stride, t->W, t->vhat, t->D, t->rf, t->seed_mul, t->init_scale,
-                 (t->cfg.flags & CTR_F_BIAS_CORRECTION) ? 0.0f : t->cfg.eps);
+    // no occurrences: one tile without any takes over the errors of the offsets
+    const u32 n_tiles = std::max<u32>(wl.n_rank_tiles, 1u), parts = rank_parts(n_tiles);
+    if (wl.probe_items == 1)
+      hipLaunchKernelGGL(k_rank_count<1>, dim3(n_tiles), dim3(BLOCK), 0, st, t->hdr, t->slots, occ_row, pend_list,
+                         tile_pending, n ? wl.n_probe_tiles : 0u, n_tiles, first_bits, tile_count, group_count);
+    else
+      hipLaunchKernelGGL(k_rank_count<PROBE_MAX_ITEMS>, dim3(blocks_for((u64)n_tiles * WAVE)), dim3(BLOCK), 0, st, t->hdr,
+                         t->slots, occ_row, pend_list, tile_pending, n ? wl.n_probe_tiles : 0u, n_tiles, first_bits,
+                         tile_count, group_count);
+    // initial rows: written with the numbering, or in a launch behind it where the batch is large (k_init_rows)
+    const bool create = init_new_rows && n > 0 && wl.probe_items != 1;
+    const float v0 = (t->cfg.flags & CTR_F_BIAS_CORRECTION) ? 0.0f : t->cfg.eps;
+    LPR_DISPATCH(t->lpr, k_rank_assign, blocks_for((u64)n_tiles * parts * WAVE), st, t->hdr, t->slots, d_keys, occ_row,
+                 first_bits, tile_count, group_count, wl.n_rank_tiles, parts, t->R, t->row_key,
+                 init_new_rows && !create ? 1u : 0u, t->values, t->tl.replica_stride, t->W, t->vhat, t->D, t->rf,
+                 t->seed_mul, t->init_scale, v0);
+    if (create)
+      LPR_DISPATCH(t->lpr, k_init_rows, std::min<u32>(blocks_for((u64)n * t->lpr), 4096), st, t->hdr, t->row_key, t->values,
+                   t->tl.replica_stride, t->W, t->vhat, t->D, t->rf, t->seed_mul, t->init_scale, v0);
   }
 }
 

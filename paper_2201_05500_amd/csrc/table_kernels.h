@@ -4,6 +4,8 @@
 // parameters; Algorithm 1's insert_into_hash_table and pull steps; the state a
 // new row starts from is Algorithm 2's "Initialize" line (m = 0, v = eps).
 #pragma once
+#include <algorithm>
+
 #include "common.h"
 
 namespace ctr {
@@ -37,6 +39,13 @@ __global__ void k_table_clear(DevHeader* hdr, Slot* slots, u64 n_slots, u32* row
 // occurrence) and is appended to its tile's list of pending occurrences (counted in LDS, so no
 // global atomic is shared between blocks).  The same launch checks the CSR offsets.
 constexpr int PROBE_MAX_ITEMS = 8;  // occurrences per thread: 8 for large batches, 1 for small ones (host's choice)
+// ranking of new keys (below)
+constexpr u32 RANK_TILE = PROBE_MAX_ITEMS * BLOCK;  // 2048 occurrences: a whole number of probe tiles of any size
+constexpr u32 RANK_WORDS = RANK_TILE / 32;
+constexpr u32 RANK_GROUP = 256;  // tiles: 39 M occurrences have 75 groups
+constexpr u32 RANK_GROUP_STRIDE = 32;  // words: a group's count has a cache line to itself, because atomics on one
+                                       // line are served one after the other (39 M occurrences: 19 k of them on
+                                       // 5 lines took 60 of k_rank_count's 84 us)
 
 __global__ void __launch_bounds__(BLOCK)
 k_probe_insert(DevHeader* hdr, Slot* slots, u32 slot_mask, const u64* __restrict__ keys, u32 n_keys,
@@ -49,7 +58,7 @@ k_probe_insert(DevHeader* hdr, Slot* slots, u32 slot_mask, const u64* __restrict
     hdr->n_rows_base = hdr->n_rows;
   }
   if (refused) return;
-  if (blockIdx.x * BLOCK + threadIdx.x < n_groups) group_count[blockIdx.x * BLOCK + threadIdx.x] = 0;
+  if (blockIdx.x * BLOCK + threadIdx.x < n_groups) group_count[(blockIdx.x * BLOCK + threadIdx.x) * RANK_GROUP_STRIDE] = 0;
   __shared__ u32 n_pend;
   if (threadIdx.x == 0) n_pend = 0;
   __syncthreads();
@@ -136,57 +145,125 @@ k_probe_insert(DevHeader* hdr, Slot* slots, u32 slot_mask, const u64* __restrict
 // New rows are numbered in order of first occurrence, so the launches below need a prefix sum over the whole
 // batch.  They are two: one that finds and counts the first occurrences, per rank tile and per group of
 // RANK_GROUP tiles, and one in which every tile that has any adds up the counts of the groups before its own and
-// of the tiles before it in its group by itself (a few hundred words that sit in L2).  A launch that only waits for the one before costs 4.5 us, and in mid-training almost no tile has new
-// keys: with flags, counts, scan, assignment, row creation and the patching of pending occurrences in launches
-// of their own they were a fifth of a step of 73 k keys.  (No spin-waits: they would need block tickets, and
-// 8 ns per ticket is more than the launch.)
-constexpr u32 RANK_TILE = PROBE_MAX_ITEMS * BLOCK;  // 2048 occurrences: a whole number of probe tiles of any size
-constexpr u32 RANK_WORDS = RANK_TILE / 32;
-constexpr u32 RANK_GROUP = 128;  // tiles: 39 M occurrences have 150 groups
+// of the tiles before it in its group by itself (a few hundred words that sit in L2).  A launch that only waits for
+// the one before costs 4.5 us, and in mid-training almost no tile has new keys: with flags, counts, scan, assignment,
+// row creation and the patching of pending occurrences in launches of their own they were a fifth of a step of 73 k
+// keys.  (No spin-waits: they would need block tickets, and 8 ns per ticket is more than the launch.)
 
-// One block per rank tile, over the pending occurrences of its probe tiles: finds those that are the first
-// occurrence of their (new) key, leaves them as a bitmap (written only where there are any) and their number.
+// Orders the LDS accesses of a wave's lanes with each other (a wave's LDS accesses are executed in order: only the
+// compiler has to keep them so).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Over the pending occurrences of a rank tile's probe tiles: finds those that are the first occurrence of their
+// (new) key, leaves them as a bitmap (written only where there are any) and their number.
+// Bound by its chain of dependent loads (count, list, entry, slot), so a thread's chains run side by side.
+// ITEMS = 1, the probe tiles of small batches (256 occurrences): a block per rank tile, a thread takes one entry of
+// each of its 8 probe tiles.  ITEMS = 8, those of large ones (2048): a wave per rank tile and no block barrier - with
+// a block each, 39 M occurrences are 19 k blocks, ten rounds of the chip.
+template <int ITEMS>
 __global__ void __launch_bounds__(BLOCK)
 k_rank_count(DevHeader* hdr, const Slot* __restrict__ slots, const u32* __restrict__ occ_row,
-             const u32* __restrict__ pend_list, const u32* __restrict__ tile_pending, u32 probe_tile,
-             u32 n_probe_tiles, u32* __restrict__ first_bits, u32* __restrict__ tile_count,
-             u32* __restrict__ group_count) {
+             const u32* __restrict__ pend_list, const u32* __restrict__ tile_pending, u32 n_probe_tiles, u32 n_tiles,
+             u32* __restrict__ first_bits, u32* __restrict__ tile_count, u32* __restrict__ group_count) {
   if (!hdr->live) return;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     hdr->pull_seen = hdr->pull_err;
     hdr->pull_err = 0;
   }
-  const u32 per = RANK_TILE / probe_tile;
-  const u32 t0 = blockIdx.x * per, t1 = min(t0 + per, n_probe_tiles);
-  u32 any = 0;
-  for (u32 t = t0; t < t1; ++t) any |= tile_pending[t];
-  if (any == 0) {  // uniform over the block
-    if (threadIdx.x == 0) tile_count[blockIdx.x] = 0;
+  constexpr bool BY_WAVE = ITEMS != 1;
+  constexpr u32 PROBE_TILE = BLOCK * ITEMS, PER = RANK_TILE / PROBE_TILE;
+  __shared__ u32 lds[BY_WAVE ? BLOCK / WAVE : 1][RANK_WORDS];
+  const u32 tile = BY_WAVE ? (blockIdx.x * BLOCK + threadIdx.x) / WAVE : blockIdx.x;
+  if (tile >= n_tiles) return;  // uniform over the block or the wave
+  u32* bits = lds[BY_WAVE ? wave_id() : 0];
+  const u32 p0 = tile * RANK_TILE;
+  u32 cnt[PER], any = 0;
+#pragma unroll
+  for (u32 t = 0; t < PER; ++t) {
+    cnt[t] = tile * PER + t < n_probe_tiles ? tile_pending[tile * PER + t] : 0u;
+    any |= cnt[t];
+  }
+  if (any == 0) {
+    if (threadIdx.x == 0 || (BY_WAVE && lane_id() == 0)) tile_count[tile] = 0;
     return;
   }
-  __shared__ u32 bits[RANK_WORDS];
-  const u32 p0 = blockIdx.x * RANK_TILE;
-  if (threadIdx.x < RANK_WORDS) bits[threadIdx.x] = 0;
-  __syncthreads();
-  for (u32 t = t0; t < t1; ++t) {
-    const u32 cnt = tile_pending[t];
-    for (u32 i = threadIdx.x; i < cnt; i += BLOCK) {
-      const u32 p = pend_list[t * probe_tile + i];
-      if (slots[occ_row[p] & ~OCC_PEND_FLAG].first_p == p) atomicOr(&bits[(p - p0) >> 5], 1u << (p & 31u));
+  // list entries at[i] of the tile's part of pend_list; those that are a first occurrence set their bit
+  constexpr u32 CHAINS = BY_WAVE ? 4 : PER;
+  const auto mark = [&](const u32 (&at)[CHAINS], const bool (&take)[CHAINS]) {
+    u32 p[CHAINS], slot[CHAINS];
+    bool first[CHAINS];
+#pragma unroll
+    for (u32 i = 0; i < CHAINS; ++i) p[i] = take[i] ? pend_list[p0 + at[i]] : p0;
+#pragma unroll
+    for (u32 i = 0; i < CHAINS; ++i) slot[i] = take[i] ? occ_row[p[i]] & ~OCC_PEND_FLAG : 0u;
+#pragma unroll
+    for (u32 i = 0; i < CHAINS; ++i) first[i] = take[i] && slots[slot[i]].first_p == p[i];
+#pragma unroll
+    for (u32 i = 0; i < CHAINS; ++i)
+      if (first[i]) atomicOr(&bits[(p[i] - p0) >> 5], 1u << (p[i] & 31u));
+  };
+  u32 at[CHAINS];
+  bool take[CHAINS];
+  const u32 lane = (u32)lane_id();
+  if constexpr (BY_WAVE) {
+    bits[lane] = 0;
+    wave_lds_fence();
+    for (u32 i0 = lane; i0 - lane < cnt[0]; i0 += CHAINS * WAVE) {
+#pragma unroll
+      for (u32 i = 0; i < CHAINS; ++i) {
+        at[i] = i0 + i * WAVE;
+        take[i] = at[i] < cnt[0];
+      }
+      mark(at, take);
     }
+    wave_lds_fence();
+  } else {
+    if (threadIdx.x < RANK_WORDS) bits[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (u32 i = 0; i < CHAINS; ++i) {
+      at[i] = i * PROBE_TILE + threadIdx.x;
+      take[i] = threadIdx.x < cnt[i];
+    }
+    mark(at, take);
+    __syncthreads();
+    if (threadIdx.x >= RANK_WORDS) return;
   }
-  __syncthreads();
-  if (threadIdx.x < RANK_WORDS) {
-    const u32 w = bits[threadIdx.x];
-    first_bits[blockIdx.x * RANK_WORDS + threadIdx.x] = w;
-    const u32 total = wave_sum((u32)__popc(w));
-    if (threadIdx.x == 0) {
-      tile_count[blockIdx.x] = total;
-      if (total) atomicAdd(&group_count[blockIdx.x / RANK_GROUP], total);
-    }
+  const u32 w = bits[lane];
+  first_bits[tile * RANK_WORDS + lane] = w;
+  const u32 total = wave_sum((u32)__popc(w));
+  if (lane == 0) {
+    tile_count[tile] = total;
+    if (total) atomicAdd(&group_count[tile / RANK_GROUP * RANK_GROUP_STRIDE], total);
   }
 }
-static_assert(RANK_WORDS == WAVE && RANK_GROUP <= BLOCK, "one wave counts a rank tile, one block a group");
+static_assert(RANK_WORDS == WAVE, "a lane of one wave holds a word of a rank tile's bitmap");
+
+// Writes columns 4 c .. 4 c + 3 of a new row's initial state, in every replica.
+__device__ __forceinline__ void init_row(u32 row, u64 key, u32 c, float* values, u64 replica_stride, u32 n_replicas,
+                                         float* vhat, u32 D, u32 rf, u64 seed_mul, float scale, float v0) {
+  f4 x, z, e;
+  x.x = init_value(seed_mul, key, 4 * c + 0, scale);
+  x.y = init_value(seed_mul, key, 4 * c + 1, scale);
+  x.z = init_value(seed_mul, key, 4 * c + 2, scale);
+  x.w = init_value(seed_mul, key, 4 * c + 3, scale);
+  z.x = z.y = z.z = z.w = 0.0f;
+  e.x = e.y = e.z = e.w = v0;
+  for (u32 j = 0; j < n_replicas; ++j) {
+    float* b = values + j * replica_stride + (u64)row * rf + 4 * c;
+    stg4(b, x);
+    if (rf == 3 * D) {
+      stg4(b + D, z);
+      stg4(b + 2 * D, e);
+    } else {
+      stg4(b + D, e);
+    }
+  }
+  if (vhat) stg4(vhat + (u64)row * D + 4 * c, e);
+}
 
 // Commits the pull or undoes it, and gives the first occurrence of every new key its row: the row id (rows in
 // use + first occurrences before it), the key of the row and its initial state in every replica:
@@ -195,96 +272,92 @@ static_assert(RANK_WORDS == WAVE && RANK_GROUP <= BLOCK, "one wave counts a rank
 // (an error of the probe, or more rows than the table has), clearing exactly the slots claimed by this pull
 // restores the index as it was.  rf = floats per row (3*D with a first moment, 2*D without); init_rows = 0: the
 // caller writes the state of every row of the batch itself (a working-set load).
+// A rank tile's new rows are dealt evenly to `parts` waves (rank_parts below), without block barriers: one wave per
+// tile where the batch is large (a tile has a dozen new rows in mid-training, and what counts is how few rounds of
+// the chip the tiles take), many where a small batch of unseen keys would otherwise write its rows from a few compute
+// units.  (First pull of 4096 keys, 256 columns, 8 replicas: a block of 256 threads per tile 574 us for numbering and
+// rows, so 33; 73 k keys of 64 columns 98 and 29.)
 template <int LPR>
 __global__ void __launch_bounds__(BLOCK)
-k_rank_assign(DevHeader* hdr, Slot* slots, const u32* __restrict__ occ_row, const u32* __restrict__ first_bits,
-              const u32* __restrict__ tile_count, const u32* __restrict__ group_count, u32 n_tiles, u64 capacity_rows, u64* __restrict__ row_key,
-              u32 init_rows, float* values, u64 replica_stride, u32 n_replicas, float* vhat, u32 D, u32 rf,
-              u64 seed_mul, float scale, float v0) {
+k_rank_assign(DevHeader* hdr, Slot* slots, const u64* __restrict__ keys, const u32* __restrict__ occ_row,
+              const u32* __restrict__ first_bits, const u32* __restrict__ tile_count,
+              const u32* __restrict__ group_count, u32 n_tiles, u32 parts, u64 capacity_rows,
+              u64* __restrict__ row_key, u32 init_rows, float* values, u64 replica_stride, u32 n_replicas, float* vhat,
+              u32 D, u32 rf, u64 seed_mul, float scale, float v0) {
   if (!hdr->live) return;
-  const u32 own = n_tiles ? tile_count[blockIdx.x] : 0u;
-  if (own == 0 && blockIdx.x != 0) return;
-  __shared__ u32 lds[8];
+  const u32 wave = (blockIdx.x * BLOCK + threadIdx.x) / WAVE, lane = (u32)lane_id();
+  const u32 tile = wave / parts, part = wave % parts;
+  const u32 in_tile = tile < n_tiles ? tile_count[tile] : 0u;
+  if (in_tile == 0 && wave != 0) return;
   u32 before = 0, total = 0;  // first occurrences in the tiles before this one, in all tiles
-  const u32 n_groups = (n_tiles + RANK_GROUP - 1) / RANK_GROUP, group = blockIdx.x / RANK_GROUP;
-  for (u32 t = threadIdx.x; t < n_groups; t += BLOCK) {
-    const u32 c = group_count[t];
+  const u32 n_groups = (n_tiles + RANK_GROUP - 1) / RANK_GROUP, group = tile / RANK_GROUP;
+  for (u32 t = lane; t < n_groups; t += WAVE) {
+    const u32 c = group_count[t * RANK_GROUP_STRIDE];
     total += c;
     if (t < group) before += c;
   }
-  if (group * RANK_GROUP + threadIdx.x < blockIdx.x) before += tile_count[group * RANK_GROUP + threadIdx.x];
+  for (u32 t = group * RANK_GROUP + lane; t < tile; t += WAVE) before += tile_count[t];
   before = wave_sum(before);
   total = wave_sum(total);
-  if (lane_id() == 0) {
-    lds[wave_id()] = before;
-    lds[4 + wave_id()] = total;
-  }
-  __syncthreads();
-  before = lds[0] + lds[1] + lds[2] + lds[3];
-  total = lds[4] + lds[5] + lds[6] + lds[7];
   const u32 base = hdr->n_rows_base;
   const u32 err = hdr->pull_seen | ((u64)base + total > capacity_rows ? ST_FULL : 0u);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {  // read by later launches only
+  if (wave == 0 && lane == 0) {  // read by later launches only
     hdr->n_unique = 0;
     hdr->status = err;
     hdr->n_new = err ? 0u : total;
     if (!err) hdr->n_rows = base + total;
   }
+  // this wave's share: the tile's new rows first .. first + own, the occurrences of which it lists in LDS
+  const u32 first = (u32)((u64)in_tile * part / parts), own = (u32)((u64)in_tile * (part + 1) / parts) - first;
   if (own == 0) return;
-
-  __shared__ u32 wbits[RANK_WORDS];
-  __shared__ u32 wrank[RANK_WORDS];
-  if (threadIdx.x < RANK_WORDS) {  // wave 0
-    const u32 w = first_bits[blockIdx.x * RANK_WORDS + threadIdx.x];
-    wbits[threadIdx.x] = w;
-    wrank[threadIdx.x] = wave_inclusive_scan((u32)__popc(w)) - (u32)__popc(w);
-  }
-  __syncthreads();
-  const u32 row0 = base + before;
-  const u32 bit = threadIdx.x & 31u;
+  __shared__ unsigned short lists[BLOCK / WAVE][RANK_TILE];
+  unsigned short* list = lists[wave_id()];
+  u32 word = first_bits[tile * RANK_WORDS + lane];
+  for (u32 rank = wave_inclusive_scan((u32)__popc(word)) - (u32)__popc(word) - first; word; word &= word - 1, ++rank)
+    if (rank < own) list[rank] = (unsigned short)(lane * 32u + (u32)__builtin_ctz(word));
+  wave_lds_fence();
+  const u32 row0 = base + before + first, p0 = tile * RANK_TILE;
 #pragma unroll 4
-  for (u32 i = 0; i < RANK_TILE / BLOCK; ++i) {  // consecutive lanes look at consecutive occurrences
-    const u32 word = i * (BLOCK / 32) + (threadIdx.x >> 5);
-    const u32 b = wbits[word];
-    if ((b >> bit) & 1u) {
-      const u32 p = blockIdx.x * RANK_TILE + word * 32u + bit;
-      Slot* s = &slots[occ_row[p] & ~OCC_PEND_FLAG];
-      if (err) {
-        s->first_p = 0xFFFFFFFFu;
-        s->key = KEY_EMPTY;
-      } else {
-        const u32 row = row0 + wrank[word] + (u32)__popc(b & ((1u << bit) - 1u));
-        s->row = row;
-        row_key[row] = s->key;
-      }
+  for (u32 i = lane; i < own; i += WAVE) {
+    const u32 p = p0 + list[i];
+    Slot* s = &slots[occ_row[p] & ~OCC_PEND_FLAG];
+    if (err) {
+      s->first_p = 0xFFFFFFFFu;
+      s->key = KEY_EMPTY;
+    } else {
+      s->row = row0 + i;
+      row_key[row0 + i] = keys[p];
     }
   }
   if (err || !init_rows) return;
-  __syncthreads();  // the keys of the tile's rows are written
-  const u32 c = threadIdx.x % LPR;
+  const u32 c = lane % LPR;
   if (c * 4 >= D) return;
-  for (u32 i = threadIdx.x / LPR; i < own; i += BLOCK / LPR) {
-    const u32 row = row0 + i;
-    const u64 key = row_key[row];
-    f4 x, z, e;
-    x.x = init_value(seed_mul, key, 4 * c + 0, scale);
-    x.y = init_value(seed_mul, key, 4 * c + 1, scale);
-    x.z = init_value(seed_mul, key, 4 * c + 2, scale);
-    x.w = init_value(seed_mul, key, 4 * c + 3, scale);
-    z.x = z.y = z.z = z.w = 0.0f;
-    e.x = e.y = e.z = e.w = v0;
-    for (u32 j = 0; j < n_replicas; ++j) {
-      float* b = values + j * replica_stride + (u64)row * rf + 4 * c;
-      stg4(b, x);
-      if (rf == 3 * D) {
-        stg4(b + D, z);
-        stg4(b + 2 * D, e);
-      } else {
-        stg4(b + D, e);
-      }
-    }
-    if (vhat) stg4(vhat + (u64)row * D + 4 * c, e);
-  }
+#pragma unroll 2
+  for (u32 i = lane / LPR; i < own; i += WAVE / LPR)
+    init_row(row0 + i, keys[p0 + list[i]], c, values, replica_stride, n_replicas, vhat, D, rf, seed_mul, scale, v0);
+}
+
+// Large batches (probe tiles of 2048 occurrences): the initial state of the rows the pull created, in a launch of its
+// own behind the numbering, 4.5 us of a step of milliseconds.  Rows are written grid-wide in ascending order, which
+// keeps the stores of the whole chip in one window of the table, where a wave per rank tile writes one stream each:
+// 39 M occurrences, 64 columns, 5.8 M new rows: numbering and rows 1545 us in one launch, 276 + 864 in two; 90 k new
+// rows: 32 and 18 + 13.
+template <int LPR>
+__global__ void __launch_bounds__(BLOCK)
+k_init_rows(const DevHeader* hdr, const u64* __restrict__ row_key, float* values, u64 replica_stride, u32 n_replicas,
+            float* vhat, u32 D, u32 rf, u64 seed_mul, float scale, float v0) {
+  if (hdr->status) return;
+  const u32 n_new = hdr->n_new, row_base = hdr->n_rows_base, groups = gridDim.x * (BLOCK / LPR), c = threadIdx.x % LPR;
+  if (c * 4 >= D) return;
+  for (u32 i = (blockIdx.x * BLOCK + threadIdx.x) / LPR; i < n_new; i += groups)
+    init_row(row_base + i, row_key[row_base + i], c, values, replica_stride, n_replicas, vhat, D, rf, seed_mul, scale, v0);
+}
+
+// Waves per rank tile of k_rank_assign: RANK_WAVES in all, half of what the chip holds at once, as long as a wave
+// still has a few of the tile's rows if all of them are new.  (Waves of tiles without new rows end after one load.)
+constexpr u32 RANK_WAVES = 4096, RANK_MAX_PARTS = 256;
+inline u32 rank_parts(u32 n_tiles) {
+  return n_tiles == 0 ? 1u : std::min(std::max(RANK_WAVES / n_tiles, 1u), RANK_MAX_PARTS);
 }
 
 // Row of an occurrence as the probe left it: a row id, or a slot whose row has been assigned since.

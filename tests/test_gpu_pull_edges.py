@@ -1,4 +1,4 @@
-"""The pull at the edges of its work geometry: rank tiles (2048 occurrences) and their groups (128 tiles), the two
+"""The pull at the edges of its work geometry: rank tiles (2048 occurrences) and their groups (256 tiles), the two
 pooling kernels and the staged row ids of the large one.  Oracle and bounds are those of parity_util."""
 import numpy as np
 import pytest
@@ -24,7 +24,7 @@ def _batch(keys, offsets, D, seed):
 
 
 @pytest.mark.parametrize("geometry", [(0, 0), (0, 8)])
-@pytest.mark.parametrize("n", [2047, 2048, 2049, 2048 * 128 - 1, 2048 * 128 + 1])
+@pytest.mark.parametrize("n", [2047, 2048, 2049, 2048 * 128 - 1, 2048 * 128 + 1, 2048 * 256 - 1, 2048 * 256 + 1])
 def test_new_rows_numbered_across_rank_tiles(n, geometry):
     """Every third key is new in its position, the others repeat an earlier or a later one."""
     D = 4
@@ -38,6 +38,53 @@ def test_new_rows_numbered_across_rank_tiles(n, geometry):
     for step in range(2):  # all pending, then all known
         run_step(gt, ot, bt, bn, what="n=%d step %d" % (n, step))
     compare_tables(gt, ot, what="n=%d" % n)
+
+
+# the new rows of a tile are dealt to up to 256 waves: fewer rows than waves, rows in one corner of a tile, whole tiles
+@pytest.mark.parametrize("geometry", [(0, 0), (0, 8)])
+@pytest.mark.parametrize("D,W", [(4, 1), (8, 3), (100, 2), (256, 2)])
+@pytest.mark.parametrize("n,new", [(1, "all"), (300, "all"), (2049, "all"), (70001, "some"), (70001, "corner")])
+def test_new_rows_begin_with_the_initial_state(n, new, D, W, geometry):
+    from paper_2201_05500_amd.binding import CTR_OK, CtrTable
+    kw = dict(init_seed=5, n_replicas=W, kstep=W > 1)
+    gt, ot = CtrTable(n + 9, D, **kw), O.OracleTable(n + 9, D, **kw)
+    assert gt.set_geometry(*geometry) == 0
+    p = np.arange(n)
+    known = {"all": p < 0, "some": np.random.default_rng(n).random(n) < 0.98, "corner": (p < 2000) | (p > 2090)}[new]
+    keys = (p.astype(np.uint64) + np.uint64(1)) * GOLDEN
+    for k in (keys[known], keys):
+        off = np.minimum(np.arange(0, k.size + 3, 3), k.size)
+        bt = to_device(_batch(k, off, D, 1))
+        assert gt.pull_pool(0, bt["keys"], bt["offsets"])[0] == CTR_OK and gt.last_status() == CTR_OK
+        assert ot.pull_pool(0, k, off.astype(np.uint32))[0] == 0
+    assert gt.n_rows == ot.n_rows == n
+    for j in range(W):
+        g, o = gt.table_export(j), ot.table_export(j)
+        for f in ("keys", "x", "m", "v", "vhat"):
+            assert (g[f] is None and o[f] is None) or np.array_equal(g[f], o[f]), (j, f)
+
+
+@pytest.mark.parametrize("n,D,W", [(4096, 256, 8), (4096, 64, 8), (1024, 256, 1)])
+def test_small_pull_of_unseen_keys_writes_its_rows_from_the_whole_chip(n, D, W):
+    """Numbering and row creation in the time of the rows' bytes at 1 TB/s, a fifth of what a copy reaches, and 40 us
+    for the launches: 145, 66 and 43 us, of which the launches take 15 to 30.  (From one workgroup per 2048 occurrences
+    the bytes alone took 574, 170 and 127 us.)"""
+    import torch
+    from paper_2201_05500_amd.binding import CTR_OK, CtrTable
+    gt = CtrTable(2 * n, D, n_replicas=W, kstep=W > 1)
+    bt = to_device(_batch((np.arange(n, dtype=np.uint64) + np.uint64(1)) * GOLDEN, np.arange(0, n + 1, 4), D, 1))
+    took = []
+    for _ in range(9):
+        assert gt.table_clear() == CTR_OK
+        torch.cuda.synchronize()
+        gt.profile_enable(True)
+        gt.profile_read()
+        assert gt.pull_pool(0, bt["keys"], bt["offsets"])[0] == CTR_OK
+        took.append(gt.profile_read()["insert"][0] * 1e-3)
+        gt.profile_enable(False)
+    assert gt.last_status() == CTR_OK and gt.n_rows == n
+    row_bytes = n * 4 * D * (3 * W + (W > 1))
+    assert sorted(took)[4] <= row_bytes / 1e12 + 40e-6, took
 
 
 @pytest.mark.parametrize("extra", [1, 2048, 6000])
