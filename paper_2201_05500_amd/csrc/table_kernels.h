@@ -5,6 +5,7 @@
 // new row starts from is Algorithm 2's "Initialize" line (m = 0, v = eps).
 #pragma once
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -508,23 +509,21 @@ __global__ void k_collect_rows(const DevHeader* hdr, const Slot* __restrict__ sl
 // On the way a training pull records the segment of every occurrence (the push needs it) and replaces
 // "slot, row assigned later" entries by the row (the sort reads them).  Two kernels:
 //  * k_pool, for large batches, is bound by the rate of L2 requests (two 128-byte lines per gathered row), so
-//    everything else is kept off that path: a block stages the boundaries and the row ids of its POOL_NS *
-//    POOL_ROUNDS segments per group in LDS with coalesced loads, and the segment ids leave coalesced (found by
-//    binary search in the staged boundaries).  A group sums two segments at a time: up to 8 row loads in flight.
+//    everything else is kept off that path: a block stages the boundaries and up to POOL_STAGED row ids of its
+//    POOL_NS * POOL_ROUNDS segments per group in LDS with coalesced loads, and the segment ids leave coalesced (found
+//    by binary search in the staged boundaries).  A group sums two segments at a time: up to 8 row loads in flight.
+//    (With room for 6 ids per segment only, and broadcast loads in blocks that have more, 300000 segments of 32
+//    columns: 8 ids each 42 us, now 33; 12 ids 55 and 42; 30 ids 121 and 79.)
 //  * k_pool_small, for grids that leave the chip mostly idle, is bound by its chain of dependent loads: one
-//    segment per group, no barrier, nothing staged.  (16384 segments of 8 columns: 15.1 -> 9.2 us; at 10 M
-//    segments of 64 columns the unstaged form costs 1.38 against 1.31 ms.)
+//    segment per group, no barrier, nothing staged (pool_segment).  16384 segments of 8 columns: 17.1 us with k_pool,
+//    6.3 here; at 10 M segments of 64 columns the unstaged form costs 1.38 against 1.31 ms.
 #ifndef CTR_POOL_NT_OUT
 #define CTR_POOL_NT_OUT 1  // the pooled output (written once, read by the next stage) leaves with the non-temporal hint
 #endif
 constexpr u32 POOL_NS = 2;      // k_pool: segments a group works on at once
 constexpr u32 POOL_ROUNDS = 2;  // such pairs per group
 constexpr u32 POOL_MIN_BLOCKS = 1024;  // grids of k_pool below this go to k_pool_small
-template <int LPR>
-constexpr u32 pool_staged_rows() {  // row ids a block of k_pool stages: 6 per segment, at most 16 KB
-  constexpr u32 want = BLOCK / LPR * POOL_NS * POOL_ROUNDS * 6;
-  return want < 4096 ? want : 4096;
-}
+constexpr u32 POOL_STAGED = 4096;  // row ids a block of k_pool stages: 16 KB, with which eight blocks still fit a CU
 
 // OUT: 1 = fp32 output, 2 = bf16 output, 3 = both; + 4 = lookup-only input, where an occurrence may have
 // no row (compile-time, so the common fp32-only training kernel carries none of the other cases).
@@ -532,12 +531,13 @@ template <int OUT>
 __device__ __forceinline__ void pool_store(u64 g, u32 D, u32 c, d4 acc, float* __restrict__ pooled,
                                            bf16_t* __restrict__ pooled_bf16) {
   const f4 o = {(float)acc.x, (float)acc.y, (float)acc.z, (float)acc.w};
+  const u64 at = g * D + 4 * c;
 #if CTR_POOL_NT_OUT
-  if constexpr (OUT & 1) stg4_stream(pooled + g * D + 4 * c, o);
+  if constexpr (OUT & 1) stg4_stream(pooled + at, o);
 #else
-  if constexpr (OUT & 1) stg4(pooled + g * D + 4 * c, o);
+  if constexpr (OUT & 1) stg4(pooled + at, o);
 #endif
-  if constexpr (OUT & 2) stg4_bf16(pooled_bf16 + g * D + 4 * c, o);  // the fp32 value, rounded again
+  if constexpr (OUT & 2) stg4_bf16(pooled_bf16 + at, o);  // the fp32 value, rounded again
 }
 
 // Adds a batch of 4 gathered rows to a segment's sum (padded entries add +0.0).
@@ -550,6 +550,70 @@ __device__ __forceinline__ void pool_add4(const f4 (&xv)[4], d4& acc) {
   acc.x += (double)f.x; acc.y += (double)f.y; acc.z += (double)f.z; acc.w += (double)f.w;
 }
 
+// Sum of one segment by its group of LPR lanes, the row ids straight from memory.  From 4 lanes on in windows of one id
+// per lane: one coalesced load brings LPR ids, which shuffles hand out, where a broadcast load per occurrence would be
+// a request each (30000 segments of 100 ids, 128 columns: 116 -> 96 us).  RESOLVE: entries whose row was assigned after the
+// probe are replaced on the way, and the segment id is recorded for every occurrence.
+template <int LPR, bool LOOKUP, bool RESOLVE>
+__device__ __forceinline__ d4 pool_segment(u32 g, u32 beg, u32 end, u32* __restrict__ occ_row,
+                                           const Slot* __restrict__ slots, u32* __restrict__ seg_of,
+                                           const float* __restrict__ values, u32 D, u32 rf, u32 c) {
+  const bool col_ok = c * 4 < D;
+  d4 acc = {0.0, 0.0, 0.0, 0.0};
+  // occurrences k .. k + 3, as far as they are the segment's; what `meanwhile` does comes behind the requests
+  const auto add4 = [&](const u32 (&r)[4], u32 k, const auto& meanwhile) {
+    f4 xv[4];
+#pragma unroll
+    for (u32 i = 0; i < 4; ++i) {
+      xv[i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+      bool take = k + i < end && col_ok;
+      if constexpr (LOOKUP) take = take && r[i] != OCC_INVALID;  // absent keys add nothing
+      if (take) xv[i] = ldg4(values + (u64)r[i] * rf + 4 * c);
+    }
+    meanwhile();
+    pool_add4(xv, acc);
+  };
+  if constexpr (LPR >= 4) {
+    for (u32 k0 = beg; k0 < end; k0 += LPR) {
+      const bool mine = k0 + c < end;
+      u32 entry = mine ? occ_row[k0 + c] : 0u;
+      if constexpr (RESOLVE) {
+        if (entry & OCC_PEND_FLAG) occ_row[k0 + c] = entry = resolve_row(entry, slots);
+      }
+#pragma unroll 1
+      for (u32 k = 0; k < LPR && k0 + k < end; k += 4) {
+        u32 r[4];
+#pragma unroll
+        for (u32 i = 0; i < 4; ++i) r[i] = __shfl(entry, (int)(k + i), LPR);
+        add4(r, k0 + k, [&]() {
+          if constexpr (RESOLVE) {
+            if (k == 0 && mine) seg_of[k0 + c] = g;
+          }
+        });
+      }
+    }
+  } else {
+    for (u32 k = beg; k < end; k += 4) {
+      u32 r[4];
+#pragma unroll
+      for (u32 i = 0; i < 4; ++i) r[i] = k + i < end ? occ_row[k + i] : 0u;
+      if constexpr (RESOLVE) {
+#pragma unroll
+        for (u32 i = 0; i < 4; ++i)
+          if (k + i < end && (r[i] & OCC_PEND_FLAG)) occ_row[k + i] = r[i] = resolve_row(r[i], slots);
+      }
+      add4(r, k, [&]() {
+        if constexpr (RESOLVE) {
+#pragma unroll
+          for (u32 i = 0; i < 4; ++i)  // lane i % LPR writes entry i
+            if (k + i < end && i % LPR == c) seg_of[k + i] = g;
+        }
+      });
+    }
+  }
+  return acc;
+}
+
 template <int LPR, int OUT>
 __device__ __forceinline__ void pool_body(DevHeader* hdr, u32* occ_row,
                                           const Slot* __restrict__ slots, u32* __restrict__ seg_of,
@@ -560,79 +624,104 @@ __device__ __forceinline__ void pool_body(DevHeader* hdr, u32* occ_row,
   if (LOOKUP ? lookup_failed(hdr) : hdr->status != 0) return;
   constexpr u32 GROUPS = BLOCK / LPR;
   constexpr u32 TILE = GROUPS * POOL_NS * POOL_ROUNDS;
-  constexpr u32 STAGED = pool_staged_rows<LPR>();
   __shared__ u32 off_lds[TILE + 1];
-  __shared__ u32 row_lds[STAGED];
+  __shared__ u32 row_lds[POOL_STAGED];
   const u32 tile_g0 = blockIdx.x * TILE;
-  const u32 tile_n = min(TILE, n_seg - tile_g0);
+  const u32 tile_n = __builtin_amdgcn_readfirstlane(min(TILE, n_seg - tile_g0));
   for (u32 i = threadIdx.x; i <= tile_n; i += BLOCK) off_lds[i] = offsets[tile_g0 + i];
   __syncthreads();
 
-  const u32 P0 = off_lds[0], P1 = off_lds[tile_n];
-  for (u32 p = P0 + threadIdx.x; p < P1; p += BLOCK) {
-    u32 entry = occ_row[p];
-    if constexpr (!LOOKUP) {
-      if (entry & OCC_PEND_FLAG) occ_row[p] = entry = resolve_row(entry, slots);
-    }
-    if (p - P0 < STAGED) row_lds[p - P0] = entry;
-    if constexpr (!LOOKUP) {
-      u32 lo = 0, hi = tile_n;  // last l with off[l] <= p (skips empty segments)
-      while (hi - lo > 1) {
-        const u32 mid = (lo + hi) >> 1;
-        if (off_lds[mid] <= p) lo = mid; else hi = mid;
+  const u32 P0 = __builtin_amdgcn_readfirstlane(off_lds[0]), P1 = __builtin_amdgcn_readfirstlane(off_lds[tile_n]);
+  // A thread takes AHEAD occurrences at a time: requests them together, then the slots of those that are pending, then
+  // searches their segments side by side.
+  const auto stage = [&](auto ahead) {
+    constexpr u32 AHEAD = decltype(ahead)::value;
+    for (u32 p0 = P0 + threadIdx.x; p0 < P1; p0 += AHEAD * BLOCK) {
+      u32 entry[AHEAD];
+      bool pending[AHEAD];
+#pragma unroll
+      for (u32 i = 0; i < AHEAD; ++i) entry[i] = p0 + i * BLOCK < P1 ? occ_row[p0 + i * BLOCK] : 0u;
+      if constexpr (!LOOKUP) {
+#pragma unroll
+        for (u32 i = 0; i < AHEAD; ++i) {
+          pending[i] = (entry[i] & OCC_PEND_FLAG) != 0;
+          entry[i] = resolve_row(entry[i], slots);
+        }
       }
-      seg_of[p] = tile_g0 + lo;
+      u32 seg[AHEAD] = {};  // last l with off[l] <= p (skips empty segments)
+      if constexpr (!LOOKUP) {
+#pragma unroll
+        for (u32 step = TILE / 2; step > 0; step >>= 1)
+#pragma unroll
+          for (u32 i = 0; i < AHEAD; ++i)
+            if (seg[i] + step < tile_n && off_lds[seg[i] + step] <= p0 + i * BLOCK) seg[i] += step;
+      }
+#pragma unroll
+      for (u32 i = 0; i < AHEAD; ++i) {
+        const u32 p = p0 + i * BLOCK;
+        if (p >= P1) break;
+        if (p - P0 < POOL_STAGED) row_lds[p - P0] = entry[i];
+        if constexpr (!LOOKUP) {
+          if (pending[i]) occ_row[p] = entry[i];
+          seg_of[p] = tile_g0 + seg[i];
+        }
+      }
     }
-  }
+  };
+  if (P1 - P0 <= BLOCK)  // uniform over the block
+    stage(std::integral_constant<u32, 1>());
+  else if (P1 - P0 <= 2 * BLOCK)
+    stage(std::integral_constant<u32, 2>());
+  else
+    stage(std::integral_constant<u32, 4>());
   __syncthreads();
 
   const u32 grp = threadIdx.x / LPR, c = threadIdx.x % LPR;
   const bool col_ok = c * 4 < D;
-  // row_at(p): row id of occurrence p; all ids of a batch are read before the first row is requested
-  const auto sum_segments = [&](const auto& row_at) {
-#pragma unroll
-    for (u32 rnd = 0; rnd < POOL_ROUNDS; ++rnd) {
-      u32 beg[POOL_NS], end[POOL_NS];
-      d4 acc[POOL_NS];
-      u32 maxlen = 0;
-#pragma unroll
-      for (u32 s = 0; s < POOL_NS; ++s) {
-        const u32 l = (rnd * POOL_NS + s) * GROUPS + grp;
-        beg[s] = l < tile_n ? off_lds[l] : P0;
-        end[s] = l < tile_n ? off_lds[l + 1] : P0;
-        acc[s] = d4{0.0, 0.0, 0.0, 0.0};
-        maxlen = max(maxlen, end[s] - beg[s]);
-      }
-      for (u32 k = 0; k < maxlen; k += 4) {
-        u32 r[POOL_NS][4];
-        f4 xv[POOL_NS][4];
-#pragma unroll
-        for (u32 s = 0; s < POOL_NS; ++s)
-#pragma unroll
-          for (u32 i = 0; i < 4; ++i) r[s][i] = row_at(min(beg[s] + k + i, P1 - 1u));
-#pragma unroll
-        for (u32 s = 0; s < POOL_NS; ++s)
-#pragma unroll
-          for (u32 i = 0; i < 4; ++i) {
-            xv[s][i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-            bool take = beg[s] + k + i < end[s] && col_ok;
-            if constexpr (LOOKUP) take = take && r[s][i] != OCC_INVALID;  // absent keys add nothing
-            if (take) xv[s][i] = ldg4(values + (u64)r[s][i] * rf + 4 * c);
-          }
-#pragma unroll
-        for (u32 s = 0; s < POOL_NS; ++s) pool_add4(xv[s], acc[s]);
-      }
-#pragma unroll
-      for (u32 s = 0; s < POOL_NS; ++s) {
-        const u32 l = (rnd * POOL_NS + s) * GROUPS + grp;
-        if (l < tile_n && col_ok) pool_store<OUT>((u64)tile_g0 + l, D, c, acc[s], pooled, pooled_bf16);
-      }
+  if (P1 - P0 > POOL_STAGED) {  // uniform over the block: segments much longer than usual
+    for (u32 l = grp; l < tile_n; l += GROUPS) {
+      const d4 acc = pool_segment<LPR, LOOKUP, false>(0u, off_lds[l], off_lds[l + 1], occ_row, slots, seg_of, values, D, rf, c);
+      if (col_ok) pool_store<OUT>((u64)tile_g0 + l, D, c, acc, pooled, pooled_bf16);
     }
-  };
-  if (P1 - P0 <= STAGED) {  // uniform over the block
-    sum_segments([&](u32 p) { return row_lds[p - P0]; });
-  } else {  // segments much longer than usual (their ids were resolved by this block above)
-    sum_segments([&](u32 p) { return occ_row[p]; });
+    return;
+  }
+#pragma unroll
+  for (u32 rnd = 0; rnd < POOL_ROUNDS; ++rnd) {
+    u32 beg[POOL_NS], end[POOL_NS];
+    d4 acc[POOL_NS];
+    u32 maxlen = 0;
+#pragma unroll
+    for (u32 s = 0; s < POOL_NS; ++s) {
+      const u32 l = (rnd * POOL_NS + s) * GROUPS + grp;
+      beg[s] = l < tile_n ? off_lds[l] : P0;
+      end[s] = l < tile_n ? off_lds[l + 1] : P0;
+      acc[s] = d4{0.0, 0.0, 0.0, 0.0};
+      maxlen = max(maxlen, end[s] - beg[s]);
+    }
+    for (u32 k = 0; k < maxlen; k += 4) {
+      u32 r[POOL_NS][4];  // all ids are read before the first row is requested
+      f4 xv[POOL_NS][4];
+#pragma unroll
+      for (u32 s = 0; s < POOL_NS; ++s)
+#pragma unroll
+        for (u32 i = 0; i < 4; ++i) r[s][i] = row_lds[min(beg[s] + k + i, P1 - 1u) - P0];
+#pragma unroll
+      for (u32 s = 0; s < POOL_NS; ++s)
+#pragma unroll
+        for (u32 i = 0; i < 4; ++i) {
+          xv[s][i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+          bool take = beg[s] + k + i < end[s] && col_ok;
+          if constexpr (LOOKUP) take = take && r[s][i] != OCC_INVALID;  // absent keys add nothing
+          if (take) xv[s][i] = ldg4(values + (u64)r[s][i] * rf + 4 * c);
+        }
+#pragma unroll
+      for (u32 s = 0; s < POOL_NS; ++s) pool_add4(xv[s], acc[s]);
+    }
+#pragma unroll
+    for (u32 s = 0; s < POOL_NS; ++s) {
+      const u32 l = (rnd * POOL_NS + s) * GROUPS + grp;
+      if (l < tile_n && col_ok) pool_store<OUT>((u64)tile_g0 + l, D, c, acc[s], pooled, pooled_bf16);
+    }
   }
 }
 
@@ -646,34 +735,8 @@ __device__ __forceinline__ void pool_small_body(DevHeader* hdr, u32* __restrict_
   if (LOOKUP ? lookup_failed(hdr) : hdr->status != 0) return;
   const u32 g = (blockIdx.x * BLOCK + threadIdx.x) / LPR, c = threadIdx.x % LPR;
   if (g >= n_seg) return;
-  const u32 beg = offsets[g], end = offsets[g + 1];
-  const bool col_ok = c * 4 < D;
-  d4 acc = {0.0, 0.0, 0.0, 0.0};
-  for (u32 k = beg; k < end; k += 4) {
-    u32 r[4];
-    f4 xv[4];
-#pragma unroll
-    for (u32 i = 0; i < 4; ++i) r[i] = k + i < end ? occ_row[k + i] : 0u;
-    if constexpr (!LOOKUP) {
-#pragma unroll
-      for (u32 i = 0; i < 4; ++i)
-        if (k + i < end && (r[i] & OCC_PEND_FLAG)) occ_row[k + i] = r[i] = resolve_row(r[i], slots);
-    }
-#pragma unroll
-    for (u32 i = 0; i < 4; ++i) {
-      xv[i] = f4{0.0f, 0.0f, 0.0f, 0.0f};
-      bool take = k + i < end && col_ok;
-      if constexpr (LOOKUP) take = take && r[i] != OCC_INVALID;
-      if (take) xv[i] = ldg4(values + (u64)r[i] * rf + 4 * c);
-    }
-    if constexpr (!LOOKUP) {  // lane i % LPR writes entry i
-#pragma unroll
-      for (u32 i = 0; i < 4; ++i)
-        if (k + i < end && i % LPR == c) seg_of[k + i] = g;
-    }
-    pool_add4(xv, acc);
-  }
-  if (col_ok) pool_store<OUT>(g, D, c, acc, pooled, pooled_bf16);
+  const d4 acc = pool_segment<LPR, LOOKUP, !LOOKUP>(g, offsets[g], offsets[g + 1], occ_row, slots, seg_of, values, D, rf, c);
+  if (c * 4 < D) pool_store<OUT>(g, D, c, acc, pooled, pooled_bf16);
 }
 
 #define CTR_POOL_ARGS                                                                                       \
