@@ -42,7 +42,8 @@ struct DevHeader {
   u64 rows_merged;  // rows averaged by all k-step merges so far (those touched since the merge before)
   u64 merge_pending;  // (row, replica) pairs whose deferred model step those merges applied
   u32 pull_seen;    // errors the probe launch of the pull in flight found (pull_err is zero again by then)
-  u32 pad[47];
+  u32 batch_ok;     // 1: the last pull succeeded, its lists are whole (0 until its numbering is done)
+  u32 pad[46];
 };
 constexpr int HDR_WORD_N_PUSH = 7;  // index of n_push among the header's 32-bit words
 static_assert(sizeof(DevHeader) == 256, "header is one 256-byte block");

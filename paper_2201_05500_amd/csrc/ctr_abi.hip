@@ -194,6 +194,7 @@ int scratch_of_current_device(char** out) {
 struct ctr_batch {
   ctr_table* t;
   u64 generation;
+  bool failed;  // its pull is known to have failed: there are no lists, whatever the status says since it was read
   u32 replica, n_keys, n_seg;
   char* ws;
   WorkLayout wl;
@@ -440,6 +441,7 @@ static int pull_pool_impl(ctr_table* t, uint32_t replica, const uint64_t* d_keys
   ctr_batch* b = &t->cur;
   b->t = t;
   b->generation = ++t->generation;
+  b->failed = false;
   b->replica = replica;
   b->n_keys = (u32)n_keys;
   b->n_seg = n_segments;
@@ -598,6 +600,10 @@ static int push_adam_impl(ctr_table* t, uint32_t replica, ctr_batch* handle, con
   if (!batch) return CTR_E_STATE;  // stale, foreign or already consumed
   if (batch->replica != replica) return CTR_E_STATE;
   if (batch->n_seg > 0 && !d_grad_pooled) return CTR_E_INVAL;
+  if (batch->failed) {  // consumed without effect, as while the status was set
+    t->has_live = false;
+    return CTR_OK;
+  }
 
   hipStream_t st = (hipStream_t)hip_stream;
   const WorkLayout& wl = batch->wl;
@@ -840,7 +846,7 @@ int ctr_batch_export(ctr_table* t, ctr_batch* handle, uint64_t* n_unique, uint64
                      uint32_t* h_inverse, void* hip_stream) {
   if (!t || !handle) return CTR_E_INVAL;
   const ctr_batch* batch = live_batch(t, handle);
-  if (!batch) return CTR_E_STATE;
+  if (!batch || batch->failed) return CTR_E_STATE;
   hipStream_t st = (hipStream_t)hip_stream;
   DevHeader h;
   if (hipMemcpyAsync(&h, t->hdr, sizeof(h), hipMemcpyDeviceToHost, st) != hipSuccess) return CTR_E_DEVICE;
@@ -929,6 +935,7 @@ int ctr_last_status(ctr_table* t, void* hip_stream) {
   if (hipMemsetAsync((char*)t->hdr + offsetof(DevHeader, status), 0, 3 * sizeof(u32), st) != hipSuccess)
     return CTR_E_DEVICE;
   if (hipStreamSynchronize(st) != hipSuccess) return CTR_E_DEVICE;
+  if (!h.batch_ok) t->cur.failed = true;  // of a live batch: the sort has left its lists as they were
   return status_code_from_bits(h.status);
 }
 

@@ -56,6 +56,7 @@ k_probe_insert(DevHeader* hdr, Slot* slots, u32 slot_mask, const u64* __restrict
   const bool refused = hdr->status != 0;  // an earlier call failed: this pull is a no-op
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     hdr->live = refused ? 0u : 1u;
+    hdr->batch_ok = 0;
     hdr->n_rows_base = hdr->n_rows;
   }
   if (refused) return;
@@ -305,6 +306,7 @@ k_rank_assign(DevHeader* hdr, Slot* slots, const u64* __restrict__ keys, const u
   if (wave == 0 && lane == 0) {  // read by later launches only
     hdr->n_unique = 0;
     hdr->status = err;
+    hdr->batch_ok = err ? 0u : 1u;
     hdr->n_new = err ? 0u : total;
     if (!err) hdr->n_rows = base + total;
   }
