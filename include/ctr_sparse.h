@@ -34,6 +34,10 @@
  *  - Determinism: the same call sequence on the same inputs gives bit-identical
  *    key->row assignment (new keys take consecutive rows in order of their
  *    first occurrence in the batch), unique sets and pooled/updated values.
+ *    Updated values: for the same workspace sizes, too.  A workspace smaller
+ *    than ctr_workspace_bytes(cfg, n_keys, ..) may be accepted (see there);
+ *    gradients are then summed, in binary64, over other spans of the batch,
+ *    and a sum's rounding to binary32 may differ in its last bit.
  *  - Limits: dim a multiple of 4 and <= 256; capacity_rows <= 2^30 and at most
  *    2^30 index slots (the power of two >= capacity_rows / load_factor: 2^29
  *    rows at a load factor of 0.5); n_keys < 2^31 per call; n_replicas <= 31.
@@ -103,7 +107,9 @@ typedef struct {
 size_t ctr_table_bytes(const ctr_config* cfg);
 
 /* Bytes of device workspace needed by a pull/push pair of at most `max_keys`
- * key occurrences in `max_segments` segments (0 if invalid). */
+ * key occurrences in `max_segments` segments (0 if invalid).  A smaller one is
+ * used as far as it goes: for batches of fewer keys, and, with longer work
+ * spans in the push, down to ctr_debug_workspace_min_bytes(cfg, n_keys). */
 size_t ctr_workspace_bytes(const ctr_config* cfg, uint64_t max_keys, uint32_t max_segments);
 
 /* Creates an empty table in caller-provided device memory (Algorithm 1: the
@@ -298,6 +304,9 @@ int ctr_last_status(ctr_table* t, void* hip_stream);
 #define CTR_STAGE_MERGE 6   /* k-step merge */
 #define CTR_STAGE_ORDER 7   /* execution order of the push's work spans (large gradient arrays only) */
 #define CTR_N_STAGES 8
+
+/* Smallest workspace that a batch of exactly `n_keys` key occurrences is accepted with (0 if invalid). */
+size_t ctr_debug_workspace_min_bytes(const ctr_config* cfg, uint64_t n_keys);
 
 /* Test hook: fixes the work geometry of later pulls and pushes instead of letting the batch size
  * choose it (span: occurrences per work span of the push, 16/32/64/128; probe_items: occurrences

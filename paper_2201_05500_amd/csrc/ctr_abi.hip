@@ -113,15 +113,18 @@ void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force
   const size_t arr = align256(n * sizeof(u32));
   L->off_occ_row = o; o += arr;
   L->off_seg_of = o; o += arr;
+  // the numbering of new rows is done before the sort begins: its arrays stand where the sort's will
+  size_t rank = o;
+  L->off_tile_count = rank; rank += align256(((size_t)L->n_rank_tiles + 1) * sizeof(u32));
+  L->off_group_count = rank; rank += align256(((size_t)L->n_rank_groups + 1) * RANK_GROUP_STRIDE * sizeof(u32));
+  L->off_first_bits = rank; rank += align256(((size_t)L->n_rank_tiles + 1) * RANK_WORDS * sizeof(u32));
   L->off_ka = o; o += arr;
   L->off_va = o; o += arr;
   L->off_kb = o; o += arr;
   L->off_vb = o; o += arr;
   L->off_hist = o; o += align256((compact ? sort_hist_words(n, L->n_spans) : SORT_HIST_WORDS) * sizeof(u32));
   L->off_digit_total = o; o += align256(RADIX * sizeof(u32));
-  L->off_tile_count = o; o += align256(((size_t)L->n_rank_tiles + 1) * sizeof(u32));
-  L->off_group_count = o; o += align256(((size_t)L->n_rank_groups + 1) * RANK_GROUP_STRIDE * sizeof(u32));
-  L->off_first_bits = o; o += align256(((size_t)L->n_rank_tiles + 1) * RANK_WORDS * sizeof(u32));
+  o = std::max(o, rank);
   L->probe_items = n >= (4u << 20) ? PROBE_MAX_ITEMS : 1;
   if (force_items) L->probe_items = force_items;
   L->probe_tile = BLOCK * L->probe_items;
@@ -137,7 +140,8 @@ void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force
 }
 
 // The layout of a batch of n keys in a workspace of that many bytes; false if it does not fit.  Below the size
-// ctr_workspace_bytes asks for, down to what spans of 16 occurrences need, the batch runs with longer spans.
+// ctr_workspace_bytes asks for, down to the compact layout, the batch runs with longer spans.  (Callers may hold a
+// workspace sized when a batch of few keys had spans of 16 occurrences: the compact layout needs no more than that.)
 bool fit_layout(u32 D, u64 n, size_t bytes, WorkLayout* L, u32 force_span, u32 force_items) {
   work_layout(D, n, L, force_span, force_items);
   if (L->total <= bytes) return true;
@@ -361,6 +365,14 @@ size_t ctr_workspace_bytes(const ctr_config* cfg, uint64_t max_keys, uint32_t ma
     }
   }
   return need;
+}
+
+size_t ctr_debug_workspace_min_bytes(const ctr_config* cfg, uint64_t n_keys) {
+  if (!config_ok(cfg) || n_keys >= (1ull << 31)) return 0;
+  WorkLayout full, compact;
+  work_layout(cfg->dim, n_keys, &full);
+  work_layout(cfg->dim, n_keys, &compact, 0, 0, true);
+  return std::min(full.total, compact.total);
 }
 
 int ctr_table_create(const ctr_config* cfg, void* d_mem, size_t bytes, void* hip_stream, ctr_table** out) {

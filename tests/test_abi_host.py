@@ -69,6 +69,36 @@ def test_table_bytes_accounts_for_every_array():
     assert k - B.ctr_table_bytes(_cfg(n_replicas=8, flags=B.CTR_F_KSTEP | B.CTR_F_KSTEP_PROSE)) == R * D * 4
 
 
+def _workspace_with_spans_of_16(D, n):
+    """Bytes of a batch's arrays when every batch below 2 M occurrences was walked in spans of 16: what a caller may
+    have sized a workspace for by ctr_workspace_bytes of that time."""
+    up = lambda b: (b + 255) & ~255
+    words = (n + 31) // 32
+    probe_tile = 2048 if n >= 4 << 20 else 256
+    probe_tiles = -(-n // probe_tile)
+    span = 128 if n >= 8 << 20 else 64 if n >= 4 << 20 else 32 if n >= 2 << 20 else 16
+    spans = -(-n // span)
+    lists = 6 * up(4 * n) + up(4 * 256 * 4096) + up(4 * 256)
+    ranks = up(4 * (-(-words // 256) + 1)) + up(4 * (words + 1))
+    pending = up(4 * probe_tile * (probe_tiles + 1)) + up(4 * (probe_tiles + 1))
+    partials = 2 * up(8 * D * spans) + up(8 * D * -(-spans // 64)) + 2 * up(4 * spans)
+    return max(lists + ranks + pending + partials, 256)
+
+
+def test_workspaces_of_the_former_sizes_are_accepted():
+    sizes = set(range(0, 70)) | {2 ** e + d for e in range(6, 31) for d in (-257, -1, 0, 1, 300)}
+    sizes |= {(k << 24) // 8 + d for k in range(1, 1024, 5) for d in (-4097, -77440, 0, 2048)}   # lists of whole sort chunks
+    sizes |= {16702448, 16683000, 33300000, 49900000, 66500000, 300000, 300001, 500001, 1000001, 1750001, 2 ** 31 - 1}
+    sizes |= {int(1.37 ** e) for e in range(20, 68)}
+    for D in (4, 8, 64, 100, 256):
+        for n in sorted(n for n in sizes if 0 <= n < 2 ** 31):
+            least = B.ctr_debug_workspace_min_bytes(_cfg(dim=D), n)
+            assert 0 < least <= B.ctr_workspace_bytes(_cfg(dim=D), n, 0), (D, n)
+            assert least <= _workspace_with_spans_of_16(D, n), (D, n, least)
+    assert B.ctr_debug_workspace_min_bytes(_cfg(dim=6), 10) == 0
+    assert B.ctr_debug_workspace_min_bytes(_cfg(), 2 ** 31) == 0
+
+
 @pytest.mark.parametrize("bad", [
     dict(dim=0), dict(dim=6), dict(dim=260), dict(capacity_rows=0), dict(capacity_rows=(1 << 30) + 1),
     dict(n_replicas=0), dict(n_replicas=32), dict(load_factor=0.95), dict(load_factor=-1.0),

@@ -80,3 +80,30 @@ def test_workspace_for_longer_spans(D, n, ws_bytes):
     gt.ws_bytes = 8 * D * n // 16
     b = to_device(b)
     assert gt.pull_pool(0, b["keys"], b["offsets"])[0] == CTR_E_NOMEM
+
+
+# lists whose sort needs nearly all of its histograms: a workspace of the former size has no room to spare there
+@pytest.mark.parametrize("D,n", [(4, 16702448), (8, 1 << 24)])
+def test_workspace_of_the_former_size_for_long_lists(D, n):
+    import torch
+    from paper_2201_05500_amd.binding import CTR_OK, CtrTable
+    from tests.test_abi_host import _workspace_with_spans_of_16
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(n)
+    keys = (60000 ** torch.rand(n, device="cuda:0", generator=gen)).long()
+    offs = torch.arange(0, n + 1, 16, dtype=torch.int32, device="cuda:0")
+    grad = torch.randn((offs.numel() - 1, D), device="cuda:0", generator=gen)
+    ws_bytes, guard, tables = _workspace_with_spans_of_16(D, n), 1 << 16, []
+    for size in (0, ws_bytes):
+        t = CtrTable(70000, D, init_seed=3)
+        if size:
+            t.reserve = lambda *a: None
+            t._ws = torch.full((size + guard,), 0x5A, dtype=torch.uint8, device="cuda:0")
+            t.ws_bytes = size
+        for step in range(2):
+            st, h, pooled = t.pull_pool(0, keys, offs)
+            assert st == CTR_OK and t.push_adam(0, h, grad) == CTR_OK and t.last_status() == CTR_OK
+        tables.append((t, t.table_export(), pooled))
+    (_, a, pa), (t, b, pb) = tables
+    assert bool((t._ws[ws_bytes:] == 0x5A).all())
+    assert torch.equal(pa, pb) and all(np.array_equal(a[f], b[f]) for f in ("keys", "x", "m", "v"))
