@@ -21,6 +21,9 @@ using namespace ctr;
 namespace {
 
 static_assert(CTR_MLP_MAX_HIDDEN + 1 <= COLSUM_MAX_JOBS, "a batch sum per hidden layer and one");
+constexpr u32 MAX_WIDTH = 65536;
+constexpr size_t GEMM_SCRATCH_MIN = (size_t)32 << 20;
+static_assert(COLSUM_SLICES * MAX_WIDTH * sizeof(float) <= GEMM_SCRATCH_MIN, "room for the batch sums of one layer");
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // Scratch for products whose contraction is split over several workgroups (gemm_kernels.h): room for
 // four fp32 partial copies of the largest weight gradient, at least 32 MiB, at most 512 MiB.  A product
@@ -29,7 +32,7 @@ size_t gemm_scratch_bytes(const ctr_mlp_config* c) {
   size_t mx = 0;
   for (u32 l = 0; l < c->n_hidden; ++l)
     mx = std::max(mx, (size_t)(l == 0 ? c->in_dim : c->hidden[l - 1]) * c->hidden[l] * sizeof(float));
-  return std::min<size_t>(std::max<size_t>(align256(4 * mx), (size_t)32 << 20), (size_t)512 << 20);
+  return std::min<size_t>(std::max<size_t>(align256(4 * mx), GEMM_SCRATCH_MIN), (size_t)512 << 20);
 }
 inline u32 blocks_for(u64 threads) { return (u32)((threads + BLOCK - 1) / BLOCK); }
 
@@ -38,7 +41,7 @@ bool mlp_config_ok(const ctr_mlp_config* c) {
   if (c->in_dim == 0 || c->in_dim % 8 != 0) return false;
   if (c->n_hidden == 0 || c->n_hidden > CTR_MLP_MAX_HIDDEN) return false;
   for (u32 i = 0; i < c->n_hidden; ++i)
-    if (c->hidden[i] == 0 || c->hidden[i] % 8 != 0 || c->hidden[i] > 65536) return false;
+    if (c->hidden[i] == 0 || c->hidden[i] % 8 != 0 || c->hidden[i] > MAX_WIDTH) return false;
   if (c->n_replicas == 0 || c->n_replicas > 31) return false;
   if (c->kstep > 1) return false;
   if (!c->kstep && c->n_replicas != 1) return false;
@@ -85,8 +88,7 @@ struct WsLayout {
 
 void ws_layout(const ctr_mlp_config* c, const MlpLayout& L, u32 B, WsLayout* S) {
   const u32 last = c->hidden[c->n_hidden - 1];
-  size_t o = 0, n_cols = last;  // columns summed over the batch: every bias, the output layer's weights
-  for (u32 i = 0; i < c->n_hidden; ++i) n_cols += c->hidden[i];
+  size_t o = 0;
   S->off_h0 = o; o += align256((size_t)B * c->in_dim * sizeof(bf16_t));
   for (u32 i = 0; i < c->n_hidden; ++i) {
     S->off_act[i] = o;
@@ -98,7 +100,7 @@ void ws_layout(const ctr_mlp_config* c, const MlpLayout& L, u32 B, WsLayout* S) 
   S->off_grads = o; o += align256((size_t)L.n_params * sizeof(float));
   S->off_gemm = o; S->gemm_bytes = gemm_scratch_bytes(c);
   S->off_partial = o;  // the sums over the batch follow the last product, whose scratch is free again
-  o += std::max(S->gemm_bytes, align256(COLSUM_SLICES * n_cols * sizeof(float)));
+  o += S->gemm_bytes;
   S->total = o;
 }
 
@@ -307,23 +309,14 @@ static int mlp_step_impl(ctr_mlp* t, uint32_t replica, const float* d_pooled, co
   hipLaunchKernelGGL(k_out_step, dim3(blocks_for((u64)B * WAVE)), dim3(BLOCK), 0, st, a_last, PB + L.w_off[lo],
                      P + L.w_off[lo] + Hl, d_labels, B, Hl, dlogit, lterm, dz);
 
-  BatchSums q{};
-  q.rows = B;
-  q.partial = (float*)(ws + S.off_partial);
-  q.lterm = lterm;
-  q.dlogit = dlogit;
-  q.loss = d_loss;
-  q.out_bias_grad = grads + L.w_off[lo] + Hl;
-  const auto add_sum = [&q](const bf16_t* x, const float* weight, u32 H, float* out) {
-    const u32 j = q.n_jobs++;
-    q.x[j] = x;
-    q.weight[j] = weight;
-    q.out[j] = out;
-    q.H[j] = H;
-    q.col0[j] = q.n_cols;
-    q.n_cols += H;
-    q.n_tiles += (H + COLSUM_TILE - 1) / COLSUM_TILE;
-  };
+  struct {
+    const bf16_t* x;
+    const float* weight;
+    u32 H;
+    float* out;
+  } sums[COLSUM_MAX_JOBS];  // taken behind the last product, in whose scratch their partial sums stand
+  u32 n_sums = 0;
+  const auto add_sum = [&](const bf16_t* x, const float* weight, u32 H, float* out) { sums[n_sums++] = {x, weight, H, out}; };
   add_sum(a_last, dlogit, Hl, grads + L.w_off[lo]);
   // hidden layers, last to first
   for (int l = (int)lo - 1; l >= 0; --l) {
@@ -342,8 +335,30 @@ static int mlp_step_impl(ctr_mlp* t, uint32_t replica, const float* d_pooled, co
       dz = below;
     }
   }
-  hipLaunchKernelGGL(k_batch_sums, dim3(2 + q.n_tiles * COLSUM_SLICES), dim3(BLOCK), 0, st, q);
-  hipLaunchKernelGGL(k_batch_sums_final, dim3(blocks_for(q.n_cols)), dim3(BLOCK), 0, st, q);
+  BatchSums q{};
+  q.rows = B;
+  q.partial = (float*)(ws + S.off_partial);
+  q.lterm = lterm;
+  q.dlogit = dlogit;
+  q.loss = d_loss;
+  q.out_bias_grad = grads + L.w_off[lo] + Hl;
+  for (u32 i = 0; i < n_sums; ++i) {
+    const u32 j = q.n_jobs++, H = sums[i].H;
+    q.x[j] = sums[i].x;
+    q.weight[j] = sums[i].weight;
+    q.out[j] = sums[i].out;
+    q.H[j] = H;
+    q.col0[j] = q.n_cols;
+    q.n_cols += H;
+    q.n_tiles += (H + COLSUM_TILE - 1) / COLSUM_TILE;
+    // one pair of launches, unless the scratch ends before the columns do (layers of tens of thousands; each pair
+    // writes the loss and the output bias's gradient, the same values every time)
+    const u64 next = i + 1 < n_sums ? (u64)q.n_cols + sums[i + 1].H : ~0ull;
+    if (next <= S.gemm_bytes / (COLSUM_SLICES * sizeof(float))) continue;
+    hipLaunchKernelGGL(k_batch_sums, dim3(2 + q.n_tiles * COLSUM_SLICES), dim3(BLOCK), 0, st, q);
+    hipLaunchKernelGGL(k_batch_sums_final, dim3(blocks_for(q.n_cols)), dim3(BLOCK), 0, st, q);
+    q.n_jobs = q.n_cols = q.n_tiles = 0;
+  }
   // dense optimizer
   const u32 amode = mode == CTR_STEP_MERGE_PENDING ? 2u : (t->cfg.kstep ? 1u : 0u);
   const u64 n4 = L.n_params >= DENSE_ADAM_WIDE_MIN ? L.n_params / 4 : 0;

@@ -47,6 +47,23 @@ def test_mlp_host_logic():
     assert L.ctr_mlp_destroy(None) == B.CTR_E_INVAL
 
 
+@pytest.mark.parametrize("in_dim,hidden", [(19200, [1024, 512, 256]), (624, [400, 200, 80]), (8, [8]), (8, [65536]),
+                                           (8, [65536, 8, 65536]), (8, [65536, 8, 65536, 8, 65536]), (64, [8] * 6),
+                                           (1024, [65536, 65536])])
+@pytest.mark.parametrize("batch", [8, 4096, 1 << 16])
+def test_mlp_workspace_needs_no_more_than_formerly(in_dim, hidden, batch):
+    """Callers may hold a workspace sized when the output gradients of two layers, the logits and the partial sums of
+    the widest layer had places of their own."""
+    from paper_2201_05500_amd import binding_mlp as BM
+    up = lambda b: (b + 255) & ~255
+    dims, widest = [in_dim] + hidden + [1], max([8] + hidden)
+    params = sum(a * b + b for a, b in zip(dims, dims[1:]))
+    scratch = min(max(up(16 * max(a * b for a, b in zip(dims, hidden))), 32 << 20), 512 << 20)
+    former = up(2 * batch * in_dim) + sum(up(2 * batch * h) for h in hidden) + 2 * up(2 * batch * widest) + \
+        2 * up(4 * batch) + up(8 * batch) + up(4 * params) + up(4 * 64 * widest) + scratch
+    assert 0 < BM.lib().ctr_mlp_workspace_bytes(C.byref(BM.make_config(in_dim, hidden)), batch) <= former
+
+
 def test_config_struct_matches_header_layout():
     # uint64, uint32, float, uint32, 4 floats, uint64, float, uint32 with natural alignment
     assert C.sizeof(B.ctr_config) == 56

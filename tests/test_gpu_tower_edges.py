@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("in_dim,hidden,B", [(8, [8], 8), (64, [128, 136], 72), (24, [264, 8, 120], 520),
-                                             (16, [8] * 6, 1000), (64, [32], 4104), (200, [1024, 48], 64)])
+                                             (16, [8] * 6, 1000), (64, [32], 4104), (200, [1024, 48], 64),
+                                             (8, [65536, 8, 65536, 8, 65536], 8)])  # sums in more than one launch
 def test_gradient_of_one_sample_is_the_same_in_every_row(in_dim, hidden, B):
     import torch
     from paper_2201_05500_amd.binding_mlp import CtrMlp
