@@ -104,6 +104,17 @@ int ctr_mlp_gemm(int a_k_contiguous, int b_k_contiguous, const uint16_t* d_a, ui
                  uint32_t ldb, uint32_t m, uint32_t n, uint32_t k, float* d_c, uint32_t ldc, void* d_scratch,
                  size_t scratch_bytes, void* hip_stream);
 
+/* Test and measurement hooks.  The product above with the given tile (64, 128 or 256 rows and columns per workgroup) and
+ * with one work item per range of the contraction (split != 0) or one for all of them; tile = 0: as ctr_mlp_gemm
+ * chooses.  The ranges are a property of m, n, k and scratch_bytes, and the result has the same bits whatever the tile
+ * and the split.  CTR_E_INVAL also where there is no such kernel: the tile of 256 takes one range per item. */
+int ctr_debug_mlp_gemm(int a_k_contiguous, int b_k_contiguous, const uint16_t* d_a, uint32_t lda, const uint16_t* d_b,
+                       uint32_t ldb, uint32_t m, uint32_t n, uint32_t k, float* d_c, uint32_t ldc, void* d_scratch,
+                       size_t scratch_bytes, uint32_t tile, int split, void* hip_stream);
+/* What ctr_mlp_gemm chooses (host only): the tile, the work items per tile, the number of ranges and their length. */
+int ctr_debug_mlp_gemm_plan(uint32_t m, uint32_t n, uint32_t k, size_t scratch_bytes, uint32_t* tile,
+                            uint32_t* items_per_tile, uint32_t* ranges, uint32_t* range_length);
+
 /* Algorithm 2's global-averaging branch over all dense parameters of the W replicas:
  * shared v = mean_j v_j; x_i = mean_j (x_j - [merge step pending in j] lr m_j / sqrt(shared v)). */
 int ctr_mlp_kstep_merge(ctr_mlp* m, void* hip_stream);

@@ -9,7 +9,8 @@ from .binding import CTR_OK, CTR_STEP_LOCAL, lib as _base_lib
 
 CTR_MLP_MAX_HIDDEN = 6
 EXPORTED = ("ctr_mlp_bytes", "ctr_mlp_workspace_bytes", "ctr_mlp_create", "ctr_mlp_destroy", "ctr_mlp_step",
-            "ctr_mlp_forward", "ctr_mlp_step_bf16", "ctr_mlp_step_bf16_grad_bf16", "ctr_mlp_forward_bf16", "ctr_mlp_gemm", "ctr_mlp_kstep_merge", "ctr_mlp_n_params", "ctr_mlp_export", "ctr_mlp_import")
+            "ctr_mlp_forward", "ctr_mlp_step_bf16", "ctr_mlp_step_bf16_grad_bf16", "ctr_mlp_forward_bf16", "ctr_mlp_gemm", "ctr_debug_mlp_gemm",
+            "ctr_debug_mlp_gemm_plan", "ctr_mlp_kstep_merge", "ctr_mlp_n_params", "ctr_mlp_export", "ctr_mlp_import")
 
 
 class ctr_mlp_config(C.Structure):
@@ -58,6 +59,10 @@ def lib():
         L.ctr_mlp_forward_bf16.argtypes = L.ctr_mlp_forward.argtypes
         L.ctr_mlp_gemm.restype = ci
         L.ctr_mlp_gemm.argtypes = [ci, ci, vp, u32, vp, u32, u32, u32, u32, vp, u32, vp, sz, vp]
+        L.ctr_debug_mlp_gemm.restype = ci
+        L.ctr_debug_mlp_gemm.argtypes = [ci, ci, vp, u32, vp, u32, u32, u32, u32, vp, u32, vp, sz, u32, ci, vp]
+        L.ctr_debug_mlp_gemm_plan.restype = ci
+        L.ctr_debug_mlp_gemm_plan.argtypes = [u32, u32, u32, sz] + [C.POINTER(u32)] * 4
         L.ctr_mlp_kstep_merge.restype = ci
         L.ctr_mlp_kstep_merge.argtypes = [vp, vp]
         L.ctr_mlp_export.restype = ci
@@ -180,3 +185,18 @@ def ctr_mlp_gemm(a_k_contiguous, b_k_contiguous, d_a, lda, d_b, ldb, m, n, k, d_
                  stream) -> int:
     return lib().ctr_mlp_gemm(1 if a_k_contiguous else 0, 1 if b_k_contiguous else 0, d_a, lda, d_b, ldb, m, n, k, d_c,
                               ldc, d_scratch, scratch_bytes, stream)
+
+
+def ctr_debug_mlp_gemm(a_k_contiguous, b_k_contiguous, d_a, lda, d_b, ldb, m, n, k, d_c, ldc, d_scratch, scratch_bytes,
+                       tile, split, stream) -> int:
+    return lib().ctr_debug_mlp_gemm(1 if a_k_contiguous else 0, 1 if b_k_contiguous else 0, d_a, lda, d_b, ldb, m, n, k,
+                                    d_c, ldc, d_scratch, scratch_bytes, tile, 1 if split else 0, stream)
+
+
+def ctr_debug_mlp_gemm_plan(m, n, k, scratch_bytes):
+    """(tile, work items per tile, ranges of the contraction, their length) that ctr_mlp_gemm chooses."""
+    v = [C.c_uint32() for _ in range(4)]
+    st = lib().ctr_debug_mlp_gemm_plan(m, n, k, scratch_bytes, *[C.byref(x) for x in v])
+    if st != CTR_OK:
+        raise ValueError("ctr_debug_mlp_gemm_plan: %d" % st)
+    return tuple(int(x.value) for x in v)

@@ -408,10 +408,10 @@ int ctr_mlp_step_bf16_grad_bf16(ctr_mlp* t, uint32_t replica, const uint16_t* d_
                        d_workspace, workspace_bytes, mode, hip_stream);
 }
 
-// The tower's matrix product on its own (testing and measurement): C32[M x N] = A B.
-int ctr_mlp_gemm(int a_k_contiguous, int b_k_contiguous, const uint16_t* d_a, uint32_t lda, const uint16_t* d_b,
-                 uint32_t ldb, uint32_t m, uint32_t n, uint32_t k, float* d_c, uint32_t ldc, void* d_scratch,
-                 size_t scratch_bytes, void* hip_stream) {
+// The tower's matrix product on its own (testing and measurement): C32[M x N] = A B.  tile = 0: as the tower runs it.
+int ctr_debug_mlp_gemm(int a_k_contiguous, int b_k_contiguous, const uint16_t* d_a, uint32_t lda, const uint16_t* d_b,
+                       uint32_t ldb, uint32_t m, uint32_t n, uint32_t k, float* d_c, uint32_t ldc, void* d_scratch,
+                       size_t scratch_bytes, uint32_t tile, int split, void* hip_stream) {
   if (!d_a || !d_b || !d_c) return CTR_E_INVAL;
   if (m == 0 || n == 0 || k == 0 || ((m | n | k | lda | ldb | ldc) % 8u) != 0u) return CTR_E_INVAL;
   if (lda < (a_k_contiguous ? k : m) || ldb < (b_k_contiguous ? k : n) || ldc < n) return CTR_E_INVAL;
@@ -422,9 +422,34 @@ int ctr_mlp_gemm(int a_k_contiguous, int b_k_contiguous, const uint16_t* d_a, ui
   g.M = m; g.N = n; g.K = k;
   g.C32 = d_c; g.ldc = ldc;
   g.epilogue = EPI_F32;
-  const hipError_t rc = gemm_enqueue(a_k_contiguous != 0, b_k_contiguous != 0, g, (float*)d_scratch,
-                                     d_scratch ? scratch_bytes : 0, (hipStream_t)hip_stream);
-  return rc == hipSuccess ? CTR_OK : (rc == hipErrorInvalidValue ? CTR_E_INVAL : CTR_E_DEVICE);
+  const size_t room = d_scratch ? scratch_bytes : 0;
+  if (!gemm_args_ok(a_k_contiguous != 0, b_k_contiguous != 0, g)) return CTR_E_INVAL;
+  GemmPlan p;
+  if (tile == 0)
+    p = gemm_plan(m, n, k, room);
+  else if (!gemm_plan_forced(m, n, k, room, tile, split != 0, &p))
+    return CTR_E_INVAL;
+  const hipError_t rc = gemm_launch(a_k_contiguous != 0, b_k_contiguous != 0, g, p, (float*)d_scratch, (hipStream_t)hip_stream);
+  return rc == hipSuccess ? CTR_OK : CTR_E_DEVICE;
+}
+
+int ctr_mlp_gemm(int a_k_contiguous, int b_k_contiguous, const uint16_t* d_a, uint32_t lda, const uint16_t* d_b,
+                 uint32_t ldb, uint32_t m, uint32_t n, uint32_t k, float* d_c, uint32_t ldc, void* d_scratch,
+                 size_t scratch_bytes, void* hip_stream) {
+  return ctr_debug_mlp_gemm(a_k_contiguous, b_k_contiguous, d_a, lda, d_b, ldb, m, n, k, d_c, ldc, d_scratch,
+                            scratch_bytes, 0, 0, hip_stream);
+}
+
+int ctr_debug_mlp_gemm_plan(uint32_t m, uint32_t n, uint32_t k, size_t scratch_bytes, uint32_t* tile, uint32_t* items_per_tile,
+                            uint32_t* ranges, uint32_t* range_length) {
+  if (m == 0 || n == 0 || k == 0 || ((m | n | k) % 8u) != 0u || !tile || !items_per_tile || !ranges || !range_length)
+    return CTR_E_INVAL;
+  const GemmPlan p = gemm_plan(m, n, k, scratch_bytes);
+  *tile = p.tile;
+  *items_per_tile = p.n_split;
+  *ranges = (k + p.k_per_sum - 1) / p.k_per_sum;
+  *range_length = p.k_per_sum;
+  return CTR_OK;
 }
 
 int ctr_mlp_kstep_merge(ctr_mlp* t, void* hip_stream) {

@@ -407,9 +407,10 @@ k_gemm_bf16(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Bp, GemmAr
 // not by the matrix cores, so requests run up to three steps ahead: half of the workgroup's threads carry the tile of A and
 // half the tile of B (8 vectors of 16 bytes per thread and step, the same for both tile sizes and both layouts), in
 // two register sets that are refilled as soon as they have been staged into the other of two LDS buffers.
-// LDS rows hold the step's k values as chunks of 16 bytes, chunk c of row r at c ^ ((r ^ r / 8) & 7): the 8 lanes
-// served together fall on 8 chunk columns for the fragment reads (8 consecutive rows), for the writes of a
-// k-contiguous operand (8 chunks of a row) and for those of a transposed one (lanes along the rows, 8 apart, so that
+// LDS rows hold the step's k values as chunks of 16 bytes, chunk c of row r at c ^ (r & 7) for T = 128 (rows of 8
+// chunks) and at c ^ ((r ^ r / 8) & 7) for T = 64 (rows of 16): the 8 lanes served together fall on 8 chunk columns
+// for the fragment reads (8 consecutive rows), for the writes of a k-contiguous operand (8 chunks of a row) and for
+// those of a transposed one (T = 128: lanes along the chunks of a row; T = 64: lanes along the rows, 8 apart, so that
 // the loads of a wave cover 128 contiguous bytes of memory).
 // A result has the same bits whatever the tile: every element is the sum of its ranges' sums (gemm_sum_ranges), each
 // accumulated along k by the same matrix instruction.  A work item that takes all ranges folds each finished one into
@@ -733,6 +734,18 @@ inline GemmPlan gemm_plan(u32 M, u32 N, u32 K, size_t partial_capacity) {
   return best;
 }
 
+// The plan with the given tile (64, 128 or 256) and with one work item per range of the contraction or one for all;
+// false if there is no such kernel (the large tile takes one range per item).
+inline bool gemm_plan_forced(u32 M, u32 N, u32 K, size_t partial_capacity, u32 tile, bool split, GemmPlan* p) {
+  const GemmRanges ranges = gemm_sum_ranges(M, N, K, partial_capacity);
+  for (const GemmTileCost& c : GEMM_TILE_COSTS)
+    if (c.tile == tile && (tile != 256 || split || ranges.n == 1)) {
+      *p = gemm_plan_one(c, split, ranges, M, N, K);
+      return true;
+    }
+  return false;
+}
+
 // Enqueues C = A B as planned (operands, sizes, outputs and epilogue fields of `g` filled in by the caller).
 inline hipError_t gemm_launch(bool a_kc, bool b_kc, GemmArgs g, const GemmPlan& p, float* partial, hipStream_t st) {
   g.tiles_m = p.tiles_m;
@@ -793,14 +806,18 @@ inline hipError_t gemm_launch(bool a_kc, bool b_kc, GemmArgs g, const GemmPlan& 
   return hipGetLastError();
 }
 
+inline bool gemm_args_ok(bool a_kc, bool b_kc, const GemmArgs& g) {
+  if (g.M == 0 || g.N == 0 || g.K == 0) return false;
+  if ((g.M | g.N | g.K | g.lda | g.ldb) % 8u != 0u) return false;
+  // lanes address an operand with 32-bit byte offsets
+  const u64 a_bytes = 2ull * g.lda * (a_kc ? g.M : g.K), b_bytes = 2ull * g.ldb * (b_kc ? g.N : g.K);
+  return a_bytes < (1ull << 32) && b_bytes < (1ull << 32);
+}
+
 // partial: fp32 scratch of partial_capacity bytes for split products.
 inline hipError_t gemm_enqueue(bool a_kc, bool b_kc, const GemmArgs& g, float* partial, size_t partial_capacity,
                                hipStream_t st) {
-  if (g.M == 0 || g.N == 0 || g.K == 0) return hipErrorInvalidValue;
-  if ((g.M | g.N | g.K | g.lda | g.ldb) % 8u != 0u) return hipErrorInvalidValue;
-  // lanes address an operand with 32-bit byte offsets
-  const u64 a_bytes = 2ull * g.lda * (a_kc ? g.M : g.K), b_bytes = 2ull * g.ldb * (b_kc ? g.N : g.K);
-  if (a_bytes >= (1ull << 32) || b_bytes >= (1ull << 32)) return hipErrorInvalidValue;
+  if (!gemm_args_ok(a_kc, b_kc, g)) return hipErrorInvalidValue;
   return gemm_launch(a_kc, b_kc, g, gemm_plan(g.M, g.N, g.K, partial ? partial_capacity : 0), partial, st);
 }
 
