@@ -309,7 +309,7 @@ int ctr_last_status(ctr_table* t, void* hip_stream);
 size_t ctr_debug_workspace_min_bytes(const ctr_config* cfg, uint64_t n_keys);
 
 /* Test hook: fixes the work geometry of later pulls and pushes instead of letting the batch size
- * choose it (span: occurrences per work span of the push, 16/32/64/128; probe_items: occurrences
+ * choose it (span: occurrences per work span of the push, 4/8/16/32/64/128; probe_items: occurrences
  * per thread of the probe, 1 or 8; 0 = by batch size), so that every code path can be exercised
  * on small inputs.  Results do not depend on the geometry.  A geometry that needs more workspace
  * than the call was given makes the call return CTR_E_NOMEM.  Errors: CTR_E_INVAL. */

@@ -661,7 +661,7 @@ static int push_adam_impl(ctr_table* t, uint32_t replica, ctr_batch* handle, con
       u32* spare = (batch->sorted_rows == ka) ? kb : ka;
       const u32 ns4 = (wl.n_spans + 3u) & ~3u;  // the sort reads 16 bytes at a time
       const u64 grad_bytes = (u64)batch->n_seg * t->D * (grad_bf16 ? 2u : 4u);
-      if (grad_bytes >= t->push_order_min_grad_bytes && batch->n_seg > 0 && 16ull * ns4 <= 4ull * n) {
+      if (grad_bytes >= t->push_order_min_grad_bytes && batch->n_seg > 0 && 16ull * ns4 <= align256(4ull * n)) {
         StageTimer tm(t, CTR_STAGE_ORDER, st);
         u32 *key_in = spare, *val_in = spare + ns4, *key_out = spare + 2 * ns4, *val_out = spare + 3 * ns4;
         u32 seg_shift = 0;
@@ -953,7 +953,7 @@ int ctr_last_status(ctr_table* t, void* hip_stream) {
 
 int ctr_debug_set_geometry(ctr_table* t, uint32_t span, uint32_t probe_items) {
   if (!t) return CTR_E_INVAL;
-  if (span != 0 && span != 16 && span != 32 && span != 64 && span != 128) return CTR_E_INVAL;
+  if (span != 0 && (span < 4 || span > MAX_SPAN || (span & (span - 1)) != 0)) return CTR_E_INVAL;
   if (probe_items != 0 && probe_items != 1 && probe_items != (uint32_t)PROBE_MAX_ITEMS) return CTR_E_INVAL;
   t->force_span = span;
   t->force_items = probe_items;

@@ -39,9 +39,13 @@ def test_captured_pull_push_replays_like_eager_steps(variant):
         if kstep:
             assert t.kstep_merge() == CTR_OK
 
+    graphed.profile_enable(True)
+    graphed.profile_read()
     for t, p in ((eager, pooled_e), (graphed, pooled_g)):     # one eager step first: workspaces exist, rows inserted
         step(t, bt, p)
     torch.cuda.synchronize()
+    assert graphed.profile_read()["order"][1] == (1 if variant.startswith("ordered_spans") else 0)
+    graphed.profile_enable(False)
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     g = torch.cuda.CUDAGraph()

@@ -107,3 +107,28 @@ def test_workspace_of_the_former_size_for_long_lists(D, n):
     (_, a, pa), (t, b, pb) = tables
     assert bool((t._ws[ws_bytes:] == 0x5A).all())
     assert torch.equal(pa, pb) and all(np.array_equal(a[f], b[f]) for f in ("keys", "x", "m", "v"))
+
+
+# spans of 4 and 8 whatever the size would choose, in list order and ordered by windows of the gradient array (whose four
+# short lists just fit the sort's spare buffer when spans have 4 occurrences: also where n is no multiple of 16)
+@pytest.mark.parametrize("order", [None, (8, 0), (8, 1), (4, 2)])
+@pytest.mark.parametrize("span", [4, 8])
+@pytest.mark.parametrize("D", [4, 12, 64, 256])
+def test_short_spans(D, span, order):
+    from paper_2201_05500_amd.binding import CTR_E_INVAL, CTR_OK, CtrTable
+    for n in (3, 64, 255, 4097, 30007):
+        rng = np.random.default_rng(n + D)
+        keys = np.where(rng.random(n) < 0.6, rng.integers(1, 4, n), rng.integers(10, 2000, n))
+        gt, ot = CtrTable(1 << 12, D, init_seed=3), O.OracleTable(1 << 12, D, init_seed=3)
+        gt.reserve(4 * n + 100000, n)                    # room for the partial sums of short spans
+        assert gt.set_geometry(span, 0) == CTR_OK
+        assert gt.set_push_order(*(order or (0, 0)), 0) == CTR_OK
+        for step in range(2):
+            b = _batch(keys, D, n + step)
+            gt.profile_enable(True)
+            gt.profile_read()
+            run_step(gt, ot, to_device(b), b, what="n=%d" % n)
+            assert gt.profile_read()["order"][1] == (1 if order else 0), n
+            gt.profile_enable(False)
+        compare_tables(gt, ot, what="n=%d" % n)
+    assert all(gt.set_geometry(bad, 0) == CTR_E_INVAL for bad in (1, 2, 3, 5, 12, 24, 256))
