@@ -41,3 +41,53 @@ def test_gradient_of_one_sample_is_the_same_in_every_row(in_dim, hidden, B):
             first = e
         assert np.array_equal(e["m"][:-1], first["m"][:-1]), r
         assert abs(e["m"][-1] - oracle.m[0][-1]) <= (B * 2.0 ** -24 + 1e-6) * abs(oracle.m[0][-1]), r
+
+
+@pytest.mark.parametrize("kstep", [False, True])
+@pytest.mark.parametrize("width", [1024, 1032])  # a remainder of 1 parameter behind the groups of 4; widths on both sides
+def test_dense_step_of_large_towers(width, kstep):
+    """Towers of 2.1 M parameters and more update 4 parameters per thread.  From the moments a step left, its model
+    step follows in binary64, rounded once: x - lr m / sqrt(den), with the tower's own second moment, the shared
+    denominator of the k-step method, or (merge step) not at all; and the bf16 copy that the products read is the
+    rounded parameter."""
+    import torch
+    from paper_2201_05500_amd.binding import CTR_OK, CTR_STEP_LOCAL, CTR_STEP_MERGE_PENDING
+    from paper_2201_05500_amd.binding_mlp import CtrMlp
+    in_dim, B, W, lr, b1, b2 = 2048, 64, 2 if kstep else 1, 1e-3, 0.9, 0.999
+    tower = CtrMlp(in_dim, [width], init_seed=4, n_replicas=W, kstep=kstep, lr=lr, beta1=b1, beta2=b2)
+    assert tower.n_params >= 4 * 256 * 2048 and tower.n_params % 4 == 1
+    f32 = lambda a: np.float64(np.float32(a))
+    rng = np.random.default_rng(width)
+    ran = {CTR_STEP_LOCAL: 0, CTR_STEP_MERGE_PENDING: 0}
+    for step in range(4):
+        mode = CTR_STEP_MERGE_PENDING if kstep and step % 2 else CTR_STEP_LOCAL
+        for r in range(W):
+            before = tower.export(r)
+            pooled = torch.from_numpy(rng.standard_normal((B, in_dim)).astype(np.float32) * np.float32(0.1)).cuda()
+            labels = torch.from_numpy((rng.random(B) < 0.3).astype(np.float32)).cuda()
+            st, _, _ = tower.step(r, pooled, labels, mode=mode)
+            assert st == CTR_OK
+            after = tower.export(r)
+            ran[mode] += 1
+            m0, v0, m, v = (a.astype(np.float64) for a in (before["m"], before["v"], after["m"], after["v"]))
+            # m and v were made from one gradient: from m's, to a rounding of m, follows v
+            g = (m - f32(b1) * m0) / (1.0 - f32(b1))
+            slack = 2.0 ** -23 * (np.abs(m) + np.abs(m0)) / (1.0 - f32(b1))   # of g
+            want = f32(b2) * v0 + (1.0 - f32(b2)) * g * g
+            assert (np.abs(v - want) <= 2.0 ** -22 * want + (1.0 - f32(b2)) * (2 * np.abs(g) * slack + slack * slack)).all()
+            assert np.count_nonzero(g) > 0.2 * g.size
+            if mode == CTR_STEP_MERGE_PENDING:
+                assert np.array_equal(after["params"], before["params"])
+            else:
+                den = before["vhat"].astype(np.float64) if kstep else v
+                x = before["params"].astype(np.float64) - f32(lr) * m / np.sqrt(den)
+                # binary64, rounded once: the last bit of a rounding that falls between two values
+                assert (np.abs(after["params"] - x) <= 2.0 ** -24 * np.abs(x) * (1 + 1e-6) + 1e-45).all()
+            st, logits = tower.forward(r, pooled)
+            assert st == CTR_OK
+            assert tower.load(r, params=after["params"], pending=mode == CTR_STEP_MERGE_PENDING) == CTR_OK
+            st, again = tower.forward(r, pooled)
+            assert st == CTR_OK and torch.equal(logits, again)
+        if kstep and step % 2:
+            assert tower.kstep_merge() == CTR_OK
+    assert ran[CTR_STEP_LOCAL] >= 4 and (not kstep or ran[CTR_STEP_MERGE_PENDING] == 4)
