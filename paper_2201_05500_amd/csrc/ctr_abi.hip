@@ -517,12 +517,12 @@ int ctr_pull_pool_bf16(ctr_table* t, uint32_t replica, const uint64_t* d_keys, u
                         workspace_bytes, batch_out, hip_stream);
 }
 
-// Enqueues the lookup-only pooling with its two per-occurrence lists in the given device arrays.
+// Enqueues the lookup-only pooling with its list of the occurrences' rows in the given device array.
 // `timed`: record the stage timers (they create HIP events on first use, so the entry point that
 // must not allocate passes false).
 static int lookup_pool_enqueue(ctr_table* t, uint32_t replica, const uint64_t* d_keys, u32 n,
                                const uint32_t* d_offsets, uint32_t n_segments, float* d_pooled, bf16_t* pb,
-                               u32* occ_row, u32* seg_of, bool timed, hipStream_t st) {
+                               u32* occ_row, bool timed, hipStream_t st) {
   const bool profile = t->profile;
   if (!timed) t->profile = false;
   {
@@ -540,7 +540,7 @@ static int lookup_pool_enqueue(ctr_table* t, uint32_t replica, const uint64_t* d
 #define CTR_POOL_LAUNCH(KERNEL) \
   if (pg.small) { CTR_POOL_LAUNCH_1(KERNEL##_small); } else { CTR_POOL_LAUNCH_1(KERNEL); }
 #define CTR_POOL_LAUNCH_1(KERNEL) \
-  LPR_DISPATCH(t->lpr, KERNEL, pg.blocks, st, t->hdr, occ_row, t->slots, seg_of, d_offsets, n_segments, vals, t->D, t->rf, d_pooled, pb)
+  LPR_DISPATCH(t->lpr, KERNEL, pg.blocks, st, t->hdr, occ_row, t->slots, (u32*)nullptr, d_offsets, n_segments, vals, t->D, t->rf, d_pooled, pb)
     if (d_pooled && pb) {
       CTR_POOL_LAUNCH(k_pool_lookup_both);
     } else if (pb) {
@@ -578,8 +578,7 @@ int ctr_lookup_pool(ctr_table* t, uint32_t replica, const uint64_t* d_keys, uint
   if (t->has_live && t->cur.ws == (char*)d_workspace) t->has_live = false;  // the live batch's lists are overwritten
   char* ws = (char*)d_workspace;
   return lookup_pool_enqueue(t, replica, d_keys, (u32)n_keys, d_offsets, n_segments, d_pooled,
-                             (bf16_t*)d_pooled_bf16, (u32*)(ws + wl.off_occ_row), (u32*)(ws + wl.off_seg_of), true,
-                             (hipStream_t)hip_stream);
+                             (bf16_t*)d_pooled_bf16, (u32*)(ws + wl.off_occ_row), true, (hipStream_t)hip_stream);
 }
 
 int ctr_lookup_pool_noalloc(ctr_table* t, uint32_t replica, const uint64_t* d_keys, uint64_t n_keys,
@@ -587,15 +586,12 @@ int ctr_lookup_pool_noalloc(ctr_table* t, uint32_t replica, const uint64_t* d_ke
                             uint16_t* d_pooled_bf16, void* hip_stream) {
   const int rc = lookup_pool_args_ok(t, replica, d_keys, n_keys, d_offsets, n_segments, d_pooled, d_pooled_bf16);
   if (rc != CTR_OK) return rc;
-  if (n_keys > CTR_NOALLOC_MAX_KEYS) return CTR_E_NOMEM;  // the fixed scratch holds two lists of that many entries
+  if (n_keys > CTR_NOALLOC_MAX_KEYS) return CTR_E_NOMEM;  // the fixed scratch holds a list of that many entries
   char* base = nullptr;
   if (scratch_of_current_device(&base) != CTR_OK) return CTR_E_DEVICE;
-  // layout of the scratch: occ_row[CTR_NOALLOC_MAX_KEYS] | seg_of[CTR_NOALLOC_MAX_KEYS]; both lists are
-  // written in full for the n_keys occurrences of the call before they are read, so nothing needs clearing
-  u32* occ_row = (u32*)base;
-  u32* seg_of = (u32*)(base + (size_t)CTR_NOALLOC_MAX_KEYS * sizeof(u32));
+  // the list is written in full for the n_keys occurrences of the call before it is read, so nothing needs clearing
   return lookup_pool_enqueue(t, replica, d_keys, (u32)n_keys, d_offsets, n_segments, d_pooled,
-                             (bf16_t*)d_pooled_bf16, occ_row, seg_of, false, (hipStream_t)hip_stream);
+                             (bf16_t*)d_pooled_bf16, (u32*)base, false, (hipStream_t)hip_stream);
 }
 
 // grad_bf16: d_grad_pooled points at bf16 rows instead of fp32 rows

@@ -102,6 +102,21 @@ def _workspace_with_spans_of_16(D, n):
     return max(lists + ranks + pending + partials, 256)
 
 
+def test_fixed_scratch_of_the_lookup_holds_one_list():
+    """The row of each key; segments are not recorded by a lookup.  (The header's constant, and the array in the
+    library that it sizes.)"""
+    import subprocess
+    import tempfile
+    with tempfile.TemporaryDirectory() as d:
+        with open(os.path.join(d, "s.c"), "w") as f:
+            f.write('#include <stdio.h>\n#include "ctr_sparse.h"\n'
+                    'int main(void) { printf("%zu %u", CTR_NOALLOC_SCRATCH_BYTES, CTR_NOALLOC_MAX_KEYS); return 0; }\n')
+        exe = os.path.join(d, "s")
+        subprocess.check_call(["gcc", "-I" + os.path.join(ROOT, "include"), os.path.join(d, "s.c"), "-o", exe])
+        size, keys = map(int, subprocess.check_output([exe]).split())
+    assert keys == B.CTR_NOALLOC_MAX_KEYS == 1 << 22 and size == 4 * keys
+
+
 def test_workspaces_of_the_former_sizes_are_accepted():
     sizes = set(range(0, 70)) | {2 ** e + d for e in range(6, 31) for d in (-257, -1, 0, 1, 300)}
     sizes |= {(k << 24) // 8 + d for k in range(1, 1024, 5) for d in (-4097, -77440, 0, 2048)}   # lists of whole sort chunks
