@@ -16,15 +16,17 @@
 //                  sort the sub-tile in LDS, then write each digit's run to
 //                  its place; runs are contiguous, so the writes coalesce.
 // A sub-tile is 256 * ITEMS elements.  Long lists take ITEMS = 16 (long runs, few histograms; bound by memory:
-// 39 M elements 289 us a pass, 320 with 8, 383 with 4); short ones are bound by the ranking chain of one sub-tile on
-// an idle chip and take fewer: 300 k elements 17.2 us with 16, 13.8 with 4; 1.25 M 22.1 with 16, 20.0 with 8.
+// 39 M elements of 24 bits 817 us, 887 with 8); short ones are bound by the ranking chain of one sub-tile on an idle
+// chip and take fewer: 300 k elements 53 us with 16, 41 with 4; 1.25 M 65 with 16, 58 with 8.
 // (Two launches instead of three, every scatter block adding up the histograms before its own: 8.6 instead of 10.2 us
 // at 20 k elements, but 14.8 instead of 11.3 at 160 k.)
 // Digits have 8 bits, or 10 or 11 where that saves a pass and the list is short.  A pass of a short list costs its
-// three launches and their chains rather than bytes, so fewer passes win: 20-bit keys, 73 k elements 36 -> 29 us,
-// 400 k 46 -> 39, 800 k 54 -> 46; 22-bit keys, 175 k 38 -> 36, 400 k 46 -> 42.  Long lists lose by it: a sub-tile then
-// leaves runs of one or two elements per digit (2.5 M elements, 20 bits 79 -> 83 us, 22 bits 80 -> 92).  Wide digits
-// keep their histograms as [chunk][digit], which a block writes and reads coalesced.
+// three launches and their chains rather than bytes, so fewer passes win: 20-bit keys, 73 k elements 32 -> 25 us,
+// 400 k 42 -> 36, 800 k 51 -> 44; 22-bit keys, 175 k 35 -> 33, 400 k 43 -> 40.  Long lists lose by it: a sub-tile then
+// leaves runs of one or two elements per digit (2.5 M elements, 20 bits 77 -> 83 us, 22 bits 78 -> 96).  Three wide
+// passes instead of four, for keys of more than 24 bits, pay for still shorter lists only: 26 bits, 20 k 42 -> 35, 73 k
+// 43 -> 40, 175 k 45 -> 48, 300 k 52 -> 56.  Wide digits keep their histograms as [chunk][digit], which a block writes
+// and reads coalesced.  (All sizes, both sides of each line: profiles/sort_sizes.txt.)
 #pragma once
 #include <algorithm>
 
@@ -32,8 +34,8 @@
 
 namespace ctr {
 
-constexpr u32 SORT_ITEMS_4_MAX = 300000, SORT_ITEMS_8_MAX = 1750000;  // elements
-constexpr u32 SORT_10_BITS_MAX = 1000000, SORT_11_BITS_MAX = 500000;
+constexpr u32 SORT_ITEMS_4_MAX = 300000, SORT_ITEMS_8_MAX = 1600000;  // elements
+constexpr u32 SORT_10_BITS_MAX = 1000000, SORT_11_BITS_MAX = 500000, SORT_3_WIDE_PASSES_MAX = 100000;
 #ifndef CTR_SORT_MAX_CHUNKS
 #define CTR_SORT_MAX_CHUNKS 4096
 #endif
@@ -341,7 +343,7 @@ inline u32 sort_enqueue(const DevHeader* hdr, const u32* keys_in, const u32* val
   const u32 wide_bits = key_bits > 20 ? 11u : 10u;
   u32 passes = (key_bits + 7) / 8;
   const u32 wide_passes = (key_bits + wide_bits - 1) / wide_bits;
-  const bool wide = wide_passes < passes && sort_takes_wide(n, wide_bits);
+  const bool wide = wide_passes < passes && sort_takes_wide(n, wide_bits) && (wide_passes < 3 || n <= SORT_3_WIDE_PASSES_MAX);
   if (wide) passes = wide_passes;
   const SortGeom geo = wide ? sort_geom_wide(n, wide_bits) : sort_geom(n);
   u32 shift = 0;

@@ -44,8 +44,8 @@ def test_span_length_changes(D, n):
     _step((5000 ** rng.random(n)).astype(np.uint64) + 1, D, 6000)
 
 
-# the sort's tiles: 1024 elements up to 300000, 2048 up to 1750000
-@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 299999, 300000, 300001, 1749999, 1750001])
+# the sort's tiles: 1024 elements up to 300000, 2048 up to 1600000
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 299999, 300000, 300001, 1599999, 1600001, 1749999, 1750001])
 def test_sort_tiles(n):
     rng = np.random.default_rng(n)
     _step((60000 ** rng.random(n)).astype(np.uint64) + 1, 4, 70000)
@@ -58,6 +58,18 @@ def test_sort_tiles(n):
 @pytest.mark.parametrize("n", [1, 4097, 500000, 500001, 1000001])
 def test_sort_digits(R, n):
     _step(np.random.default_rng(R + n).integers(1, R, n), 4, R)
+
+
+# tables of more than 2^24 rows: three wide digits for short lists, four of 8 bits from 100001 on
+@pytest.mark.parametrize("R", [(1 << 24) + 1, 1 << 26])
+@pytest.mark.parametrize("n", [5, 4097, 100000, 100001, 300001, 500001])
+def test_sort_digits_of_large_tables(R, n):
+    from paper_2201_05500_amd.binding import CtrTable
+    gt, ot = CtrTable(R, 4, init_seed=3), O.OracleTable(n + 8, 4, init_seed=3)   # rows in use count, not the capacity
+    for step in range(2):
+        b = _batch(np.random.default_rng(n + step).integers(1, n + 1, n), 4, step)
+        run_step(gt, ot, to_device(b), b)
+    compare_tables(gt, ot)
 
 
 # a workspace with room for spans of 16 occurrences only (shorter ones are asked for), and one below that
