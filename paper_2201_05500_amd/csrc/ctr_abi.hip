@@ -87,9 +87,12 @@ inline u32 lanes_per_row(u32 D) {
 }
 
 // Occurrences per span of the push.  The span walk is sequential, so its parallelism is n / span lane groups:
-// shorter spans for smaller batches, down to what keeps a wave on every SIMD (64 Ki lanes) - the walk of a batch that
-// leaves the chip idle is a chain of dependent loads - but every span border costs partial sums and fix-up work.
-// (73 k occurrences of 8 columns, span walk + fix-up: 28 us with 16, 16 us with 4; 160 k of 16 columns: 31 us with 16, 24 us with 8.)
+// shorter spans for smaller batches - the walk of a batch that leaves the chip idle is a chain of dependent loads - but
+// every span border costs partial sums and fix-up work.  Below 2 M occurrences the line is drawn by lanes, at those that
+// keep a wave on every SIMD (64 Ki): 73 k occurrences of 8 columns, span walk + fix-up, 34 us with 16, 23 us with 4; 160 k
+// of 16 columns 38 us with 16, 30 with 8.  From 2 M on it is drawn by occurrences, which suits rows of 32 columns and
+// more (4 M of 64 columns: 396 us with 16, 372 with 64) and costs narrower ones up to a third (8 M of 4 columns: 381 us
+// with the 64 they get, 319 with 8).  (All sizes: profiles/push_spans.txt.)
 inline u32 push_span(u32 D, u64 n) {
   if (n >= (8u << 20)) return 128;
   if (n >= (4u << 20)) return 64;

@@ -415,9 +415,9 @@ k_gemm_bf16(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Bp, GemmAr
 // A result has the same bits whatever the tile: every element is the sum of its ranges' sums (gemm_sum_ranges), each
 // accumulated along k by the same matrix instruction.  A work item that takes all ranges folds each finished one into
 // `sum`, one that takes a single range leaves it for k_gemm_reduce.
-// Measured, best split of each (us, 256-wide tiles -> these): 1000 x 400 x 624 22 -> 8.3; 8 x 1024 x 19200 33 -> 17;
-// 4096 x 512 x 1024 33 -> 16; 4096 x 1024 x 512 26 -> 14; 16384 x 512 x 1024 51 -> 34; 640 x 96 x 16384 37 -> 21.
-// 4096 x 3200 x 1024 41 -> 53 and larger stay with the large tile.
+// Measured, best split of each (us, 256-wide tiles -> these): 1000 x 400 x 624 21 -> 9.0; 8 x 1024 x 19200 33 -> 18;
+// 4096 x 512 x 1024 33 -> 16; 4096 x 1024 x 512 26 -> 14; 16384 x 512 x 1024 44 -> 31; 640 x 96 x 16384 37 -> 21.
+// 4096 x 3200 x 1024 39 -> 50 and larger stay with the large tile.
 constexpr u32 SMALL_TILE_ELEMS = 8192;                  // T * steps: one operand tile, 16 KB
 constexpr u32 SMALL_LDS_BYTES = 4 * 2 * SMALL_TILE_ELEMS;
 
@@ -685,8 +685,9 @@ struct GemmPlan {
   double cost;  // estimated time, us
 };
 
-// Times the plan is made from, in us, fitted to sweeps over tile and split of 45 products from 8 x 256 x 512 to
-// 19200 x 1024 x 16384 (which it predicts to about a fifth).
+// Times the plan is made from, in us, fitted to sweeps over tile and split of products from 8 x 256 x 512 to 19200 x
+// 1024 x 16384.  It predicts what it takes to a third, mostly to a tenth, and takes the fastest of the five for 57 of 60
+// products (the others lose 1, 9 and 16 %): profiles/gemm_tiles.txt, which ctr_debug_mlp_gemm can measure again.
 struct GemmTileCost {
   u32 tile, bk;
   double fixed;         // launch, first requests and epilogue of a work item
