@@ -281,7 +281,7 @@ __device__ __forceinline__ void init_row(u32 row, u64 key, u32 c, float* values,
 // rows, so 33; 73 k keys of 64 columns 98 and 29.)
 template <int LPR>
 __global__ void __launch_bounds__(BLOCK)
-k_rank_assign(DevHeader* hdr, Slot* slots, const u64* __restrict__ keys, const u32* __restrict__ occ_row,
+k_rank_assign(DevHeader* hdr, Slot* slots, const u64* __restrict__ keys, u32* __restrict__ occ_row,
               const u32* __restrict__ first_bits, const u32* __restrict__ tile_count,
               const u32* __restrict__ group_count, u32 n_tiles, u32 parts, u64 capacity_rows,
               u64* __restrict__ row_key, u32 init_rows, float* values, u64 replica_stride, u32 n_replicas, float* vhat,
@@ -329,6 +329,7 @@ k_rank_assign(DevHeader* hdr, Slot* slots, const u64* __restrict__ keys, const u
       s->key = KEY_EMPTY;
     } else {
       s->row = row0 + i;
+      occ_row[p] = row0 + i;  // the first occurrence is resolved here, the others by whoever reads them next
       row_key[row0 + i] = keys[p];
     }
   }
