@@ -741,7 +741,8 @@ int ctr_kstep_merge(ctr_table* t, void* hip_stream) {
   if (!(t->cfg.flags & CTR_F_KSTEP)) return CTR_E_INVAL;
   hipStream_t st = (hipStream_t)hip_stream;
   StageTimer tm(t, CTR_STAGE_MERGE, st);
-  const u32 grid = (u32)std::min<u64>((t->R * t->lpr + BLOCK - 1) / BLOCK, 256 * 8);  // 8 blocks per compute unit
+  const u32 most = merge_blocks(t->tl.replica_stride * sizeof(float) * t->W, t->W, (t->cfg.flags & CTR_F_KSTEP_PROSE) != 0);
+  const u32 grid = (u32)std::min<u64>((t->R * t->lpr + BLOCK - 1) / BLOCK, most);
   if (t->cfg.flags & CTR_F_KSTEP_PROSE) {
     LPR_DISPATCH(t->lpr, k_merge_prose, grid, st, t->hdr, t->values, t->tl.replica_stride, t->W, t->vhat,
                  t->row_state, t->D, t->cfg.lr);

@@ -732,10 +732,9 @@ __device__ __forceinline__ void merge_body(DevHeader* hdr, float* __restrict__ v
       if (!PROSE) pend += (u32)__popc(st & ~RS_TOUCHED);
     }
   }
-  // rows averaged (and deferred steps applied) by this launch, for the byte accounting of the merge.  One
-  // atomic per block and counter, and the host launches no more blocks than the chip holds: atomics on one
-  // address are served one after the other, about 8 ns each, and with one per wave of a grid-sized launch
-  // they alone took 134 us for a table of 262144 rows.
+  // rows averaged (and deferred steps applied) by this launch, for the byte accounting of the merge.  One atomic
+  // per block and counter, and a bounded number of blocks (merge_blocks): atomics on one address are served one after
+  // the other, and with one per wave of a grid-sized launch they alone took 134 us for a table of 262144 rows.
   __shared__ u32 counts[2][BLOCK / WAVE];
   for (int off = WAVE / 2; off > 0; off >>= 1) {
     merged += __shfl_xor(merged, off, WAVE);
@@ -791,6 +790,15 @@ __global__ void __launch_bounds__(BLOCK) k_stream_copy(const vf4* __restrict__ s
     }
   }
   for (; i < n16; i += stride) dst[i] = src[i];
+}
+
+// Most blocks of a merge over tables of that many bytes in all.  Few, because each costs its atomics (100 k rows of 64
+// columns, 2 replicas: 56 us with 2048, 92 with 16384); but a merge of half a millisecond and more hides them, and the
+// blocks of a CU (2 of k_merge's, 5 of k_merge_prose's, by their registers) end more evenly when there are many: 4 M
+// rows of 8 columns, 31 replicas 6.5 ms with 2048, 5.9 with 16384; 4 M of 64 columns, 2 replicas, prose reading 1.82 and
+// 1.70 ms.  The printed algorithm over few replicas does not gain (1.92 and 1.95 ms).
+inline u32 merge_blocks(u64 value_bytes, u32 n_replicas, bool prose) {
+  return value_bytes >= 2500000000ull && (prose || n_replicas >= 8) ? 16384u : 2048u;
 }
 
 }  // namespace ctr

@@ -144,3 +144,19 @@ def test_short_spans(D, span, order):
             gt.profile_enable(False)
         compare_tables(gt, ot, what="n=%d" % n)
     assert all(gt.set_geometry(bad, 0) == CTR_E_INVAL for bad in (1, 2, 3, 5, 12, 24, 256))
+
+
+# more rows than the merge's blocks hold at once: 2048 blocks of 256 rows of 4 columns, 8192 of them at 16 lanes per row
+@pytest.mark.parametrize("prose", [False, True])
+@pytest.mark.parametrize("D,R", [(4, 524288 + 777), (64, 32768 + 99)])
+def test_merge_of_more_rows_than_its_grid(D, R, prose):
+    from paper_2201_05500_amd.binding import CTR_OK, CTR_STEP_LOCAL, CTR_STEP_MERGE_PENDING, CtrTable
+    kw = dict(init_seed=3, n_replicas=2, kstep=True)
+    gt, ot = CtrTable(R, D, prose=prose, **kw), O.OracleTable(R, D, variant=O.VAR_PROSE if prose else O.VAR_ALG2, **kw)
+    for r in range(2):
+        keys = np.arange(1, R + 1)[r::2] if r else np.arange(1, R + 1)
+        b = _batch(keys, D, r)
+        run_step(gt, ot, to_device(b), b, replica=r, mode=CTR_STEP_LOCAL if prose else CTR_STEP_MERGE_PENDING, check_batch=False)
+    assert gt.kstep_merge() == CTR_OK and ot.kstep_merge() == 0
+    compare_tables(gt, ot)
+    assert gt.merge_stats() == (R, 0 if prose else R + R // 2)
