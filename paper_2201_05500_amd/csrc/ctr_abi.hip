@@ -90,15 +90,21 @@ inline u32 lanes_per_row(u32 D) {
 // shorter spans for smaller batches - the walk of a batch that leaves the chip idle is a chain of dependent loads - but
 // every span border costs partial sums and fix-up work.  Below 2 M occurrences the line is drawn by lanes, at those that
 // keep a wave on every SIMD (64 Ki): 73 k occurrences of 8 columns, span walk + fix-up, 34 us with 16, 23 us with 4; 160 k
-// of 16 columns 38 us with 16, 30 with 8.  From 2 M on it is drawn by occurrences, which suits rows of 32 columns and
-// more (4 M of 64 columns: 396 us with 16, 372 with 64) and costs narrower ones up to a third (8 M of 4 columns: 381 us
-// with the 64 they get, 319 with 8).  (All sizes: profiles/push_spans.txt.)
+// of 16 columns 38 us with 16, 30 with 8.  Not below 8 for rows of 32 and 64 lanes: a wave adds the partial sums of so
+// wide a row one or two at a time (8000 occurrences of 256 columns, keys of a power law: 37 us with 16, 39 with 8, 46 with
+// 4; 4000 with 3000 keys 30, 23 and 20; 4000 of 128 columns, power law, 32, 27 and 29).  From 2 M on the line is drawn by
+// occurrences, which suits rows of 32 columns and more (4 M of 64 columns: 396 us with 16, 372 with 64) and costs
+// narrower ones up to a third (8 M of 4 columns: 381 us with the 64 they get, 319 with 8).  A batch of one or two keys
+// pays for short spans all the same (200 k occurrences of one key, 8 columns: 32 us, 27 with 16).
+// (All sizes: profiles/push_spans.txt.)
 inline u32 push_span(u32 D, u64 n) {
   if (n >= (8u << 20)) return 128;
   if (n >= (4u << 20)) return 64;
   if (n >= (2u << 20)) return 32;
-  const u64 lanes = n * lanes_per_row(D);
-  return lanes >= (1u << 20) ? 16 : lanes >= (1u << 19) ? 8 : 4;
+  const u32 lpr = lanes_per_row(D);
+  const u64 lanes = n * lpr;
+  const u32 span = lanes >= (1u << 20) ? 16 : lanes >= (1u << 19) ? 8 : 4;
+  return std::max(span, lpr < 32 ? 4u : 8u);
 }
 
 // force_span / force_items: 0 = chosen by batch size; otherwise the geometry a test asks for.  compact: spans of at

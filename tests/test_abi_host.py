@@ -117,6 +117,16 @@ def test_fixed_scratch_of_the_lookup_holds_one_list():
     assert keys == B.CTR_NOALLOC_MAX_KEYS == 1 << 22 and size == 4 * keys
 
 
+@pytest.mark.parametrize("D", [4, 8, 64, 100, 128, 132, 256])
+def test_workspace_for_many_keys_serves_every_smaller_batch(D):
+    """Batches just below a size from which spans are longer need more than those at it: the answer for max_keys covers
+    them, so it never falls as max_keys grows."""
+    sizes = sorted({2 ** e + d for e in range(9, 25) for d in (-1, 0, 1)} | {int(1.13 ** e) for e in range(10, 135)})
+    answers = [B.ctr_workspace_bytes(_cfg(dim=D), n, 0) for n in sizes]
+    assert all(a <= b for a, b in zip(answers, answers[1:]))
+    assert all(B.ctr_debug_workspace_min_bytes(_cfg(dim=D), n) <= a for n, a in zip(sizes, answers))
+
+
 def test_workspaces_of_the_former_sizes_are_accepted():
     sizes = set(range(0, 70)) | {2 ** e + d for e in range(6, 31) for d in (-257, -1, 0, 1, 300)}
     sizes |= {(k << 24) // 8 + d for k in range(1, 1024, 5) for d in (-4097, -77440, 0, 2048)}   # lists of whole sort chunks
