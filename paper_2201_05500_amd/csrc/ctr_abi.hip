@@ -76,8 +76,8 @@ bool table_layout(const ctr_config* c, TableLayout* L) {
 
 struct WorkLayout {
   u32 n_rank_tiles, n_rank_groups, probe_items, probe_tile, n_probe_tiles, span, n_spans, n_span_blocks;
-  size_t off_occ_row, off_seg_of, off_ka, off_va, off_kb, off_vb, off_hist, off_digit_total, off_tile_count, off_group_count, off_first_bits, off_pend_list, off_tile_pending,
-      off_head, off_tail, off_block_head, off_span_flags, off_span_rows, total;
+  size_t off_occ_row, off_seg_of, off_ka, off_va, off_kb, off_vb, off_hist, off_digit_total, off_tile_count,
+      off_group_count, off_first_bits, off_pend_list, off_tile_pending, off_head, off_tail, off_block_head, off_span_flags, off_span_rows, total;
 };
 
 inline u32 lanes_per_row(u32 D) {

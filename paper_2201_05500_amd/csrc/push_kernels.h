@@ -496,7 +496,8 @@ __device__ __forceinline__ void combine_groups(d4& a) {
 }
 
 // Adds the partial sums first, first + GPW, ... below end in this order.  Wide rows leave a wave few groups and long
-// lists: four partials are requested together.  (Narrower rows lose by the registers: fix-up of 16 columns 10.1 -> 13.7 us, of 64 columns 63 -> 78.)
+// lists: four partials are requested together.  (Narrower rows lose by the registers: fix-up of 16 columns 10.1 -> 13.7
+// us, of 64 columns 63 -> 78.)
 template <int LPR>
 __device__ __forceinline__ void add_partials(const double* __restrict__ part, u32 first, u32 end, u32 D, u32 c, d4& a) {
   constexpr u32 GPW = WAVE / LPR, BATCH = LPR >= 32 ? 4 : 1;
