@@ -85,7 +85,7 @@ def main():
     lines = []
     lines.append("rocprofv3 summary `%s`%s" % (a.name, (": " + a.note) if a.note else ""))
     if a.command:
-        lines.append("commands (from the repository root on the GPU box):")
+        lines.append("commands (from the repository root):")
         lines.append("  rocprofv3 --kernel-trace --stats --output-format csv -d %s -- %s" % (a.trace_dir, a.command))
         lines.append("  rocprofv3 --pmc FETCH_SIZE --output-format csv -d %s -- %s" % (a.fetch_dir, a.command))
         lines.append("  rocprofv3 --pmc WRITE_SIZE --output-format csv -d %s -- %s" % (a.write_dir, a.command))
