@@ -82,7 +82,7 @@ void mem_layout(const ctr_mlp_config* c, const MlpLayout& L, MemLayout* M) {
 }
 
 struct WsLayout {
-  size_t off_h0, off_act[CTR_MLP_MAX_HIDDEN], off_dz, off_dlogit, off_lterm, off_grads, off_partial, off_gemm,
+  size_t off_h0, off_act[CTR_MLP_MAX_HIDDEN], off_dz, off_dlogit, off_lterm, off_grads, off_gemm,
       gemm_bytes, total;
 };
 
@@ -99,7 +99,6 @@ void ws_layout(const ctr_mlp_config* c, const MlpLayout& L, u32 B, WsLayout* S) 
   S->off_lterm = o; o += align256((size_t)B * sizeof(double));
   S->off_grads = o; o += align256((size_t)L.n_params * sizeof(float));
   S->off_gemm = o; S->gemm_bytes = gemm_scratch_bytes(c);
-  S->off_partial = o;  // the sums over the batch follow the last product, whose scratch is free again
   o += S->gemm_bytes;
   S->total = o;
 }
@@ -140,20 +139,19 @@ bool product_forward(const MlpLayout& L, u32 l, u32 B, const bf16_t* h, const bf
   return gemm_enqueue(true, false, g, (float*)(ws + S.off_gemm), S.gemm_bytes, st) == hipSuccess;
 }
 
-bool product_weight_grad(const MlpLayout& L, u32 l, u32 B, const bf16_t* h, const bf16_t* dz, float* dw, char* ws,
-                         const WsLayout& S, hipStream_t st) {
+GemmArgs weight_grad_args(const MlpLayout& L, u32 l, u32 B, const bf16_t* h, const bf16_t* dz, float* dw) {
   GemmArgs g{};
   g.A = h; g.lda = L.in[l];
   g.B = dz; g.ldb = L.out[l];
   g.M = L.in[l]; g.N = L.out[l]; g.K = B;
   g.C32 = dw; g.ldc = L.out[l];
   g.epilogue = EPI_F32;
-  return gemm_enqueue(false, false, g, (float*)(ws + S.off_gemm), S.gemm_bytes, st) == hipSuccess;
+  return g;
 }
 
 // exactly one of out32 / out16 / (mask, out16): fp32, bf16, or bf16 gated by the sign of `mask`
-bool product_input_grad(const MlpLayout& L, u32 l, u32 B, const bf16_t* dz, const bf16_t* w, float* out32,
-                        bf16_t* out16, const bf16_t* mask, char* ws, const WsLayout& S, hipStream_t st) {
+GemmArgs input_grad_args(const MlpLayout& L, u32 l, u32 B, const bf16_t* dz, const bf16_t* w, float* out32, bf16_t* out16,
+                         const bf16_t* mask) {
   GemmArgs g{};
   g.A = dz; g.lda = L.out[l];
   g.B = w; g.ldb = L.out[l];
@@ -161,7 +159,55 @@ bool product_input_grad(const MlpLayout& L, u32 l, u32 B, const bf16_t* dz, cons
   g.C32 = out32; g.C16 = out16; g.ldc = L.in[l];
   g.mask = mask;
   g.epilogue = out32 ? EPI_F32 : (mask ? EPI_RELU_MASK_BF16 : EPI_BF16);
-  return gemm_enqueue(true, true, g, (float*)(ws + S.off_gemm), S.gemm_bytes, st) == hipSuccess;
+  return g;
+}
+
+// How the backward pass of a step is launched, by its sizes.
+// A layer whose two products take less time together than one after the other runs them in one launch (paired); its
+// input gradient then has a place of its own instead of the activation's.  The partial sums of split weight gradients and of
+// the sums over the batch stay where they are until the optimizer adds them (kept).  All that stands in the scratch of
+// the products; where it does not fit, every product and every sum is finished by its own launches, in turn.
+struct BackwardPlan {
+  bool kept, paired[CTR_MLP_MAX_HIDDEN];
+  GemmPlan w[CTR_MLP_MAX_HIDDEN], i[CTR_MLP_MAX_HIDDEN];
+  size_t off_w[CTR_MLP_MAX_HIDDEN], off_dz[CTR_MLP_MAX_HIDDEN], off_sums, off_rest;  // in the scratch
+};
+
+inline size_t split_bytes(const GemmPlan& p, u64 M, u64 N) { return p.n_split > 1 ? p.n_split * M * N * sizeof(float) : 0; }
+
+void backward_plan(const MlpLayout& L, u32 B, size_t room, BackwardPlan* P) {
+  const u32 hidden = L.n_layers - 1;
+  size_t o = 0, rest = 0;
+  u64 cols = L.in[hidden];
+  for (u32 l = 0; l < hidden; ++l) {
+    const u32 in = L.in[l], out = L.out[l];
+    P->w[l] = gemm_plan(in, out, B, room);
+    P->i[l] = gemm_plan(B, in, out, room);
+    GemmPlan w, i;
+    P->paired[l] = gemm_pair_plan(in, out, B, B, in, out, room, &w, &i) < P->w[l].cost + P->i[l].cost;
+    if (P->paired[l]) {
+      P->w[l] = w;
+      P->i[l] = i;
+    }
+    P->off_w[l] = o;
+    o += align256(split_bytes(P->w[l], in, out));
+    P->off_dz[l] = o;
+    if (P->paired[l] && l > 0) o += align256((size_t)B * in * sizeof(bf16_t));
+    rest = std::max(rest, split_bytes(P->i[l], B, in));
+    cols += out;
+  }
+  P->off_sums = o;
+  o += align256((size_t)COLSUM_SLICES * cols * sizeof(float));
+  P->off_rest = o;
+  P->kept = o + rest <= room;
+  if (P->kept) return;
+  for (u32 l = 0; l < hidden; ++l) {
+    P->paired[l] = false;
+    P->w[l] = gemm_plan(L.in[l], L.out[l], B, room);
+    P->i[l] = gemm_plan(B, L.in[l], L.out[l], room);
+    P->off_w[l] = 0;
+  }
+  P->off_sums = P->off_rest = 0;
 }
 
 // Forward through the hidden layers; activations stay in the workspace.
@@ -305,67 +351,102 @@ static int mlp_step_impl(ctr_mlp* t, uint32_t replica, const float* d_pooled, co
   const u32 lo = L.n_layers - 1;
   const u32 Hl = L.in[lo];
   const bf16_t* a_last = (const bf16_t*)(ws + S.off_act[lo - 1]);
-  bf16_t* dz = (bf16_t*)(ws + S.off_dz);
+  bf16_t* dz_last = (bf16_t*)(ws + S.off_dz);
+  const bf16_t* dz = dz_last;
   hipLaunchKernelGGL(k_out_step, dim3(blocks_for((u64)B * WAVE)), dim3(BLOCK), 0, st, a_last, PB + L.w_off[lo],
-                     P + L.w_off[lo] + Hl, d_labels, B, Hl, dlogit, lterm, dz);
+                     P + L.w_off[lo] + Hl, d_labels, B, Hl, dlogit, lterm, dz_last);
 
-  struct {
-    const bf16_t* x;
-    const float* weight;
-    u32 H;
-    float* out;
-  } sums[COLSUM_MAX_JOBS];  // taken behind the last product, in whose scratch their partial sums stand
-  u32 n_sums = 0;
-  const auto add_sum = [&](const bf16_t* x, const float* weight, u32 H, float* out) { sums[n_sums++] = {x, weight, H, out}; };
-  add_sum(a_last, dlogit, Hl, grads + L.w_off[lo]);
-  // hidden layers, last to first
-  for (int l = (int)lo - 1; l >= 0; --l) {
-    const bf16_t* h_prev = l == 0 ? h0 : (const bf16_t*)(ws + S.off_act[l - 1]);
-    if (!product_weight_grad(L, (u32)l, B, h_prev, dz, grads + L.w_off[l], ws, S, st)) return CTR_E_DEVICE;
-    add_sum(dz, nullptr, L.out[l], grads + L.w_off[l] + (u64)L.in[l] * L.out[l]);
-    // dH_prev[B x i] = dZ[B x o] W^T[o x i]: for the first layer the gradient of the pooled input; for a hidden
-    // layer gated by the ReLU below and rounded to bf16 on the way out (the next dZ).  It takes the place of the
-    // activation that gates it, which nothing reads any more: an element is read and written by the same thread.
-    if (l == 0) {
-      if (!product_input_grad(L, 0, B, dz, PB + L.w_off[0], d_grad_pooled, d_grad_pooled_bf16, nullptr, ws, S, st))
-        return CTR_E_DEVICE;
-    } else {
-      bf16_t* below = (bf16_t*)(ws + S.off_act[l - 1]);
-      if (!product_input_grad(L, (u32)l, B, dz, PB + L.w_off[l], nullptr, below, below, ws, S, st)) return CTR_E_DEVICE;
-      dz = below;
-    }
-  }
-  BatchSums q{};
+  BackwardPlan plan;
+  backward_plan(L, B, S.gemm_bytes, &plan);
+  char* scratch = ws + S.off_gemm;
+  GradSource src{};
+  src.n_layers = L.n_layers;
+  BatchSums q{};  // of all layers; taken behind the last product
   q.rows = B;
-  q.partial = (float*)(ws + S.off_partial);
+  q.partial = (float*)(scratch + plan.off_sums);
   q.lterm = lterm;
   q.dlogit = dlogit;
   q.loss = d_loss;
   q.out_bias_grad = grads + L.w_off[lo] + Hl;
-  for (u32 i = 0; i < n_sums; ++i) {
-    const u32 j = q.n_jobs++, H = sums[i].H;
-    q.x[j] = sums[i].x;
-    q.weight[j] = sums[i].weight;
-    q.out[j] = sums[i].out;
+  u32 job_layer[COLSUM_MAX_JOBS];
+  const auto add_sum = [&](u32 l, const bf16_t* x, const float* weight, u32 H, float* out) {
+    const u32 j = q.n_jobs++;
+    job_layer[j] = l;
+    q.x[j] = x;
+    q.weight[j] = weight;
+    q.out[j] = out;
     q.H[j] = H;
     q.col0[j] = q.n_cols;
     q.n_cols += H;
     q.n_tiles += (H + COLSUM_TILE - 1) / COLSUM_TILE;
+  };
+  add_sum(lo, a_last, dlogit, Hl, grads + L.w_off[lo]);
+  bool sums_taken = false;
+  // hidden layers, last to first
+  for (int l = (int)lo - 1; l >= 0; --l) {
+    const bf16_t* h_prev = l == 0 ? h0 : (const bf16_t*)(ws + S.off_act[l - 1]);
+    float* dw = grads + L.w_off[l];
+    const GemmArgs w = weight_grad_args(L, (u32)l, B, h_prev, dz, dw);
+    float* w_partial = (float*)(scratch + plan.off_w[l]);
+    add_sum((u32)l, dz, nullptr, L.out[l], dw + (u64)L.in[l] * L.out[l]);
+    // dH_prev[B x i] = dZ[B x o] W^T[o x i]: for the first layer the gradient of the pooled input; for a hidden
+    // layer gated by the ReLU below and rounded to bf16 on the way out (the next dZ).  In a launch of its own it takes
+    // the place of the activation that gates it, which nothing reads any more: an element is read and written by the
+    // same thread.
+    const bf16_t* mask = l == 0 ? nullptr : h_prev;
+    bf16_t* below = l == 0 ? d_grad_pooled_bf16 : plan.paired[l] ? (bf16_t*)(scratch + plan.off_dz[l]) : (bf16_t*)(ws + S.off_act[l - 1]);
+    const GemmArgs i = input_grad_args(L, (u32)l, B, dz, PB + L.w_off[l], l == 0 ? d_grad_pooled : nullptr, below, mask);
+    if (plan.paired[l]) {
+      if (!gemm_args_ok(false, false, w) || !gemm_args_ok(true, true, i)) return CTR_E_DEVICE;
+      GemmArgs gw = w, gi = i;
+      gemm_set_plan(gw, plan.w[l], w_partial);
+      gemm_set_plan(gi, plan.i[l], nullptr);
+      const u32 n_w = gw.tiles_m * gw.tiles_n * gw.n_split, n_i = gi.tiles_m * gi.tiles_n;
+      sums_taken = l == 0;
+      hipLaunchKernelGGL(k_gemm_backward, dim3(n_w + n_i + (l == 0 ? batch_sums_blocks(q) : 0)), dim3(BLOCK), 0, st, gw.A,
+                         gw.B, gw, gi.A, gi.B, gi, n_w, n_i, q);
+    } else {
+      if (!gemm_args_ok(false, false, w) || !gemm_args_ok(true, true, i)) return CTR_E_DEVICE;
+      if (gemm_launch(false, false, w, plan.w[l], w_partial, plan.kept, st) != hipSuccess) return CTR_E_DEVICE;
+      if (gemm_launch(true, true, i, plan.i[l], (float*)(scratch + plan.off_rest), false, st) != hipSuccess) return CTR_E_DEVICE;
+    }
+    const bool split = plan.kept && plan.w[l].n_split > 1;
+    src.weights[l] = {split ? w_partial : dw, (u64)L.in[l] * L.out[l], split ? plan.w[l].n_split : 1u};
+    dz = below;
+  }
+  if (plan.kept) {
+    if (!sums_taken) hipLaunchKernelGGL(k_batch_sums, dim3(batch_sums_blocks(q)), dim3(BLOCK), 0, st, q);
+  } else {
     // one pair of launches, unless the scratch ends before the columns do (layers of tens of thousands; each pair
     // writes the loss and the output bias's gradient, the same values every time)
-    const u64 next = i + 1 < n_sums ? (u64)q.n_cols + sums[i + 1].H : ~0ull;
-    if (next <= S.gemm_bytes / (COLSUM_SLICES * sizeof(float))) continue;
-    hipLaunchKernelGGL(k_batch_sums, dim3(2 + q.n_tiles * COLSUM_SLICES), dim3(BLOCK), 0, st, q);
-    hipLaunchKernelGGL(k_batch_sums_final, dim3(blocks_for(q.n_cols)), dim3(BLOCK), 0, st, q);
+    const BatchSums all = q;
     q.n_jobs = q.n_cols = q.n_tiles = 0;
+    for (u32 j = 0; j < all.n_jobs; ++j) {
+      add_sum(job_layer[j], all.x[j], all.weight[j], all.H[j], all.out[j]);
+      const u64 next = j + 1 < all.n_jobs ? (u64)q.n_cols + all.H[j + 1] : ~0ull;
+      if (next <= S.gemm_bytes / (COLSUM_SLICES * sizeof(float))) continue;
+      hipLaunchKernelGGL(k_batch_sums, dim3(batch_sums_blocks(q)), dim3(BLOCK), 0, st, q);
+      hipLaunchKernelGGL(k_batch_sums_final, dim3(blocks_for(q.n_cols)), dim3(BLOCK), 0, st, q);
+      q.n_jobs = q.n_cols = q.n_tiles = 0;
+    }
   }
   // dense optimizer
+  for (u32 l = 0; l < L.n_layers; ++l) {
+    src.w_off[l] = L.w_off[l];
+    src.n_weights[l] = (u64)L.in[l] * L.out[l];
+    src.biases[l] = {grads + L.w_off[l] + src.n_weights[l], 0, 1};
+  }
+  src.w_off[L.n_layers] = L.n_params;
+  src.weights[lo] = {grads + L.w_off[lo], 0, 1};
+  if (plan.kept)
+    for (u32 j = 0; j < q.n_jobs; ++j)  // the first sum is the output layer's weight gradient, the others are of biases
+      (j == 0 ? src.weights : src.biases)[job_layer[j]] = {q.partial + q.col0[j], q.n_cols, COLSUM_SLICES};
   const u32 amode = mode == CTR_STEP_MERGE_PENDING ? 2u : (t->cfg.kstep ? 1u : 0u);
   const u64 n4 = L.n_params >= DENSE_ADAM_WIDE_MIN ? L.n_params / 4 : 0;
   const DenseAdam adam = {(double)t->cfg.beta1, (double)t->cfg.beta2, (double)t->cfg.lr, amode};
   hipLaunchKernelGGL(k_dense_adam, dim3(blocks_for(L.n_params - 3 * n4)), dim3(BLOCK), 0, st,
                      t->params + (u64)replica * t->M.stride, t->m + (u64)replica * t->M.stride,
-                     t->v + (u64)replica * t->M.stride, t->vhat, grads, t->pb + (u64)replica * t->M.stride,
+                     t->v + (u64)replica * t->M.stride, t->vhat, src, t->pb + (u64)replica * t->M.stride,
                      L.n_params, n4, adam);
   if (mode == CTR_STEP_MERGE_PENDING) t->pend_mask |= 1u << replica;
   return launch_status();
@@ -429,7 +510,7 @@ int ctr_debug_mlp_gemm(int a_k_contiguous, int b_k_contiguous, const uint16_t* d
     p = gemm_plan(m, n, k, room);
   else if (!gemm_plan_forced(m, n, k, room, tile, split != 0, &p))
     return CTR_E_INVAL;
-  const hipError_t rc = gemm_launch(a_k_contiguous != 0, b_k_contiguous != 0, g, p, (float*)d_scratch, (hipStream_t)hip_stream);
+  const hipError_t rc = gemm_launch(a_k_contiguous != 0, b_k_contiguous != 0, g, p, (float*)d_scratch, false, (hipStream_t)hip_stream);
   return rc == hipSuccess ? CTR_OK : CTR_E_DEVICE;
 }
 

@@ -26,6 +26,7 @@
 // their first ones (they only feed elements of C that are never stored), k beyond a range as zeros.
 #pragma once
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 
@@ -195,10 +196,10 @@ struct GemmTile {
 // their operand panels.
 struct GemmItem {
   u32 m0, n0, split, k_begin, k_end;
-  __device__ __forceinline__ GemmItem(const GemmArgs& g, u32 tile) {
+  __device__ __forceinline__ GemmItem(const GemmArgs& g, u32 tile, u32 block) {
     const u32 tiles = g.tiles_m * g.tiles_n, total = tiles * g.n_split;
-    u32 id = blockIdx.x;
-    if (total % 8u == 0u) id = (blockIdx.x % 8u) * (total / 8u) + blockIdx.x / 8u;
+    u32 id = block;
+    if (total % 8u == 0u) id = (block % 8u) * (total / 8u) + block / 8u;
     const u32 tid = id % tiles, group_size = GEMM_GROUP_M * g.tiles_n, first_m = (tid / group_size) * GEMM_GROUP_M;
     const u32 gm = min(GEMM_GROUP_M, g.tiles_m - first_m);
     m0 = __builtin_amdgcn_readfirstlane((first_m + (tid % group_size) % gm) * tile);
@@ -263,13 +264,15 @@ __device__ __forceinline__ void gemm_tiles_step(const char* __restrict__ rd, cha
         acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][mi], b[kk][ni], acc[mi][ni], 0, 0, 0);
 }
 
+template <int T, int S>
+constexpr u32 gemm_tiles_lds() { return S * 2 * T * 128; }
+
 template <int T, int WN, int S, bool A_KC, bool B_KC>
-__global__ void __launch_bounds__(128 * WN, 2)
-k_gemm_tiles(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Bp, GemmArgs g) {
+__device__ __forceinline__ void gemm_tiles_body(char* lds, u32 block, const bf16_t* __restrict__ Ap,
+                                                const bf16_t* __restrict__ Bp, const GemmArgs& g) {
   constexpr int WAVES = 2 * WN;
-  constexpr u32 FM = T / 64, FN = T / WN / 32, STEP = 2 * T * 128, RING = S * STEP;
-  __shared__ __align__(16) char lds[RING];
-  const GemmItem it(g, T);
+  constexpr u32 FM = T / 64, FN = T / WN / 32, STEP = 2 * T * 128, RING = gemm_tiles_lds<T, S>();
+  const GemmItem it(g, T, block);
   const u32 n_steps = (it.k_end - it.k_begin + GEMM_BK - 1) / GEMM_BK;  // the last one may reach beyond k_end
   const u32 w = (u32)__builtin_amdgcn_readfirstlane(wave_id()), lane = (u32)lane_id(), wm = w / WN, wn = w % WN;
   typedef GemmTile<T, A_KC, WAVES> TA;
@@ -335,6 +338,13 @@ k_gemm_tiles(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Bp, GemmA
     const f4 v = *reinterpret_cast<const f4*>(region + row * COLS + (lane % LANES) * 4);
     if (m < g.M && n < g.N) gemm_emit4(g, epilogue, m, n, v, it.split);
   }
+}
+
+template <int T, int WN, int S, bool A_KC, bool B_KC>
+__global__ void __launch_bounds__(128 * WN, 2)
+k_gemm_tiles(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Bp, GemmArgs g) {
+  __shared__ __align__(16) char lds[gemm_tiles_lds<T, S>()];
+  gemm_tiles_body<T, WN, S, A_KC, B_KC>(lds, blockIdx.x, Ap, Bp, g);
 }
 
 // ---------------------------------------------------------------- tiles of 256
@@ -430,7 +440,7 @@ template <bool A_KC, bool B_KC>
 __global__ void __launch_bounds__(LARGE_BLOCK, 2)
 k_gemm_large(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Bp, GemmArgs g) {
   __shared__ __align__(16) char lds[2 * LARGE_STEP + 8 * 4096];  // two steps; a 32 x 32 block of C for each wave
-  const GemmItem it(g, 256);
+  const GemmItem it(g, 256, blockIdx.x);
   const u32 n_steps = (it.k_end - it.k_begin + GEMM_BK - 1) / GEMM_BK, n_full = (it.k_end - it.k_begin) / GEMM_BK;
   const u32 w = (u32)__builtin_amdgcn_readfirstlane(wave_id());
   LargeWork<A_KC, B_KC> t{{w, g.lda, g.M, it.m0}, {w, g.lda, g.M, it.m0 + 128}, {w, g.ldb, g.N, it.n0},
@@ -593,6 +603,31 @@ inline GemmPlan gemm_plan(u32 M, u32 N, u32 K, size_t partial_capacity) {
   return best;
 }
 
+// Two products in one launch of tiles of 64, the second unsplit: estimated time, us, and the first one's plan.  A product
+// that leaves the chip idle costs its chain of steps, whatever runs beside it.
+inline double gemm_pair_plan(u32 M1, u32 N1, u32 K1, u32 M2, u32 N2, u32 K2, size_t partial_capacity, GemmPlan* first,
+                             GemmPlan* second) {
+  const GemmTileCost& c = GEMM_TILE_COSTS[2];
+  const GemmRanges r1 = gemm_sum_ranges(M1, N1, K1, partial_capacity), r2 = gemm_sum_ranges(M2, N2, K2, partial_capacity);
+  *second = gemm_plan_one(c, false, r2, M2, N2, K2);
+  double best = 0.0;
+  for (bool split : {false, true}) {
+    if (split && r1.n == 1) break;
+    const GemmPlan p = gemm_plan_one(c, split, r1, M1, N1, K1);
+    const double items1 = (double)p.tiles_m * p.tiles_n * p.n_split, items2 = (double)second->tiles_m * second->tiles_n;
+    const double steps1 = (std::min(K1, p.k_per_split) + GEMM_BK - 1) / GEMM_BK, steps2 = (K2 + GEMM_BK - 1) / GEMM_BK;
+    const double at_once = (double)GEMM_CUS * c.per_cu, more = std::max(0.0, std::ceil((items1 + items2) / at_once) - 1.0);
+    const double work = (items1 * steps1 + items2 * steps2) / at_once * c.step2 + more * c.next;
+    const double cost = c.fixed + std::max(std::max(steps1, steps2) * c.step_few, work) +
+                        (split ? (p.n_split + 1.0) * M1 * N1 * 4.0 / 5e6 : 0.0);
+    if (!split || cost < best) {
+      best = cost;
+      *first = p;
+    }
+  }
+  return best;
+}
+
 // The plan with the given tile (64, 128 or 256) and with one work item per range of the contraction or one for all;
 // false if there is no such kernel (the large tile takes one range per item).
 inline bool gemm_plan_forced(u32 M, u32 N, u32 K, size_t partial_capacity, u32 tile, bool split, GemmPlan* p) {
@@ -605,14 +640,20 @@ inline bool gemm_plan_forced(u32 M, u32 N, u32 K, size_t partial_capacity, u32 t
   return false;
 }
 
-// Enqueues C = A B as planned (operands, sizes, outputs and epilogue fields of `g` filled in by the caller).
-inline hipError_t gemm_launch(bool a_kc, bool b_kc, GemmArgs g, const GemmPlan& p, float* partial, hipStream_t st) {
+inline void gemm_set_plan(GemmArgs& g, const GemmPlan& p, float* partial) {
   g.tiles_m = p.tiles_m;
   g.tiles_n = p.tiles_n;
   g.n_split = p.n_split;
   g.k_per_split = p.k_per_split;
   g.k_per_sum = p.k_per_sum;
   g.partial = partial;
+}
+
+// Enqueues C = A B as planned (operands, sizes, outputs and epilogue fields of `g` filled in by the caller).
+// keep_partial: the sums of a split product are left in `partial`, [range][m][n], for a later launch to add.
+inline hipError_t gemm_launch(bool a_kc, bool b_kc, GemmArgs g, const GemmPlan& p, float* partial, bool keep_partial,
+                              hipStream_t st) {
+  gemm_set_plan(g, p, partial);
   // an output that no cache holds leaves without displacing the operands
   if (g.epilogue == EPI_F32 && (u64)g.M * g.N * sizeof(float) >= GEMM_STREAM_BYTES) g.epilogue = EPI_F32_STREAM;
   const u32 grid = p.tiles_m * p.tiles_n * p.n_split;
@@ -636,7 +677,7 @@ inline hipError_t gemm_launch(bool a_kc, bool b_kc, GemmArgs g, const GemmPlan& 
   }
 #undef CTR_GEMM_LAUNCH
 #undef CTR_GEMM_PARAMS
-  if (g.n_split > 1) {
+  if (g.n_split > 1 && !keep_partial) {
     const u64 mn = (u64)g.M * g.N;
     hipLaunchKernelGGL(k_gemm_reduce, dim3((u32)((mn / 4 + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, st, g);
   }
@@ -655,7 +696,7 @@ inline bool gemm_args_ok(bool a_kc, bool b_kc, const GemmArgs& g) {
 inline hipError_t gemm_enqueue(bool a_kc, bool b_kc, const GemmArgs& g, float* partial, size_t partial_capacity,
                                hipStream_t st) {
   if (!gemm_args_ok(a_kc, b_kc, g)) return hipErrorInvalidValue;
-  return gemm_launch(a_kc, b_kc, g, gemm_plan(g.M, g.N, g.K, partial ? partial_capacity : 0), partial, st);
+  return gemm_launch(a_kc, b_kc, g, gemm_plan(g.M, g.N, g.K, partial ? partial_capacity : 0), partial, false, st);
 }
 
 }  // namespace ctr
