@@ -78,6 +78,11 @@ __device__ __forceinline__ u64 ld_relaxed(const u64* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Keeps the requests before it there: a kernel that must not act while the table holds an error asks for its first data
+// before it looks at the status, so that the two latencies pass together (0.5 us of a launch that is a chain of a few
+// loads).  Without this the compiler moves the loads behind the branch.
+__device__ __forceinline__ void requested() { asm volatile("" ::: "memory"); }
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (WAVE - 1); }
 __device__ __forceinline__ int wave_id() { return threadIdx.x >> 6; }
 

@@ -301,8 +301,8 @@ __device__ __forceinline__ void push_span_body(const DevHeader* hdr, const u32* 
                                                double* __restrict__ tail_part, u32* __restrict__ span_flags,
                                                u32* __restrict__ span_rows, const u32* __restrict__ order,
                                                const u32* __restrict__ cold_count) {
-  if (hdr->status) return;
   AdamParams P = P_in;
+  const u32 status = hdr->status;
   if constexpr (KIND == STEP_ADAM_KINGMA) {
     P.bc1 = hdr->bc1;
     P.bc2 = hdr->bc2;
@@ -327,22 +327,42 @@ __device__ __forceinline__ void push_span_body(const DevHeader* hdr, const u32* 
   const u32 e = min(b + span, n);
   const bool col_ok = c * 4 < D;
 
-  bool first_row_open = (b > 0) && (sr[b - 1] == sr[b]);  // the span starts inside a row begun earlier
+  // LPR >= PB: the group keeps a window of LPR consecutive list entries (lane c holds entry window start + c, plus the first
+  // row id after the window) and refills it with three loads every LPR occurrences.  Narrower groups take the entries of one
+  // batch.  Either is requested one step ahead: a batch would begin with a latency of its own.
+  constexpr bool WINDOW = LPR > PB && LPR % PB == 0;
+  u32 win_r = NO_ROW, win_g = 0u, win_next = NO_ROW;  // the window
+  u32 ahead_r = NO_ROW, ahead_g = 0u, ahead_next = NO_ROW;  // the one after it
+  u32 batch_r[PB + 1], batch_g[PB];
+  const auto request = [&](u32 i0) {
+    if constexpr (WINDOW) {
+      ahead_r = (i0 + c < n) ? sr[i0 + c] : NO_ROW;
+      ahead_g = (i0 + c < e) ? ss[i0 + c] : 0u;
+      ahead_next = (i0 + LPR < n) ? sr[i0 + LPR] : NO_ROW;
+    } else {
+#pragma unroll
+      for (int i = 0; i <= PB; ++i) batch_r[i] = (i0 + i < n) ? sr[i0 + i] : NO_ROW;
+#pragma unroll
+      for (int i = 0; i < PB; ++i) batch_g[i] = (i0 + i < e) ? ss[i0 + i] : 0u;
+    }
+  };
+  const u32 row_before = b > 0 ? sr[b - 1] : NO_ROW, first_row = sr[b];
+  request(b);
+  requested();
+  if (status) return;
+  bool first_row_open = row_before == first_row;  // the span starts inside a row begun earlier
   u32 flags = 0, started = 0;
   d4 acc = {0.0, 0.0, 0.0, 0.0};
 
-  // LPR > PB: the group keeps a window of LPR consecutive list entries (lane c holds entry
-  // window start + c, plus the first row id after the window) and refills it with three loads
-  // every LPR occurrences, instead of two small loads per batch of PB
-  u32 win_r = NO_ROW, win_g = 0u, win_next = NO_ROW;
   for (u32 i0 = b; i0 < e; i0 += PB) {
     u32 r[PB + 1], g[PB];
-    if constexpr (LPR > PB && LPR % PB == 0) {
+    if constexpr (WINDOW) {
       const u32 o = (i0 - b) % LPR;
       if (o == 0) {
-        win_r = (i0 + c < n) ? sr[i0 + c] : NO_ROW;
-        win_g = (i0 + c < e) ? ss[i0 + c] : 0u;
-        win_next = (i0 + LPR < n) ? sr[i0 + LPR] : NO_ROW;
+        win_r = ahead_r;
+        win_g = ahead_g;
+        win_next = ahead_next;
+        if (i0 + LPR < e) request(i0 + LPR);
       }
 #pragma unroll
       for (int i = 0; i <= PB; ++i) {
@@ -351,18 +371,12 @@ __device__ __forceinline__ void push_span_body(const DevHeader* hdr, const u32* 
       }
 #pragma unroll
       for (int i = 0; i < PB; ++i) g[i] = __shfl(win_g, (int)(o + i), LPR);
-    } else if constexpr (LPR > PB) {  // one coalesced index load per group, then broadcast
-      const u32 mine_r = (c <= PB && i0 + c < n) ? sr[i0 + c] : NO_ROW;
-      const u32 mine_g = (c < PB && i0 + c < e) ? ss[i0 + c] : 0u;
-#pragma unroll
-      for (int i = 0; i <= PB; ++i) r[i] = __shfl(mine_r, i, LPR);
-#pragma unroll
-      for (int i = 0; i < PB; ++i) g[i] = __shfl(mine_g, i, LPR);
     } else {
 #pragma unroll
-      for (int i = 0; i <= PB; ++i) r[i] = (i0 + i < n) ? sr[i0 + i] : NO_ROW;
+      for (int i = 0; i <= PB; ++i) r[i] = batch_r[i];
 #pragma unroll
-      for (int i = 0; i < PB; ++i) g[i] = (i0 + i < e) ? ss[i0 + i] : 0u;
+      for (int i = 0; i < PB; ++i) g[i] = batch_g[i];
+      if (i0 + PB < e) request(i0 + PB);
     }
     bool valid[PB], ends[PB], whole[PB];
     bool fo = first_row_open;
@@ -431,7 +445,7 @@ __device__ __forceinline__ void push_span_body(const DevHeader* hdr, const u32* 
     }
   }
   if (c == 0) {
-    span_flags[s] = (sr[b] << 2) | flags;  // first row id of the span above the two flag bits
+    span_flags[s] = (first_row << 2) | flags;  // first row id of the span above the two flag bits
     span_rows[s] = started;                // rows that START in this span
   }
 }
@@ -523,19 +537,21 @@ __global__ void __launch_bounds__(BLOCK)
 k_push_block_heads(const DevHeader* hdr, const u32* __restrict__ sr, u32 n_spans, u32 span, u32 D,
                    const double* __restrict__ head_part, double* __restrict__ block_head,
                    const u32* __restrict__ span_flags, u32* __restrict__ span_rows) {
-  if (hdr->status) return;
   const u32 j = (blockIdx.x * BLOCK + threadIdx.x) / WAVE;  // wave-uniform
-  const u32 first = j * SPANS_PER_BLOCK;
+  const u32 first = j * SPANS_PER_BLOCK, status = hdr->status;
   if (first >= n_spans) return;
   const int lane = lane_id();
   const u32 t = first + lane;
-  const u32 started = wave_sum(t < n_spans ? span_rows[t] : 0u);
+  const u32 rows = t < n_spans ? span_rows[t] : 0u, flags = t < n_spans ? span_flags[t] : 0u;
+  const u32 row = j ? sr[first * span - 1] : 0u;
+  requested();
+  if (status) return;
+  const u32 started = wave_sum(rows);
   if (lane == 0) span_rows[first] = started;
   if (j == 0) return;
   const u32 c = lane % LPR, grp = lane / LPR;
   const bool col_ok = c * 4 < D;
-  const u32 row = sr[first * span - 1];
-  const u32 n_lead = leading_true(t < n_spans && (span_flags[t] >> 2) == row);  // coalesced, unlike sr[t * span]
+  const u32 n_lead = leading_true(t < n_spans && (flags >> 2) == row);  // coalesced, unlike sr[t * span]
   if (n_lead == 0) return;
   d4 acc = {0.0, 0.0, 0.0, 0.0};
   if (col_ok) add_partials<LPR>(head_part, first + grp, first + n_lead, D, c, acc);
@@ -564,13 +580,21 @@ __device__ __forceinline__ void push_fixup_body(DevHeader* hdr, const u32* __res
                                                 const double* __restrict__ block_head,
                                                 const u32* __restrict__ span_flags,
                                                 const u32* __restrict__ span_rows) {
-  if (hdr->status) return;
+  constexpr u32 LANES = fixup_lanes(LPR);
+  const int lane = lane_id();
+  const u32 own = (blockIdx.x * BLOCK + threadIdx.x) / LANES, own_c = lane % LANES, status = hdr->status;
+  const u32 own_flags = own < n_spans ? span_flags[own] : 0u;
+  u32 next[FIXUP_NEAR];
+#pragma unroll
+  for (u32 k = 0; k < FIXUP_NEAR; ++k) next[k] = own + 1 + k < n_spans ? span_flags[own + 1 + k] >> 2 : NO_ROW;
+  const u32 last = own + 1 < n_spans ? sr[(own + 1) * span - 1] : 0u;  // of the span; a tail means that the list goes on
+  requested();
+  if (status) return;
   AdamParams P = P_in;
   if constexpr (KIND == STEP_ADAM_KINGMA) {
     P.bc1 = hdr->bc1;
     P.bc2 = hdr->bc2;
   }
-  const int lane = lane_id();
   if (blockIdx.x == 0) {
     __shared__ u32 rows[BLOCK / WAVE];
     u32 sum = 0;
@@ -581,15 +605,10 @@ __device__ __forceinline__ void push_fixup_body(DevHeader* hdr, const u32* __res
     __syncthreads();
     if (threadIdx.x == 0) hdr->n_unique = rows[0] + rows[1] + rows[2] + rows[3];
   }
-  constexpr u32 LANES = fixup_lanes(LPR);
-  const u32 own = (blockIdx.x * BLOCK + threadIdx.x) / LANES, own_c = lane % LANES;
-  const bool tail = own < n_spans && (span_flags[own] & SF_TAIL);
+  const bool tail = own_flags & SF_TAIL;
   bool far = false;
   if (tail) {
-    const u32 row = sr[(own + 1) * span - 1];  // a tail means the span is full and the list goes on
-    u32 next[FIXUP_NEAR];
-#pragma unroll
-    for (u32 k = 0; k < FIXUP_NEAR; ++k) next[k] = own + 1 + k < n_spans ? span_flags[own + 1 + k] >> 2 : NO_ROW;
+    const u32 row = last;
     u32 n_near = 0;
 #pragma unroll
     for (u32 k = 0; k < FIXUP_NEAR; ++k) n_near += (n_near == k && next[k] == row) ? 1u : 0u;

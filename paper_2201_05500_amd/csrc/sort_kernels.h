@@ -57,7 +57,13 @@ template <int R>
 __global__ void __launch_bounds__(BLOCK)
 k_sort_hist(const DevHeader* hdr, const u32* __restrict__ keys, SortGeom geo, u32 shift, u32 digit_mask,
             u32* __restrict__ hist) {
-  if (hdr->status) return;
+  const u32 beg = blockIdx.x * geo.chunk_elems;  // multiple of 1024, so 16-byte aligned
+  const u32 end = min(beg + geo.chunk_elems, geo.n);
+  const u32 status = hdr->status, e0 = beg + threadIdx.x * 4;
+  uint4 k4 = {0u, 0u, 0u, 0u};  // of the thread's first step; the next one's are requested while a step is counted
+  if (e0 + 4 <= end) k4 = *reinterpret_cast<const uint4*>(keys + e0);
+  requested();
+  if (status) return;
   // COPIES histograms per wave, chosen by lane: a popular digit (row ids of popular keys share
   // their high bits) would otherwise serialise all 64 lanes on one LDS address
   constexpr int COPIES = R == RADIX ? HIST_COPIES : 1;
@@ -67,14 +73,12 @@ k_sort_hist(const DevHeader* hdr, const u32* __restrict__ keys, SortGeom geo, u3
 #pragma unroll
     for (int q = 0; q < R / BLOCK; ++q) h[i][q * BLOCK + threadIdx.x] = 0;
   __syncthreads();
-  const u32 beg = blockIdx.x * geo.chunk_elems;  // multiple of 1024, so 16-byte aligned
-  const u32 end = min(beg + geo.chunk_elems, geo.n);
   u32* mine = h[wave_id() * COPIES + (lane_id() & (COPIES - 1))];
-  for (u32 e = beg + threadIdx.x * 4; e < end; e += BLOCK * 4) {
+  for (u32 e = e0; e < end; e += BLOCK * 4) {
     if (e + 4 <= end) {
-      const uint4 k4 = *reinterpret_cast<const uint4*>(keys + e);
       const u32 d0 = (k4.x >> shift) & digit_mask, d1 = (k4.y >> shift) & digit_mask;
       const u32 d2 = (k4.z >> shift) & digit_mask, d3 = (k4.w >> shift) & digit_mask;
+      if (e + BLOCK * 4 + 4 <= end) k4 = *reinterpret_cast<const uint4*>(keys + e + BLOCK * 4);
       // the digit of the wave's first key is counted with ballots (one add for the whole wave):
       // under a popular digit that takes most of the keys away from the LDS atomics
       const u32 ref = (u32)__builtin_amdgcn_readfirstlane((int)d0);
@@ -101,36 +105,48 @@ k_sort_hist(const DevHeader* hdr, const u32* __restrict__ keys, SortGeom geo, u3
 }
 
 // grid = RADIX blocks; block d turns hist[d][0..n_chunks) into exclusive prefix sums.
-__global__ void k_sort_scan(const DevHeader* hdr, u32* __restrict__ hist, u32 n_chunks,
-                            u32* __restrict__ digit_total) {
-  if (hdr->status) return;
+constexpr u32 SCAN_PER = (SORT_MAX_CHUNKS + BLOCK - 1) / BLOCK;  // most entries of a thread: they stay in registers
+__global__ void __launch_bounds__(BLOCK)
+k_sort_scan(const DevHeader* hdr, u32* __restrict__ hist, u32 n_chunks, u32* __restrict__ digit_total) {
   __shared__ u32 lds[4];
   u32* row = hist + blockIdx.x * n_chunks;
   const u32 per = (n_chunks + BLOCK - 1) / BLOCK;  // consecutive entries per thread
   const u32 c0 = threadIdx.x * per;
-  const u32 c1 = min(c0 + per, n_chunks);
-  u32 s = 0;
-  for (u32 i = c0; i < c1; ++i) s += row[i];
-  u32 total;
+  const u32 n = c0 < n_chunks ? min(per, n_chunks - c0) : 0u;
+  u32 v[SCAN_PER], s = 0, total;
+  const u32 status = hdr->status;
+#pragma unroll
+  for (u32 i = 0; i < SCAN_PER; ++i) v[i] = i < n ? row[c0 + i] : 0u;
+  requested();
+  if (status) return;
+#pragma unroll
+  for (u32 i = 0; i < SCAN_PER; ++i) s += v[i];
   u32 ex = block_exclusive_scan(s, lds, total);
-  for (u32 i = c0; i < c1; ++i) {
-    const u32 v = row[i];
-    row[i] = ex;
-    ex += v;
+#pragma unroll
+  for (u32 i = 0; i < SCAN_PER; ++i) {
+    if (i < n) row[c0 + i] = ex;
+    ex += v[i];
   }
   if (threadIdx.x == 0) digit_total[blockIdx.x] = total;
 }
 
-// The same for hist[chunk][digit]: a block takes 16 neighbouring digits, 16 groups of threads a share of the chunks.
+// The same for hist[chunk][digit]: a block takes 16 neighbouring digits, 16 groups of threads a share of the chunks, of
+// which the entries stay in registers.
+constexpr u32 SCAN_WIDE_PER = 32;
 __global__ void __launch_bounds__(BLOCK)
 k_sort_scan_wide(const DevHeader* hdr, u32* __restrict__ hist, u32 n_chunks, u32 radix, u32* __restrict__ digit_total) {
-  if (hdr->status) return;
   __shared__ u32 sums[16][16];
   const u32 in = threadIdx.x & 15u, group = threadIdx.x >> 4, d = blockIdx.x * 16 + in;
-  const u32 per = (n_chunks + 15) / 16, c0 = min(group * per, n_chunks), c1 = min(c0 + per, n_chunks);
-  u32 s = 0;
-#pragma unroll 8
-  for (u32 i = c0; i < c1; ++i) s += hist[i * radix + d];
+  const u32 per = (n_chunks + 15) / 16, c0 = min(group * per, n_chunks), n = min(per, n_chunks - c0);
+  u32* at = hist + c0 * radix + d;
+  u32 v[SCAN_WIDE_PER], s = 0;
+  const u32 status = hdr->status;
+#pragma unroll
+  for (u32 i = 0; i < SCAN_WIDE_PER; ++i) v[i] = i < n ? at[i * radix] : 0u;
+  requested();
+  if (status) return;
+#pragma unroll
+  for (u32 i = 0; i < SCAN_WIDE_PER; ++i) s += v[i];
   sums[group][in] = s;
   __syncthreads();
   u32 ex = 0, total = 0;
@@ -140,11 +156,10 @@ k_sort_scan_wide(const DevHeader* hdr, u32* __restrict__ hist, u32 n_chunks, u32
     if (g < group) ex += v;
     total += v;
   }
-#pragma unroll 8
-  for (u32 i = c0; i < c1; ++i) {
-    const u32 v = hist[i * radix + d];
-    hist[i * radix + d] = ex;
-    ex += v;
+#pragma unroll
+  for (u32 i = 0; i < SCAN_WIDE_PER; ++i) {
+    if (i < n) at[i * radix] = ex;
+    ex += v[i];
   }
   if (group == 0) digit_total[d] = total;
 }
@@ -154,7 +169,6 @@ __global__ void __launch_bounds__(BLOCK)
 k_sort_scatter(const DevHeader* hdr, const u32* __restrict__ keys_in, const u32* __restrict__ vals_in,
                u32* __restrict__ keys_out, u32* __restrict__ vals_out, SortGeom geo, u32 shift,
                u32 digit_mask, const u32* __restrict__ hist, const u32* __restrict__ digit_total) {
-  if (hdr->status) return;
   constexpr int TILE = BLOCK * ITEMS, DIGITS = R / BLOCK;  // digits a thread owns: DIGITS neighbouring ones
   constexpr int BITS = __builtin_ctz(R);
   __shared__ u32 scan_lds[4];
@@ -164,23 +178,39 @@ k_sort_scatter(const DevHeader* hdr, const u32* __restrict__ keys_in, const u32*
   __shared__ u32 lvals[TILE];
 
   const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
-  u32 gbase[DIGITS];  // next global position of the thread's digits for this chunk
+  const u32 chunk_beg = blockIdx.x * geo.chunk_elems;
+  const u32 chunk_end = min(chunk_beg + geo.chunk_elems, geo.n);
+  u32 k[ITEMS], v[ITEMS];
+  const auto request = [&](u32 sub) {  // waves own consecutive quarters of a sub-tile
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      const u32 at = sub + w * (TILE / 4) + i * WAVE + lane;
+      k[i] = at < chunk_end ? keys_in[at] : 0u;
+      v[i] = at < chunk_end ? vals_in[at] : 0u;
+    }
+  };
+  const u32 status = hdr->status;
+  u32 gbase[DIGITS], count[DIGITS];  // gbase: next global position of the thread's digits for this chunk
+#pragma unroll
+  for (int q = 0; q < DIGITS; ++q) {
+    const u32 d = tid * DIGITS + q;
+    count[q] = digit_total[d];
+    gbase[q] = hist[R == RADIX ? d * geo.n_chunks + blockIdx.x : blockIdx.x * R + d];
+  }
+  request(chunk_beg);
+  requested();
+  if (status) return;
   {
     u32 sum = 0, total;
 #pragma unroll
-    for (int q = 0; q < DIGITS; ++q) {
-      gbase[q] = sum;
-      sum += digit_total[tid * DIGITS + q];
-    }
-    const u32 ex = block_exclusive_scan(sum, scan_lds, total);
+    for (int q = 0; q < DIGITS; ++q) sum += count[q];
+    u32 ex = block_exclusive_scan(sum, scan_lds, total);
 #pragma unroll
     for (int q = 0; q < DIGITS; ++q) {
-      const u32 d = tid * DIGITS + q;
-      gbase[q] += ex + hist[R == RADIX ? d * geo.n_chunks + blockIdx.x : blockIdx.x * R + d];
+      gbase[q] += ex;
+      ex += count[q];
     }
   }
-  const u32 chunk_beg = blockIdx.x * geo.chunk_elems;
-  const u32 chunk_end = min(chunk_beg + geo.chunk_elems, geo.n);
   const u64 lanes_below = (1ull << lane) - 1ull;
 
   for (u32 sub = chunk_beg; sub < chunk_end; sub += TILE) {
@@ -191,15 +221,8 @@ k_sort_scatter(const DevHeader* hdr, const u32* __restrict__ keys_in, const u32*
       for (int q = 0; q < DIGITS; ++q) whist[i][q * BLOCK + tid] = 0;
     __syncthreads();
 
-    u32 k[ITEMS], v[ITEMS], rank[ITEMS];
+    u32 rank[ITEMS];
     volatile u32* my_hist = whist[w];
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      const u32 local = w * (TILE / 4) + i * WAVE + lane;  // waves own consecutive quarters
-      const bool valid = local < n_valid;
-      k[i] = valid ? keys_in[sub + local] : 0u;
-      v[i] = valid ? vals_in[sub + local] : 0u;
-    }
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
       const u32 local = w * (TILE / 4) + i * WAVE + lane;
@@ -261,6 +284,7 @@ k_sort_scatter(const DevHeader* hdr, const u32* __restrict__ keys_in, const u32*
         lvals[pos] = v[i];
       }
     }
+    if (sub + TILE < chunk_end) request(sub + TILE);
     __syncthreads();
 
     for (u32 j = tid; j < n_valid; j += BLOCK) {

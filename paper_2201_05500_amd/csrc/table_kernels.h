@@ -53,7 +53,11 @@ k_probe_insert(DevHeader* hdr, Slot* slots, u32 slot_mask, const u64* __restrict
                const u32* __restrict__ offsets, u32 n_seg, u32* __restrict__ occ_row,
                u32* __restrict__ pend_list, u32* __restrict__ tile_pending, u32 items,
                u32* __restrict__ group_count, u32 n_groups) {
+  const u32 tile0 = blockIdx.x * (BLOCK * items);
+  u64 key = KEY_EMPTY;  // the thread's next occurrence: requested one ahead
+  if (tile0 + threadIdx.x < n_keys) key = keys[tile0 + threadIdx.x];
   const bool refused = hdr->status != 0;  // an earlier call failed: this pull is a no-op
+  requested();
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     hdr->live = refused ? 0u : 1u;
     hdr->batch_ok = 0;
@@ -64,7 +68,6 @@ k_probe_insert(DevHeader* hdr, Slot* slots, u32 slot_mask, const u64* __restrict
   __shared__ u32 n_pend;
   if (threadIdx.x == 0) n_pend = 0;
   __syncthreads();
-  const u32 tile0 = blockIdx.x * (BLOCK * items);
   const int lane = lane_id();
 
 #pragma unroll 1
@@ -80,9 +83,11 @@ k_probe_insert(DevHeader* hdr, Slot* slots, u32 slot_mask, const u64* __restrict
       if (bad) atomicOr(&hdr->pull_err, ST_INVAL);
     }
 
+    const u64 this_key = key;
+    if (it + 1 < items && p + BLOCK < n_keys) key = keys[p + BLOCK];
     bool pending = false;
     if (p < n_keys) {
-      const u64 key = keys[p];
+      const u64 key = this_key;
       u32 out = OCC_INVALID;
       if (key == KEY_EMPTY) {
         atomicOr(&hdr->pull_err, ST_BADKEY);
@@ -170,24 +175,24 @@ __global__ void __launch_bounds__(BLOCK)
 k_rank_count(DevHeader* hdr, const Slot* __restrict__ slots, const u32* __restrict__ occ_row,
              const u32* __restrict__ pend_list, const u32* __restrict__ tile_pending, u32 n_probe_tiles, u32 n_tiles,
              u32* __restrict__ first_bits, u32* __restrict__ tile_count, u32* __restrict__ group_count) {
-  if (!hdr->live) return;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    hdr->pull_seen = hdr->pull_err;
-    hdr->pull_err = 0;
-  }
   constexpr bool BY_WAVE = ITEMS != 1;
   constexpr u32 PROBE_TILE = BLOCK * ITEMS, PER = RANK_TILE / PROBE_TILE;
   __shared__ u32 lds[BY_WAVE ? BLOCK / WAVE : 1][RANK_WORDS];
   const u32 tile = BY_WAVE ? (blockIdx.x * BLOCK + threadIdx.x) / WAVE : blockIdx.x;
-  if (tile >= n_tiles) return;  // uniform over the block or the wave
   u32* bits = lds[BY_WAVE ? wave_id() : 0];
-  const u32 p0 = tile * RANK_TILE;
+  const u32 p0 = tile * RANK_TILE, live = hdr->live;
   u32 cnt[PER], any = 0;
 #pragma unroll
-  for (u32 t = 0; t < PER; ++t) {
-    cnt[t] = tile * PER + t < n_probe_tiles ? tile_pending[tile * PER + t] : 0u;
-    any |= cnt[t];
+  for (u32 t = 0; t < PER; ++t) cnt[t] = tile * PER + t < n_probe_tiles ? tile_pending[tile * PER + t] : 0u;
+  requested();
+  if (!live) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    hdr->pull_seen = hdr->pull_err;
+    hdr->pull_err = 0;
   }
+  if (tile >= n_tiles) return;  // uniform over the block or the wave
+#pragma unroll
+  for (u32 t = 0; t < PER; ++t) any |= cnt[t];
   if (any == 0) {
     if (threadIdx.x == 0 || (BY_WAVE && lane_id() == 0)) tile_count[tile] = 0;
     return;
@@ -286,10 +291,11 @@ k_rank_assign(DevHeader* hdr, Slot* slots, const u64* __restrict__ keys, u32* __
               const u32* __restrict__ group_count, u32 n_tiles, u32 parts, u64 capacity_rows,
               u64* __restrict__ row_key, u32 init_rows, float* values, u64 replica_stride, u32 n_replicas, float* vhat,
               u32 D, u32 rf, u64 seed_mul, float scale, float v0) {
-  if (!hdr->live) return;
   const u32 wave = (blockIdx.x * BLOCK + threadIdx.x) / WAVE, lane = (u32)lane_id();
-  const u32 tile = wave / parts, part = wave % parts;
+  const u32 tile = wave / parts, part = wave % parts, live = hdr->live;
   const u32 in_tile = tile < n_tiles ? tile_count[tile] : 0u;
+  requested();
+  if (!live) return;
   if (in_tile == 0 && wave != 0) return;
   u32 before = 0, total = 0;  // first occurrences in the tiles before this one, in all tiles
   const u32 n_groups = (n_tiles + RANK_GROUP - 1) / RANK_GROUP, group = tile / RANK_GROUP;
@@ -411,19 +417,13 @@ __global__ void k_load_rows(const DevHeader* hdr, const u32* __restrict__ occ_ro
 __global__ void __launch_bounds__(BLOCK)
 k_lookup(DevHeader* hdr, const Slot* __restrict__ slots, u32 slot_mask, const u64* __restrict__ keys, u32 n_keys,
          const u32* __restrict__ offsets, u32 n_seg, u32* __restrict__ occ_row) {
-  if (hdr->status) return;
-  const u32 p = blockIdx.x * BLOCK + threadIdx.x;
-  if (p <= n_seg) {
-    const u32 a = offsets[p];
-    bool bad = (p == 0 && a != 0);
-    if (p == n_seg)
-      bad = bad || (a != n_keys);
-    else
-      bad = bad || (offsets[p + 1] < a);
-    if (bad) atomicOr(&hdr->pull_err, ST_INVAL);
-  }
+  const u32 p = blockIdx.x * BLOCK + threadIdx.x, status = hdr->status;
+  const u32 a = p <= n_seg ? offsets[p] : 0u, b = p < n_seg ? offsets[p + 1] : n_keys;
+  const u64 key = p < n_keys ? keys[p] : KEY_EMPTY;
+  requested();
+  if (status) return;
+  if (p <= n_seg && ((p == 0 && a != 0) || (p == n_seg ? a != n_keys : b < a))) atomicOr(&hdr->pull_err, ST_INVAL);
   if (p >= n_keys) return;
-  const u64 key = keys[p];
   u32 out = OCC_INVALID;
   if (key == KEY_EMPTY) {
     atomicOr(&hdr->pull_err, ST_BADKEY);
@@ -465,12 +465,13 @@ __global__ void k_collect_rows(const DevHeader* hdr, const Slot* __restrict__ sl
                                const u64* __restrict__ keys, u32 n, const float* __restrict__ values, u32 D,
                                u32 rf, float* __restrict__ x_dst, float* __restrict__ m_dst,
                                float* __restrict__ v_dst, u32* __restrict__ found) {
-  if (hdr->status) return;
   const u64 p64 = ((u64)blockIdx.x * BLOCK + threadIdx.x) / LPR;  // n * LPR threads can pass 2^32
-  const u32 c = threadIdx.x % LPR;
+  const u32 c = threadIdx.x % LPR, status = hdr->status;
   if (p64 >= n) return;
   const u32 p = (u32)p64;
   const u64 key = keys[p];
+  requested();
+  if (status) return;
   u32 row = ROW_PENDING;
   if (key != KEY_EMPTY) {
     u32 h = (u32)hash_key(key) & slot_mask;
@@ -624,14 +625,17 @@ __device__ __forceinline__ void pool_body(DevHeader* hdr, u32* occ_row,
                                           const float* __restrict__ values, u32 D, u32 rf,
                                           float* __restrict__ pooled, bf16_t* __restrict__ pooled_bf16) {
   constexpr bool LOOKUP = (OUT & 4) != 0;
-  if (LOOKUP ? lookup_failed(hdr) : hdr->status != 0) return;
   constexpr u32 GROUPS = BLOCK / LPR;
   constexpr u32 TILE = GROUPS * POOL_NS * POOL_ROUNDS;
   __shared__ u32 off_lds[TILE + 1];
   __shared__ u32 row_lds[POOL_STAGED];
   const u32 tile_g0 = blockIdx.x * TILE;
   const u32 tile_n = __builtin_amdgcn_readfirstlane(min(TILE, n_seg - tile_g0));
-  for (u32 i = threadIdx.x; i <= tile_n; i += BLOCK) off_lds[i] = offsets[tile_g0 + i];
+  const u32 off0 = threadIdx.x <= tile_n ? offsets[tile_g0 + threadIdx.x] : 0u;
+  requested();
+  if (LOOKUP ? lookup_failed(hdr) : hdr->status != 0) return;
+  if (threadIdx.x <= tile_n) off_lds[threadIdx.x] = off0;
+  for (u32 i = threadIdx.x + BLOCK; i <= tile_n; i += BLOCK) off_lds[i] = offsets[tile_g0 + i];
   __syncthreads();
 
   const u32 P0 = __builtin_amdgcn_readfirstlane(off_lds[0]), P1 = __builtin_amdgcn_readfirstlane(off_lds[tile_n]);
@@ -735,10 +739,12 @@ __device__ __forceinline__ void pool_small_body(DevHeader* hdr, u32* __restrict_
                                                 const float* __restrict__ values, u32 D, u32 rf,
                                                 float* __restrict__ pooled, bf16_t* __restrict__ pooled_bf16) {
   constexpr bool LOOKUP = (OUT & 4) != 0;
-  if (LOOKUP ? lookup_failed(hdr) : hdr->status != 0) return;
   const u32 g = (blockIdx.x * BLOCK + threadIdx.x) / LPR, c = threadIdx.x % LPR;
+  const u32 beg = g < n_seg ? offsets[g] : 0u, end = g < n_seg ? offsets[g + 1] : 0u;
+  requested();
+  if (LOOKUP ? lookup_failed(hdr) : hdr->status != 0) return;
   if (g >= n_seg) return;
-  const d4 acc = pool_segment<LPR, LOOKUP, !LOOKUP>(g, offsets[g], offsets[g + 1], occ_row, slots, seg_of, values, D, rf, c);
+  const d4 acc = pool_segment<LPR, LOOKUP, !LOOKUP>(g, beg, end, occ_row, slots, seg_of, values, D, rf, c);
   if (c * 4 < D) pool_store<OUT>(g, D, c, acc, pooled, pooled_bf16);
 }
 
