@@ -714,7 +714,7 @@ static int push_adam_impl(ctr_table* t, uint32_t replica, ctr_batch* handle, con
     }
     {
       StageTimer tm(t, CTR_STAGE_FIXUP, st);
-      LPR_DISPATCH(t->lpr, k_push_block_heads, blocks_for((u64)wl.n_span_blocks * WAVE), st, t->hdr,
+      LPR_DISPATCH(t->lpr, k_push_block_heads, blocks_for((u64)wl.n_span_blocks * head_waves(t->lpr) * WAVE), st, t->hdr,
                    batch->sorted_rows, wl.n_spans, wl.span, t->D, head, block_head, span_flags, span_rows);
       const u32 fgrid = blocks_for((u64)wl.n_spans * fixup_lanes(t->lpr));
       switch (kind) {

@@ -510,11 +510,11 @@ __device__ __forceinline__ void combine_groups(d4& a) {
 }
 
 // Adds the partial sums first, first + GPW, ... below end in this order.  Wide rows leave a wave few groups and long
-// lists: four partials are requested together.  (Narrower rows lose by the registers: fix-up of 16 columns 10.1 -> 13.7
-// us, of 64 columns 63 -> 78.)
+// lists: eight partials are requested together.  (Narrower rows lose by the registers, with four: fix-up of 16 columns
+// 10.1 -> 13.7 us, of 64 columns 63 -> 78.)
 template <int LPR>
 __device__ __forceinline__ void add_partials(const double* __restrict__ part, u32 first, u32 end, u32 D, u32 c, d4& a) {
-  constexpr u32 GPW = WAVE / LPR, BATCH = LPR >= 32 ? 4 : 1;
+  constexpr u32 GPW = WAVE / LPR, BATCH = LPR >= 32 ? 8 : 1;
   for (u32 k = first; k < end; k += BATCH * GPW) {
     d4 p[BATCH];
 #pragma unroll
@@ -529,15 +529,19 @@ __device__ __forceinline__ void add_partials(const double* __restrict__ part, u3
   }
 }
 
-// One wave per block of SPANS_PER_BLOCK spans: sums the heads of the block's leading spans that continue the row
+// Per block of SPANS_PER_BLOCK spans: sums the heads of the block's leading spans that continue the row
 // open at the block's start (block j >= 1), and the block's counts of rows that start in a span, left in the place of
-// the first of them.
+// the first of them.  A wave per block, or, where a wave has one or two groups only (LPR >= 32), four that take a quarter of
+// the heads each.
+constexpr u32 head_waves(u32 lpr) { return lpr >= 32 ? BLOCK / WAVE : 1; }
+
 template <int LPR>
 __global__ void __launch_bounds__(BLOCK)
 k_push_block_heads(const DevHeader* hdr, const u32* __restrict__ sr, u32 n_spans, u32 span, u32 D,
                    const double* __restrict__ head_part, double* __restrict__ block_head,
                    const u32* __restrict__ span_flags, u32* __restrict__ span_rows) {
-  const u32 j = (blockIdx.x * BLOCK + threadIdx.x) / WAVE;  // wave-uniform
+  constexpr u32 WAVES = head_waves(LPR), SHARE = SPANS_PER_BLOCK / WAVES;
+  const u32 j = (blockIdx.x * BLOCK + threadIdx.x) / (WAVES * WAVE), part = WAVES > 1 ? (u32)wave_id() : 0u;  // wave-uniform
   const u32 first = j * SPANS_PER_BLOCK, status = hdr->status;
   if (first >= n_spans) return;
   const int lane = lane_id();
@@ -547,15 +551,26 @@ k_push_block_heads(const DevHeader* hdr, const u32* __restrict__ sr, u32 n_spans
   requested();
   if (status) return;
   const u32 started = wave_sum(rows);
-  if (lane == 0) span_rows[first] = started;
+  if constexpr (WAVES > 1) __syncthreads();  // all have read span_rows[first]
+  if (lane == 0 && part == 0) span_rows[first] = started;
   if (j == 0) return;
   const u32 c = lane % LPR, grp = lane / LPR;
   const bool col_ok = c * 4 < D;
   const u32 n_lead = leading_true(t < n_spans && (flags >> 2) == row);  // coalesced, unlike sr[t * span]
   if (n_lead == 0) return;
   d4 acc = {0.0, 0.0, 0.0, 0.0};
-  if (col_ok) add_partials<LPR>(head_part, first + grp, first + n_lead, D, c, acc);
+  if (col_ok) add_partials<LPR>(head_part, first + part * SHARE + grp, first + min(n_lead, (part + 1) * SHARE), D, c, acc);
   combine_groups<LPR>(acc);
+  if constexpr (WAVES > 1) {
+    __shared__ d4 shares[WAVES - 1][LPR];
+    if (part > 0 && grp == 0) shares[part - 1][c] = acc;
+    __syncthreads();
+    if (part > 0) return;
+#pragma unroll
+    for (u32 p = 0; p + 1 < WAVES; ++p) {
+      acc.x += shares[p][c].x; acc.y += shares[p][c].y; acc.z += shares[p][c].z; acc.w += shares[p][c].w;
+    }
+  }
   if (grp == 0 && col_ok) store_partial(block_head, j, D, c, acc);
 }
 

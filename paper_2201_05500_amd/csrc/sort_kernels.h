@@ -8,7 +8,7 @@
 // (ceil(log2 R) bits), so sorting them costs half the passes of sorting the
 // 64-bit keys.
 //
-// One pass = three launches:
+// One pass = three launches, two for short lists:
 //   k_sort_hist    per-chunk digit histogram           -> hist[digit][chunk] (wide digits: hist[chunk][digit])
 //   k_sort_scan    per digit: exclusive scan over chunks, digit totals
 //   k_sort_scatter per chunk: for each sub-tile, rank elements
@@ -18,8 +18,11 @@
 // A sub-tile is 256 * ITEMS elements.  Long lists take ITEMS = 16 (long runs, few histograms; bound by memory:
 // 39 M elements of 24 bits 817 us, 887 with 8); short ones are bound by the ranking chain of one sub-tile on an idle
 // chip and take fewer: 300 k elements 53 us with 16, 41 with 4; 1.25 M 65 with 16, 58 with 8.
-// (Two launches instead of three, every scatter block adding up the histograms before its own: 8.6 instead of 10.2 us
-// at 20 k elements, but 14.8 instead of 11.3 at 160 k.)
+// Lists of few chunks do without the scan: every scatter block adds up the histograms before its own while its elements
+// are on their way (two passes of 8 bits: 1000 elements 16.8 -> 13.3 us, 32 k 20.3 -> 16.4, 64 k 20.6 -> 19.1, 73 k 20.7 ->
+// 21.1; two of 10 bits: 4 k 20.2 -> 16.5, 8 k 20.6 -> 18.6, 16 k 21.0 -> 23.1; of 11 bits: 1000 20.2 -> 15.0, 4 k 21.3 -> 21.2).
+// (Also measured, and not gaining: the scan done by the last block of every 16 or 32 chunks to end; blocks of 1024 threads, whose
+// lists have fewer chunks.)
 // Digits have 8 bits, or 10 or 11 where that saves a pass and the list is short.  A pass of a short list costs its
 // three launches and their chains rather than bytes, so fewer passes win: 20-bit keys, 73 k elements 32 -> 25 us,
 // 400 k 42 -> 36, 800 k 51 -> 44; 22-bit keys, 175 k 35 -> 33, 400 k 43 -> 40.  Long lists lose by it: a sub-tile then
@@ -36,6 +39,8 @@ namespace ctr {
 
 constexpr u32 SORT_ITEMS_4_MAX = 300000, SORT_ITEMS_8_MAX = 1600000;  // elements
 constexpr u32 SORT_10_BITS_MAX = 1000000, SORT_11_BITS_MAX = 500000, SORT_3_WIDE_PASSES_MAX = 100000;
+// most chunks of 1024 elements that a scatter block adds up itself, for digits of 8, 10 and 11 bits
+constexpr u32 SORT_SHORT_CHUNKS = 64, SORT_SHORT_CHUNKS_10 = 8, SORT_SHORT_CHUNKS_11 = 3;
 #ifndef CTR_SORT_MAX_CHUNKS
 #define CTR_SORT_MAX_CHUNKS 4096
 #endif
@@ -53,7 +58,8 @@ struct SortGeom {
   u32 items;        // elements per thread of a sub-tile: 4, 8 or 16
 };
 
-template <int R>
+// ROWS: hist[chunk][digit], otherwise hist[digit][chunk].
+template <int R, bool ROWS>
 __global__ void __launch_bounds__(BLOCK)
 k_sort_hist(const DevHeader* hdr, const u32* __restrict__ keys, SortGeom geo, u32 shift, u32 digit_mask,
             u32* __restrict__ hist) {
@@ -100,7 +106,7 @@ k_sort_hist(const DevHeader* hdr, const u32* __restrict__ keys, SortGeom geo, u3
     u32 total = 0;
 #pragma unroll
     for (int i = 0; i < 4 * COPIES; ++i) total += h[i][d];
-    hist[R == RADIX ? d * geo.n_chunks + blockIdx.x : blockIdx.x * R + d] = total;
+    hist[ROWS ? blockIdx.x * R + d : d * geo.n_chunks + blockIdx.x] = total;
   }
 }
 
@@ -164,7 +170,9 @@ k_sort_scan_wide(const DevHeader* hdr, u32* __restrict__ hist, u32 n_chunks, u32
   if (group == 0) digit_total[d] = total;
 }
 
-template <int ITEMS, int R>
+// SCANNED: hist holds the prefix sums of a scan launch, [digit][chunk] or, of wide digits, [chunk][digit]; otherwise the
+// counts, [chunk][digit], of few chunks, which every block adds up itself.
+template <int ITEMS, int R, bool SCANNED>
 __global__ void __launch_bounds__(BLOCK)
 k_sort_scatter(const DevHeader* hdr, const u32* __restrict__ keys_in, const u32* __restrict__ vals_in,
                u32* __restrict__ keys_out, u32* __restrict__ vals_out, SortGeom geo, u32 shift,
@@ -191,13 +199,33 @@ k_sort_scatter(const DevHeader* hdr, const u32* __restrict__ keys_in, const u32*
   };
   const u32 status = hdr->status;
   u32 gbase[DIGITS], count[DIGITS];  // gbase: next global position of the thread's digits for this chunk
-#pragma unroll
-  for (int q = 0; q < DIGITS; ++q) {
-    const u32 d = tid * DIGITS + q;
-    count[q] = digit_total[d];
-    gbase[q] = hist[R == RADIX ? d * geo.n_chunks + blockIdx.x : blockIdx.x * R + d];
-  }
   request(chunk_beg);
+  if constexpr (SCANNED) {
+#pragma unroll
+    for (int q = 0; q < DIGITS; ++q) {
+      const u32 d = tid * DIGITS + q;
+      count[q] = digit_total[d];
+      gbase[q] = hist[R == RADIX ? d * geo.n_chunks + blockIdx.x : blockIdx.x * R + d];
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < DIGITS; ++q) count[q] = gbase[q] = 0;
+    constexpr u32 SIDE = 32 / DIGITS;  // chunks requested together
+    for (u32 c0 = 0; c0 < geo.n_chunks; c0 += SIDE) {
+      u32 h[SIDE][DIGITS];
+#pragma unroll
+      for (u32 i = 0; i < SIDE; ++i)
+#pragma unroll
+        for (int q = 0; q < DIGITS; ++q) h[i][q] = c0 + i < geo.n_chunks ? hist[(c0 + i) * R + tid * DIGITS + q] : 0u;
+#pragma unroll
+      for (u32 i = 0; i < SIDE; ++i)
+#pragma unroll
+        for (int q = 0; q < DIGITS; ++q) {
+          count[q] += h[i][q];
+          gbase[q] += c0 + i < blockIdx.x ? h[i][q] : 0u;
+        }
+    }
+  }
   requested();
   if (status) return;
   {
@@ -337,14 +365,14 @@ inline size_t sort_hist_words(u64 n, u64 n_spans) {
 inline void sort_pass_enqueue(const DevHeader* hdr, const u32* keys_in, const u32* vals_in, u32* keys_out, u32* vals_out,
                               const SortGeom& geo, u32 shift, u32 digit_mask, u32* hist, u32* digit_total,
                               hipStream_t st) {
-  hipLaunchKernelGGL(k_sort_hist<RADIX>, dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
+  hipLaunchKernelGGL((k_sort_hist<RADIX, false>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
   hipLaunchKernelGGL(k_sort_scan, dim3(RADIX), dim3(BLOCK), 0, st, hdr, hist, geo.n_chunks, digit_total);
-#define CTR_SORT_SCATTER(ITEMS, R)                                                                                \
-  hipLaunchKernelGGL((k_sort_scatter<ITEMS, R>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, vals_in,      \
+#define CTR_SORT_SCATTER(ITEMS, R, SCANNED)                                                                        \
+  hipLaunchKernelGGL((k_sort_scatter<ITEMS, R, SCANNED>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, vals_in,      \
                      keys_out, vals_out, geo, shift, digit_mask, hist, digit_total)
-  if (geo.items == 4) CTR_SORT_SCATTER(4, RADIX);
-  else if (geo.items == 8) CTR_SORT_SCATTER(8, RADIX);
-  else CTR_SORT_SCATTER(16, RADIX);
+  if (geo.items == 4) CTR_SORT_SCATTER(4, RADIX, true);
+  else if (geo.items == 8) CTR_SORT_SCATTER(8, RADIX, true);
+  else CTR_SORT_SCATTER(16, RADIX, true);
 }
 
 // A pass of wide digits (R = 1024 or 2048; the digit totals stand behind the histograms).
@@ -353,12 +381,22 @@ inline void sort_pass_wide_enqueue(const DevHeader* hdr, const u32* keys_in, con
                                    u32* vals_out, const SortGeom& geo, u32 shift, u32 digit_mask, u32* hist,
                                    hipStream_t st) {
   u32* digit_total = hist + (size_t)R * geo.n_chunks;
-  hipLaunchKernelGGL(k_sort_hist<R>, dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
+  hipLaunchKernelGGL((k_sort_hist<R, true>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
   hipLaunchKernelGGL(k_sort_scan_wide, dim3(R / 16), dim3(BLOCK), 0, st, hdr, hist, geo.n_chunks, (u32)R, digit_total);
-  if (geo.items == 4) CTR_SORT_SCATTER(4, R);
-  else CTR_SORT_SCATTER(8, R);
-#undef CTR_SORT_SCATTER
+  if (geo.items == 4) CTR_SORT_SCATTER(4, R, true);
+  else CTR_SORT_SCATTER(8, R, true);
 }
+
+// A pass without a scan, of a list of few chunks (4 elements per thread).
+template <int R>
+inline void sort_pass_short_enqueue(const DevHeader* hdr, const u32* keys_in, const u32* vals_in, u32* keys_out,
+                                    u32* vals_out, const SortGeom& geo, u32 shift, u32 digit_mask, u32* hist,
+                                    hipStream_t st) {
+  const u32* digit_total = nullptr;
+  hipLaunchKernelGGL((k_sort_hist<R, true>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
+  CTR_SORT_SCATTER(4, R, false);
+}
+#undef CTR_SORT_SCATTER
 
 // Sorts n (key, value) pairs by the low key_bits bits of the key, between the two pairs of arrays; returns which of
 // them (0 = a, 1 = b) holds the result.
@@ -374,9 +412,15 @@ inline u32 sort_enqueue(const DevHeader* hdr, const u32* keys_in, const u32* val
   for (u32 p = 0; p < passes; ++p) {
     const u32 bits = (key_bits - shift + (passes - p) - 1) / (passes - p);  // spread evenly over the passes
     const u32 mask = (1u << bits) - 1u;
-    if (!wide) sort_pass_enqueue(hdr, keys_in, vals_in, keys[p & 1], vals[p & 1], geo, shift, mask, hist, digit_total, st);
-    else if (wide_bits == 10) sort_pass_wide_enqueue<1024>(hdr, keys_in, vals_in, keys[p & 1], vals[p & 1], geo, shift, mask, hist, st);
-    else sort_pass_wide_enqueue<2048>(hdr, keys_in, vals_in, keys[p & 1], vals[p & 1], geo, shift, mask, hist, st);
+#define CTR_SORT_PASS(KIND, R) sort_pass_##KIND##_enqueue<R>(hdr, keys_in, vals_in, keys[p & 1], vals[p & 1], geo, shift, mask, hist, st)
+    const bool few = geo.n_chunks <= (!wide ? SORT_SHORT_CHUNKS : wide_bits == 10 ? SORT_SHORT_CHUNKS_10 : SORT_SHORT_CHUNKS_11);
+    if (!wide && few) CTR_SORT_PASS(short, RADIX);
+    else if (!wide) sort_pass_enqueue(hdr, keys_in, vals_in, keys[p & 1], vals[p & 1], geo, shift, mask, hist, digit_total, st);
+    else if (wide_bits == 10 && few) CTR_SORT_PASS(short, 1024);
+    else if (wide_bits == 10) CTR_SORT_PASS(wide, 1024);
+    else if (few) CTR_SORT_PASS(short, 2048);
+    else CTR_SORT_PASS(wide, 2048);
+#undef CTR_SORT_PASS
     keys_in = keys[p & 1];
     vals_in = vals[p & 1];
     shift += bits;

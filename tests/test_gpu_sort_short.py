@@ -1,0 +1,27 @@
+"""Sorts without a scan launch: one element, a chunk, the most chunks that go without one and one more, for digits of 8, 10
+and 11 bits.  And the sums of rows that cross many spans, whose partial sums several waves share."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_push_edges import _step
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("R,chunks", [(1 << 8, 64), (1 << 16, 64), ((1 << 16) + 1, 8), (1 << 20, 8), ((1 << 20) + 1, 3), (1 << 22, 3),
+                                      ((1 << 22) + 1, 64)])
+@pytest.mark.parametrize("offset", [None, -1, 0, 1, 1024])
+def test_lists_around_the_most_chunks_without_a_scan(R, chunks, offset):
+    n = 1 if offset is None else chunks * 1024 + offset
+    rng = np.random.default_rng(n)
+    _step((min(R - 1, 60000) ** rng.random(n)).astype(np.uint64) + 1, 4, R)
+
+
+# 16 spans are a wave's share, 64 a block; spans have 8 occurrences here
+@pytest.mark.parametrize("D", [100, 128, 256])
+@pytest.mark.parametrize("spans", [16, 17, 63, 64, 65, 80, 129, 700])
+def test_rows_over_many_spans_of_wide_rows(D, spans):
+    rng = np.random.default_rng(spans)
+    lengths = [8 * 61 + 3, 8 * spans, 5, 8 * spans + 9, 40]
+    keys = np.repeat(np.arange(1, len(lengths) + 1), lengths)
+    _step(rng.permutation(keys), D, 64)
