@@ -194,6 +194,15 @@ def _np_ptr(a: Optional[np.ndarray]):
     return None if a is None else a.ctypes.data_as(C.c_void_p)
 
 
+def current_stream(torch, device) -> int:
+    """The address of torch's current stream on the device.  torch's own look-up of it without the Stream object around
+    it where there is one: a call needs it once, and the object costs as much as two kernel launches (5 us)."""
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or device.index is None:
+        return int(torch.cuda.current_stream(device).cuda_stream)
+    return raw(device.index)
+
+
 class CtrTable:
     """Owns the torch allocations for one table and forwards to the ABI."""
 
@@ -218,6 +227,7 @@ class CtrTable:
         self._ws = None
         self._ws_of_live_batch = None
         self.ws_bytes = 0
+        self._ws_keys, self._ws_need = -1, 0  # the most keys reserved for, and what they need
         self._handle = None
         st, h = ctr_table_create(self.cfg, self._mem.data_ptr(), nbytes, self.stream)
         if st != CTR_OK:
@@ -228,9 +238,12 @@ class CtrTable:
 
     @property
     def stream(self) -> int:
-        return int(self._torch.cuda.current_stream(self.device).cuda_stream)
+        return current_stream(self._torch, self.device)
 
     def reserve(self, max_keys: int, max_segments: int):
+        # a workspace covers every batch of at most the keys it was sized for
+        if 0 <= max_keys <= self._ws_keys and self.ws_bytes >= self._ws_need:
+            return
         need = ctr_workspace_bytes(self.cfg, max_keys, max_segments)
         if need == 0:
             raise ValueError("invalid workspace request")
@@ -242,6 +255,7 @@ class CtrTable:
             self._ws_of_live_batch = self._ws
             self._ws = self._torch.empty(need, dtype=self._torch.uint8, device=self.device)
             self.ws_bytes = need
+        self._ws_keys, self._ws_need = max_keys, need
 
     def close(self):
         if self._handle:

@@ -5,7 +5,7 @@ import ctypes as C
 
 import numpy as np
 
-from .binding import CTR_OK, CTR_STEP_LOCAL, lib as _base_lib
+from .binding import CTR_OK, CTR_STEP_LOCAL, current_stream, lib as _base_lib
 
 CTR_MLP_MAX_HIDDEN = 6
 EXPORTED = ("ctr_mlp_bytes", "ctr_mlp_workspace_bytes", "ctr_mlp_create", "ctr_mlp_destroy", "ctr_mlp_step",
@@ -96,6 +96,7 @@ class CtrMlp:
         self.n_params = int(lib().ctr_mlp_n_params(C.byref(self.cfg)))
         self._mem = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         self._ws, self.ws_bytes, self._handle = None, 0, None
+        self._ws_batch, self._ws_need = None, 0  # the batch size last reserved for
         out = C.c_void_p()
         st = lib().ctr_mlp_create(C.byref(self.cfg), self._mem.data_ptr(), nbytes, self.stream, C.byref(out))
         if st != CTR_OK:
@@ -104,9 +105,11 @@ class CtrMlp:
 
     @property
     def stream(self) -> int:
-        return int(self._torch.cuda.current_stream(self.device).cuda_stream)
+        return current_stream(self._torch, self.device)
 
     def reserve(self, batch):
+        if batch == self._ws_batch and self.ws_bytes >= self._ws_need:
+            return
         need = int(lib().ctr_mlp_workspace_bytes(C.byref(self.cfg), batch))
         if need == 0:
             raise ValueError("invalid batch")
@@ -114,6 +117,7 @@ class CtrMlp:
             self._torch.cuda.synchronize(self.device)
             self._ws = self._torch.empty(need, dtype=self._torch.uint8, device=self.device)
             self.ws_bytes = need
+        self._ws_batch, self._ws_need = batch, need
 
     def close(self):
         if self._handle:
