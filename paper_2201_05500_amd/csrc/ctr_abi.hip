@@ -651,7 +651,7 @@ static int push_adam_impl(ctr_table* t, uint32_t replica, ctr_batch* handle, con
     u32* span_rows = (u32*)(batch->ws + wl.off_span_rows);
 #define CTR_SPAN_LAUNCH(KERNEL)                                                                                   \
   LPR_DISPATCH(t->lpr, KERNEL, grid, st, t->hdr, batch->sorted_rows, batch->sorted_segs, n, wl.span, d_grad_pooled, \
-               vals, t->vhat, t->row_state, t->D, t->rf, P, head, tail, span_flags, span_rows, order, cold_count)
+               vals, t->vhat, t->row_state, t->D, t->rf, P, head, tail, block_head, span_flags, span_rows, order, cold_count)
 #define CTR_FIXUP_LAUNCH(KERNEL)                                                                                 \
   LPR_DISPATCH(t->lpr, KERNEL, fgrid, st, t->hdr, batch->sorted_rows, n, wl.n_spans, wl.span, vals, t->vhat,       \
                t->row_state, t->D, t->rf, P, head, tail, block_head, span_flags, span_rows)
@@ -714,7 +714,8 @@ static int push_adam_impl(ctr_table* t, uint32_t replica, ctr_batch* handle, con
     }
     {
       StageTimer tm(t, CTR_STAGE_FIXUP, st);
-      LPR_DISPATCH(t->lpr, k_push_block_heads, blocks_for((u64)wl.n_span_blocks * head_waves(t->lpr) * WAVE), st, t->hdr,
+      if (!span_sums_heads(t->lpr) || order)
+        LPR_DISPATCH(t->lpr, k_push_block_heads, blocks_for((u64)wl.n_span_blocks * head_waves(t->lpr) * WAVE), st, t->hdr,
                    batch->sorted_rows, wl.n_spans, wl.span, t->D, head, block_head, span_flags, span_rows);
       const u32 fgrid = blocks_for((u64)wl.n_spans * fixup_lanes(t->lpr));
       switch (kind) {

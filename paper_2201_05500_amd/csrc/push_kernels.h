@@ -287,20 +287,62 @@ __device__ __forceinline__ void push_hot_body(const DevHeader* hdr, const u32* _
   }
 }
 
+// Number of leading lanes (from lane 0) whose predicate holds; wave-uniform.
+__device__ __forceinline__ u32 leading_true(bool pred) {
+  const u64 inv = ~__ballot(pred);
+  return inv ? (u32)(__ffsll((long long)inv) - 1) : 64u;
+}
+
+// Combines per-group binary64 partial sums of a wave (groups of LPR lanes, same column layout).
+template <int LPR>
+__device__ __forceinline__ void combine_groups(d4& a) {
+#pragma unroll
+  for (int off = LPR; off < WAVE; off <<= 1) {
+    a.x += __shfl_xor(a.x, off, WAVE);
+    a.y += __shfl_xor(a.y, off, WAVE);
+    a.z += __shfl_xor(a.z, off, WAVE);
+    a.w += __shfl_xor(a.w, off, WAVE);
+  }
+}
+
+// Adds the partial sums first, first + GPW, ... below end in this order.  Wide rows leave a wave few groups and long
+// lists: eight partials are requested together.  (Narrower rows lose by the registers, with four: fix-up of 16 columns
+// 10.1 -> 13.7 us, of 64 columns 63 -> 78.)
+template <int LPR>
+__device__ __forceinline__ void add_partials(const double* __restrict__ part, u32 first, u32 end, u32 D, u32 c, d4& a) {
+  constexpr u32 GPW = WAVE / LPR, BATCH = LPR >= 32 ? 8 : 1;
+  for (u32 k = first; k < end; k += BATCH * GPW) {
+    d4 p[BATCH];
+#pragma unroll
+    for (u32 i = 0; i < BATCH; ++i) {
+      p[i] = d4{0.0, 0.0, 0.0, 0.0};
+      if (k + i * GPW < end) add_partial(part, k + i * GPW, D, c, p[i]);
+    }
+#pragma unroll
+    for (u32 i = 0; i < BATCH; ++i) {
+      a.x += p[i].x; a.y += p[i].y; a.z += p[i].z; a.w += p[i].w;
+    }
+  }
+}
+
 // Span walk.  Each batch of PB occurrences issues, before anything is consumed,
 // the PB gradient-row loads and the x/m/v loads of every row that ends inside
 // the batch, so that a group keeps several KB in flight instead of one
 // dependent row at a time.
 // GB: the gradient rows are bf16 (two bytes per component, widened exactly) instead of fp32.
+// Groups of up to 4 lanes walk whole blocks of spans per workgroup: in list order the workgroup leaves what
+// k_push_block_heads would (a launch of its own costs 3 to 5 us behind this one).
+constexpr bool span_sums_heads(u32 lpr) { return lpr * SPANS_PER_BLOCK <= BLOCK; }
+
 template <int LPR, int KIND, bool GB>
 __device__ __forceinline__ void push_span_body(const DevHeader* hdr, const u32* __restrict__ sr,
                                                const u32* __restrict__ ss, u32 n, u32 span,
                                                const void* __restrict__ grad_any, float* __restrict__ values,
                                                const float* __restrict__ vhat, u32* __restrict__ row_state, u32 D,
                                                u32 rf, const AdamParams& P_in, double* __restrict__ head_part,
-                                               double* __restrict__ tail_part, u32* __restrict__ span_flags,
-                                               u32* __restrict__ span_rows, const u32* __restrict__ order,
-                                               const u32* __restrict__ cold_count) {
+                                               double* __restrict__ tail_part, double* __restrict__ block_head,
+                                               u32* __restrict__ span_flags, u32* __restrict__ span_rows,
+                                               const u32* __restrict__ order, const u32* __restrict__ cold_count) {
   AdamParams P = P_in;
   const u32 status = hdr->status;
   if constexpr (KIND == STEP_ADAM_KINGMA) {
@@ -322,9 +364,11 @@ __device__ __forceinline__ void push_span_body(const DevHeader* hdr, const u32* 
     if (s >= n_spans) return;
   }
   const u32 c = threadIdx.x % LPR;
-  const u32 b = s * span;
-  if (b >= n) return;
-  const u32 e = min(b + span, n);
+  const bool heads = span_sums_heads(LPR) && !order;  // then every wave goes on to the end
+  const u32 b = min(s, (n + span - 1) / span) * span;
+  const bool active = b < n;
+  if (!active && !heads) return;
+  const u32 e = active ? min(b + span, n) : b;
   const bool col_ok = c * 4 < D;
 
   // LPR >= PB: the group keeps a window of LPR consecutive list entries (lane c holds entry window start + c, plus the first
@@ -346,7 +390,7 @@ __device__ __forceinline__ void push_span_body(const DevHeader* hdr, const u32* 
       for (int i = 0; i < PB; ++i) batch_g[i] = (i0 + i < e) ? ss[i0 + i] : 0u;
     }
   };
-  const u32 row_before = b > 0 ? sr[b - 1] : NO_ROW, first_row = sr[b];
+  const u32 row_before = active && b > 0 ? sr[b - 1] : NO_ROW, first_row = active ? sr[b] : NO_ROW;
   request(b);
   requested();
   if (status) return;
@@ -434,7 +478,7 @@ __device__ __forceinline__ void push_span_body(const DevHeader* hdr, const u32* 
   }
 
   // the last occurrence did not end its row: the row goes on in the next span
-  if (sr[e - 1] == ((e < n) ? sr[e] : NO_ROW)) {
+  if (active && sr[e - 1] == ((e < n) ? sr[e] : NO_ROW)) {
     if (first_row_open) {  // the whole span lies inside one row that began earlier
       if (col_ok) store_partial(head_part, s, D, c, acc);
       flags |= SF_HEAD;
@@ -444,21 +488,45 @@ __device__ __forceinline__ void push_span_body(const DevHeader* hdr, const u32* 
       ++started;
     }
   }
-  if (c == 0) {
+  if (c == 0 && active) {
     span_flags[s] = (first_row << 2) | flags;  // first row id of the span above the two flag bits
-    span_rows[s] = started;                // rows that START in this span
+    if (!heads) span_rows[s] = started;        // rows that START in this span
+  }
+  if constexpr (span_sums_heads(LPR)) {
+    if (!heads) return;
+    constexpr u32 SPANS = BLOCK / LPR;
+    __shared__ u32 first_rows[SPANS], rows_started[SPANS], rows_before[SPANS / SPANS_PER_BLOCK];
+    const u32 own = threadIdx.x / LPR;
+    if (c == 0) {
+      first_rows[own] = first_row;  // NO_ROW beyond the last span
+      rows_started[own] = started;
+      if (own % SPANS_PER_BLOCK == 0) rows_before[own / SPANS_PER_BLOCK] = row_before;
+    }
+    __syncthreads();  // also the partial sums have been left
+    const u32 w = wave_id(), first = blockIdx.x * SPANS + w * SPANS_PER_BLOCK;
+    if (w >= SPANS / SPANS_PER_BLOCK || first * span >= n) return;
+    const u32 lane = lane_id(), row = rows_before[w], all = wave_sum(rows_started[w * SPANS_PER_BLOCK + lane]);
+    if (lane == 0) span_rows[first] = all;
+    if (row == NO_ROW) return;
+    const u32 n_lead = leading_true(first_rows[w * SPANS_PER_BLOCK + lane] == row);
+    if (n_lead == 0) return;
+    d4 sum = {0.0, 0.0, 0.0, 0.0};
+    if (col_ok) add_partials<LPR>(head_part, first + lane / LPR, first + n_lead, D, c, sum);
+    combine_groups<LPR>(sum);
+    if (lane / LPR == 0 && col_ok) store_partial(block_head, first / SPANS_PER_BLOCK, D, c, sum);
   }
 }
+
 
 #define CTR_PUSH_SPAN_ARGS                                                                                      \
   const DevHeader *hdr, const u32 *__restrict__ sr, const u32 *__restrict__ ss, u32 n, u32 span,               \
       const void *__restrict__ grad, float *__restrict__ values, const float *__restrict__ vhat,               \
       u32 *__restrict__ row_state, u32 D, u32 rf, AdamParams P, double *__restrict__ head_part,                \
-      double *__restrict__ tail_part, u32 *__restrict__ span_flags, u32 *__restrict__ span_rows,               \
-      const u32 *__restrict__ order, const u32 *__restrict__ cold_count
+      double *__restrict__ tail_part, double *__restrict__ block_head, u32 *__restrict__ span_flags,           \
+      u32 *__restrict__ span_rows, const u32 *__restrict__ order, const u32 *__restrict__ cold_count
 #define CTR_PUSH_SPAN_PASS                                                                                      \
-  hdr, sr, ss, n, span, grad, values, vhat, row_state, D, rf, P, head_part, tail_part, span_flags, span_rows, \
-      order, cold_count
+  hdr, sr, ss, n, span, grad, values, vhat, row_state, D, rf, P, head_part, tail_part, block_head, span_flags, \
+      span_rows, order, cold_count
 
 // one kernel per step kind (the dispatch macro on the host takes kernels templated on LPR only)
 #define CTR_DEFINE_PUSH_SPAN(NAME, KIND)                                                          \
@@ -490,44 +558,6 @@ CTR_DEFINE_PUSH_SPAN(k_push_span, STEP_ADAM_OWN)
 CTR_DEFINE_PUSH_SPAN(k_push_span_shared, STEP_ADAM_SHARED)
 CTR_DEFINE_PUSH_SPAN(k_push_span_adagrad, STEP_ADAGRAD)
 CTR_DEFINE_PUSH_SPAN(k_push_span_kingma, STEP_ADAM_KINGMA)
-
-// Number of leading lanes (from lane 0) whose predicate holds; wave-uniform.
-__device__ __forceinline__ u32 leading_true(bool pred) {
-  const u64 inv = ~__ballot(pred);
-  return inv ? (u32)(__ffsll((long long)inv) - 1) : 64u;
-}
-
-// Combines per-group binary64 partial sums of a wave (groups of LPR lanes, same column layout).
-template <int LPR>
-__device__ __forceinline__ void combine_groups(d4& a) {
-#pragma unroll
-  for (int off = LPR; off < WAVE; off <<= 1) {
-    a.x += __shfl_xor(a.x, off, WAVE);
-    a.y += __shfl_xor(a.y, off, WAVE);
-    a.z += __shfl_xor(a.z, off, WAVE);
-    a.w += __shfl_xor(a.w, off, WAVE);
-  }
-}
-
-// Adds the partial sums first, first + GPW, ... below end in this order.  Wide rows leave a wave few groups and long
-// lists: eight partials are requested together.  (Narrower rows lose by the registers, with four: fix-up of 16 columns
-// 10.1 -> 13.7 us, of 64 columns 63 -> 78.)
-template <int LPR>
-__device__ __forceinline__ void add_partials(const double* __restrict__ part, u32 first, u32 end, u32 D, u32 c, d4& a) {
-  constexpr u32 GPW = WAVE / LPR, BATCH = LPR >= 32 ? 8 : 1;
-  for (u32 k = first; k < end; k += BATCH * GPW) {
-    d4 p[BATCH];
-#pragma unroll
-    for (u32 i = 0; i < BATCH; ++i) {
-      p[i] = d4{0.0, 0.0, 0.0, 0.0};
-      if (k + i * GPW < end) add_partial(part, k + i * GPW, D, c, p[i]);
-    }
-#pragma unroll
-    for (u32 i = 0; i < BATCH; ++i) {
-      a.x += p[i].x; a.y += p[i].y; a.z += p[i].z; a.w += p[i].w;
-    }
-  }
-}
 
 // Per block of SPANS_PER_BLOCK spans: sums the heads of the block's leading spans that continue the row
 // open at the block's start (block j >= 1), and the block's counts of rows that start in a span, left in the place of
