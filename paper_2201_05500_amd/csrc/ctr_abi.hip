@@ -92,30 +92,41 @@ inline u32 lanes_per_row(u32 D) {
 // keep a wave on every SIMD (64 Ki): 73 k occurrences of 8 columns, span walk + fix-up, 34 us with 16, 23 us with 4; 160 k
 // of 16 columns 38 us with 16, 30 with 8.  Not below 8 for rows of 32 and 64 lanes: a wave adds the partial sums of so
 // wide a row one or two at a time (8000 occurrences of 256 columns, keys of a power law: 37 us with 16, 39 with 8, 46 with
-// 4; 4000 with 3000 keys 30, 23 and 20; 4000 of 128 columns, power law, 32, 27 and 29).  From 2 M on the line is drawn by
-// occurrences, which suits rows of 32 columns and more (4 M of 64 columns: 396 us with 16, 372 with 64) and costs
-// narrower ones up to a third (8 M of 4 columns: 381 us with the 64 they get, 319 with 8).  A batch of one or two keys
+// 4; 4000 with 3000 keys 30, 23 and 20; 4000 of 128 columns, power law, 32, 27 and 29).   From 2 M on rows
+// of up to 16 columns keep 16, those of 16 columns from 4 M on, where keys repeat much (as many keys as a quarter of the
+// occurrences, 1 M at most: 8 M of 4 columns 320 us with 16, 370 with 64; 12 M of 16 columns 440 and 542 with 128; 2.5 M 113 and
+// 115 with 32) and mostly where they do not (16 M keys: 12 M of 16 columns 574 us with 16, 668 with 128; 2.5 M 142 and 135 with
+// 32; but 12 M of 8 columns 641 and 599 with 128).  Rows of 32 columns take 32 and then 64 (8 M: 361 us with 32, 371 with
+// 128; 12 M 479 with 64, 524 with 128), and wider ones longer spans, which cost them less than partial sums (4 M of 64 columns:
+// 394 us with 16, 365 with 32, 373 with 64).  A batch of one or two keys
 // pays for short spans all the same (200 k occurrences of one key, 8 columns: 32 us, 27 with 16).
 // (All sizes: profiles/push_spans.txt.)
 inline u32 push_span(u32 D, u64 n) {
-  if (n >= (8u << 20)) return 128;
-  if (n >= (4u << 20)) return 64;
-  if (n >= (2u << 20)) return 32;
   const u32 lpr = lanes_per_row(D);
+  if (n >= (2u << 20)) {
+    if (lpr <= 4) return lpr == 4 && n < (4u << 20) ? 32 : 16;
+    if (lpr == 8) return n >= (10u << 20) ? 64 : 32;
+    return n >= (8u << 20) ? 128 : n >= (4u << 20) ? 64 : 32;
+  }
   const u64 lanes = n * lpr;
   const u32 span = lanes >= (1u << 20) ? 16 : lanes >= (1u << 19) ? 8 : 4;
   return std::max(span, lpr < 32 ? 4u : 8u);
 }
 
+// The shortest spans of a batch in a workspace that has no room for those of push_span (whatever the width).
+inline u32 compact_span(u64 n) {
+  return n >= (8u << 20) ? 128 : n >= (4u << 20) ? 64 : n >= (2u << 20) ? 32 : 16;
+}
+
 // force_span / force_items: 0 = chosen by batch size; otherwise the geometry a test asks for.  compact: spans of at
-// least 16 and no more room for the sort's histograms than the list needs, for a workspace that holds no more.
+// least compact_span and no more room for the sort's histograms than the list needs, for a workspace that holds no more.
 void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force_items = 0, bool compact = false) {
   const u64 n = n_keys;
   L->n_rank_tiles = (u32)((n + RANK_TILE - 1) / RANK_TILE);
   L->n_rank_groups = (L->n_rank_tiles + RANK_GROUP - 1) / RANK_GROUP;
   L->span = push_span(D, n);
   if (force_span) L->span = force_span;
-  if (compact) L->span = std::max(L->span, 16u);
+  if (compact) L->span = std::max(L->span, compact_span(n));
   L->n_spans = (u32)((n + L->span - 1) / L->span);
   L->n_span_blocks = (L->n_spans + SPANS_PER_BLOCK - 1) / SPANS_PER_BLOCK;
   size_t o = 0;
@@ -367,7 +378,7 @@ size_t ctr_workspace_bytes(const ctr_config* cfg, uint64_t max_keys, uint32_t ma
   work_layout(cfg->dim, max_keys, &L);
   size_t need = L.total;
   const u64 lpr = lanes_per_row(cfg->dim);  // the first size of every span length of push_span
-  for (u64 threshold : {((u64)1 << 19) / lpr, ((u64)1 << 20) / lpr, (u64)2 << 20, (u64)4 << 20, (u64)8 << 20}) {
+  for (u64 threshold : {((u64)1 << 19) / lpr, ((u64)1 << 20) / lpr, (u64)2 << 20, (u64)4 << 20, (u64)8 << 20, (u64)10 << 20}) {
     if (threshold - 1 < max_keys) {
       work_layout(cfg->dim, threshold - 1, &L);
       need = std::max(need, L.total);

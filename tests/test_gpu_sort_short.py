@@ -25,3 +25,10 @@ def test_rows_over_many_spans_of_wide_rows(D, spans):
     lengths = [8 * 61 + 3, 8 * spans, 5, 8 * spans + 9, 40]
     keys = np.repeat(np.arange(1, len(lengths) + 1), lengths)
     _step(rng.permutation(keys), D, 64)
+
+
+# one below and at the sizes from 2 M on where the span length changes for narrow rows
+@pytest.mark.parametrize("D,n", [(4, (2 << 20) - 1), (4, 2 << 20), (16, (4 << 20) - 1), (16, 4 << 20)])
+def test_span_length_of_narrow_rows_in_long_lists(D, n):
+    rng = np.random.default_rng(n)
+    _step((200000 ** rng.random(n)).astype(np.uint64) + 1, D, 200002)
