@@ -166,9 +166,11 @@ GemmArgs input_grad_args(const MlpLayout& L, u32 l, u32 B, const bf16_t* dz, con
 // A layer whose two products take less time together than one after the other runs them in one launch (paired); its
 // input gradient then has a place of its own instead of the activation's.  The partial sums of split weight gradients and of
 // the sums over the batch stay where they are until the optimizer adds them (kept).  All that stands in the scratch of
-// the products; where it does not fit, every product and every sum is finished by its own launches, in turn.
+// the products; where it does not fit, every product and every sum is finished by its own launches, in turn, but for the
+// first layer's weight gradient, the last product of all: its partial sums have the scratch to themselves (first_kept),
+// the sums over the batch then stand where its finished gradient would.
 struct BackwardPlan {
-  bool kept, paired[CTR_MLP_MAX_HIDDEN];
+  bool kept, first_kept, paired[CTR_MLP_MAX_HIDDEN];
   GemmPlan w[CTR_MLP_MAX_HIDDEN], i[CTR_MLP_MAX_HIDDEN];
   size_t off_w[CTR_MLP_MAX_HIDDEN], off_dz[CTR_MLP_MAX_HIDDEN], off_sums, off_rest;  // in the scratch
 };
@@ -200,6 +202,7 @@ void backward_plan(const MlpLayout& L, u32 B, size_t room, BackwardPlan* P) {
   o += align256((size_t)COLSUM_SLICES * cols * sizeof(float));
   P->off_rest = o;
   P->kept = o + rest <= room;
+  P->first_kept = false;
   if (P->kept) return;
   for (u32 l = 0; l < hidden; ++l) {
     P->paired[l] = false;
@@ -208,6 +211,8 @@ void backward_plan(const MlpLayout& L, u32 B, size_t room, BackwardPlan* P) {
     P->off_w[l] = 0;
   }
   P->off_sums = P->off_rest = 0;
+  const u64 first = (u64)L.in[0] * L.out[0];  // a split product's partial sums always fit; the sums of all columns have to
+  P->first_kept = P->w[0].n_split > 1 && P->i[0].n_split == 1 && COLSUM_SLICES * cols <= first;
 }
 
 // Forward through the hidden layers; activations stay in the workspace.
@@ -363,7 +368,7 @@ static int mlp_step_impl(ctr_mlp* t, uint32_t replica, const float* d_pooled, co
   src.n_layers = L.n_layers;
   BatchSums q{};  // of all layers; taken behind the last product
   q.rows = B;
-  q.partial = (float*)(scratch + plan.off_sums);
+  q.partial = plan.first_kept ? grads + L.w_off[0] : (float*)(scratch + plan.off_sums);
   q.lterm = lterm;
   q.dlogit = dlogit;
   q.loss = d_loss;
@@ -407,14 +412,16 @@ static int mlp_step_impl(ctr_mlp* t, uint32_t replica, const float* d_pooled, co
                          gw.B, gw, gi.A, gi.B, gi, n_w, n_i, q);
     } else {
       if (!gemm_args_ok(false, false, w) || !gemm_args_ok(true, true, i)) return CTR_E_DEVICE;
-      if (gemm_launch(false, false, w, plan.w[l], w_partial, plan.kept, st) != hipSuccess) return CTR_E_DEVICE;
+      const bool keep = plan.kept || (l == 0 && plan.first_kept);
+      if (gemm_launch(false, false, w, plan.w[l], w_partial, keep, st) != hipSuccess) return CTR_E_DEVICE;
       if (gemm_launch(true, true, i, plan.i[l], (float*)(scratch + plan.off_rest), false, st) != hipSuccess) return CTR_E_DEVICE;
     }
-    const bool split = plan.kept && plan.w[l].n_split > 1;
+    const bool split = (plan.kept || (l == 0 && plan.first_kept)) && plan.w[l].n_split > 1;
     src.weights[l] = {split ? w_partial : dw, (u64)L.in[l] * L.out[l], split ? plan.w[l].n_split : 1u};
     dz = below;
   }
-  if (plan.kept) {
+  const bool sums_kept = plan.kept || plan.first_kept;
+  if (sums_kept) {
     if (!sums_taken) hipLaunchKernelGGL(k_batch_sums, dim3(batch_sums_blocks(q)), dim3(BLOCK), 0, st, q);
   } else {
     // one pair of launches, unless the scratch ends before the columns do (layers of tens of thousands; each pair
@@ -438,7 +445,7 @@ static int mlp_step_impl(ctr_mlp* t, uint32_t replica, const float* d_pooled, co
   }
   src.w_off[L.n_layers] = L.n_params;
   src.weights[lo] = {grads + L.w_off[lo], 0, 1};
-  if (plan.kept)
+  if (sums_kept)
     for (u32 j = 0; j < q.n_jobs; ++j)  // the first sum is the output layer's weight gradient, the others are of biases
       (j == 0 ? src.weights : src.biases)[job_layer[j]] = {q.partial + q.col0[j], q.n_cols, COLSUM_SLICES};
   const u32 amode = mode == CTR_STEP_MERGE_PENDING ? 2u : (t->cfg.kstep ? 1u : 0u);

@@ -282,12 +282,13 @@ __device__ __forceinline__ T grad_sum(const GradSource& src, u64 i, const Load& 
   if (bias) at -= src.n_weights[l];
   const GradTerms t = bias ? src.biases[l] : src.weights[l];
   T s = load(t.p + at);
-  for (u32 k = 1; k < t.n; k += 8) {  // eight terms are requested together and added in order
-    T v[8];
+  constexpr u32 SIDE = sizeof(T) == sizeof(float) ? 32 : 8;  // terms requested together and added in order
+  for (u32 k = 1; k < t.n; k += SIDE) {
+    T v[SIDE];
 #pragma unroll
-    for (u32 j = 0; j < 8; ++j) v[j] = load(t.p + min(k + j, t.n - 1u) * t.stride + at);
+    for (u32 j = 0; j < SIDE; ++j) v[j] = k + j < t.n ? load(t.p + (k + j) * t.stride + at) : T{};
 #pragma unroll
-    for (u32 j = 0; j < 8; ++j)
+    for (u32 j = 0; j < SIDE; ++j)
       if (k + j < t.n) s = s + v[j];
   }
   return s;
