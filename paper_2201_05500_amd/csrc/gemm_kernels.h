@@ -127,21 +127,25 @@ __device__ __forceinline__ void gemm_barrier() {
 
 // The tile of R rows (of A; columns of B) x 64 k of an operand, carried by WAVES waves with N loads each.  A load brings
 // 1 KB of the tile's LDS image: 8 rows of 64 k, or LINES k of R values.
-// Swizzle: chunk c of a row lies at c ^ (row & 7) (k-contiguous: 8 lanes read one chunk of 8 rows); at c ^ 4 (k & 3) or,
-// with rows of 128 bytes, c ^ 4 (k / 2 & 1) (otherwise: 32 lanes read 64 bytes of 4 consecutive k).
+// Swizzle: chunk c of a row lies at c ^ (row & 7) ^ (row / 8 & 1) (k-contiguous: 16 lanes, whom the 64 banks serve together,
+// read one chunk of 16 rows, two rows to the banks; with row & 7 alone rows r and r + 8 met: 40 % of the LDS clocks of the
+// 16384 x 1024 x 19200 product were conflicts); at c ^ 4 (k & 3) or, with rows of 128 bytes, c ^ 4 (k / 2 & 1) (otherwise: 32
+// lanes read 64 bytes of 4 consecutive k).
 template <int R, bool KC, int WAVES>
 struct GemmTile {
   static constexpr u32 N = R / 8 / WAVES, CHUNKS = KC ? 8 : R / 8, LINES = 64 / CHUNKS;
-  u32 lane_off;  // from the load's first byte to this lane's 16
+  static_assert(N % 2 == 0, "load j of every wave begins at a row whose (row / 8 & 1) is j's");
+  u32 lane_off[KC ? 2 : 1];  // from the load's first byte to this lane's 16, of even and odd loads
   u32 line_bytes, row0, total, w;
   __device__ __forceinline__ GemmTile(u32 wave, u32 ld, u32 rows_total, u32 first_row)
       : line_bytes(2u * ld), row0(first_row), total(rows_total), w(wave) {
     const u32 lane = (u32)lane_id(), line = lane / CHUNKS, pos = lane % CHUNKS;
     if constexpr (KC) {
-      lane_off = line * line_bytes + (pos ^ line) * 16;
+      lane_off[0] = line * line_bytes + (pos ^ line) * 16;
+      lane_off[1] = line * line_bytes + (pos ^ line ^ 1u) * 16;
     } else {
       const u32 row = row0 + (pos ^ swizzle(line)) * 8;
-      lane_off = line * line_bytes + (row < total ? row : 0u) * 2u;
+      lane_off[0] = line * line_bytes + (row < total ? row : 0u) * 2u;
     }
   }
   static __device__ __forceinline__ u32 swizzle(u32 k) { return R == 64 ? (k >> 1 & 1u) << 2 : (k & 3u) << 2; }
@@ -160,11 +164,11 @@ struct GemmTile {
 #pragma unroll
     for (u32 j = 0; j < N; ++j) {
       if constexpr (INSIDE) {
-        gemm_to_lds(b, dst + j * 1024, lane_off, load_off(j, k0));
+        gemm_to_lds(b, dst + j * 1024, lane_off[KC ? j & 1 : 0], load_off(j, k0));
       } else {
         const u32 lane = (u32)lane_id(), line = lane / CHUNKS;
-        const u32 k = k0 + (KC ? ((lane % CHUNKS) ^ line) * 8 : (w * N + j) * LINES + line);
-        gemm_to_lds(b, dst + j * 1024, (lane_off + load_off(j, k0)) | (k < k_end ? 0u : GEMM_NOWHERE), 0);
+        const u32 k = k0 + (KC ? ((lane % CHUNKS) ^ line ^ (j & 1u)) * 8 : (w * N + j) * LINES + line);
+        gemm_to_lds(b, dst + j * 1024, (lane_off[KC ? j & 1 : 0] + load_off(j, k0)) | (k < k_end ? 0u : GEMM_NOWHERE), 0);
       }
     }
   }
@@ -179,7 +183,7 @@ struct GemmTile {
   static __device__ __forceinline__ bf16x8 fragment(const char* tile, u32 row, u32 kk) {
     const u32 l = (u32)lane_id();
     if constexpr (KC) {
-      return *reinterpret_cast<const bf16x8*>(tile + (row + (l & 31u)) * 128 + (((2 * kk) ^ ((l >> 5) ^ (l & 7u))) << 4));
+      return *reinterpret_cast<const bf16x8*>(tile + (row + (l & 31u)) * 128 + (((2 * kk) ^ ((l >> 5) ^ (l & 7u) ^ (l >> 3 & 1u))) << 4));
     } else {
       // 16 lanes take 4 k x 16 rows: lane 4 t + q addresses rows 4 q .. 4 q + 3 of k = t and receives row 4 t + q
       const u32 g = l >> 4, j = l & 15u, chunk = row / 8 + 2 * (g & 1u) + (j >> 1 & 1u);
@@ -229,11 +233,10 @@ __device__ __forceinline__ void gemm_wave_fence() {
 // the step S - 1 ahead is requested into.
 // A work item that takes all ranges of its contraction folds each finished one into `sum`, one that takes a single range
 // leaves it for k_gemm_reduce.
-// Bound by LDS: a step's fragments leave at 128 bytes a clock and CU and its tiles arrive at 64, one after the other
-// (T = 128: 64 KB and 32 KB, 1024 clocks, against 512 of matrix instructions; parts measured alone: fragments 0.26 us,
-// tiles 0.30, together 0.45, with the products 0.55), so neither more steps in flight nor fragments read a step ahead
-// gain (both measured).  Two workgroups of T = 128 fit a CU with S = 2; where there is one at most per CU, its latency
-// shows, and 8 waves with S = 4 are faster (4096 x 1024 x 3200: 40 -> 35 us; 16384 x 512 x 1024, two per CU: 28 with 8
+// A step of T = 128 takes 0.5 us on a CU that has one item, against 0.21 of matrix instructions; the arrival of its 32 KB alone
+// takes 0.30 (45 bytes a clock into one CU's LDS), whatever is in flight: neither more steps in the ring nor fragments read a
+// step ahead gain (both measured).  Two workgroups of T = 128 fit a CU with S = 2; where there is one at most per CU, its
+// latency shows, and 8 waves with S = 4 are faster (4096 x 1024 x 3200: 40 -> 35 us; 16384 x 512 x 1024, two per CU: 28 with 8
 // waves, 23 with 4).
 // Through registers, with transposes of 8 x 8 blocks in them, these took (us -> now): 1000 x 400 x 624 8.4 -> 6.5;
 // 4096 x 1024 x 3200 60 -> 35; 4096 x 512 x 1024 14.2 -> 10.3; 16384 x 512 x 1024 30 -> 23; 3200 x 1024 x 4096 64 -> 42;
@@ -364,9 +367,11 @@ k_gemm_tiles(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Bp, GemmA
 //     phase p, and a barrier lies between;
 //   * a unit's place is overwritten by requests of phase p + 2 at the earliest, and every wave waits for its reads of phase p
 //     at the end of that phase.
-// Bound by LDS like the smaller tiles (192 KB of fragments at 128 and 64 KB of tiles at 64 bytes a clock: 2560 clocks a
-// step against 2048 of matrix instructions).  With 4 waves of 128 x 128, operands through registers and one step in flight
-// the products of a layer of 19200 x 1024 and 16384 samples took (us -> now) 752 -> 465 forward (1.39 PFLOP/s), 930 -> 600
+// The forward product keeps the matrix cores busy 87 % of its clocks, at the 1.5 GHz that the chip's power leaves them
+// (counters: SQ_VALU_MFMA_BUSY_CYCLES of GRBM_GUI_ACTIVE), the weight gradient 69 % (300 tiles in 4 ranges are 4.7 rounds of
+// the chip, and their partial sums are stored), the input gradient 56 % (16 steps per tile: its first requests and stores).
+// With 4 waves of 128 x 128, operands through registers and one step in flight
+// the products of a layer of 19200 x 1024 and 16384 samples took (us -> now) 752 -> 460 forward (1.40 PFLOP/s), 930 -> 600
 // weight gradient, 790 -> 605 input gradient (1.26 GB of fp32 leave: with the non-temporal hint, 690 without, 540 if
 // nothing is stored).  Workgroups that walk several tiles and request the next one's units before they store: no gain.
 constexpr u32 LARGE_UNIT = 128 * 128, LARGE_STEP = 4 * LARGE_UNIT;
