@@ -487,14 +487,18 @@ static int pull_pool_impl(ctr_table* t, uint32_t replica, const uint64_t* d_keys
   u32* occ_row = (u32*)(b->ws + wl.off_occ_row);
   u32* seg_of = (u32*)(b->ws + wl.off_seg_of);
   enqueue_lookup_insert(t, wl, b->ws, (const u64*)d_keys, n, d_offsets, n_segments, true, st);
+  const SortPlan plan = sort_plan(n, t->row_bits);
+  u32* hist = (u32*)(b->ws + wl.off_hist);
   if (n_segments > 0) {
     StageTimer tm(t, CTR_STAGE_POOL, st);
     const float* vals = t->values + (u64)replica * t->tl.replica_stride;
     const PoolGrid pg = pool_grid(n_segments, t->lpr);
+    const SortFirst first = sort_first(plan, hist, n ? pg.blocks : 0u);
+    const u32 grid = pg.blocks + (n ? plan.geo.n_chunks : 0u);
 #define CTR_POOL_LAUNCH(KERNEL) \
   if (pg.small) { CTR_POOL_LAUNCH_1(KERNEL##_small); } else { CTR_POOL_LAUNCH_1(KERNEL); }
 #define CTR_POOL_LAUNCH_1(KERNEL) \
-  LPR_DISPATCH(t->lpr, KERNEL, pg.blocks, st, t->hdr, occ_row, t->slots, seg_of, d_offsets, n_segments, vals, t->D, t->rf, d_pooled, d_pooled_bf16)
+  LPR_DISPATCH(t->lpr, KERNEL, grid, st, t->hdr, occ_row, t->slots, seg_of, d_offsets, n_segments, vals, t->D, t->rf, d_pooled, d_pooled_bf16, first)
     if (d_pooled && d_pooled_bf16) {
       CTR_POOL_LAUNCH(k_pool_both);
     } else if (d_pooled_bf16) {
@@ -507,11 +511,10 @@ static int pull_pool_impl(ctr_table* t, uint32_t replica, const uint64_t* d_keys
   }
   if (n > 0) {
     StageTimer tm(t, CTR_STAGE_SORT, st);
-    u32* hist = (u32*)(b->ws + wl.off_hist);
     u32* digit_total = (u32*)(b->ws + wl.off_digit_total);
     u32* const keys[2] = {(u32*)(b->ws + wl.off_ka), (u32*)(b->ws + wl.off_kb)};
     u32* const vals[2] = {(u32*)(b->ws + wl.off_va), (u32*)(b->ws + wl.off_vb)};
-    const u32 last = sort_enqueue(t->hdr, occ_row, seg_of, keys, vals, n, t->row_bits, hist, digit_total, st);
+    const u32 last = sort_enqueue(t->hdr, occ_row, seg_of, keys, vals, plan, n_segments > 0, hist, digit_total, st);
     b->sorted_rows = keys[last];
     b->sorted_segs = vals[last];
   }
@@ -560,7 +563,7 @@ static int lookup_pool_enqueue(ctr_table* t, uint32_t replica, const uint64_t* d
 #define CTR_POOL_LAUNCH(KERNEL) \
   if (pg.small) { CTR_POOL_LAUNCH_1(KERNEL##_small); } else { CTR_POOL_LAUNCH_1(KERNEL); }
 #define CTR_POOL_LAUNCH_1(KERNEL) \
-  LPR_DISPATCH(t->lpr, KERNEL, pg.blocks, st, t->hdr, occ_row, t->slots, (u32*)nullptr, d_offsets, n_segments, vals, t->D, t->rf, d_pooled, pb)
+  LPR_DISPATCH(t->lpr, KERNEL, pg.blocks, st, t->hdr, occ_row, t->slots, (u32*)nullptr, d_offsets, n_segments, vals, t->D, t->rf, d_pooled, pb, SortFirst{})
     if (d_pooled && pb) {
       CTR_POOL_LAUNCH(k_pool_lookup_both);
     } else if (pb) {
@@ -688,7 +691,7 @@ static int push_adam_impl(ctr_table* t, uint32_t replica, ctr_batch* handle, con
         hipLaunchKernelGGL(k_span_keys, dim3(blocks_for(wl.n_spans)), dim3(BLOCK), 0, st, t->hdr, batch->sorted_rows,
                            batch->sorted_segs, n, wl.span, wl.n_spans, seg_shift, t->push_windows,
                            t->push_split == 2u ? 1u : 0u, key_in, val_in);
-        sort_pass_enqueue(t->hdr, key_in, val_in, key_out, val_out, g2, 0u, 255u, hist, digit_total, st);
+        sort_pass_enqueue(t->hdr, key_in, val_in, key_out, val_out, g2, 0u, 255u, hist, digit_total, false, st);
         order = val_out;
         if (t->push_split == 1u) {
           cold_count = digit_total + t->push_windows;  // spans with the key one past the last window

@@ -58,6 +58,53 @@ struct SortGeom {
   u32 items;        // elements per thread of a sub-tile: 4, 8 or 16
 };
 
+// The histograms of a list's first pass, taken beside the pooling by blocks of its launch behind n_pool_blocks of them
+// (a launch of its own costs 3 to 6 us); n_pool_blocks 0: there is none.  rows: hist[chunk][digit].
+struct SortFirst {
+  u32 n_pool_blocks, digit_mask, log2_radix, rows;
+  SortGeom geo;
+  u32* hist;
+};
+
+constexpr u32 SORT_FIRST_WORDS = 4096;  // LDS: 16 histograms of 256 digits, 4 of 1024, 2 of 2048
+
+// row_of: the row of an entry of the list.
+template <class RowOf>
+__device__ __forceinline__ void sort_first_hist(const SortFirst& f, u32 chunk, const u32* __restrict__ entries, u32* lds,
+                                                const RowOf& row_of) {
+  const u32 radix = 1u << f.log2_radix;
+  for (u32 i = threadIdx.x; i < SORT_FIRST_WORDS; i += BLOCK) lds[i] = 0;
+  __syncthreads();
+  const u32 beg = chunk * f.geo.chunk_elems, end = min(beg + f.geo.chunk_elems, f.geo.n);
+  u32* mine = lds + (((u32)wave_id() * 4 + ((u32)lane_id() & 3u)) >> (f.log2_radix - 8)) * radix;
+  for (u32 e = beg + threadIdx.x * 4; e < end; e += BLOCK * 4) {
+    u32 d[4];
+    if (e + 4 <= end) {
+      const uint4 v = *reinterpret_cast<const uint4*>(entries + e);
+      d[0] = row_of(v.x); d[1] = row_of(v.y); d[2] = row_of(v.z); d[3] = row_of(v.w);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) d[i] &= f.digit_mask;
+      // see k_sort_hist
+      const u32 ref = (u32)__builtin_amdgcn_readfirstlane((int)d[0]);
+      u32 n_ref = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        n_ref += (u32)__popcll(__ballot(d[i] == ref));
+        if (d[i] != ref) atomicAdd(&mine[d[i]], 1u);
+      }
+      if (lane_id() == __ffsll((long long)__ballot(true)) - 1) atomicAdd(&mine[ref], n_ref);
+    } else {
+      for (u32 j = e; j < end; ++j) atomicAdd(&mine[row_of(entries[j]) & f.digit_mask], 1u);
+    }
+  }
+  __syncthreads();
+  for (u32 d = threadIdx.x; d < radix; d += BLOCK) {
+    u32 total = 0;
+    for (u32 i = d; i < SORT_FIRST_WORDS; i += radix) total += lds[i];
+    f.hist[f.rows ? chunk * radix + d : d * f.geo.n_chunks + chunk] = total;
+  }
+}
+
 // ROWS: hist[chunk][digit], otherwise hist[digit][chunk].
 template <int R, bool ROWS>
 __global__ void __launch_bounds__(BLOCK)
@@ -361,11 +408,11 @@ inline size_t sort_hist_words(u64 n, u64 n_spans) {
   return words;
 }
 
-// One pass over the digit (key >> shift) & digit_mask.
+// One pass over the digit (key >> shift) & digit_mask; counted: its histograms have been taken.
 inline void sort_pass_enqueue(const DevHeader* hdr, const u32* keys_in, const u32* vals_in, u32* keys_out, u32* vals_out,
-                              const SortGeom& geo, u32 shift, u32 digit_mask, u32* hist, u32* digit_total,
+                              const SortGeom& geo, u32 shift, u32 digit_mask, u32* hist, u32* digit_total, bool counted,
                               hipStream_t st) {
-  hipLaunchKernelGGL((k_sort_hist<RADIX, false>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
+  if (!counted) hipLaunchKernelGGL((k_sort_hist<RADIX, false>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
   hipLaunchKernelGGL(k_sort_scan, dim3(RADIX), dim3(BLOCK), 0, st, hdr, hist, geo.n_chunks, digit_total);
 #define CTR_SORT_SCATTER(ITEMS, R, SCANNED)                                                                        \
   hipLaunchKernelGGL((k_sort_scatter<ITEMS, R, SCANNED>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, vals_in,      \
@@ -378,10 +425,10 @@ inline void sort_pass_enqueue(const DevHeader* hdr, const u32* keys_in, const u3
 // A pass of wide digits (R = 1024 or 2048; the digit totals stand behind the histograms).
 template <int R>
 inline void sort_pass_wide_enqueue(const DevHeader* hdr, const u32* keys_in, const u32* vals_in, u32* keys_out,
-                                   u32* vals_out, const SortGeom& geo, u32 shift, u32 digit_mask, u32* hist,
+                                   u32* vals_out, const SortGeom& geo, u32 shift, u32 digit_mask, u32* hist, bool counted,
                                    hipStream_t st) {
   u32* digit_total = hist + (size_t)R * geo.n_chunks;
-  hipLaunchKernelGGL((k_sort_hist<R, true>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
+  if (!counted) hipLaunchKernelGGL((k_sort_hist<R, true>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
   hipLaunchKernelGGL(k_sort_scan_wide, dim3(R / 16), dim3(BLOCK), 0, st, hdr, hist, geo.n_chunks, (u32)R, digit_total);
   if (geo.items == 4) CTR_SORT_SCATTER(4, R, true);
   else CTR_SORT_SCATTER(8, R, true);
@@ -390,42 +437,65 @@ inline void sort_pass_wide_enqueue(const DevHeader* hdr, const u32* keys_in, con
 // A pass without a scan, of a list of few chunks (4 elements per thread).
 template <int R>
 inline void sort_pass_short_enqueue(const DevHeader* hdr, const u32* keys_in, const u32* vals_in, u32* keys_out,
-                                    u32* vals_out, const SortGeom& geo, u32 shift, u32 digit_mask, u32* hist,
+                                    u32* vals_out, const SortGeom& geo, u32 shift, u32 digit_mask, u32* hist, bool counted,
                                     hipStream_t st) {
   const u32* digit_total = nullptr;
-  hipLaunchKernelGGL((k_sort_hist<R, true>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
+  if (!counted) hipLaunchKernelGGL((k_sort_hist<R, true>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
   CTR_SORT_SCATTER(4, R, false);
 }
 #undef CTR_SORT_SCATTER
 
-// Sorts n (key, value) pairs by the low key_bits bits of the key, between the two pairs of arrays; returns which of
-// them (0 = a, 1 = b) holds the result.
-inline u32 sort_enqueue(const DevHeader* hdr, const u32* keys_in, const u32* vals_in, u32* const (&keys)[2],
-                        u32* const (&vals)[2], u64 n, u32 key_bits, u32* hist, u32* digit_total, hipStream_t st) {
+// How a list of n elements is sorted by the low key_bits bits of its keys.
+struct SortPlan {
+  u32 passes, log2_radix, key_bits;
+  bool scanned;  // with a scan launch per pass
+  SortGeom geo;
+  u32 bits(u32 pass, u32 shift) const { return (key_bits - shift + (passes - pass) - 1) / (passes - pass); }  // spread evenly
+  bool rows() const { return log2_radix != 8 || !scanned; }  // hist[chunk][digit]
+};
+
+inline SortPlan sort_plan(u64 n, u32 key_bits) {
+  SortPlan p;
   const u32 wide_bits = key_bits > 20 ? 11u : 10u;
-  u32 passes = (key_bits + 7) / 8;
+  p.key_bits = key_bits;
+  p.passes = (key_bits + 7) / 8;
   const u32 wide_passes = (key_bits + wide_bits - 1) / wide_bits;
-  const bool wide = wide_passes < passes && sort_takes_wide(n, wide_bits) && (wide_passes < 3 || n <= SORT_3_WIDE_PASSES_MAX);
-  if (wide) passes = wide_passes;
-  const SortGeom geo = wide ? sort_geom_wide(n, wide_bits) : sort_geom(n);
+  const bool wide = wide_passes < p.passes && sort_takes_wide(n, wide_bits) && (wide_passes < 3 || n <= SORT_3_WIDE_PASSES_MAX);
+  if (wide) p.passes = wide_passes;
+  p.log2_radix = wide ? wide_bits : 8;
+  p.geo = wide ? sort_geom_wide(n, wide_bits) : sort_geom(n);
+  p.scanned = p.geo.n_chunks > (!wide ? SORT_SHORT_CHUNKS : wide_bits == 10 ? SORT_SHORT_CHUNKS_10 : SORT_SHORT_CHUNKS_11);
+  return p;
+}
+
+// The part of the first pass that the pooling launch takes over.
+inline SortFirst sort_first(const SortPlan& p, u32* hist, u32 n_pool_blocks) {
+  return {n_pool_blocks, (1u << p.bits(0, 0)) - 1u, p.log2_radix, p.rows() ? 1u : 0u, p.geo, hist};
+}
+
+// Sorts the (key, value) pairs as planned, between the two pairs of arrays; returns which of them (0 = a, 1 = b) holds the
+// result.  counted: the first pass's histograms have been taken (sort_first).
+inline u32 sort_enqueue(const DevHeader* hdr, const u32* keys_in, const u32* vals_in, u32* const (&keys)[2],
+                        u32* const (&vals)[2], const SortPlan& plan, bool counted, u32* hist, u32* digit_total,
+                        hipStream_t st) {
   u32 shift = 0;
-  for (u32 p = 0; p < passes; ++p) {
-    const u32 bits = (key_bits - shift + (passes - p) - 1) / (passes - p);  // spread evenly over the passes
-    const u32 mask = (1u << bits) - 1u;
-#define CTR_SORT_PASS(KIND, R) sort_pass_##KIND##_enqueue<R>(hdr, keys_in, vals_in, keys[p & 1], vals[p & 1], geo, shift, mask, hist, st)
-    const bool few = geo.n_chunks <= (!wide ? SORT_SHORT_CHUNKS : wide_bits == 10 ? SORT_SHORT_CHUNKS_10 : SORT_SHORT_CHUNKS_11);
-    if (!wide && few) CTR_SORT_PASS(short, RADIX);
-    else if (!wide) sort_pass_enqueue(hdr, keys_in, vals_in, keys[p & 1], vals[p & 1], geo, shift, mask, hist, digit_total, st);
-    else if (wide_bits == 10 && few) CTR_SORT_PASS(short, 1024);
-    else if (wide_bits == 10) CTR_SORT_PASS(wide, 1024);
-    else if (few) CTR_SORT_PASS(short, 2048);
-    else CTR_SORT_PASS(wide, 2048);
+  for (u32 p = 0; p < plan.passes; ++p, counted = false) {
+    const u32 bits = plan.bits(p, shift), mask = (1u << bits) - 1u;
+#define CTR_SORT_PASS(KIND, R) \
+  sort_pass_##KIND##_enqueue<R>(hdr, keys_in, vals_in, keys[p & 1], vals[p & 1], plan.geo, shift, mask, hist, counted, st)
+    if (plan.log2_radix == 8 && plan.scanned)
+      sort_pass_enqueue(hdr, keys_in, vals_in, keys[p & 1], vals[p & 1], plan.geo, shift, mask, hist, digit_total, counted, st);
+    else if (plan.log2_radix == 8) CTR_SORT_PASS(short, RADIX);
+    else if (plan.log2_radix == 10 && plan.scanned) CTR_SORT_PASS(wide, 1024);
+    else if (plan.log2_radix == 10) CTR_SORT_PASS(short, 1024);
+    else if (plan.scanned) CTR_SORT_PASS(wide, 2048);
+    else CTR_SORT_PASS(short, 2048);
 #undef CTR_SORT_PASS
     keys_in = keys[p & 1];
     vals_in = vals[p & 1];
     shift += bits;
   }
-  return (passes - 1) & 1;
+  return (plan.passes - 1) & 1;
 }
 
 }  // namespace ctr

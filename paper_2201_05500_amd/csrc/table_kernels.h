@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "sort_kernels.h"
 
 namespace ctr {
 
@@ -618,17 +619,30 @@ __device__ __forceinline__ d4 pool_segment(u32 g, u32 beg, u32 end, u32* __restr
   return acc;
 }
 
+// True for the blocks of a training pull's pooling launch that count digits instead (SortFirst).
+__device__ __forceinline__ bool pool_takes_hist(const DevHeader* hdr, const u32* occ_row, const Slot* __restrict__ slots,
+                                                const SortFirst& first, u32* lds) {
+  if (first.n_pool_blocks == 0 || blockIdx.x < first.n_pool_blocks) return false;
+  if (hdr->status) return true;
+  // an entry is the same row before and after a pooling block has put the row in the place of its slot
+  sort_first_hist(first, blockIdx.x - first.n_pool_blocks, occ_row, lds, [&](u32 entry) { return resolve_row(entry, slots); });
+  return true;
+}
+static_assert(SORT_FIRST_WORDS <= POOL_STAGED, "the histograms fit where the pooling stages its row ids");
+
 template <int LPR, int OUT>
 __device__ __forceinline__ void pool_body(DevHeader* hdr, u32* occ_row,
                                           const Slot* __restrict__ slots, u32* __restrict__ seg_of,
                                           const u32* __restrict__ offsets, u32 n_seg,
                                           const float* __restrict__ values, u32 D, u32 rf,
-                                          float* __restrict__ pooled, bf16_t* __restrict__ pooled_bf16) {
+                                          float* __restrict__ pooled, bf16_t* __restrict__ pooled_bf16,
+                                          const SortFirst& first) {
   constexpr bool LOOKUP = (OUT & 4) != 0;
   constexpr u32 GROUPS = BLOCK / LPR;
   constexpr u32 TILE = GROUPS * POOL_NS * POOL_ROUNDS;
   __shared__ u32 off_lds[TILE + 1];
   __shared__ u32 row_lds[POOL_STAGED];
+  if (!LOOKUP && pool_takes_hist(hdr, occ_row, slots, first, row_lds)) return;
   const u32 tile_g0 = blockIdx.x * TILE;
   const u32 tile_n = __builtin_amdgcn_readfirstlane(min(TILE, n_seg - tile_g0));
   const u32 off0 = threadIdx.x <= tile_n ? offsets[tile_g0 + threadIdx.x] : 0u;
@@ -737,8 +751,13 @@ __device__ __forceinline__ void pool_small_body(DevHeader* hdr, u32* __restrict_
                                                 const Slot* __restrict__ slots, u32* __restrict__ seg_of,
                                                 const u32* __restrict__ offsets, u32 n_seg,
                                                 const float* __restrict__ values, u32 D, u32 rf,
-                                                float* __restrict__ pooled, bf16_t* __restrict__ pooled_bf16) {
+                                                float* __restrict__ pooled, bf16_t* __restrict__ pooled_bf16,
+                                                const SortFirst& first) {
   constexpr bool LOOKUP = (OUT & 4) != 0;
+  if constexpr (!LOOKUP) {
+    __shared__ u32 lds[SORT_FIRST_WORDS];
+    if (pool_takes_hist(hdr, occ_row, slots, first, lds)) return;
+  }
   const u32 g = (blockIdx.x * BLOCK + threadIdx.x) / LPR, c = threadIdx.x % LPR;
   const u32 beg = g < n_seg ? offsets[g] : 0u, end = g < n_seg ? offsets[g + 1] : 0u;
   requested();
@@ -751,15 +770,15 @@ __device__ __forceinline__ void pool_small_body(DevHeader* hdr, u32* __restrict_
 #define CTR_POOL_ARGS                                                                                       \
   DevHeader *hdr, u32 *__restrict__ occ_row, const Slot *__restrict__ slots, u32 *__restrict__ seg_of, \
       const u32 *__restrict__ offsets, u32 n_seg, const float *__restrict__ values, u32 D, u32 rf,          \
-      float *__restrict__ pooled, bf16_t *__restrict__ pooled_bf16
+      float *__restrict__ pooled, bf16_t *__restrict__ pooled_bf16, SortFirst first
 #define CTR_DEFINE_POOL(NAME, OUT)                                                                           \
   template <int LPR>                                                                                         \
   __global__ void __launch_bounds__(BLOCK) NAME(CTR_POOL_ARGS) {                                             \
-    pool_body<LPR, OUT>(hdr, occ_row, slots, seg_of, offsets, n_seg, values, D, rf, pooled, pooled_bf16);    \
+    pool_body<LPR, OUT>(hdr, occ_row, slots, seg_of, offsets, n_seg, values, D, rf, pooled, pooled_bf16, first);    \
   }                                                                                                          \
   template <int LPR>                                                                                         \
   __global__ void __launch_bounds__(BLOCK) NAME##_small(CTR_POOL_ARGS) {                                     \
-    pool_small_body<LPR, OUT>(hdr, occ_row, slots, seg_of, offsets, n_seg, values, D, rf, pooled, pooled_bf16); \
+    pool_small_body<LPR, OUT>(hdr, occ_row, slots, seg_of, offsets, n_seg, values, D, rf, pooled, pooled_bf16, first); \
   }
 CTR_DEFINE_POOL(k_pool, 1)
 CTR_DEFINE_POOL(k_pool_bf16, 2)
