@@ -305,12 +305,16 @@ __device__ __forceinline__ void combine_groups(d4& a) {
   }
 }
 
-// Adds the partial sums first, first + GPW, ... below end in this order.  Wide rows leave a wave few groups and long
-// lists: eight partials are requested together.  (Narrower rows lose by the registers, with four: fix-up of 16 columns
-// 10.1 -> 13.7 us, of 64 columns 63 -> 78.)
-template <int LPR>
+// Adds the partial sums first, first + GPW, ... below end in this order, as many requested together as BATCH says.  Wide rows
+// leave a wave few groups and long lists: the sums of a block of spans, few waves in all, request eight, the fix-up, whose
+// many waves are limited by registers, two (200 columns, 83 k spans: 72 us with one, 55 with two, 60 with four, 108 with
+// eight), and for narrower rows one (with four: 16 columns 10.1 -> 13.7 us, 64 columns 63 -> 78).
+constexpr u32 head_batch(u32 lpr) { return lpr >= 32 ? 8 : 1; }
+constexpr u32 fixup_batch(u32 lpr) { return lpr >= 32 ? 2 : 1; }
+
+template <int LPR, u32 BATCH>
 __device__ __forceinline__ void add_partials(const double* __restrict__ part, u32 first, u32 end, u32 D, u32 c, d4& a) {
-  constexpr u32 GPW = WAVE / LPR, BATCH = LPR >= 32 ? 8 : 1;
+  constexpr u32 GPW = WAVE / LPR;
   for (u32 k = first; k < end; k += BATCH * GPW) {
     d4 p[BATCH];
 #pragma unroll
@@ -511,7 +515,7 @@ __device__ __forceinline__ void push_span_body(const DevHeader* hdr, const u32* 
     const u32 n_lead = leading_true(first_rows[w * SPANS_PER_BLOCK + lane] == row);
     if (n_lead == 0) return;
     d4 sum = {0.0, 0.0, 0.0, 0.0};
-    if (col_ok) add_partials<LPR>(head_part, first + lane / LPR, first + n_lead, D, c, sum);
+    if (col_ok) add_partials<LPR, head_batch(LPR)>(head_part, first + lane / LPR, first + n_lead, D, c, sum);
     combine_groups<LPR>(sum);
     if (lane / LPR == 0 && col_ok) store_partial(block_head, first / SPANS_PER_BLOCK, D, c, sum);
   }
@@ -589,7 +593,7 @@ k_push_block_heads(const DevHeader* hdr, const u32* __restrict__ sr, u32 n_spans
   const u32 n_lead = leading_true(t < n_spans && (flags >> 2) == row);  // coalesced, unlike sr[t * span]
   if (n_lead == 0) return;
   d4 acc = {0.0, 0.0, 0.0, 0.0};
-  if (col_ok) add_partials<LPR>(head_part, first + part * SHARE + grp, first + min(n_lead, (part + 1) * SHARE), D, c, acc);
+  if (col_ok) add_partials<LPR, head_batch(LPR)>(head_part, first + part * SHARE + grp, first + min(n_lead, (part + 1) * SHARE), D, c, acc);
   combine_groups<LPR>(acc);
   if constexpr (WAVES > 1) {
     __shared__ d4 shares[WAVES - 1][LPR];
@@ -629,10 +633,16 @@ __device__ __forceinline__ void push_fixup_body(DevHeader* hdr, const u32* __res
   const int lane = lane_id();
   const u32 own = (blockIdx.x * BLOCK + threadIdx.x) / LANES, own_c = lane % LANES, status = hdr->status;
   const u32 own_flags = own < n_spans ? span_flags[own] : 0u;
-  u32 next[FIXUP_NEAR];
+  u32 next[FIXUP_NEAR], last = 0;  // rows at the beginning of the next spans, at the end of this one
+  const auto request = [&]() {
 #pragma unroll
-  for (u32 k = 0; k < FIXUP_NEAR; ++k) next[k] = own + 1 + k < n_spans ? span_flags[own + 1 + k] >> 2 : NO_ROW;
-  const u32 last = own + 1 < n_spans ? sr[(own + 1) * span - 1] : 0u;  // of the span; a tail means that the list goes on
+    for (u32 k = 0; k < FIXUP_NEAR; ++k) next[k] = own + 1 + k < n_spans ? span_flags[own + 1 + k] >> 2 : NO_ROW;
+    if (own + 1 < n_spans) last = sr[(own + 1) * span - 1];  // a tail means that the list goes on
+  };
+  // a wave of one or two spans, most of which have no tail, would make many requests in vain (256 columns, 83 k spans: 60
+  // -> 75 us)
+  constexpr bool EARLY = LANES < 32;
+  if (EARLY) request();
   requested();
   if (status) return;
   AdamParams P = P_in;
@@ -653,6 +663,7 @@ __device__ __forceinline__ void push_fixup_body(DevHeader* hdr, const u32* __res
   const bool tail = own_flags & SF_TAIL;
   bool far = false;
   if (tail) {
+    if (!EARLY) request();
     const u32 row = last;
     u32 n_near = 0;
 #pragma unroll
@@ -684,12 +695,12 @@ __device__ __forceinline__ void push_fixup_body(DevHeader* hdr, const u32* __res
     // spans after s inside its block (at most SPANS_PER_BLOCK - 1 = one per lane)
     const u32 t = s + 1 + lane;
     const u32 n_in = leading_true(t < blk_end && (span_flags[t] >> 2) == row);
-    if (col_ok) add_partials<LPR>(head_part, s + 1 + grp, s + 1 + n_in, D, c, acc);
+    if (col_ok) add_partials<LPR, fixup_batch(LPR)>(head_part, s + 1 + grp, s + 1 + n_in, D, c, acc);
     if (s + 1 + n_in == blk_end) {  // the row reaches the end of the block: go on block by block
       for (u32 jb = s / SPANS_PER_BLOCK + 1; jb < n_blocks; jb += WAVE) {
         const u32 jj = jb + lane;
         const u32 nb = leading_true(jj < n_blocks && (span_flags[jj * SPANS_PER_BLOCK] >> 2) == row);
-        if (col_ok) add_partials<LPR>(block_head, jb + grp, jb + nb, D, c, acc);
+        if (col_ok) add_partials<LPR, fixup_batch(LPR)>(block_head, jb + grp, jb + nb, D, c, acc);
         if (nb < WAVE) break;
       }
     }
