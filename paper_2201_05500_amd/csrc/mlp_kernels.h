@@ -5,6 +5,8 @@
 // (k-step Adam) on the dense parameters.  bf16 rounding is nearest-even, done here by hand so that
 // it is the same rule everywhere: (u + 0x7FFF + ((u >> 16) & 1)) >> 16 on the fp32 bit pattern.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 #include "gemm_kernels.h"
 
@@ -282,22 +284,33 @@ __device__ __forceinline__ T grad_sum(const GradSource& src, u64 i, const Load& 
   if (bias) at -= src.n_weights[l];
   const GradTerms t = bias ? src.biases[l] : src.weights[l];
   T s = load(t.p + at);
-  constexpr u32 SIDE = sizeof(T) == sizeof(float) ? 32 : 8;  // terms requested together and added in order
-  for (u32 k = 1; k < t.n; k += SIDE) {
-    T v[SIDE];
+  // terms are requested together (the last ones again, beyond the end) and added in order: a few of a split product, many of
+  // the batch sums
+  const auto add = [&](auto side) {
+    constexpr u32 SIDE = decltype(side)::value;
+    for (u32 k = 1; k < t.n; k += SIDE) {
+      T v[SIDE];
 #pragma unroll
-    for (u32 j = 0; j < SIDE; ++j) v[j] = k + j < t.n ? load(t.p + (k + j) * t.stride + at) : T{};
+      for (u32 j = 0; j < SIDE; ++j) v[j] = load(t.p + min(k + j, t.n - 1u) * t.stride + at);
 #pragma unroll
-    for (u32 j = 0; j < SIDE; ++j)
-      if (k + j < t.n) s = s + v[j];
-  }
+      for (u32 j = 0; j < SIDE; ++j)
+        if (k + j < t.n) s = s + v[j];
+    }
+  };
+  if (t.n > 32)
+    add(std::integral_constant<u32, sizeof(T) == sizeof(float) ? 32 : 16>());
+  else if (t.n > 4)
+    add(std::integral_constant<u32, 8>());
+  else
+    add(std::integral_constant<u32, 4>());
   return s;
 }
 
 __global__ void __launch_bounds__(BLOCK)
 k_dense_adam(float* __restrict__ params, float* __restrict__ m, float* __restrict__ v, const float* __restrict__ vhat,
              GradSource src, bf16_t* __restrict__ pb, u64 n, u64 n4, DenseAdam step) {
-  const u64 t = (u64)blockIdx.x * BLOCK + threadIdx.x;
+  // from the last parameters on: those of the small layers, with many terms to add, are not the end of the launch
+  const u64 t = (u64)(gridDim.x - 1u - blockIdx.x) * BLOCK + threadIdx.x;
   if (t < n4) {  // layers begin and biases begin at multiples of 4
     const u64 i = t * 4;
     f4 mm = ldg4_stream(m + i), vv = ldg4_stream(v + i), x = {0.0f, 0.0f, 0.0f, 0.0f}, den = x;
