@@ -1,6 +1,7 @@
 // Device-side building blocks shared by the kernels of the sparse embedding cycle (gfx950, wave64).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace ctr {
@@ -38,14 +39,16 @@ struct DevHeader {
   u32 n_new;        // rows created by the last pull
   u32 n_unique;     // distinct keys of the last pushed batch
   u32 n_push;       // pushes accepted so far: the step count t of the bias-corrected row update
-  double bc1, bc2;  // 1 / (1 - beta1^t), 1 / (1 - beta2^t) of the push in flight (bias-corrected form only)
   u64 rows_merged;  // rows averaged by all k-step merges so far (those touched since the merge before)
   u64 merge_pending;  // (row, replica) pairs whose deferred model step those merges applied
   u32 pull_seen;    // errors the probe launch of the pull in flight found (pull_err is zero again by then)
   u32 batch_ok;     // 1: the last pull succeeded, its lists are whole (0 until its numbering is done)
-  u32 pad[46];
+  u32 push_t;       // number of the push in flight (bias-corrected form only, as what follows)
+  u32 pad0;
+  double bc[2][2];  // 1 / (1 - beta1^t), 1 / (1 - beta2^t) of push t at [t & 1], from the end of the push before on
+  u32 pad[40];
 };
-constexpr int HDR_WORD_N_PUSH = 7;  // index of n_push among the header's 32-bit words
+constexpr u32 HDR_WORD_N_PUSH = offsetof(DevHeader, n_push) / 4, HDR_WORD_BC = offsetof(DevHeader, bc) / 4;
 static_assert(sizeof(DevHeader) == 256, "header is one 256-byte block");
 
 // 64-bit finalizer of MurmurHash3 (public domain): slot choice in the key index.

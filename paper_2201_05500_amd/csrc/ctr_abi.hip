@@ -439,6 +439,8 @@ int ctr_table_create(const ctr_config* cfg, void* d_mem, size_t bytes, void* hip
   const u32 grid = (u32)std::min<u64>((work + BLOCK - 1) / BLOCK, 8192);
   hipLaunchKernelGGL(k_table_clear, dim3(grid), dim3(BLOCK), 0, st, t->hdr, t->slots, L.n_slots, t->row_state,
                      t->R, 0u);
+  if (cfg->flags & CTR_F_BIAS_CORRECTION)
+    hipLaunchKernelGGL(k_push_count, dim3(1), dim3(WAVE), 0, st, t->hdr, (double)cfg->beta1, (double)cfg->beta2, 0u);
   if (launch_status() != CTR_OK) {
     delete t;
     return CTR_E_DEVICE;
@@ -639,8 +641,8 @@ static int push_adam_impl(ctr_table* t, uint32_t replica, ctr_batch* handle, con
   hipStream_t st = (hipStream_t)hip_stream;
   const WorkLayout& wl = batch->wl;
   const u32 n = batch->n_keys;
-  if (flags & CTR_F_BIAS_CORRECTION)  // the step count lives on the device: an empty batch counts, a refused one does not
-    hipLaunchKernelGGL(k_push_begin, dim3(1), dim3(WAVE), 0, st, t->hdr, (double)t->cfg.beta1, (double)t->cfg.beta2);
+  if (n == 0 && (flags & CTR_F_BIAS_CORRECTION))  // the step count lives on the device: an empty batch counts, a refused one does not
+    hipLaunchKernelGGL(k_push_count, dim3(1), dim3(WAVE), 0, st, t->hdr, (double)t->cfg.beta1, (double)t->cfg.beta2, 1u);
   if (n > 0) {
     AdamParams P;
     P.b1 = (double)t->cfg.beta1;

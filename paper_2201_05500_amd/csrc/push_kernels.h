@@ -199,14 +199,20 @@ __device__ __forceinline__ void add_partial(const double* __restrict__ part, u32
   a.x += p[0]; a.y += p[1]; a.z += p[2]; a.w += p[3];
 }
 
-// First launch of a push under the bias-corrected update: counts the push (only if the table accepts it:
-// while a deferred error is pending every push is a no-op and must not advance the step count) and
-// leaves the two correction factors of step t in the header for the row-update launches that follow.
-__global__ void k_push_begin(DevHeader* hdr, double b1, double b2) {
+// The bias-corrected update's factors.  hdr->n_push counts the pushes accepted so far (while a deferred error is pending every
+// push is a no-op and must not advance it); the factors of the next one stand ready in hdr->bc[(n_push + 1) & 1].  A push takes
+// no launch of its own for them: its span walk, which reads n_push, leaves its number in hdr->push_t; its fix-up, which
+// reads that, leaves n_push and the next factors, which nothing reads before the next push.
+__device__ __forceinline__ void push_factors(DevHeader* hdr, u32 t, double b1, double b2) {
+  hdr->bc[t & 1u][0] = 1.0 / (1.0 - pow(b1, (double)t));
+  hdr->bc[t & 1u][1] = 1.0 / (1.0 - pow(b2, (double)t));
+}
+// Of a new table (count 0: the first push's factors), or of a push without occurrences.
+__global__ void k_push_count(DevHeader* hdr, double b1, double b2, u32 count) {
   if (threadIdx.x != 0 || blockIdx.x != 0 || hdr->status) return;
-  const u32 t = ++hdr->n_push;
-  hdr->bc1 = 1.0 / (1.0 - pow(b1, (double)t));
-  hdr->bc2 = 1.0 / (1.0 - pow(b2, (double)t));
+  const u32 t = hdr->n_push + count;
+  hdr->n_push = t;
+  push_factors(hdr, t + 1, b1, b2);
 }
 
 // Sort key of a span for the windowed execution order: the window of the gradient array its first
@@ -339,7 +345,7 @@ __device__ __forceinline__ void add_partials(const double* __restrict__ part, u3
 constexpr bool span_sums_heads(u32 lpr) { return lpr * SPANS_PER_BLOCK <= BLOCK; }
 
 template <int LPR, int KIND, bool GB>
-__device__ __forceinline__ void push_span_body(const DevHeader* hdr, const u32* __restrict__ sr,
+__device__ __forceinline__ void push_span_body(DevHeader* hdr, const u32* __restrict__ sr,
                                                const u32* __restrict__ ss, u32 n, u32 span,
                                                const void* __restrict__ grad_any, float* __restrict__ values,
                                                const float* __restrict__ vhat, u32* __restrict__ row_state, u32 D,
@@ -350,8 +356,10 @@ __device__ __forceinline__ void push_span_body(const DevHeader* hdr, const u32* 
   AdamParams P = P_in;
   const u32 status = hdr->status;
   if constexpr (KIND == STEP_ADAM_KINGMA) {
-    P.bc1 = hdr->bc1;
-    P.bc2 = hdr->bc2;
+    const u32 t = hdr->n_push + 1u;
+    P.bc1 = hdr->bc[t & 1u][0];
+    P.bc2 = hdr->bc[t & 1u][1];
+    if (!status && blockIdx.x == 0 && threadIdx.x == 0) hdr->push_t = t;
   }
   constexpr int PB = CTR_PUSH_PB;
   u32 s = (blockIdx.x * BLOCK + threadIdx.x) / LPR;
@@ -523,7 +531,7 @@ __device__ __forceinline__ void push_span_body(const DevHeader* hdr, const u32* 
 
 
 #define CTR_PUSH_SPAN_ARGS                                                                                      \
-  const DevHeader *hdr, const u32 *__restrict__ sr, const u32 *__restrict__ ss, u32 n, u32 span,               \
+  DevHeader *hdr, const u32 *__restrict__ sr, const u32 *__restrict__ ss, u32 n, u32 span,               \
       const void *__restrict__ grad, float *__restrict__ values, const float *__restrict__ vhat,               \
       u32 *__restrict__ row_state, u32 D, u32 rf, AdamParams P, double *__restrict__ head_part,                \
       double *__restrict__ tail_part, double *__restrict__ block_head, u32 *__restrict__ span_flags,           \
@@ -617,7 +625,7 @@ k_push_block_heads(const DevHeader* hdr, const u32* __restrict__ sr, u32 n_spans
 // long rows of a wave's spans wait for each other (2 lanes: 8.8 us for 4.6 k spans that take 4.6).
 // The first workgroup also adds up the blocks' counts of rows: the distinct keys of the batch.  (In a launch of its
 // own that cost 2.5 to 6.5 us; with an atomic per workgroup of the launch before, 6 us at 300 k spans.)
-constexpr u32 FIXUP_NEAR = 4, FIXUP_MIN_LANES = 16;
+constexpr u32 FIXUP_NEAR = 4, FIXUP_MIN_LANES = 16, FIXUP_EARLY_BLOCKS = 2048;
 constexpr u32 fixup_lanes(u32 lpr) { return lpr < FIXUP_MIN_LANES ? FIXUP_MIN_LANES : lpr; }
 
 template <int LPR, int KIND>
@@ -639,16 +647,21 @@ __device__ __forceinline__ void push_fixup_body(DevHeader* hdr, const u32* __res
     for (u32 k = 0; k < FIXUP_NEAR; ++k) next[k] = own + 1 + k < n_spans ? span_flags[own + 1 + k] >> 2 : NO_ROW;
     if (own + 1 < n_spans) last = sr[(own + 1) * span - 1];  // a tail means that the list goes on
   };
-  // a wave of one or two spans, most of which have no tail, would make many requests in vain (256 columns, 83 k spans: 60
-  // -> 75 us)
-  constexpr bool EARLY = LANES < 32;
-  if (EARLY) request();
+  // Small grids ask for that at once, too.  Where the chip is full, most spans have no tail and the requests were in vain
+  // (16 columns, 78 k spans: 10.3 -> 11.4 us; 200 columns, 83 k: 60 -> 75; but 8 columns, 18 k: 6.4 -> 5.6).
+  const bool early = gridDim.x <= FIXUP_EARLY_BLOCKS;
+  if (early) request();
   requested();
   if (status) return;
   AdamParams P = P_in;
   if constexpr (KIND == STEP_ADAM_KINGMA) {
-    P.bc1 = hdr->bc1;
-    P.bc2 = hdr->bc2;
+    const u32 t = hdr->push_t;
+    P.bc1 = hdr->bc[t & 1u][0];
+    P.bc2 = hdr->bc[t & 1u][1];
+    if (blockIdx.x == min(1u, gridDim.x - 1u) && threadIdx.x == BLOCK - 1) {  // early, and beside the counting block
+      hdr->n_push = t;
+      push_factors(hdr, t + 1u, P.b1, P.b2);
+    }
   }
   if (blockIdx.x == 0) {
     __shared__ u32 rows[BLOCK / WAVE];
@@ -663,7 +676,7 @@ __device__ __forceinline__ void push_fixup_body(DevHeader* hdr, const u32* __res
   const bool tail = own_flags & SF_TAIL;
   bool far = false;
   if (tail) {
-    if (!EARLY) request();
+    if (!early) request();
     const u32 row = last;
     u32 n_near = 0;
 #pragma unroll

@@ -45,6 +45,7 @@ constexpr u32 SORT_SHORT_CHUNKS = 64, SORT_SHORT_CHUNKS_10 = 8, SORT_SHORT_CHUNK
 #define CTR_SORT_MAX_CHUNKS 4096
 #endif
 constexpr int SORT_MAX_CHUNKS = CTR_SORT_MAX_CHUNKS;
+static_assert(SORT_MAX_CHUNKS % BLOCK == 0, "k_sort_scan");
 constexpr int RADIX = 256;
 #ifndef CTR_HIST_COPIES
 #define CTR_HIST_COPIES 4
@@ -157,26 +158,27 @@ k_sort_hist(const DevHeader* hdr, const u32* __restrict__ keys, SortGeom geo, u3
   }
 }
 
-// grid = RADIX blocks; block d turns hist[d][0..n_chunks) into exclusive prefix sums.
-constexpr u32 SCAN_PER = (SORT_MAX_CHUNKS + BLOCK - 1) / BLOCK;  // most entries of a thread: they stay in registers
+// grid = RADIX blocks; block d turns hist[d][0..n_chunks) into exclusive prefix sums.  A thread's entries (PER at most, 1 for
+// lists of up to 256 chunks) stay in registers.
+template <u32 PER>
 __global__ void __launch_bounds__(BLOCK)
 k_sort_scan(const DevHeader* hdr, u32* __restrict__ hist, u32 n_chunks, u32* __restrict__ digit_total) {
   __shared__ u32 lds[4];
   u32* row = hist + blockIdx.x * n_chunks;
-  const u32 per = (n_chunks + BLOCK - 1) / BLOCK;  // consecutive entries per thread
+  const u32 per = PER == 1 ? 1u : (n_chunks + BLOCK - 1) / BLOCK;  // consecutive entries per thread
   const u32 c0 = threadIdx.x * per;
   const u32 n = c0 < n_chunks ? min(per, n_chunks - c0) : 0u;
-  u32 v[SCAN_PER], s = 0, total;
+  u32 v[PER], s = 0, total;
   const u32 status = hdr->status;
 #pragma unroll
-  for (u32 i = 0; i < SCAN_PER; ++i) v[i] = i < n ? row[c0 + i] : 0u;
+  for (u32 i = 0; i < PER; ++i) v[i] = i < n ? row[c0 + i] : 0u;
   requested();
   if (status) return;
 #pragma unroll
-  for (u32 i = 0; i < SCAN_PER; ++i) s += v[i];
+  for (u32 i = 0; i < PER; ++i) s += v[i];
   u32 ex = block_exclusive_scan(s, lds, total);
 #pragma unroll
-  for (u32 i = 0; i < SCAN_PER; ++i) {
+  for (u32 i = 0; i < PER; ++i) {
     if (i < n) row[c0 + i] = ex;
     ex += v[i];
   }
@@ -413,7 +415,12 @@ inline void sort_pass_enqueue(const DevHeader* hdr, const u32* keys_in, const u3
                               const SortGeom& geo, u32 shift, u32 digit_mask, u32* hist, u32* digit_total, bool counted,
                               hipStream_t st) {
   if (!counted) hipLaunchKernelGGL((k_sort_hist<RADIX, false>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, geo, shift, digit_mask, hist);
-  hipLaunchKernelGGL(k_sort_scan, dim3(RADIX), dim3(BLOCK), 0, st, hdr, hist, geo.n_chunks, digit_total);
+  if (geo.n_chunks <= BLOCK)
+    hipLaunchKernelGGL(k_sort_scan<1>, dim3(RADIX), dim3(BLOCK), 0, st, hdr, hist, geo.n_chunks, digit_total);
+  else if (geo.n_chunks <= 4 * BLOCK)
+    hipLaunchKernelGGL(k_sort_scan<4>, dim3(RADIX), dim3(BLOCK), 0, st, hdr, hist, geo.n_chunks, digit_total);
+  else
+    hipLaunchKernelGGL(k_sort_scan<SORT_MAX_CHUNKS / BLOCK>, dim3(RADIX), dim3(BLOCK), 0, st, hdr, hist, geo.n_chunks, digit_total);
 #define CTR_SORT_SCATTER(ITEMS, R, SCANNED)                                                                        \
   hipLaunchKernelGGL((k_sort_scatter<ITEMS, R, SCANNED>), dim3(geo.n_chunks), dim3(BLOCK), 0, st, hdr, keys_in, vals_in,      \
                      keys_out, vals_out, geo, shift, digit_mask, hist, digit_total)

@@ -20,7 +20,8 @@ __global__ void k_table_clear(DevHeader* hdr, Slot* slots, u64 n_slots, u32* row
                               u32 keep_step_count) {
   const u64 tid = (u64)blockIdx.x * BLOCK + threadIdx.x;
   const u64 stride = (u64)gridDim.x * BLOCK;
-  if (tid < 64 && !(keep_step_count && tid == HDR_WORD_N_PUSH)) reinterpret_cast<u32*>(hdr)[tid] = 0;
+  const bool count = tid == HDR_WORD_N_PUSH || (tid >= HDR_WORD_BC && tid < HDR_WORD_BC + 8);  // and the next push's factors
+  if (tid < 64 && !(keep_step_count && count)) reinterpret_cast<u32*>(hdr)[tid] = 0;
   for (u64 i = tid; i < n_slots; i += stride) {
     Slot s;
     s.key = KEY_EMPTY;
