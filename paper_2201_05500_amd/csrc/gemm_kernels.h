@@ -501,7 +501,8 @@ k_gemm_large(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Bp, GemmA
 
 // Second launch of a split product: adds the partial tiles in the order of the splits and applies the epilogue.
 // SIDE partials are requested together: 8 where the chip is full of threads, which then wait for memory, all 32 of a small
-// product, which waits for its chain of requests (8 x 1024 outputs, 30 partials: 6.3 -> 4.3 us).
+// product, which waits for its chain of requests (8 x 1024 outputs, 30 partials: 4.5 -> 4.3 us by the kernel's own
+// clock, a prediction of 8 requests with such products 37.5 -> 36.0).
 constexpr u32 GEMM_REDUCE_FEW = 64 * 1024;  // threads
 template <u32 SIDE>
 __global__ void __launch_bounds__(BLOCK) k_gemm_reduce(GemmArgs g) {

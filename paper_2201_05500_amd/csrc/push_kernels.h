@@ -26,7 +26,7 @@ constexpr u32 SPANS_PER_BLOCK = 64;  // one wave lane per span when scanning a b
 constexpr u32 SF_HEAD = 1u, SF_TAIL = 2u;
 constexpr u32 NO_ROW = 0xFFFFFFFFu;
 #ifndef CTR_PUSH_PB
-#define CTR_PUSH_PB 2  // occurrences per batch of the span walk (2: 71 VGPRs, 7 waves/SIMD; measured best)
+#define CTR_PUSH_PB 2  // occurrences per batch of the span walk (with the entries a step ahead about 85 VGPRs, 5 waves/SIMD)
 #endif
 // cache hints of the span walk's three traffic classes (0 = plain access, 1 = non-temporal)
 #ifndef CTR_PUSH_NT_GRAD
