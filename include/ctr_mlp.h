@@ -76,7 +76,8 @@ int ctr_mlp_forward(ctr_mlp* m, uint32_t replica, const float* d_pooled, uint32_
 
 /* The same two calls for an input that is already bfloat16 (d_pooled_bf16[batch * in_dim], the
  * output of ctr_pull_pool_bf16; read in place, must stay unchanged until the step's work has
- * run).  The results equal those of the fp32 calls on an input that rounds to these bf16 values. */
+ * run, but for the step's own gradient, which may overlap it: it is written when the input has been
+ * read for the last time).  The results equal those of the fp32 calls on an input that rounds to these bf16 values. */
 int ctr_mlp_step_bf16(ctr_mlp* m, uint32_t replica, const uint16_t* d_pooled_bf16, const float* d_labels,
                       uint32_t batch, float* d_grad_pooled, float* d_loss, void* d_workspace,
                       size_t workspace_bytes, uint32_t mode, void* hip_stream);
@@ -114,6 +115,14 @@ int ctr_debug_mlp_gemm(int a_k_contiguous, int b_k_contiguous, const uint16_t* d
 /* What ctr_mlp_gemm chooses (host only): the tile, the work items per tile, the number of ranges and their length. */
 int ctr_debug_mlp_gemm_plan(uint32_t m, uint32_t n, uint32_t k, size_t scratch_bytes, uint32_t* tile,
                             uint32_t* items_per_tile, uint32_t* ranges, uint32_t* range_length);
+
+/* How ctr_mlp_step launches its backward pass for a batch of that size (host only; in_place != 0: the gradient overlaps a
+ * bf16 input).  kept: 2 if the partial sums of split weight gradients and of the sums over the batch stay where they are
+ * until the optimizer adds them, 1 if those of the first layer do, 0 if every sum is finished by launches of its own.
+ * Of each hidden layer (arrays of n_hidden): whether its two products share a launch, and the ranges that the weight
+ * gradient's and the input gradient's work items take each one of (1: an item takes all). */
+int ctr_debug_mlp_backward_plan(const ctr_mlp_config* cfg, uint32_t batch, int in_place, uint32_t* kept, uint32_t* paired,
+                                uint32_t* weight_ranges, uint32_t* input_ranges);
 
 /* Algorithm 2's global-averaging branch over all dense parameters of the W replicas:
  * shared v = mean_j v_j; x_i = mean_j (x_j - [merge step pending in j] lr m_j / sqrt(shared v)). */

@@ -10,7 +10,7 @@ from .binding import CTR_OK, CTR_STEP_LOCAL, current_stream, lib as _base_lib
 CTR_MLP_MAX_HIDDEN = 6
 EXPORTED = ("ctr_mlp_bytes", "ctr_mlp_workspace_bytes", "ctr_mlp_create", "ctr_mlp_destroy", "ctr_mlp_step",
             "ctr_mlp_forward", "ctr_mlp_step_bf16", "ctr_mlp_step_bf16_grad_bf16", "ctr_mlp_forward_bf16", "ctr_mlp_gemm", "ctr_debug_mlp_gemm",
-            "ctr_debug_mlp_gemm_plan", "ctr_mlp_kstep_merge", "ctr_mlp_n_params", "ctr_mlp_export", "ctr_mlp_import")
+            "ctr_debug_mlp_gemm_plan", "ctr_debug_mlp_backward_plan", "ctr_mlp_kstep_merge", "ctr_mlp_n_params", "ctr_mlp_export", "ctr_mlp_import")
 
 
 class ctr_mlp_config(C.Structure):
@@ -63,6 +63,8 @@ def lib():
         L.ctr_debug_mlp_gemm.argtypes = [ci, ci, vp, u32, vp, u32, u32, u32, u32, vp, u32, vp, sz, u32, ci, vp]
         L.ctr_debug_mlp_gemm_plan.restype = ci
         L.ctr_debug_mlp_gemm_plan.argtypes = [u32, u32, u32, sz] + [C.POINTER(u32)] * 4
+        L.ctr_debug_mlp_backward_plan.restype = ci
+        L.ctr_debug_mlp_backward_plan.argtypes = [cfgp, u32, ci] + [C.POINTER(u32)] * 4
         L.ctr_mlp_kstep_merge.restype = ci
         L.ctr_mlp_kstep_merge.argtypes = [vp, vp]
         L.ctr_mlp_export.restype = ci
@@ -204,3 +206,14 @@ def ctr_debug_mlp_gemm_plan(m, n, k, scratch_bytes):
     if st != CTR_OK:
         raise ValueError("ctr_debug_mlp_gemm_plan: %d" % st)
     return tuple(int(x.value) for x in v)
+
+
+def ctr_debug_mlp_backward_plan(in_dim, hidden, batch, in_place=False):
+    """(kept, paired, weight ranges, input ranges) of the backward pass, the last three a tuple with an entry per hidden
+    layer; see include/ctr_mlp.h."""
+    cfg, kept = make_config(in_dim, hidden), C.c_uint32()
+    layers = [(C.c_uint32 * CTR_MLP_MAX_HIDDEN)() for _ in range(3)]
+    st = lib().ctr_debug_mlp_backward_plan(C.byref(cfg), batch, 1 if in_place else 0, C.byref(kept), *layers)
+    if st != CTR_OK:
+        raise ValueError("ctr_debug_mlp_backward_plan: %d" % st)
+    return (int(kept.value),) + tuple(tuple(int(v) for v in a[:len(hidden)]) for a in layers)

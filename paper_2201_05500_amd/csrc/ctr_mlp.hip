@@ -164,7 +164,8 @@ GemmArgs input_grad_args(const MlpLayout& L, u32 l, u32 B, const bf16_t* dz, con
 
 // How the backward pass of a step is launched, by its sizes.
 // A layer whose two products take less time together than one after the other runs them in one launch (paired); its
-// input gradient then has a place of its own instead of the activation's.  The partial sums of split weight gradients and of
+// input gradient then has a place of its own instead of the activation's.  (in_place: the first layer's overlaps its input, which
+// the weight gradient has to have read before.)  The partial sums of split weight gradients and of
 // the sums over the batch stay where they are until the optimizer adds them (kept).  All that stands in the scratch of
 // the products; where it does not fit, every product and every sum is finished by its own launches, in turn, but for the
 // first layer's weight gradient, the last product of all: its partial sums have the scratch to themselves (first_kept),
@@ -175,9 +176,13 @@ struct BackwardPlan {
   size_t off_w[CTR_MLP_MAX_HIDDEN], off_dz[CTR_MLP_MAX_HIDDEN], off_sums, off_rest;  // in the scratch
 };
 
+inline bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+  return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
+}
+
 inline size_t split_bytes(const GemmPlan& p, u64 M, u64 N) { return p.n_split > 1 ? p.n_split * M * N * sizeof(float) : 0; }
 
-void backward_plan(const MlpLayout& L, u32 B, size_t room, BackwardPlan* P) {
+void backward_plan(const MlpLayout& L, u32 B, size_t room, bool in_place, BackwardPlan* P) {
   const u32 hidden = L.n_layers - 1;
   size_t o = 0, rest = 0;
   u64 cols = L.in[hidden];
@@ -186,7 +191,7 @@ void backward_plan(const MlpLayout& L, u32 B, size_t room, BackwardPlan* P) {
     P->w[l] = gemm_plan(in, out, B, room);
     P->i[l] = gemm_plan(B, in, out, room);
     GemmPlan w, i;
-    P->paired[l] = gemm_pair_plan(in, out, B, B, in, out, room, &w, &i) < P->w[l].cost + P->i[l].cost;
+    P->paired[l] = gemm_pair_plan(in, out, B, B, in, out, room, &w, &i) < P->w[l].cost + P->i[l].cost && !(in_place && l == 0);
     if (P->paired[l]) {
       P->w[l] = w;
       P->i[l] = i;
@@ -361,8 +366,11 @@ static int mlp_step_impl(ctr_mlp* t, uint32_t replica, const float* d_pooled, co
   hipLaunchKernelGGL(k_out_step, dim3(blocks_for((u64)B * WAVE)), dim3(BLOCK), 0, st, a_last, PB + L.w_off[lo],
                      P + L.w_off[lo] + Hl, d_labels, B, Hl, dlogit, lterm, dz_last);
 
+  const size_t n0 = (size_t)B * L.in[0];
+  const bool in_place = d_grad_pooled ? overlap(h0, n0 * sizeof(bf16_t), d_grad_pooled, n0 * sizeof(float))
+                                      : overlap(h0, n0 * sizeof(bf16_t), d_grad_pooled_bf16, n0 * sizeof(bf16_t));
   BackwardPlan plan;
-  backward_plan(L, B, S.gemm_bytes, &plan);
+  backward_plan(L, B, S.gemm_bytes, in_place, &plan);
   char* scratch = ws + S.off_gemm;
   GradSource src{};
   src.n_layers = L.n_layers;
@@ -537,6 +545,23 @@ int ctr_debug_mlp_gemm_plan(uint32_t m, uint32_t n, uint32_t k, size_t scratch_b
   *items_per_tile = p.n_split;
   *ranges = (k + p.k_per_sum - 1) / p.k_per_sum;
   *range_length = p.k_per_sum;
+  return CTR_OK;
+}
+
+int ctr_debug_mlp_backward_plan(const ctr_mlp_config* cfg, uint32_t batch, int in_place, uint32_t* kept, uint32_t* paired,
+                                uint32_t* weight_ranges, uint32_t* input_ranges) {
+  if (!mlp_config_ok(cfg) || batch == 0 || batch % 8 != 0 || batch > CTR_MLP_MAX_BATCH) return CTR_E_INVAL;
+  if (!kept || !paired || !weight_ranges || !input_ranges) return CTR_E_INVAL;
+  MlpLayout L;
+  make_layout(cfg, &L);
+  BackwardPlan P;
+  backward_plan(L, batch, gemm_scratch_bytes(cfg), in_place != 0, &P);
+  *kept = P.kept ? 2u : P.first_kept ? 1u : 0u;
+  for (u32 l = 0; l < cfg->n_hidden; ++l) {
+    paired[l] = P.paired[l] ? 1u : 0u;
+    weight_ranges[l] = P.w[l].n_split;
+    input_ranges[l] = P.i[l].n_split;
+  }
   return CTR_OK;
 }
 
