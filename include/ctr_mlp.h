@@ -75,7 +75,8 @@ int ctr_mlp_forward(ctr_mlp* m, uint32_t replica, const float* d_pooled, uint32_
                     void* d_workspace, size_t workspace_bytes, void* hip_stream);
 
 /* The same two calls for an input that is already bfloat16 (d_pooled_bf16[batch * in_dim], the
- * output of ctr_pull_pool_bf16; read in place, must stay unchanged until the step's work has
+ * output of ctr_pull_pool_bf16; read in place where it is 16-byte aligned, copied to the
+ * workspace first where it is not; must stay unchanged until the step's work has
  * run, but for the step's own gradient, which may overlap it: it is written when the input has been
  * read for the last time).  The results equal those of the fp32 calls on an input that rounds to these bf16 values. */
 int ctr_mlp_step_bf16(ctr_mlp* m, uint32_t replica, const uint16_t* d_pooled_bf16, const float* d_labels,

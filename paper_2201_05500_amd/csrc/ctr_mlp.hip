@@ -220,19 +220,30 @@ void backward_plan(const MlpLayout& L, u32 B, size_t room, bool in_place, Backwa
   P->first_kept = P->w[0].n_split > 1 && P->i[0].n_split == 1 && COLSUM_SLICES * cols <= first;
 }
 
+// The input as the products read it: fp32 is rounded to bf16 into the workspace, bf16 is read where it stands.  The products'
+// loads to LDS take 16 bytes at a multiple of 16: an input that begins elsewhere goes to the workspace as well.
+const bf16_t* tower_input(const MlpLayout& L, const float* d_pooled, const bf16_t* d_pooled_bf16, u32 B, char* ws, const WsLayout& S,
+                          hipStream_t st) {
+  const u64 n = (u64)B * L.in[0];
+  bf16_t* h0 = (bf16_t*)(ws + S.off_h0);
+  if (!d_pooled_bf16) {
+    hipLaunchKernelGGL(k_cast_bf16, dim3(blocks_for(n / 4)), dim3(BLOCK), 0, st, d_pooled, h0, n);
+    return h0;
+  }
+  const uintptr_t at = (uintptr_t)d_pooled_bf16;
+  if (at % 16 == 0) return d_pooled_bf16;
+  if (at % 8 == 0)
+    hipLaunchKernelGGL(k_copy<uint2>, dim3(blocks_for(n / 4)), dim3(BLOCK), 0, st, (const uint2*)d_pooled_bf16, (uint2*)h0, n / 4);
+  else
+    hipLaunchKernelGGL(k_copy<bf16_t>, dim3(blocks_for(n)), dim3(BLOCK), 0, st, d_pooled_bf16, h0, n);
+  return h0;
+}
+
 // Forward through the hidden layers; activations stay in the workspace.
-// The input is either fp32 (rounded to bf16 into the workspace) or already bf16 (used in place).
-bool forward_hidden(ctr_mlp* t, u32 replica, const float* d_pooled, const bf16_t* d_pooled_bf16, u32 B, char* ws,
-                    const WsLayout& S, hipStream_t st) {
+bool forward_hidden(ctr_mlp* t, u32 replica, const bf16_t* h, u32 B, char* ws, const WsLayout& S, hipStream_t st) {
   const MlpLayout& L = t->L;
   const float* P = t->params + (u64)replica * t->M.stride;
   const bf16_t* PB = t->pb + (u64)replica * t->M.stride;
-  const bf16_t* h = d_pooled_bf16;
-  if (!h) {
-    const u64 n0 = (u64)B * L.in[0];
-    hipLaunchKernelGGL(k_cast_bf16, dim3(blocks_for(n0 / 4)), dim3(BLOCK), 0, st, d_pooled, (bf16_t*)(ws + S.off_h0), n0);
-    h = (const bf16_t*)(ws + S.off_h0);
-  }
   for (u32 l = 0; l + 1 < L.n_layers; ++l) {
     bf16_t* a = (bf16_t*)(ws + S.off_act[l]);
     if (!product_forward(L, l, B, h, PB + L.w_off[l], P + L.w_off[l] + (u64)L.in[l] * L.out[l], a, ws, S, st)) return false;
@@ -319,8 +330,8 @@ static int mlp_forward_impl(ctr_mlp* t, uint32_t replica, const float* d_pooled,
   if (workspace_bytes < S.total) return CTR_E_NOMEM;
   hipStream_t st = (hipStream_t)hip_stream;
   char* ws = (char*)d_workspace;
-  if (!forward_hidden(t, replica, d_pooled, d_pooled_bf16, batch, ws, S, st)) return CTR_E_DEVICE;
   const MlpLayout& L = t->L;
+  if (!forward_hidden(t, replica, tower_input(L, d_pooled, d_pooled_bf16, batch, ws, S, st), batch, ws, S, st)) return CTR_E_DEVICE;
   const u32 lo = L.n_layers - 1;
   const u64 base = (u64)replica * t->M.stride + L.w_off[lo];
   hipLaunchKernelGGL(k_out_forward, dim3(blocks_for((u64)batch * WAVE)), dim3(BLOCK), 0, st,
@@ -354,8 +365,8 @@ static int mlp_step_impl(ctr_mlp* t, uint32_t replica, const float* d_pooled, co
   const bf16_t* PB = t->pb + (u64)replica * t->M.stride;
 
   double* lterm = (double*)(ws + S.off_lterm);
-  const bf16_t* h0 = d_pooled_bf16 ? d_pooled_bf16 : (const bf16_t*)(ws + S.off_h0);
-  if (!forward_hidden(t, replica, d_pooled, d_pooled_bf16, B, ws, S, st)) return CTR_E_DEVICE;
+  const bf16_t* h0 = tower_input(L, d_pooled, d_pooled_bf16, B, ws, S, st);
+  if (!forward_hidden(t, replica, h0, B, ws, S, st)) return CTR_E_DEVICE;
 
   // output layer: logits, loss terms, and back through the last ReLU
   const u32 lo = L.n_layers - 1;

@@ -29,6 +29,12 @@ __global__ void k_cast_bf16(const float* __restrict__ src, bf16_t* __restrict__ 
   *reinterpret_cast<ushort4*>(dst + i) = o;
 }
 
+template <class T>
+__global__ void k_copy(const T* __restrict__ src, T* __restrict__ dst, u64 n) {
+  const u64 i = (u64)blockIdx.x * BLOCK + threadIdx.x;
+  if (i < n) dst[i] = src[i];
+}
+
 // Output layer (width 1): logit[b] = a[b, :] . w + bias.  One wave per sample, fixed summation order.
 __global__ void k_out_forward(const bf16_t* __restrict__ a, const bf16_t* __restrict__ w, const float* __restrict__ bias,
                               u32 rows, u32 H, float* __restrict__ logits) {

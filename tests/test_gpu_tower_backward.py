@@ -96,3 +96,28 @@ def test_gradient_over_the_input(in_dim, hidden, B, grad_bf16, at):
     assert torch.equal(got, want) and torch.equal(loss, over_loss)
     a, b = apart.export(), over.export()
     assert all(np.array_equal(a[k], b[k]) for k in ("params", "m", "v"))
+
+
+# one of the 16-byte aligned places, 8 bytes beside it, 2 and 14
+@pytest.mark.parametrize("in_dim,hidden,B", [(624, [400, 200, 80], 1000), (8, [8], 8), (3200, [1024, 512, 256], 4096), (1600, [256, 128], 16384)])
+@pytest.mark.parametrize("beside", [0, 4, 1, 7])
+def test_input_at_any_alignment(in_dim, hidden, B, beside):
+    import torch
+    from paper_2201_05500_amd.binding_mlp import CtrMlp
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(in_dim + B)
+    x = torch.randn((B, in_dim), generator=gen, device="cuda:0").to(torch.bfloat16)
+    y = (torch.rand(B, generator=gen, device="cuda:0") < 0.3).float()
+    memory = torch.full((x.numel() + 16,), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    pooled = memory[beside:beside + x.numel()].view(B, in_dim)
+    pooled.copy_(x)
+    assert x.data_ptr() % 16 == 0 and pooled.data_ptr() % 16 == 2 * beside
+    results = []
+    for p in (x, pooled):
+        tower = CtrMlp(in_dim, hidden, init_seed=5)
+        st, logits = tower.forward(0, p)
+        assert st == 0
+        st, loss, grad = tower.step(0, p, y)
+        assert st == 0
+        results.append([logits, loss, grad] + [torch.from_numpy(tower.export()[k]) for k in ("params", "m", "v")])
+    assert all(torch.equal(a, b) for a, b in zip(*results))
