@@ -377,8 +377,8 @@ k_sort_scatter(const DevHeader* hdr, const u32* __restrict__ keys_in, const u32*
 // ---------------------------------------------------------------- host side
 
 // How a list of n elements is cut into the chunks the sort's launches work on.
-inline SortGeom sort_geom(u64 n, u32 items, u64 max_chunks) {
-  SortGeom g;
+constexpr SortGeom sort_geom(u64 n, u32 items, u64 max_chunks) {
+  SortGeom g{};
   g.items = items;
   const u64 tile = (u64)BLOCK * g.items, tiles = (n + tile - 1) / tile;
   const u64 chunks = std::min<u64>(std::max<u64>(tiles, 1), max_chunks);
@@ -397,10 +397,15 @@ inline SortGeom sort_geom(u64 n) {
 constexpr size_t SORT_HIST_WORDS = (size_t)RADIX * SORT_MAX_CHUNKS;
 
 // Geometry of a list of n elements that takes digits of `bits` (10 or 11) bits.
-inline bool sort_takes_wide(u64 n, u32 bits) { return n <= (bits == 10 ? SORT_10_BITS_MAX : SORT_11_BITS_MAX); }
-inline SortGeom sort_geom_wide(u64 n, u32 bits) {
+constexpr bool sort_takes_wide(u64 n, u32 bits) { return n <= (bits == 10 ? SORT_10_BITS_MAX : SORT_11_BITS_MAX); }
+constexpr SortGeom sort_geom_wide(u64 n, u32 bits) {
   return sort_geom(n, n <= SORT_ITEMS_4_MAX ? 4u : 8u, (SORT_HIST_WORDS >> bits) - 1);
 }
+// the most chunks: of the longest list, and of the longest one that takes 4 elements per thread
+constexpr bool sort_scan_wide_holds(u64 n, u32 bits) { return sort_geom_wide(n, bits).n_chunks <= 16 * SCAN_WIDE_PER; }
+static_assert(sort_scan_wide_holds(SORT_10_BITS_MAX, 10) && sort_scan_wide_holds(SORT_11_BITS_MAX, 11) &&
+                  sort_scan_wide_holds(SORT_ITEMS_4_MAX, 10) && sort_scan_wide_holds(SORT_ITEMS_4_MAX, 11),
+              "k_sort_scan_wide keeps SCAN_WIDE_PER entries per thread");
 
 // Words of `hist` that a list of n elements uses, whatever its keys, and the order of a push's n_spans spans.
 inline size_t sort_hist_words(u64 n, u64 n_spans) {
