@@ -118,6 +118,8 @@ template <int N>
 __device__ __forceinline__ void gemm_wait_loads() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
+// This wave's LDS reads are done: behind a barrier, others may overwrite what they read.
+__device__ __forceinline__ void gemm_wait_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 // The bare barrier: __syncthreads() would wait for every load in flight.
 __device__ __forceinline__ void gemm_barrier() {
   __builtin_amdgcn_sched_barrier(0);
@@ -311,6 +313,7 @@ __device__ __forceinline__ void gemm_tiles_body(char* lds, u32 block, const bf16
   u32 rd = 0, wr = (S - 1) * STEP;
   for (u32 s = 0; s < n_steps; ++s) {
     gemm_wait_loads<(S - 2) * (TA::N + TB::N)>();  // steps behind the last one are requested, too: the count stays
+    gemm_wait_reads();  // of the step before: its products have them already
     gemm_barrier();
     if (left == 0) {
       fold();
@@ -429,7 +432,7 @@ __device__ __forceinline__ void large_phase(char* lds, u32 buf, LargeWork<A_KC, 
     for (u32 i = 0; i < 2; ++i) c[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk][i], fb[kk], c[i], 0, 0, 0);
   __builtin_amdgcn_s_setprio(0);
   __builtin_amdgcn_sched_barrier(0);
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  gemm_wait_reads();
   gemm_barrier();
 }
 
@@ -471,7 +474,7 @@ k_gemm_large(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Bp, GemmA
 #pragma unroll
     for (u32 i = 0; i < 2; ++i)
       t.fa0[kk][i] = LargeWork<A_KC, B_KC>::TA::fragment((const char*)lds + LARGE_A0, t.wm * 64 + i * 32, kk);
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  gemm_wait_reads();
   if (w >= 4) gemm_barrier();  // half a phase behind from here on
   u32 buf = 0, s = 0;
   for (; s + 2 < n_full; ++s, buf ^= LARGE_STEP) large_step<true>(lds, buf, t, it.k_begin + s * GEMM_BK);
