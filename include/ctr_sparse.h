@@ -308,6 +308,10 @@ int ctr_last_status(ctr_table* t, void* hip_stream);
 /* Smallest workspace that a batch of exactly `n_keys` key occurrences is accepted with (0 if invalid). */
 size_t ctr_debug_workspace_min_bytes(const ctr_config* cfg, uint64_t n_keys);
 
+/* Occurrences per work span that a push of `n_keys` key occurrences takes in a workspace of ctr_workspace_bytes (0 if
+ * invalid).  Host only. */
+int ctr_debug_push_span(const ctr_config* cfg, uint64_t n_keys);
+
 /* Test hook: fixes the work geometry of later pulls and pushes instead of letting the batch size
  * choose it (span: occurrences per work span of the push, 4/8/16/32/64/128; probe_items: occurrences
  * per thread of the probe, 1 or 8; 0 = by batch size), so that every code path can be exercised

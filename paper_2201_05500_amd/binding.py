@@ -29,7 +29,7 @@ EXPORTED = (
     "ctr_table_bytes", "ctr_workspace_bytes", "ctr_table_create", "ctr_table_destroy",
     "ctr_pull_pool", "ctr_pull_pool_bf16", "ctr_lookup_pool", "ctr_lookup_pool_noalloc", "ctr_push_adam", "ctr_push_adam_bf16", "ctr_kstep_merge", "ctr_table_load", "ctr_table_collect", "ctr_table_clear",
     "ctr_table_size", "ctr_table_export",
-    "ctr_batch_export", "ctr_batch_stats", "ctr_merge_stats", "ctr_stream_copy", "ctr_last_status", "ctr_debug_workspace_min_bytes", "ctr_debug_set_geometry", "ctr_debug_set_push_order", "ctr_profile_enable",
+    "ctr_batch_export", "ctr_batch_stats", "ctr_merge_stats", "ctr_stream_copy", "ctr_last_status", "ctr_debug_workspace_min_bytes", "ctr_debug_push_span", "ctr_debug_set_geometry", "ctr_debug_set_push_order", "ctr_profile_enable",
     "ctr_profile_read",
 )
 
@@ -71,6 +71,8 @@ def lib():
     L.ctr_workspace_bytes.argtypes = [cfgp, u64, u32]
     L.ctr_debug_workspace_min_bytes.restype = sz
     L.ctr_debug_workspace_min_bytes.argtypes = [cfgp, u64]
+    L.ctr_debug_push_span.restype = C.c_int
+    L.ctr_debug_push_span.argtypes = [cfgp, u64]
     L.ctr_table_create.restype = ci
     L.ctr_table_create.argtypes = [cfgp, vp, sz, vp, C.POINTER(vp)]
     L.ctr_table_destroy.restype = ci
@@ -133,6 +135,10 @@ def ctr_workspace_bytes(cfg: ctr_config, max_keys: int, max_segments: int) -> in
 
 def ctr_debug_workspace_min_bytes(cfg: ctr_config, n_keys: int) -> int:
     return int(lib().ctr_debug_workspace_min_bytes(C.byref(cfg), n_keys))
+
+
+def ctr_debug_push_span(cfg: ctr_config, n_keys: int) -> int:
+    return int(lib().ctr_debug_push_span(C.byref(cfg), n_keys))
 
 
 def ctr_table_create(cfg: ctr_config, d_mem: int, nbytes: int, stream: int):

@@ -92,21 +92,37 @@ inline u32 lanes_per_row(u32 D) {
 // keep a wave on every SIMD (64 Ki): 73 k occurrences of 8 columns, span walk + fix-up, 34 us with 16, 23 us with 4; 160 k
 // of 16 columns 38 us with 16, 30 with 8.  Not below 8 for rows of 32 and 64 lanes: a wave adds the partial sums of so
 // wide a row one or two at a time (8000 occurrences of 256 columns, keys of a power law: 37 us with 16, 39 with 8, 46 with
-// 4; 4000 with 3000 keys 30, 23 and 20; 4000 of 128 columns, power law, 32, 27 and 29).   From 2 M on rows
-// of up to 16 columns keep 16, those of 16 columns from 4 M on, where keys repeat much (as many keys as a quarter of the
-// occurrences, 1 M at most: 8 M of 4 columns 320 us with 16, 370 with 64; 12 M of 16 columns 440 and 542 with 128; 2.5 M 113 and
-// 115 with 32) and mostly where they do not (16 M keys: 12 M of 16 columns 574 us with 16, 668 with 128; 2.5 M 142 and 135 with
-// 32; but 12 M of 8 columns 641 and 599 with 128).  Rows of 32 columns take 32 and then 64 (8 M: 361 us with 32, 371 with
-// 128; 12 M 479 with 64, 524 with 128), and wider ones longer spans, which cost them less than partial sums (4 M of 64 columns:
-// 394 us with 16, 365 with 32, 373 with 64).  A batch of one or two keys
-// pays for short spans all the same (200 k occurrences of one key, 8 columns: 32 us, 27 with 16).
+// 4; 4000 with 3000 keys 30, 23 and 20; 4000 of 128 columns, power law, 32, 27 and 29).
+// From 2 M on the span walk takes what the gradient rows take, and the length decides how evenly its waves fill the chip:
+// spans of 32, 64 and 128 from 2, 4 and 8 Mi occurrences on are 1024 to 2048 waves for every lane of a row, so rows of 1, 2 and 3
+// lanes lose by them where the last wave of a SIMD is nearly alone (8.5 M of 4 columns, two waves per SIMD, 1037 in all: 596 us,
+// 513 with 16) and gain where it is not (14 M: 740 and 774): a power law over 2^24 keys.  Where keys repeat, spans of 16 lose
+// nowhere but at 2.5 to 3 M of 8 columns (a power law over half as many keys as occurrences: 6 M of 8 columns 288 us with 64, 278
+// with 16; 12 M of 12 columns 716 with 128, 629 with 16), and that a table has no more rows than that is known.  So: 16 for
+// such tables, and for others where no power law, over n keys or over 2^24, is more than 2 % behind the longer spans.
+// Rows of 16 columns gain by 16 from 4 Mi on under every power law (12 M: 417 and 531 with 128; over 2^24 keys 552 and 660).
+// (Keys drawn evenly from 2^24, nearly all of them once, would rather have the longer spans at 2.8 to 3.5 Mi of 4 columns, by up to
+// 13 %, and from 14 Mi on of 16 columns, by 4 %.)
+// Rows of 32 columns take 32 and then 64 (8 M: 361 us with 32, 371 with 128; 12 M 479 with 64, 524 with 128), and wider ones longer
+// spans, which cost them less than partial sums (4 M of 64 columns: 394 us with 16, 365 with 32, 373 with 64).
+// A batch of one or two keys pays for short spans all the same (200 k occurrences of one key, 8 columns: 32 us, 27 with 16).
+// Short spans of long lists cost memory, 16 bytes per column and span: 39 M occurrences of 16 columns take a workspace of
+// 1.64 GiB with 16, 1.11 with 128; of 4 columns 1.20 and 1.05.
 // (All sizes: profiles/push_spans.txt.)
-inline u32 push_span(u32 D, u64 n) {
+constexpr u64 SPAN_STEP = 1 << 18;  // the lines from 2 Mi to 16 Mi occurrences are multiples of this
+inline u32 push_span(u32 D, u64 rows, u64 n) {
   const u32 lpr = lanes_per_row(D);
   if (n >= (2u << 20)) {
-    if (lpr <= 4) return lpr == 4 && n < (4u << 20) ? 32 : 16;
-    if (lpr == 8) return n >= (10u << 20) ? 64 : 32;
-    return n >= (8u << 20) ? 128 : n >= (4u << 20) ? 64 : 32;
+    const u32 longer = n >= (8u << 20) ? 128 : n >= (4u << 20) ? 64 : 32;
+    const u64 at = n / SPAN_STEP;  // in quarters of 2^20
+    const bool repeat = rows <= n / 2;
+    if (lpr > 8) return longer;
+    if (lpr == 8) return at >= 40 ? 64 : 32;
+    if (D == 16) return at >= 16 ? 16 : 32;
+    const bool shorter = D == 4   ? repeat || at < 14 || (at >= 16 && at < 20) || (at >= 32 && at < 48) || at >= 64
+                         : D == 8 ? (repeat && at >= 12) || at < 10 || (at >= 32 && at < 40) || at >= 48
+                                  : (repeat && at >= 16) || (at >= 22 && at < 32) || at >= 42;
+    return shorter ? 16 : longer;
   }
   const u64 lanes = n * lpr;
   const u32 span = lanes >= (1u << 20) ? 16 : lanes >= (1u << 19) ? 8 : 4;
@@ -120,11 +136,11 @@ inline u32 compact_span(u64 n) {
 
 // force_span / force_items: 0 = chosen by batch size; otherwise the geometry a test asks for.  compact: spans of at
 // least compact_span and no more room for the sort's histograms than the list needs, for a workspace that holds no more.
-void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force_items = 0, bool compact = false) {
+void work_layout(u32 D, u64 rows, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force_items = 0, bool compact = false) {
   const u64 n = n_keys;
   L->n_rank_tiles = (u32)((n + RANK_TILE - 1) / RANK_TILE);
   L->n_rank_groups = (L->n_rank_tiles + RANK_GROUP - 1) / RANK_GROUP;
-  L->span = push_span(D, n);
+  L->span = push_span(D, rows, n);
   if (force_span) L->span = force_span;
   if (compact) L->span = std::max(L->span, compact_span(n));
   L->n_spans = (u32)((n + L->span - 1) / L->span);
@@ -162,11 +178,11 @@ void work_layout(u32 D, u64 n_keys, WorkLayout* L, u32 force_span = 0, u32 force
 // The layout of a batch of n keys in a workspace of that many bytes; false if it does not fit.  Below the size
 // ctr_workspace_bytes asks for, down to the compact layout, the batch runs with longer spans.  (Callers may hold a
 // workspace sized when a batch of few keys had spans of 16 occurrences: the compact layout needs no more than that.)
-bool fit_layout(u32 D, u64 n, size_t bytes, WorkLayout* L, u32 force_span, u32 force_items) {
-  work_layout(D, n, L, force_span, force_items);
+bool fit_layout(u32 D, u64 rows, u64 n, size_t bytes, WorkLayout* L, u32 force_span, u32 force_items) {
+  work_layout(D, rows, n, L, force_span, force_items);
   if (L->total <= bytes) return true;
   if (force_span) return false;
-  work_layout(D, n, L, 0, force_items, true);
+  work_layout(D, rows, n, L, 0, force_items, true);
   return L->total <= bytes;
 }
 
@@ -375,24 +391,30 @@ size_t ctr_workspace_bytes(const ctr_config* cfg, uint64_t max_keys, uint32_t ma
   // at most max_keys occurrences, i.e. the largest layout over max_keys itself and the last size of
   // every geometry class below it (inside a class the layout only grows with the size).
   WorkLayout L;
-  work_layout(cfg->dim, max_keys, &L);
-  size_t need = L.total;
-  const u64 lpr = lanes_per_row(cfg->dim);  // the first size of every span length of push_span
-  for (u64 threshold : {((u64)1 << 19) / lpr, ((u64)1 << 20) / lpr, (u64)2 << 20, (u64)4 << 20, (u64)8 << 20, (u64)10 << 20}) {
-    if (threshold - 1 < max_keys) {
-      work_layout(cfg->dim, threshold - 1, &L);
-      need = std::max(need, L.total);
-    }
-  }
+  size_t need = 0;
+  const auto cover = [&](u64 n) {
+    if (n > max_keys) return;
+    work_layout(cfg->dim, cfg->capacity_rows, n, &L);
+    need = std::max(need, L.total);
+  };
+  const u64 lpr = lanes_per_row(cfg->dim);
+  cover(max_keys);
+  for (u64 first : {((u64)1 << 19) / lpr, ((u64)1 << 20) / lpr, (u64)2 * cfg->capacity_rows}) cover(first - 1);  // first sizes of a length
+  for (u64 n = (u64)2 << 20; n <= (u64)16 << 20; n += SPAN_STEP) cover(n - 1);
   return need;
 }
 
 size_t ctr_debug_workspace_min_bytes(const ctr_config* cfg, uint64_t n_keys) {
   if (!config_ok(cfg) || n_keys >= (1ull << 31)) return 0;
   WorkLayout full, compact;
-  work_layout(cfg->dim, n_keys, &full);
-  work_layout(cfg->dim, n_keys, &compact, 0, 0, true);
+  work_layout(cfg->dim, cfg->capacity_rows, n_keys, &full);
+  work_layout(cfg->dim, cfg->capacity_rows, n_keys, &compact, 0, 0, true);
   return std::min(full.total, compact.total);
+}
+
+int ctr_debug_push_span(const ctr_config* cfg, uint64_t n_keys) {
+  if (!config_ok(cfg) || n_keys >= (1ull << 31)) return 0;
+  return (int)push_span(cfg->dim, cfg->capacity_rows, n_keys);
 }
 
 int ctr_table_create(const ctr_config* cfg, void* d_mem, size_t bytes, void* hip_stream, ctr_table** out) {
@@ -469,7 +491,7 @@ static int pull_pool_impl(ctr_table* t, uint32_t replica, const uint64_t* d_keys
   if (n_segments > 0 && !d_pooled && !d_pooled_bf16) return CTR_E_INVAL;
   if (((uintptr_t)d_workspace & 255) != 0) return CTR_E_INVAL;
   WorkLayout wl;
-  if (!fit_layout(t->D, n_keys, workspace_bytes, &wl, t->force_span, t->force_items)) return CTR_E_NOMEM;
+  if (!fit_layout(t->D, t->R, n_keys, workspace_bytes, &wl, t->force_span, t->force_items)) return CTR_E_NOMEM;
 
   t->has_live = false;  // an unpushed batch goes stale
   ctr_batch* b = &t->cur;
@@ -599,7 +621,7 @@ int ctr_lookup_pool(ctr_table* t, uint32_t replica, const uint64_t* d_keys, uint
   if (rc != CTR_OK) return rc;
   if (!d_workspace || ((uintptr_t)d_workspace & 255) != 0) return CTR_E_INVAL;
   WorkLayout wl;
-  if (!fit_layout(t->D, n_keys, workspace_bytes, &wl, t->force_span, t->force_items)) return CTR_E_NOMEM;
+  if (!fit_layout(t->D, t->R, n_keys, workspace_bytes, &wl, t->force_span, t->force_items)) return CTR_E_NOMEM;
   if (t->has_live && t->cur.ws == (char*)d_workspace) t->has_live = false;  // the live batch's lists are overwritten
   char* ws = (char*)d_workspace;
   return lookup_pool_enqueue(t, replica, d_keys, (u32)n_keys, d_offsets, n_segments, d_pooled,
@@ -784,7 +806,7 @@ int ctr_table_load(ctr_table* t, const uint64_t* d_keys, uint64_t n_keys, const 
   if (n_keys > 0 && (!d_keys || !d_x || !d_v || (has_m && !d_m))) return CTR_E_INVAL;
   if (((uintptr_t)d_workspace & 255) != 0) return CTR_E_INVAL;
   WorkLayout wl;
-  if (!fit_layout(t->D, n_keys, workspace_bytes, &wl, t->force_span, t->force_items)) return CTR_E_NOMEM;
+  if (!fit_layout(t->D, t->R, n_keys, workspace_bytes, &wl, t->force_span, t->force_items)) return CTR_E_NOMEM;
   t->has_live = false;  // the workspace of an unpushed batch may be this one: it goes stale
   ++t->generation;
   hipStream_t st = (hipStream_t)hip_stream;

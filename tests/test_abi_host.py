@@ -117,14 +117,44 @@ def test_fixed_scratch_of_the_lookup_holds_one_list():
     assert keys == B.CTR_NOALLOC_MAX_KEYS == 1 << 22 and size == 4 * keys
 
 
-@pytest.mark.parametrize("D", [4, 8, 64, 100, 128, 132, 256])
-def test_workspace_for_many_keys_serves_every_smaller_batch(D):
+@pytest.mark.parametrize("rows", [1 << 16, 1 << 22, 1 << 24])
+@pytest.mark.parametrize("D", [4, 8, 12, 16, 24, 32, 64, 100, 128, 132, 256])
+def test_workspace_for_many_keys_serves_every_smaller_batch(D, rows):
     """Batches just below a size from which spans are longer need more than those at it: the answer for max_keys covers
     them, so it never falls as max_keys grows."""
-    sizes = sorted({2 ** e + d for e in range(9, 25) for d in (-1, 0, 1)} | {int(1.13 ** e) for e in range(10, 135)})
-    answers = [B.ctr_workspace_bytes(_cfg(dim=D), n, 0) for n in sizes]
+    cfg = _cfg(dim=D, capacity_rows=rows)
+    sizes = {2 ** e + d for e in range(9, 25) for d in (-1, 0, 1)} | {int(1.13 ** e) for e in range(10, 135)}
+    sizes = sorted(sizes | {(k << 18) + d for k in range(4, 130) for d in (-1, 0)} | {2 * rows - 1, 2 * rows})
+    answers = [B.ctr_workspace_bytes(cfg, n, 0) for n in sizes]
     assert all(a <= b for a, b in zip(answers, answers[1:]))
-    assert all(B.ctr_debug_workspace_min_bytes(_cfg(dim=D), n) <= a for n, a in zip(sizes, answers))
+    assert all(B.ctr_debug_workspace_min_bytes(cfg, n) <= a for n, a in zip(sizes, answers))
+    # room for the partial sums, 16 bytes per column and span, of the batch with the most spans up to max_keys
+    most = 0
+    for n, a in zip(sizes, answers):
+        most = max(most, -(-n // B.ctr_debug_push_span(cfg, n)))
+        assert a >= 16 * D * most, (n, a)
+
+
+def test_spans_of_narrow_rows():
+    """From 2 Mi occurrences on: 16 for rows of 4, 8 and 12 columns where the table's rows show that keys repeat, or where a power
+    law over many keys does not lose by it; else 32, 64 and 128 from 2, 4 and 8 Mi on (profiles/push_spans.txt)."""
+    few, many = 1 << 18, 1 << 24
+    span = lambda D, rows, mi, d=0: B.ctr_debug_push_span(_cfg(dim=D, capacity_rows=rows), int(mi * (1 << 20)) + d)
+    lines = {4: [(2, 16), (3.5, 32), (4, 16), (5, 64), (8, 16), (12, 128), (16, 16)],
+             8: [(2, 16), (2.5, 32), (4, 64), (8, 16), (10, 128), (12, 16)],
+             12: [(2, 32), (4, 64), (5.5, 16), (8, 128), (10.5, 16)],
+             16: [(2, 32), (4, 16)], 20: [(2, 32), (10, 64)], 32: [(2, 32), (10, 64)], 36: [(2, 32), (4, 64), (8, 128)],
+             256: [(2, 32), (4, 64), (8, 128)]}
+    for D, steps in lines.items():
+        for (at, want), end in zip(steps, [s[0] for s in steps[1:]] + [2047]):
+            assert span(D, many, at) == span(D, many, end, -1) == want, (D, at)
+    for D, steps in {4: [(2, 16)], 8: [(2, 16), (2.5, 32), (3, 16)], 12: [(2, 32), (4, 16)], 16: [(2, 32), (4, 16)]}.items():
+        for (at, want), end in zip(steps, [s[0] for s in steps[1:]] + [2047]):
+            assert span(D, few, at) == span(D, few, end, -1) == want, (D, at)
+    for D in (4, 8, 12):  # twice as many occurrences as rows
+        rows = {4: 6 << 20, 8: 2 << 20, 12: 9 << 19}[D]
+        assert span(D, rows, 2 * rows / (1 << 20)) == 16 and span(D, rows, 2 * rows / (1 << 20), -1) == {4: 16, 8: 32, 12: 128}[D]
+    assert B.ctr_debug_push_span(_cfg(dim=6), 10) == B.ctr_debug_push_span(_cfg(), 1 << 31) == 0
 
 
 def test_workspaces_of_the_former_sizes_are_accepted():
@@ -166,11 +196,11 @@ def test_workspace_bytes_grow_with_keys_and_dim():
 
 
 def test_workspace_bytes_never_shrink_with_the_batch_size():
-    """The work geometry changes at 2, 4 and 8 Mi occurrences (shorter spans below each threshold need more
-    partial sums): a workspace sized for max_keys must cover every smaller batch."""
-    for dim in (16, 64):
+    """The work geometry changes at 2, 4 and 8 Mi occurrences, of 20 to 32 columns at 10 Mi (shorter spans below each
+    threshold need more partial sums): a workspace sized for max_keys must cover every smaller batch."""
+    for dim in (16, 24, 32, 64):
         sizes = [1, 1000, (1 << 20), (2 << 20) - 1, 2 << 20, (3 << 20), (4 << 20) - 1, 4 << 20, (6 << 20),
-                 (8 << 20) - 1, 8 << 20, 12 << 20, 40 << 20]
+                 (8 << 20) - 1, 8 << 20, (10 << 20) - 1, 10 << 20, 12 << 20, 40 << 20]
         need = [B.ctr_workspace_bytes(_cfg(dim=dim), n, 10) for n in sizes]
         assert all(a <= b for a, b in zip(need, need[1:])), (dim, need)
         assert all(n > 0 for n in need)

@@ -32,3 +32,22 @@ def test_rows_over_many_spans_of_wide_rows(D, spans):
 def test_span_length_of_narrow_rows_in_long_lists(D, n):
     rng = np.random.default_rng(n)
     _step((200000 ** rng.random(n)).astype(np.uint64) + 1, D, 200002)
+
+
+# the same in tables of many rows (or, of 8 columns at 3 Mi, of few), and of 32 columns at 10 Mi, whose gradients are walked in windows
+@pytest.mark.parametrize("D,first,rows", [(4, 7 << 19, 1 << 22), (8, 5 << 19, 1 << 22), (8, 3 << 20, 1 << 18), (12, 11 << 19, 1 << 22),
+                                          (32, 10 << 20, 1 << 20)])
+@pytest.mark.parametrize("below", [1, 0])
+def test_lines_of_the_span_length_in_long_lists(D, first, rows, below):
+    from oracle import ctr_oracle as O
+    from paper_2201_05500_amd.binding import CtrTable, ctr_debug_push_span
+    from tests.parity_util import compare_tables, run_step, to_device
+    from tests.test_gpu_push_edges import _batch
+    n = first - below
+    gt, ot = CtrTable(rows, D, init_seed=3), O.OracleTable(200002, D, init_seed=3)  # rows in use count, not the capacity
+    assert ctr_debug_push_span(gt.cfg, first - 1) != ctr_debug_push_span(gt.cfg, first)
+    keys = (200000 ** np.random.default_rng(n).random(n)).astype(np.uint64) + 1
+    for step in range(2):
+        b = _batch(keys, D, 1 + step)
+        run_step(gt, ot, to_device(b), b)
+    compare_tables(gt, ot)
