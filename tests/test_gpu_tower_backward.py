@@ -16,11 +16,24 @@ def _product(a_kc, b_kc, A, B, M, N, K, room):
     return C
 
 
-# small towers (all layers paired, the weight gradients split and not), one whose first layer is not paired, one layer only,
-# and one whose partial sums do not fit beside each other
-@pytest.mark.parametrize("in_dim,hidden,B", [(8, [8], 8), (72, [136, 64], 264), (624, [400, 200, 80], 1000),
-                                             (256, [128, 64], 4104), (3200, [1024, 512, 256], 4096), (64, [72, 40, 24, 16, 8, 8], 520),
-                                             (4800, [1024, 512], 16384), (2048, [4096], 2048)])
+# tests/test_backward_plan.py says which routes these take
+TOWERS = [
+    # small ones (all layers paired, the weight gradients split and not), one whose first layer is not paired, one layer only,
+    # and one whose partial sums do not fit beside each other
+    (8, [8], 8), (72, [136, 64], 264), (624, [400, 200, 80], 1000), (256, [128, 64], 4104), (3200, [1024, 512, 256], 4096),
+    (64, [72, 40, 24, 16, 8, 8], 520), (4800, [1024, 512], 16384), (2048, [4096], 2048),
+    # split weight gradients of layers that are not paired, left to the optimizer; the upper layer alone not paired
+    (640, [264], 16384), (64, [512, 256], 16384), (16, [1840, 1792], 1816),
+    # split input gradients behind kept sums
+    (64, [2048], 64), (16, [16, 1800], 8),
+    # only the first layer's partial sums kept: above it unsplit weight gradients, split input gradients
+    (352, [408, 1360, 128], 4184), (184, [1592, 8, 1200], 5408),
+    # nothing kept: split weight gradients and not, split input gradients, of the first layer and above
+    (64, [856, 424], 8032), (8, [1408, 152], 5192), (800, [824, 424, 32], 6384), (240, [896, 8, 1672], 6152),
+    (232, [144, 1560, 544], 4776)]
+
+
+@pytest.mark.parametrize("in_dim,hidden,B", TOWERS)
 @pytest.mark.parametrize("grad_bf16", [False, True])
 def test_gradients_are_those_of_the_products(in_dim, hidden, B, grad_bf16):
     import torch
