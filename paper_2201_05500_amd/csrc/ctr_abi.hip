@@ -89,22 +89,22 @@ inline u32 lanes_per_row(u32 D) {
 // Occurrences per span of the push.  The span walk is sequential, so its parallelism is n / span lane groups:
 // shorter spans for smaller batches - the walk of a batch that leaves the chip idle is a chain of dependent loads - but
 // every span border costs partial sums and fix-up work.  Below 2 M occurrences the line is drawn by lanes, at those that
-// keep a wave on every SIMD (64 Ki): 73 k occurrences of 8 columns, span walk + fix-up, 34 us with 16, 23 us with 4; 160 k
-// of 16 columns 38 us with 16, 30 with 8.  Not below 8 for rows of 32 and 64 lanes: a wave adds the partial sums of so
-// wide a row one or two at a time (8000 occurrences of 256 columns, keys of a power law: 37 us with 16, 39 with 8, 46 with
-// 4; 4000 with 3000 keys 30, 23 and 20; 4000 of 128 columns, power law, 32, 27 and 29).
+// keep a wave on every SIMD (64 Ki): 73 k occurrences of 8 columns, span walk + fix-up, 32 us with 16, 19 us with 4; 160 k
+// of 16 columns 33 us with 16, 25 with 8.  Not below 8 for rows of 32 and 64 lanes, which paid more for partial sums before
+// four waves took those of a block of spans (8000 occurrences of 256 columns, keys of a power law, then: 37 us with 16, 39 with 8,
+// 46 with 4; now 39, 34 and 34, and 4000 of 128 columns 33, 27 and 23).
 // From 2 M on the span walk takes what the gradient rows take, and the length decides how evenly its waves fill the chip:
 // spans of 32, 64 and 128 from 2, 4 and 8 Mi occurrences on are 1024 to 2048 waves for every lane of a row, so rows of 1, 2 and 3
-// lanes lose by them where the last wave of a SIMD is nearly alone (8.5 M of 4 columns, two waves per SIMD, 1037 in all: 596 us,
-// 513 with 16) and gain where it is not (14 M: 740 and 774): a power law over 2^24 keys.  Where keys repeat, spans of 16 lose
-// nowhere but at 2.5 to 3 M of 8 columns (a power law over half as many keys as occurrences: 6 M of 8 columns 288 us with 64, 278
-// with 16; 12 M of 12 columns 716 with 128, 629 with 16), and that a table has no more rows than that is known.  So: 16 for
+// lanes lose by them where the last wave of a SIMD is nearly alone (8.5 M of 4 columns, two waves per SIMD, 1037 in all: 597 us,
+// 514 with 16) and gain where it is not (14 M: 737 and 774): a power law over 2^24 keys.  Where keys repeat, spans of 16 lose
+// nowhere but at 2.5 to 3 M of 8 columns (a power law over half as many keys as occurrences: 8 M of 8 columns 390 us with 64, 374
+// with 16; 12 M of 12 columns 705 with 128, 625 with 16), and that a table has no more rows than that is known.  So: 16 for
 // such tables, and for others where no power law, over n keys or over 2^24, is more than 2 % behind the longer spans.
-// Rows of 16 columns gain by 16 from 4 Mi on under every power law (12 M: 417 and 531 with 128; over 2^24 keys 552 and 660).
+// Rows of 16 columns gain by 16 from 4 Mi on under every power law (12 M: 416 and 533 with 128; over 2^24 keys 553 and 666).
 // (Keys drawn evenly from 2^24, nearly all of them once, would rather have the longer spans at 2.8 to 3.5 Mi of 4 columns, by up to
 // 13 %, and from 14 Mi on of 16 columns, by 4 %.)
-// Rows of 32 columns take 32 and then 64 (8 M: 361 us with 32, 371 with 128; 12 M 479 with 64, 524 with 128), and wider ones longer
-// spans, which cost them less than partial sums (4 M of 64 columns: 394 us with 16, 365 with 32, 373 with 64).
+// Rows of 32 columns take 32 and then 64 (8 M: 356 us with 32, 408 with 128; 12 M 494 with 64, 532 with 128), and wider ones longer
+// spans, which cost them less than partial sums (4.3 M of 64 columns: 433 us with 16, 398 with 32, 410 with 64).
 // A batch of one or two keys pays for short spans all the same (200 k occurrences of one key, 8 columns: 32 us, 27 with 16).
 // Short spans of long lists cost memory, 16 bytes per column and span: 39 M occurrences of 16 columns take a workspace of
 // 1.64 GiB with 16, 1.11 with 128; of 4 columns 1.20 and 1.05.

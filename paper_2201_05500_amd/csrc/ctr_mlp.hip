@@ -163,13 +163,14 @@ GemmArgs input_grad_args(const MlpLayout& L, u32 l, u32 B, const bf16_t* dz, con
 }
 
 // How the backward pass of a step is launched, by its sizes.
-// A layer whose two products take less time together than one after the other runs them in one launch (paired); its
-// input gradient then has a place of its own instead of the activation's.  (in_place: the first layer's overlaps its input, which
-// the weight gradient has to have read before.)  The partial sums of split weight gradients and of
-// the sums over the batch stay where they are until the optimizer adds them (kept).  All that stands in the scratch of
-// the products; where it does not fit, every product and every sum is finished by its own launches, in turn, but for the
-// first layer's weight gradient, the last product of all: its partial sums have the scratch to themselves (first_kept),
-// the sums over the batch then stand where its finished gradient would.
+// A layer whose two products take less time together than one after the other runs them in one launch (paired); its input
+// gradient then has a place of its own instead of the activation's.  (One after the other is priced with the second launch of a
+// split weight gradient, 3 us, which kept sums do without.  in_place: the first layer's input gradient overlaps its input, which
+// the weight gradient has to have read before.)  The partial sums of split weight gradients and of the sums over the batch stay
+// where they are until the optimizer adds them (kept).  All that stands in the scratch of the products; where it does not
+// fit, every product and every sum is finished by its own launches, in turn, but for the first layer's weight gradient, the
+// last product of all: its partial sums have the scratch to themselves (first_kept), the sums over the batch then stand
+// where its finished gradient would.
 struct BackwardPlan {
   bool kept, first_kept, paired[CTR_MLP_MAX_HIDDEN];
   GemmPlan w[CTR_MLP_MAX_HIDDEN], i[CTR_MLP_MAX_HIDDEN];

@@ -35,7 +35,6 @@ namespace ctr {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 constexpr u32 GEMM_BM = 256, GEMM_BN = 256, GEMM_BK = 64;
 constexpr u32 GEMM_GROUP_M = 8;  // tile rows walked together (operand reuse in L2)
@@ -131,8 +130,8 @@ __device__ __forceinline__ void gemm_barrier() {
 // 1 KB of the tile's LDS image: 8 rows of 64 k, or LINES k of R values.
 // Swizzle: chunk c of a row lies at c ^ (row & 7) ^ (row / 8 & 1) (k-contiguous: 16 lanes, whom the 64 banks serve together,
 // read one chunk of 16 rows, two rows to the banks; with row & 7 alone rows r and r + 8 met: 40 % of the LDS clocks of the
-// 16384 x 1024 x 19200 product were conflicts); at c ^ 4 (k & 3) or, with rows of 128 bytes, c ^ 4 (k / 2 & 1) (otherwise: 32
-// lanes read 64 bytes of 4 consecutive k).
+// 16384 x 1024 x 19200 product were conflicts, profiles/gemm_counters.txt); at c ^ 4 (k & 3) or, with rows of 128 bytes,
+// c ^ 4 (k / 2 & 1) (otherwise: 32 lanes read 64 bytes of 4 consecutive k).
 template <int R, bool KC, int WAVES>
 struct GemmTile {
   static constexpr u32 N = R / 8 / WAVES, CHUNKS = KC ? 8 : R / 8, LINES = 64 / CHUNKS;
@@ -370,12 +369,12 @@ k_gemm_tiles(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Bp, GemmA
 //     phase p, and a barrier lies between;
 //   * a unit's place is overwritten by requests of phase p + 2 at the earliest, and every wave waits for its reads of phase p
 //     at the end of that phase.
-// The forward product keeps the matrix cores busy 87 % of its clocks, at the 1.5 GHz that the chip's power leaves them
-// (counters: SQ_VALU_MFMA_BUSY_CYCLES of GRBM_GUI_ACTIVE), the weight gradient 69 % (300 tiles in 4 ranges are 4.7 rounds of
-// the chip, and their partial sums are stored), the input gradient 56 % (16 steps per tile: its first requests and stores).
+// The forward product keeps the matrix cores busy 88 % of its clocks, at the 1.5 GHz that the chip's power leaves them
+// (counters: profiles/gemm_counters.txt), the weight gradient 69 % (300 tiles in 4 ranges are 4.7 rounds of the chip, and their
+// partial sums are stored), the input gradient 56 % (16 steps per tile: its first requests and stores).
 // With 4 waves of 128 x 128, operands through registers and one step in flight
 // the products of a layer of 19200 x 1024 and 16384 samples took (us -> now) 752 -> 460 forward (1.40 PFLOP/s), 930 -> 600
-// weight gradient, 790 -> 605 input gradient (1.26 GB of fp32 leave: with the non-temporal hint, 690 without, 540 if
+// weight gradient, 790 -> 605 input gradient (event pairs; 1.26 GB of fp32 leave: with the non-temporal hint, 690 without, 540 if
 // nothing is stored).  Workgroups that walk several tiles and request the next one's units before they store: no gain.
 constexpr u32 LARGE_UNIT = 128 * 128, LARGE_STEP = 4 * LARGE_UNIT;
 constexpr u32 LARGE_A0 = 0, LARGE_A1 = LARGE_UNIT, LARGE_B0 = 2 * LARGE_UNIT, LARGE_B1 = 3 * LARGE_UNIT;
@@ -531,7 +530,8 @@ __global__ void __launch_bounds__(BLOCK) k_gemm_reduce(GemmArgs g) {
 // The ranges of K whose sums are taken on their own and then added in order: a property of the product's size, so
 // that its result does not depend on how it is executed.  The cut is the one that minimises (rounds of 256
 // workgroups with 256 x 256 tiles) x (contraction steps per work item + a fixed cost per item) + the cost of adding
-// the partials, within the scratch there is for them.
+// the partials, within the scratch there is for them.  The ranges decide the bits of a result, so the prices here stay those of
+// the kernels that they were first made for (3 us per step of a tile; GEMM_TILE_COSTS has what a step takes now).
 struct GemmRanges {
   u32 n, length;  // length: a multiple of GEMM_BK
 };
@@ -547,7 +547,7 @@ inline GemmRanges gemm_sum_ranges(u32 M, u32 N, u32 K, size_t partial_capacity) 
     const size_t need = s > 1 ? (size_t)s * M * N * sizeof(float) : 0;
     if (need > partial_capacity) break;
     const double rounds = (double)(u64)((tiles * s + cus - 1) / cus);
-    // unit: one contraction step of one tile (~3 us); fixed cost per item ~2 steps; the partials move
+    // unit: one contraction step of one tile (then 3 us); fixed cost per item ~2 steps; the partials move
     // (s + 1) x M x N x 4 bytes at ~4 TB/s
     const double cost = rounds * (steps_per + 2.0) + (s > 1 ? (s + 1.0) * M * N * 4.0 / 4e12 / 3e-6 : 0.0);
     if (s == 1 || cost < best) {
