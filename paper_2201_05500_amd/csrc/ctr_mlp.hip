@@ -165,7 +165,7 @@ GemmArgs input_grad_args(const MlpLayout& L, u32 l, u32 B, const bf16_t* dz, con
 // How the backward pass of a step is launched, by its sizes.
 // A layer whose two products take less time together than one after the other runs them in one launch (paired); its input
 // gradient then has a place of its own instead of the activation's.  (One after the other is priced with the second launch of a
-// split weight gradient, 3 us, which kept sums do without.  in_place: the first layer's input gradient overlaps its input, which
+// split weight gradient, which kept sums do without.  in_place: the first layer's input gradient overlaps its input, which
 // the weight gradient has to have read before.)  The partial sums of split weight gradients and of the sums over the batch stay
 // where they are until the optimizer adds them (kept).  All that stands in the scratch of the products; where it does not
 // fit, every product and every sum is finished by its own launches, in turn, but for the first layer's weight gradient, the

@@ -569,7 +569,12 @@ struct GemmPlan {
 // 16384 (profiles/gemm_tiles.txt, which ctr_debug_mlp_gemm can measure again).  A step of a large tile is 1.5 us whatever
 // the others do.  Smaller tiles share a CU: a step of T = 128 takes 0.62 us with 8 waves while every CU has one item at most,
 // 0.8 with two on a few CUs and 1.1 with two on all of them, where the L2s feed the tiles.
+// An item of T = 64 behind another costs its stores even where the contraction has a step or two: 1.5 us (priced at 1.0, outputs
+// of 35 MB took that tile: 14584 x 600 x 8 16.6 us, 14.3 with T = 128).  A split product's second launch is 2.4 us (priced at 3.2,
+// contractions of 13 to 16 steps stayed whole: 176 x 24 x 848 7.7 us, 6.7 split).  Over the 972 products of 160 random towers what
+// is taken is 0.3 % behind the fastest, 9 of them by more than 10 % (with the former two prices 0.7 %, 36).
 constexpr u32 GEMM_CUS = 256;
+constexpr double GEMM_SECOND_LAUNCH = 2.4;
 struct GemmTileCost {
   u32 tile, per_cu;              // work items a CU takes at once
   double fixed;                  // launch, first requests and epilogue of a work item
@@ -580,7 +585,7 @@ struct GemmTileCost {
 constexpr GemmTileCost GEMM_TILE_COSTS[3] = {
     {256, 1, 8.0, 1.5, 1.5, 1.5, 1.5, 9.0},
     {128, 2, 5.0, 0.62, 0.72, 0.8, 1.1, 3.0},
-    {64, 2, 3.4, 0.28, 0.28, 0.45, 0.45, 1.0},
+    {64, 2, 3.4, 0.28, 0.28, 0.45, 0.45, 1.5},
 };
 // fp32 outputs from here on (the last-level cache's size) are stored with the non-temporal hint: 1.26 GB 690 -> 605 us; 52 MB
 // 33.1 and 32.4, but there the next kernel still finds them.
@@ -600,8 +605,7 @@ inline GemmPlan gemm_plan_one(const GemmTileCost& c, bool split, const GemmRange
   const double both = rest > GEMM_CUS ? (double)(rest - GEMM_CUS) / GEMM_CUS : 0.0;  // share of the CUs with two items
   const double rest_step = rest == 0 ? 0.0 : rest > GEMM_CUS ? c.step_two + both * (c.step2 - c.step_two) : full ? c.step1 : c.step_few;
   p.cost = c.fixed + steps * (full * c.step2 + rest_step) + (full + (rest ? 1 : 0) - 1.0) * c.next;
-  // the second launch; the partials move at about 5 TB/s
-  if (p.n_split > 1) p.cost += 3.2 + (p.n_split + 1.0) * M * N * 4.0 / 5e6;
+  if (p.n_split > 1) p.cost += GEMM_SECOND_LAUNCH + (p.n_split + 1.0) * M * N * 4.0 / 5e6;  // the partials move at about 5 TB/s
   return p;
 }
 

@@ -25,6 +25,14 @@ def test_ranges_of_the_sizes_compared_bit_by_bit():
         assert plan(m, n, k, 0)[2] == 1                      # no room for partial sums: one range
 
 
+@pytest.mark.parametrize("size,tile,split", [((176, 24, 848), 64, True), ((8, 8, 960), 64, True), ((64, 64, 512), 64, False),
+                                             ((14584, 600, 8), 256, False), ((7384, 464, 8), 128, False), ((2000, 400, 8), 64, False)])
+def test_lines_between_tiles_and_splits(size, tile, split):
+    """Contractions of 13 steps and more are split where the chip has room; large outputs of short ones take larger tiles."""
+    got, items, _, _ = plan(*size, ROOM)
+    assert (got, items > 1) == (tile, split)
+
+
 @pytest.mark.parametrize("bad", [(0, 8, 8), (8, 12, 8), (8, 8, 4)])
 def test_refused_sizes(bad):
     with pytest.raises(ValueError):

@@ -29,7 +29,7 @@ TOWERS = [
     # only the first layer's partial sums kept: above it unsplit weight gradients, split input gradients
     (352, [408, 1360, 128], 4184), (184, [1592, 8, 1200], 5408),
     # nothing kept: split weight gradients and not, split input gradients, of the first layer and above
-    (64, [856, 424], 8032), (8, [1408, 152], 5192), (800, [824, 424, 32], 6384), (240, [896, 8, 1672], 6152),
+    (64, [856, 424], 8032), (8, [1896, 1096], 3944), (784, [1176, 248, 128], 6000), (240, [896, 8, 1672], 6152),
     (232, [144, 1560, 544], 4776)]
 
 
