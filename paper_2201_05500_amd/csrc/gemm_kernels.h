@@ -502,9 +502,10 @@ k_gemm_large(const bf16_t* __restrict__ Ap, const bf16_t* __restrict__ Bp, GemmA
 }
 
 // Second launch of a split product: adds the partial tiles in the order of the splits and applies the epilogue.
-// SIDE partials are requested together: 8 where the chip is full of threads, which then wait for memory, all 32 of a small
-// product, which waits for its chain of requests (8 x 1024 outputs, 30 partials: 4.5 -> 4.3 us by the kernel's own
-// clock, a prediction of 8 requests with such products 37.5 -> 36.0).
+// SIDE partials are requested together behind the first: 8 where the chip is full of threads, which then wait for memory, all 31
+// of a small product, which waits for its chain of requests (8 x 1024 outputs, 30 partials: 4.5 -> 4.3 us by the kernel's own
+// clock, a prediction of 8 requests with such products 37.5 -> 36.0), unless 8 are all there are (8 x 1024 x 2160, 9 partials,
+// both launches: 6.6 us with 8, 7.4 with 32; 10 partials 7.35 and 7.4; 20 9.2 and 8.3).
 constexpr u32 GEMM_REDUCE_FEW = 64 * 1024;  // threads
 template <u32 SIDE>
 __global__ void __launch_bounds__(BLOCK) k_gemm_reduce(GemmArgs g) {
@@ -697,7 +698,7 @@ inline hipError_t gemm_launch(bool a_kc, bool b_kc, GemmArgs g, const GemmPlan& 
   if (g.n_split > 1 && !keep_partial) {
     const u64 mn = (u64)g.M * g.N;
     const dim3 blocks((u32)((mn / 4 + BLOCK - 1) / BLOCK));
-    if (mn / 4 <= GEMM_REDUCE_FEW && g.n_split > 8)
+    if (mn / 4 <= GEMM_REDUCE_FEW && g.n_split > 9)
       hipLaunchKernelGGL(k_gemm_reduce<32>, blocks, dim3(BLOCK), 0, st, g);
     else
       hipLaunchKernelGGL(k_gemm_reduce<8>, blocks, dim3(BLOCK), 0, st, g);

@@ -19,7 +19,7 @@ def test_ranges_of_the_sizes_compared_bit_by_bit():
     lengths = {s: plan(*s, ROOM)[2:] for s in BITS}
     assert lengths == {(72, 136, 264): (1, 320), (640, 96, 640): (3, 256), (264, 200, 1288): (6, 256),
                        (136, 72, 9224): (29, 320), (1000, 400, 5768): (19, 320), (1032, 520, 5768): (13, 448),
-                       (1032, 520, 8200): (15, 576)}
+                       (1032, 520, 8200): (15, 576), (16, 200, 2160): (9, 256), (16, 200, 2560): (10, 256)}
     for (m, n, k), (ranges, length) in lengths.items():
         assert length % 64 == 0 and (ranges - 1) * length < k <= ranges * length
         assert plan(m, n, k, 0)[2] == 1                      # no room for partial sums: one range

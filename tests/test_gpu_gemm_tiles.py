@@ -37,9 +37,10 @@ def test_product_of_whole_numbers_is_exact(M, N, K, a_kc, b_kc):
 
 
 # (M, N, K): tests/test_gemm_plan.py has the ranges of each: one, many of 256, many whose length is an odd number of 64s
-# (a step of the 64-wide tile, 128, then reaches beyond a range's end in mid-contraction), a last one that ends in mid-step
+# (a step of the 64-wide tile, 128, then reaches beyond a range's end in mid-contraction), a last one that ends in mid-step; the
+# most ranges whose partial sums a small product adds eight at a time, and one more
 BITS = [(72, 136, 264), (640, 96, 640), (264, 200, 1288), (136, 72, 9224), (1000, 400, 5768), (1032, 520, 5768),
-        (1032, 520, 8200)]
+        (1032, 520, 8200), (16, 200, 2160), (16, 200, 2560)]
 
 
 @pytest.mark.parametrize("a_kc,b_kc", [(True, False), (False, False), (True, True), (False, True)])
