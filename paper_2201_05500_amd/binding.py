@@ -416,6 +416,7 @@ class CtrTable:
         """Test hook (ctr_debug_set_geometry); the workspace is grown for the larger probe tiles."""
         st = lib().ctr_debug_set_geometry(self._handle, span, probe_items)
         self._ws_slack = 1 << 20 if (span or probe_items) else 0
+        self._ws_keys = -1  # what was reserved before was reserved without it
         return st
 
     def set_push_order(self, windows=0, split_launch=0, min_grad_bytes=256 << 20):

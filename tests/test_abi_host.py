@@ -242,3 +242,23 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
         B.lib()
     with pytest.raises(RuntimeError, match="missing"):          # the tower's binding loads the same library
         BM.lib()
+
+
+def test_geometry_set_after_a_reservation_has_its_room():
+    """ctr_debug_set_geometry may need a larger workspace for the keys that room was reserved for before."""
+    import types
+
+    import torch
+    t = object.__new__(B.CtrTable)
+    t._torch = types.SimpleNamespace(cuda=types.SimpleNamespace(synchronize=lambda device: None), empty=torch.empty, uint8=torch.uint8)
+    t.device, t.cfg, t._handle = torch.device("cpu"), _cfg(), None
+    t._ws, t._ws_of_live_batch, t.ws_bytes, t._ws_keys, t._ws_need = None, None, 0, -1, 0
+    t.reserve(1000, 10)
+    first = t.ws_bytes
+    assert first == B.ctr_workspace_bytes(t.cfg, 1000, 10)
+    t.set_geometry(4, 8)
+    t.reserve(1000, 10)
+    assert t.ws_bytes == first + (1 << 20) and t._ws.numel() == t.ws_bytes
+    t.set_geometry(0, 0)
+    t.reserve(1000, 10)
+    assert t.ws_bytes == first + (1 << 20)

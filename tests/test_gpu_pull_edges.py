@@ -200,3 +200,17 @@ def test_long_segments_are_gathered_at_the_rate_of_short_ones():
         gt.profile_enable(False)
     assert gt.last_status() == CTR_OK
     assert sorted(took)[5] <= n * D * 4 / 11.5e12, took
+
+
+# geometries that need more room than the batches before them, whose size the workspace has
+@pytest.mark.parametrize("D,n,geometry", [(8, 300, (0, 8)), (4, 2048, (0, 8)), (256, 1000, (4, 0)), (64, 6000, (4, 8))])
+def test_workspace_grows_for_a_geometry_set_later(D, n, geometry):
+    rng = np.random.default_rng(n)
+    off = np.minimum(np.arange(0, n + 5, 5), n)
+    gt, ot = _tables(n, D)
+    bn = _batch((rng.integers(0, n, n).astype(np.uint64) + np.uint64(1)) * GOLDEN, off, D, n)
+    bt = to_device(bn)
+    for step, g in enumerate(((0, 0), geometry, (0, 0))):
+        assert gt.set_geometry(*g) == 0
+        run_step(gt, ot, bt, bn, what="n=%d step %d" % (n, step))
+    compare_tables(gt, ot, what="n=%d" % n)
