@@ -50,20 +50,14 @@ constexpr u32 RANK_GROUP_STRIDE = 32;  // words: a group's count has a cache lin
                                        // line are served one after the other (39 M occurrences: 19 k of them on
                                        // 5 lines took 60 of k_rank_count's 84 us)
 
-// Small grids request a thread's key before they look at the status and the offsets: one latency of a chain of few.  In a large
-// grid of one occurrence per thread others hide it, and where all keys are new the waves meet at the slots of the popular ones:
-// a power law over as many keys, empty table, pull of 2.4 M occurrences of 4 columns 693 us, 797 with early requests; 3.3 M
-// of 32 columns 952 and 970 (a table that has the keys: the same within 1 %).
-constexpr u32 PROBE_EARLY_BLOCKS = 2048;
 __global__ void __launch_bounds__(BLOCK)
 k_probe_insert(DevHeader* hdr, Slot* slots, u32 slot_mask, const u64* __restrict__ keys, u32 n_keys,
                const u32* __restrict__ offsets, u32 n_seg, u32* __restrict__ occ_row,
                u32* __restrict__ pend_list, u32* __restrict__ tile_pending, u32 items,
                u32* __restrict__ group_count, u32 n_groups) {
   const u32 tile0 = blockIdx.x * (BLOCK * items);
-  u64 key = KEY_EMPTY;  // the thread's next occurrence, requested one ahead: early, or where a thread has several
-  const bool early = items > 1 || gridDim.x <= PROBE_EARLY_BLOCKS;
-  if (early && tile0 + threadIdx.x < n_keys) key = keys[tile0 + threadIdx.x];
+  u64 key = KEY_EMPTY;  // the thread's next occurrence: requested one ahead
+  if (tile0 + threadIdx.x < n_keys) key = keys[tile0 + threadIdx.x];
   const bool refused = hdr->status != 0;  // an earlier call failed: this pull is a no-op
   requested();
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -91,7 +85,7 @@ k_probe_insert(DevHeader* hdr, Slot* slots, u32 slot_mask, const u64* __restrict
       if (bad) atomicOr(&hdr->pull_err, ST_INVAL);
     }
 
-    const u64 this_key = early || p >= n_keys ? key : keys[p];
+    const u64 this_key = key;
     if (it + 1 < items && p + BLOCK < n_keys) key = keys[p + BLOCK];
     bool pending = false;
     if (p < n_keys) {
